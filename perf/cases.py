@@ -227,6 +227,116 @@ def run(state):
     return {k: s[k] for k in named if s[k] is not None}
 
 
+# ------------------------------------------------------------------------------------------ the same in 64 bits
+def _held(parts, dtype):
+    """float64 tensors of a parameter set as a handle of this type holds it: matrices of a bf16 one rounded once."""
+    tensors = {k: torch.as_tensor(v).cuda() for k, v in parts.items()}
+    if dtype == "bf16":
+        tensors = {k: v.bfloat16().float() if v.dim() == 2 else v for k, v in tensors.items()}
+    return {k: v.double() for k, v in tensors.items()}
+
+
+def _gru_step(w, x, h):
+    H = h.shape[-1]
+    gx, gh = x @ w["W_ih"].T + w["b_ih"], h @ w["W_hh"].T + w["b_hh"]
+    r, z = torch.sigmoid(gx[..., :2 * H] + gh[..., :2 * H]).split(H, -1)
+    n = torch.tanh(gx[..., 2 * H:] + r * gh[..., 2 * H:])
+    return (1 - z) * n + z * h
+
+
+def _first_layer(w, obs):
+    D = obs.shape[-1]
+    return torch.relu(obs @ w["W1"][:, :D].T + w["W1"][:, D:].T + w["b1"])          # the agent's id is a one-hot: a column
+
+
+def _q_values(w, obs):
+    """Q [B, slots, N, A] of whole episodes, hidden state zero before the first slot."""
+    x = _first_layer(w, obs)
+    h, hidden = torch.zeros_like(x[:, 0]), []
+    for s in range(x.shape[1]):
+        h = _gru_step(w, x[:, s], h)
+        hidden.append(h)
+    return torch.stack(hidden, 1) @ w["W2"].T + w["b2"]
+
+
+def _mixed(w, q, state):
+    """Q_total [B, T] of agents' values q [B, T, N] under global states [B, T, S]."""
+    M = w["v2"].numel()
+    w1 = (state @ w["Hw1"].T + w["hb1"]).abs().unflatten(-1, (-1, M))
+    hidden = torch.nn.functional.elu((q[..., None] * w1).sum(-2) + state @ w["Hb1"].T + w["hbb1"])
+    offset = torch.relu(state @ w["V1"].T + w["c1"]) @ w["v2"] + w["c2"]
+    return (hidden * (state @ w["Hw2"].T + w["hb2"]).abs()).sum(-1) + offset
+
+
+def _packed(grads, like):
+    return torch.cat([grads[k].reshape(-1) for k in like])
+
+
+def _rmsprop(weights, grad, sq_avg):
+    sq_avg = RMS_ALPHA * sq_avg.double() + (1 - RMS_ALPHA) * grad ** 2
+    return weights.double() - LEARN_RATE * grad / (sq_avg.sqrt() + RMS_EPS), sq_avg
+
+
+def exact(case, seed):
+    """What run() returns, as plain float64 tensor operations give it for the networks that the handles hold. Actions
+    are left out (they depend on the library's random numbers), and with the double estimator whatever hangs on its
+    choice of action (two that tie within rounding may be taken either way)."""
+    s = prepare(case, seed)
+    kind, dims = case["kind"], wl.dims(case)
+    nets = [_held(wl.unpack_weights(dims, wl.make_weights(dict(case, seed=int(seed) & 0x7FFFFFFF), stream)), case["dtype"])
+            for stream in range(2)]
+    if kind in ("decide", "decide_listed"):
+        envs = s["index"].long() if kind == "decide_listed" else slice(None)
+        w = nets[0]
+        h = s["h_in"][envs].double() * (1 - s["reset"][envs].double())[:, None, None]
+        h_new = _gru_step(w, _first_layer(w, s["obs"][envs].double()), h)
+        out = dict(h_out=s["h_out"].double(), action=None)
+        out["h_out"][envs] = h_new
+        if s["q"] is not None:
+            out["q"] = s["q"].double()
+            out["q"][envs] = h_new @ w["W2"].T + w["b2"]
+        return out
+    batch = {k: s[k] for k in ("obs", "avail", "actions", "reward", "terminated", "filled")}
+    if kind == "unroll_pool":
+        batch = {k: v[s["index"].long()] for k, v in batch.items()}
+    obs, filled, running = batch["obs"].double(), batch["filled"].double(), 1 - batch["terminated"].double()
+    leaves = {k: v.requires_grad_(kind == "learn") for k, v in nets[0].items()}
+    q_all = _q_values(leaves, obs)
+    q_taken = q_all[:, :-1].gather(-1, batch["actions"].long()[..., None])[..., 0] * filled[..., None]
+    with torch.no_grad():
+        q_target = _q_values(nets[1], obs)[:, 1:].masked_fill(batch["avail"][:, 1:] == 0, -math.inf)
+        next_max = q_target.max(-1).values * filled[..., None]
+        td_target = (batch["reward"].double()[..., None] + GAMMA * running[..., None] * next_max) * filled[..., None]
+    out = dict(q_taken=q_taken, next_max=next_max, td_target=td_target)
+    if kind != "learn":
+        if s["q_all"] is not None:
+            out["q_all"] = q_all
+        if kind == "unroll_pool":
+            out.update(next_max=None, td_target=None, next_action=None)
+        return out
+    mdims = (case["N"], case["M"], case["S"])
+    mixers = []
+    for stream in range(2):
+        packed = _mixer_weights(dict(seed=int(seed) & 0x7FFFFFFF, N=case["N"], S=case["S"]), mdims, stream)
+        mixers.append(_held({k: packed[a:b].reshape(shape) for k, (a, b, shape) in wl.mixer_slices(*mdims).items()}, case["dtype"]))
+    mleaves = {k: v.requires_grad_() for k, v in mixers[0].items()}
+    states = s["state"].double()
+    q_total = _mixed(mleaves, q_taken, states[:, :-1])
+    with torch.no_grad():
+        y_total = batch["reward"].double() + GAMMA * running * _mixed(mixers[1], next_max, states[:, 1:])
+        td_err = (y_total - q_total) * filled
+        loss = torch.stack([(td_err ** 2).sum(), filled.sum()])
+    names = list(leaves.values()) + list(mleaves.values()) + [q_taken]
+    grads = torch.autograd.grad(q_total, names, -2.0 * td_err / loss[1])
+    grad = _packed(dict(zip(leaves, grads)), leaves)
+    mixer_grad = _packed(dict(zip(mleaves, grads[len(leaves):])), mleaves)
+    weights, sq_avg = _rmsprop(s["weights"], grad, s["sq_avg"])
+    mixer_weights, mixer_sq_avg = _rmsprop(s["mixer_weights"], mixer_grad, s["mixer_sq_avg"])
+    out.update(q_total=q_total, y_total=y_total, td_err=td_err, loss=loss, grad_q=grads[-1], grad=grad, mixer_grad=mixer_grad,
+               weights=weights, mixer_weights=mixer_weights, sq_avg=sq_avg, mixer_sq_avg=mixer_sq_avg)
+    return {k: v.detach() for k, v in out.items()}
+
+
 # ------------------------------------------------------------------------------------------ accounting
 def work(case):
     kind, N, D, A, H = case["kind"], case["N"], case["D"], case["A"], case["H"]
