@@ -12,6 +12,8 @@
 //                                      four GRU matrices stay on chip: W_hh, W_hh^T and W_ih^T as operand
 //                                      fragments in registers (four waves, one per SIMD, up to 512 registers
 //                                      each), W_ih in LDS.  The adjoints go to global memory.
+//   bptt_back_split_kernel             the same for 64 hidden units, the recurrence's chain and everything that hangs
+//                                      on nothing behind it on different waves
 //   tn_gemm_kernel                     the weight gradients are sums over all (row, slot) samples of outer
 //                                      products adjoint x activation: C[p][q] = sum_m A[m][p] B[m][q], four
 //                                      times (W_ih, W_hh, W1, W2).  The samples are split into chunks, one
@@ -331,6 +333,285 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
     if (a.t_begin > 0) {
 #pragma unroll
         for (int j = 0; j < NBC; ++j) *reinterpret_cast<f32x4 *>(carry_row + 16 * j) = dh[j];
+    }
+}
+
+// The same for 64 hidden units, cut into two roles.  What bounds it is issue and latency, not memory or the matrix
+// cores: four waves in one role issue some 500 instructions each per slot, one wave per SIMD, so that nothing hides
+// a wait (1.9 us per slot, fp32; one barrier per slot instead of two in that form: 1.75 us).  But only
+// dL/dh_t -> adjoints -> dL/dh_{t-1} is a chain; the gates of a slot and the adjoint of x hang on nothing behind them.
+// Eight waves, two per SIMD: in the step of slot t
+//
+//   chain waves 0..3  dL/dh_t = carry + W_hh^T adjoints(t+1), then slot t's adjoints from its gate factors, to LDS as
+//                     operand and to memory
+//   gate waves 4..7   W_ih^T adjoints(t+1) -> dpre1 of slot t+1; the gates of slot t-1 -> factors, in LDS; x and h of
+//                     slot t-2 to LDS as operand, the loads of slot t-3
+//
+// and ONE barrier per slot.  Every LDS buffer is double-buffered on the parity of its slot: written in one step, read
+// in the next, written again only in the one after.  All weights are in registers.  Waves w and w + 4 own the same
+// 16 units, in the same lanes.  Measured on the whole learner iteration (mixer and products included): 64 episodes of
+// 120 slots x 5 agents, fp32, 562 -> 502 us; 4 x 60 x 3 fp32 247 -> 220 us; 37 x 83 x 5 bf16 316 -> 292 us.
+// (128 hidden units keep bptt_back_kernel: eight waves already hold 144 registers of weights each, and its one-barrier
+// form took 327 us per hundred slots against 313.)
+template <int P> struct BpttSplit {
+    static constexpr int H = 64, KS = H / 32, FBK = H / 16, kFrag = P * 1024;
+    static constexpr int kFactors = 5;
+    static constexpr int oH = 0, oX = oH + 2 * KS * kFrag, oDa = oX + 2 * KS * kFrag, kDaBytes = 4 * KS * kFrag;
+    static constexpr int oFac = oDa + 2 * kDaBytes, kFacBytes = kFactors * FBK * 1024;
+    static constexpr int oBias = oFac + 2 * kFacBytes, kBytes = oBias + 4 * H * 4;       // biases r, z, n input side, n hidden side
+};
+
+template <int P>
+__global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
+{
+    using Bs = BpttSplit<P>;
+    constexpr int H = Bs::H, KS = Bs::KS, FBK = Bs::FBK, kFrag = Bs::kFrag;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    typedef bf16x8 (*FragBuf)[P][64];
+    float *const bias_lds = reinterpret_cast<float *>(lds + Bs::oBias);
+
+    const NetFrags &net = a.net;
+    const int lane = threadIdx.x & 63, q4 = lane >> 4, c = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3;
+    const int N = net.N, A = net.A, T = a.T, S = T + 1;
+    const int rows = a.B * N;
+    const int row = blockIdx.x * 16 + c;
+    const bool valid = row < rows;
+    const int b = valid ? row / N : 0, n = valid ? row % N : 0;
+    const int unit0 = 16 * w + 4 * q4;                             // the lane's four units
+
+    // Stores of rows past the end go beyond the descriptor, which drops them: the loops are straight-line code.
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr uint32_t kDrop = 0xFFFFFFF0u, kElem = P == 1 ? 2u : 4u;
+    const size_t samples = (size_t)rows * T;
+    auto store4 = [&](const f32x4 &v, const __amdgpu_buffer_rsrc_t &buf, uint32_t at, uint32_t drop_mask) {
+        if constexpr (P == 1) {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            bf16x4 r;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = (__bf16)v[i];
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), buf, (at * 2u) | drop_mask, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), buf, (at * 4u) | drop_mask, 0, 0);
+        }
+    };
+    auto operand = [&](int at) {                                   // at: byte offset of a fragment
+        Frag<P> f;
+        const FragBuf p = reinterpret_cast<FragBuf>(lds + at);
+        f.hi = p[0][0][lane];
+        if constexpr (P == 2) f.lo = p[0][1][lane];
+        return f;
+    };
+    auto publish = [&](int at, const f32x4 &v) {
+        const f32x4 one[1] = {v};
+        publish_blocks<P, 1>(reinterpret_cast<FragBuf>(lds + at), w, lane, one);
+    };
+    auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
+    auto fac_of = [&](int t, int f) { return reinterpret_cast<f32x4 *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + (f * FBK + w) * 1024) + lane; };
+    uint32_t drop = valid ? 0u : kDrop;
+    asm volatile("" : "+v"(drop));
+    const uint32_t bt0 = (uint32_t)b * T, btn0 = bt0 * N + n;      // the host bounds 4 H samples to 2^30
+
+    if (wave < 4) {
+        // ---------------------------------------------------------------- chain wave
+        const __amdgpu_buffer_rsrc_t da_buf = __builtin_amdgcn_make_buffer_rsrc(a.da, 0, (int)(uint32_t)(samples * 4 * H * kElem), kRawBuffer);
+        const __amdgpu_buffer_rsrc_t dq_buf = __builtin_amdgcn_make_buffer_rsrc(a.dq, 0, (int)(uint32_t)(samples * a.a16 * kElem), kRawBuffer);
+        const uint32_t drop_dq = (16 * w < a.a16) ? drop : kDrop;  // wave w writes block w of the row's dQ
+        WFrag<P> whhT[3 * KS];
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) whhT[ks] = load_wfrag<P>(net.whhT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+        {
+            const int i = (int)threadIdx.x, gate = i / H, j = i % H;      // 256 threads, 4 H biases
+            const float *src = gate == 0 ? net.bias_r : gate == 1 ? net.bias_z : gate == 2 ? net.bias_in : net.bias_hn;
+            bias_lds[i] = src[j];
+            static_assert(4 * H == 256, "one bias per thread of the chain waves");
+        }
+        // no adjoints behind the last slot: the first step's products add nothing
+        for (int i = threadIdx.x; i < Bs::kDaBytes / 16; i += 256) reinterpret_cast<uint4 *>(lds + da_at(a.t_end))[i] = make_uint4(0, 0, 0, 0);
+
+        // A slot's inputs are asked for two steps ahead, its action (which picks the row of W2) two more; three register
+        // sets take turns in the unrolled loop, for a set that is copied has to have arrived.
+        struct In { f32x4 w2; float gq_raw; uint32_t fil; int u, u_ahead; };
+        auto action = [&](int t) { return a.actions[btn0 + (uint32_t)max(t, 0) * N]; };
+        auto fetch = [&](In &in, int t, int u_raw) {
+            const uint32_t at = (uint32_t)max(t, 0);
+            in.u = min(max(u_raw, 0), A - 1);
+            in.fil = a.filled[bt0 + at];
+            in.gq_raw = a.grad_q[btn0 + at * N];
+            in.w2 = *reinterpret_cast<const f32x4 *>(net.w2_plain + (uint32_t)(in.u * H + unit0));
+            in.u_ahead = action(t - 2);
+        };
+        const uint32_t carry_at = (uint32_t)row * H + unit0;       // rows past the end have room too
+        f32x4 carry = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (a.t_end < T) carry = *reinterpret_cast<const f32x4 *>(a.carry + carry_at);
+        In set_a, set_b, set_c;
+        fetch(set_a, a.t_end - 1, action(a.t_end - 1));
+        fetch(set_b, a.t_end - 2, action(a.t_end - 2));
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) settle(whhT[ks]);
+        asm volatile("" : "+v"(set_a.w2), "+v"(set_a.gq_raw), "+v"(set_a.fil), "+v"(set_a.u), "+v"(set_a.u_ahead), "+v"(carry));
+        asm volatile("" : "+v"(set_b.w2), "+v"(set_b.gq_raw), "+v"(set_b.fil), "+v"(set_b.u), "+v"(set_b.u_ahead));
+
+        auto back_product = [&](int t) {                           // carry += W_hh^T adjoints(t)
+#pragma unroll
+            for (int ks = 0; ks < 3 * KS; ++ks) mma16<P>(carry, whhT[ks], operand(da_at(t) + (ks < 2 * KS ? ks : ks + KS) * kFrag));
+        };
+        auto step = [&](const In &in, In &nxt, int t) {
+            fetch(nxt, t - 2, in.u_ahead);
+            f32x4 fac[Bs::kFactors];
+#pragma unroll
+            for (int f = 0; f < Bs::kFactors; ++f) fac[f] = *fac_of(t, f);
+            back_product(t + 1);
+            const float gq = (valid && in.fil) ? in.gq_raw : 0.0f;
+            f32x4 dan, dar, daz, dahn;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float dht = carry[r] + gq * in.w2[r];        // Q_t[u] = W2[u] . h_t + b2[u]
+                dan[r] = dht * fac[0][r];
+                dahn[r] = dan[r] * fac[1][r];
+                dar[r] = dan[r] * fac[2][r];
+                daz[r] = dht * fac[3][r];
+                carry[r] = dht * fac[4][r];
+            }
+            publish(da_at(t) + 0 * KS * kFrag, dar);
+            publish(da_at(t) + 1 * KS * kFrag, daz);
+            publish(da_at(t) + 2 * KS * kFrag, dan);
+            publish(da_at(t) + 3 * KS * kFrag, dahn);
+            const uint32_t m = btn0 + (uint32_t)t * N, at = m * 4 * H + unit0;
+            store4(dan, da_buf, at + 0 * H, drop);
+            store4(dar, da_buf, at + 1 * H, drop);
+            store4(daz, da_buf, at + 2 * H, drop);
+            store4(dahn, da_buf, at + 3 * H, drop);
+            f32x4 v;                                               // the adjoint of Q_t, dense
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (16 * w + 4 * q4 + r == in.u) ? gq : 0.0f;
+            store4(v, dq_buf, m * a.a16 + 16 * w + 4 * q4, drop_dq);
+            lds_barrier();
+        };
+        lds_barrier();                                             // biases, zeros, the last slot's x and h
+        lds_barrier();                                             // its factors
+        for (int t = a.t_end - 1;;) {
+            step(set_a, set_c, t);
+            if (--t < a.t_begin) break;
+            step(set_b, set_a, t);
+            if (--t < a.t_begin) break;
+            step(set_c, set_b, t);
+            if (--t < a.t_begin) break;
+        }
+        if (a.t_begin > 0) {
+            back_product(a.t_begin);
+            *reinterpret_cast<f32x4 *>(a.carry + carry_at) = carry;
+        }
+    } else {
+        // ---------------------------------------------------------------- gate wave
+        const __amdgpu_buffer_rsrc_t pre_buf = __builtin_amdgcn_make_buffer_rsrc(a.dpre1, 0, (int)(uint32_t)(samples * H * kElem), kRawBuffer);
+        WFrag<P> whh[3][KS], wih[3][KS], wihT[3 * KS];
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const size_t at = ((size_t)((gate * FBK + w) * KS + ks) * P) * 64 + lane;
+                whh[gate][ks] = load_wfrag<P>(net.whh_16 + at);
+                wih[gate][ks] = load_wfrag<P>(net.wih_16 + at);
+            }
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) wihT[ks] = load_wfrag<P>(net.wihT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+
+        // x of a one-plane network stays the bf16 that it is in memory: an operand as it lies
+        using XRegs = std::conditional_t<P == 1, uint2, f32x4>;
+        struct In { f32x4 h; XRegs x; };
+        const uint32_t saved0 = ((uint32_t)b * S * N + n) * H + unit0;
+        auto fetch = [&](In &in, int t) {
+            const uint32_t at = saved0 + (uint32_t)max(t, 0) * (uint32_t)(N * H);
+            in.h = *reinterpret_cast<const f32x4 *>(a.h_all + at);
+            in.x = *reinterpret_cast<const XRegs *>(static_cast<const char *>(a.x_all) + (size_t)at * kElem);
+        };
+        uint32_t positive = 0;                                     // x > 0 of the slots put down so far, four bits each
+        auto put_down = [&](const In &in, int t) {
+            publish(Bs::oH + (t & 1) * KS * kFrag, in.h);
+            uint32_t bits = 0;
+            if constexpr (P == 1) {
+                char *at = lds + Bs::oX + (t & 1) * KS * kFrag + (w / 2) * kFrag + lane * 16 + (w & 1) * 8;
+                *reinterpret_cast<uint2 *>(at) = in.x;
+                bits = (__uint_as_float(in.x.x << 16) > 0.0f ? 1u : 0u) | (__uint_as_float(in.x.x & 0xFFFF0000u) > 0.0f ? 2u : 0u)
+                       | (__uint_as_float(in.x.y << 16) > 0.0f ? 4u : 0u) | (__uint_as_float(in.x.y & 0xFFFF0000u) > 0.0f ? 8u : 0u);
+            } else {
+                publish(Bs::oX + (t & 1) * KS * kFrag, in.x);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bits |= in.x[r] > 0.0f ? 1u << r : 0u;
+            }
+            positive = positive << 4 | bits;
+        };
+        auto gates = [&](const In &in, int t) {
+            f32x4 acc_r = load_feature4(bias_lds, w, q4), acc_z = load_feature4(bias_lds + H, w, q4);
+            f32x4 acc_in = load_feature4(bias_lds + 2 * H, w, q4), acc_hn = load_feature4(bias_lds + 3 * H, w, q4);
+            f32x4 *const acc_h[3] = {&acc_r, &acc_z, &acc_hn}, *const acc_x[3] = {&acc_r, &acc_z, &acc_in};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const WFrag<P> *const wh[3] = {&whh[0][ks], &whh[1][ks], &whh[2][ks]}, *const wx[3] = {&wih[0][ks], &wih[1][ks], &wih[2][ks]};
+                mma16_across<P, 3>(acc_h, wh, operand(Bs::oH + ((t & 1) * KS + ks) * kFrag));
+                mma16_across<P, 3>(acc_x, wx, operand(Bs::oX + ((t & 1) * KS + ks) * kFrag));
+            }
+            f32x4 fac[Bs::kFactors];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float rr = sigmoidf_fast(acc_r[r]), zz = sigmoidf_fast(acc_z[r]);
+                const float nn = tanhf_fast(acc_in[r] + rr * acc_hn[r]);
+                fac[0][r] = (1.0f - zz) * (1.0f - nn * nn);        // dL/dh_t -> n
+                fac[1][r] = rr;                                    // n -> n hidden side
+                fac[2][r] = acc_hn[r] * rr * (1.0f - rr);          // n -> r
+                fac[3][r] = (in.h[r] - nn) * zz * (1.0f - zz);     // dL/dh_t -> z
+                fac[4][r] = zz;                                    // dL/dh_t -> what passes the cell by
+            }
+#pragma unroll
+            for (int f = 0; f < Bs::kFactors; ++f) *fac_of(t, f) = fac[f];
+        };
+        // dpre1 of slot t, whose x was put down `ago` slots before the last
+        auto input_side = [&](int t, int ago, uint32_t drop_mask) {
+            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < 3 * KS; ++ks) mma16<P>(acc, wihT[ks], operand(da_at(t) + ks * kFrag));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = positive >> (4 * ago + r) & 1u ? acc[r] : 0.0f;
+            store4(acc, pre_buf, (btn0 + (uint32_t)t * N) * H + unit0, drop_mask);
+        };
+        In set_a, set_b, set_c;                                    // in turn: slot t-1's, slot t-2's, the one asked for
+        fetch(set_c, a.t_end - 1);
+        fetch(set_a, a.t_end - 2);
+        fetch(set_b, a.t_end - 3);
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) { settle(whh[gate][ks]); settle(wih[gate][ks]); }
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) settle(wihT[ks]);
+        for (In *in : {&set_a, &set_b, &set_c}) {
+            asm volatile("" : "+v"(in->h));
+            if constexpr (P == 1) asm volatile("" : "+v"(in->x.x), "+v"(in->x.y));
+            else asm volatile("" : "+v"(in->x));
+        }
+        put_down(set_c, a.t_end - 1);
+        lds_barrier();
+        gates(set_c, a.t_end - 1);
+        put_down(set_a, a.t_end - 2);
+        lds_barrier();
+        auto step = [&](const In &at_gates, const In &next, In &asked, int t) {
+            fetch(asked, t - 3);
+            gates(at_gates, t - 1);
+            input_side(t + 1, 2, t + 1 < a.t_end ? drop : kDrop);
+            put_down(next, t - 2);
+            lds_barrier();
+        };
+        for (int t = a.t_end - 1;;) {
+            step(set_a, set_b, set_c, t);
+            if (--t < a.t_begin) break;
+            step(set_b, set_c, set_a, t);
+            if (--t < a.t_begin) break;
+            step(set_c, set_a, set_b, t);
+            if (--t < a.t_begin) break;
+        }
+        input_side(a.t_begin, 2, drop);
     }
 }
 
@@ -973,6 +1254,17 @@ hipError_t back_dispatch(const BpttArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
+template <int P>
+hipError_t back_split_dispatch(const BpttArgs &a, hipStream_t stream)
+{
+    const int tiles = (a.B * a.net.N + 15) / 16;
+    hipError_t err = allow_large_lds<bptt_back_split_kernel<P>>(kLdsLimit);
+    if (err != hipSuccess) return err;
+    constexpr size_t kLds = BpttSplit<P>::kBytes;
+    hipLaunchKernelGGL((bptt_back_split_kernel<P>), dim3(tiles), dim3(512), kLds, stream, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 size_t tn_partial_bytes(long M, int chunk, int P, int q_total)
@@ -1188,8 +1480,8 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     a.carry = reinterpret_cast<float *>(ws + plan.off_carry);
     auto reverse = [&](int t_begin, int t_end, hipStream_t on) {
         a.t_begin = t_begin; a.t_end = t_end;
-        if (H == 64 && net.planes == 2) return back_dispatch<64, 2, 4>(a, on);
-        if (H == 64 && net.planes == 1) return back_dispatch<64, 1, 4>(a, on);
+        if (H == 64 && net.planes == 2) return back_split_dispatch<2>(a, on);
+        if (H == 64 && net.planes == 1) return back_split_dispatch<1>(a, on);
         if (H == 128 && net.planes == 1) return back_dispatch<128, 1, 8>(a, on);
         return hipErrorInvalidValue;
     };

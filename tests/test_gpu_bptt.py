@@ -104,6 +104,20 @@ def test_gradient_matches_the_oracle(ci, B, T, over):
     net.close()
 
 
+# The reverse recurrence of a 64-unit network walks the slots in an unrolled loop of three with two slots of inputs in
+# flight: the fewest slots, every remainder, and row counts on both sides of a tile of sixteen.
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("dtype,B,N", [("fp32", 1, 2), ("fp32", 17, 1), ("bf16", 5, 3), ("bf16", 16, 1)])
+def test_gradient_of_the_fewest_slots(dtype, B, N, T):
+    cfg = dict(wl.config(0), dtype=dtype, N=N, B=B, T=T)
+    w = wl.make_weights(cfg, 0)
+    u = wl.make_unroll_inputs(cfg, B=B, T=T)
+    g = np.random.default_rng(7).standard_normal(u["actions"].shape).astype(np.float32)
+    net = binding.QNet(wl.dims(cfg), w, dtype)
+    compare(cfg, gpu_grad(net, cfg, u, g), *oracle_grad(cfg, w, u, g))
+    net.close()
+
+
 def test_full_size_launch_on_a_few_live_episodes():
     """The workload's full batch in the launch configuration the benchmark times; the upstream gradient is
     non-zero for three episodes only, so the oracle has to walk just those (the sum is linear in it), while
