@@ -1222,7 +1222,12 @@ Plan make_plan(const NetFrags &net, int B, int T)
     const size_t R = (size_t)B * net.N, S = (size_t)T + 1, H = net.H;
     p.a16 = (net.A + 15) / 16 * 16;
     const long M = (long)R * T;
-    p.chunks = (int)std::min<long>(256, (M + 31) / 32);
+    // Every chunk's partial sums are written once and read once more, up to 221 KB each, where 32 samples are 60 KB at
+    // most: few chunks for few samples.  Two planes: the products of a launch come in pairs, 128 chunks each, which
+    // are the chip's 256 compute units once, where up to 256 each were one wave and a part of another.  One plane
+    // (products alone in their launch too): 256 once every chunk has 128 samples.  Learner iterations against up to 256
+    // chunks of any size: 64 x 120 x 5 fp32 502 -> 481 us (with 128 chunks), 37 x 83 x 5 bf16 292 -> 280 us (with 120).
+    p.chunks = (int)(net.planes == 2 ? std::min<long>(128, (M + 31) / 32) : std::min<long>(256, (M + 127) / 128));
     if (p.chunks < 1) p.chunks = 1;
     p.chunk = (int)(((M + p.chunks - 1) / p.chunks + 63) / 64 * 64);      // whole rounds of two steps of 32 samples
     size_t off = 0;
@@ -1232,7 +1237,9 @@ Plan make_plan(const NetFrags &net, int B, int T)
     p.off_dpre1 = off;  off = align_up(off + R * T * H * adj + 4);
     p.off_dq = off;     off = align_up(off + R * T * p.a16 * adj + 4);
     // the four products run together: room for all their partial results
-    const long chunks_real = (M + p.chunk - 1) / p.chunk;
+    // (one-plane networks: or the two halves' chunks, of 64 samples or more, up to 128 each)
+    const long chunks_own = (M + p.chunk - 1) / p.chunk;
+    const long chunks_real = net.planes == 1 ? std::max(chunks_own, std::min<long>(128, M / 128 + 1)) : chunks_own;
     auto part = [&](size_t P, size_t Qt) { return (size_t)chunks_real * (P > 128 ? 384 : 128) * ((Qt + 15) / 16 * 16) * 4; };
     // (one-plane networks: twice, for the two halves of the slots whose products run apart, each in up to 256 chunks)
     const size_t need = (net.planes == 1 ? 2 : 1) * (2 * part(3 * H, H + 1) + part(H, (size_t)net.D + net.N) + part(net.A, H + 1));
