@@ -10,8 +10,7 @@
 //                                      pre-activations, and carries dL/dh back through W_hh^T; W_ih^T gives
 //                                      the adjoint of x and, through the ReLU, of fc1's pre-activation.  All
 //                                      four GRU matrices stay on chip: W_hh, W_hh^T and W_ih^T as operand
-//                                      fragments in registers (four waves, one per SIMD, up to 512 registers
-//                                      each), W_ih in LDS.  The adjoints go to global memory.
+//                                      fragments in registers (eight waves, two per SIMD), W_ih in LDS.  The adjoints go to global memory.
 //   bptt_back_split_kernel             the same for 64 hidden units, the recurrence's chain and everything that hangs
 //                                      on nothing behind it on different waves
 //   tn_gemm_kernel                     the weight gradients are sums over all (row, slot) samples of outer
@@ -94,8 +93,8 @@ __device__ __forceinline__ void publish_blocks(bf16x8 (*dst)[P][64], int w, int 
     }
 }
 
-// NW waves share the H / 16 blocks of hidden units: four waves (one per SIMD, up to 512 registers) or eight
-// (two per SIMD, one block each, so that one wave's waits are another's work).
+// NW waves share the H / 16 blocks of hidden units; launched for 128 units with eight (two per SIMD, one block each,
+// so that one wave's waits are another's work).
 template <int H, int P, int NW>
 __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
 {
