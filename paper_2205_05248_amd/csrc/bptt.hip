@@ -341,22 +341,25 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
 // dL/dh_t -> adjoints -> dL/dh_{t-1} is a chain; the gates of a slot and the adjoint of x hang on nothing behind them.
 // Eight waves, two per SIMD: in the step of slot t
 //
-//   chain waves 0..3  dL/dh_t = carry + W_hh^T adjoints(t+1), then slot t's adjoints from its gate factors, to LDS as
-//                     operand and to memory
-//   gate waves 4..7   W_ih^T adjoints(t+1) -> dpre1 of slot t+1; the gates of slot t-1 -> factors, in LDS; x and h of
-//                     slot t-2 to LDS as operand, the loads of slot t-3
+//   chain waves 0..3  dL/dh_t = carry + W_hh^T adjoints(t+1), beside it W_ih^T adjoints(t+1) -> dpre1 of slot t+1 (the
+//                     same operands, and matrix instructions that do not wait for each other), then slot t's
+//                     adjoints from its gate factors, to LDS as operand and to memory
+//   gate waves 4..7   the gates of slot t-1 -> factors, in LDS; x and h of slot t-2 to LDS as operand, the loads of
+//                     slot t-3
 //
 // and ONE barrier per slot.  Every LDS buffer is double-buffered on the parity of its slot: written in one step, read
 // in the next, written again only in the one after.  All weights are in registers.  Waves w and w + 4 own the same
 // 16 units, in the same lanes.  Measured on the whole learner iteration (mixer and products included): 64 episodes of
-// 120 slots x 5 agents, fp32, 562 -> 502 us; 4 x 60 x 3 fp32 247 -> 220 us; 37 x 83 x 5 bf16 316 -> 292 us.
+// 120 slots x 5 agents, fp32, 562 -> 502 us; 4 x 60 x 3 fp32 247 -> 220 us; 37 x 83 x 5 bf16 316 -> 292 us.  With the
+// adjoint of x on the gate waves, which then issue more than the chain does; on the chain waves another 481 -> 468,
+// 220 -> 215 and 281 -> 278 us (figures after the products' chunks had changed).
 // (128 hidden units keep bptt_back_kernel: eight waves already hold 144 registers of weights each, and its one-barrier
 // form took 327 us per hundred slots against 313.)
 template <int P> struct BpttSplit {
     static constexpr int H = 64, KS = H / 32, FBK = H / 16, kFrag = P * 1024;
     static constexpr int kFactors = 5;
     static constexpr int oH = 0, oX = oH + 2 * KS * kFrag, oDa = oX + 2 * KS * kFrag, kDaBytes = 4 * KS * kFrag;
-    static constexpr int oFac = oDa + 2 * kDaBytes, kFacBytes = kFactors * FBK * 1024;
+    static constexpr int oFac = oDa + 2 * kDaBytes, kFacBytes = kFactors * FBK * 1024 + FBK * 256;      // five factors of every unit, and four bits a lane: x > 0
     static constexpr int oBias = oFac + 2 * kFacBytes, kBytes = oBias + 4 * H * 4;       // biases r, z, n input side, n hidden side
 };
 
@@ -408,6 +411,7 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
     };
     auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
     auto fac_of = [&](int t, int f) { return reinterpret_cast<f32x4 *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + (f * FBK + w) * 1024) + lane; };
+    auto bits_of = [&](int t) { return reinterpret_cast<uint32_t *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + Bs::kFactors * FBK * 1024 + w * 256) + lane; };
     uint32_t drop = valid ? 0u : kDrop;
     asm volatile("" : "+v"(drop));
     const uint32_t bt0 = (uint32_t)b * T, btn0 = bt0 * N + n;      // the host bounds 4 H samples to 2^30
@@ -417,9 +421,13 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
         const __amdgpu_buffer_rsrc_t da_buf = __builtin_amdgcn_make_buffer_rsrc(a.da, 0, (int)(uint32_t)(samples * 4 * H * kElem), kRawBuffer);
         const __amdgpu_buffer_rsrc_t dq_buf = __builtin_amdgcn_make_buffer_rsrc(a.dq, 0, (int)(uint32_t)(samples * a.a16 * kElem), kRawBuffer);
         const uint32_t drop_dq = (16 * w < a.a16) ? drop : kDrop;  // wave w writes block w of the row's dQ
-        WFrag<P> whhT[3 * KS];
+        const __amdgpu_buffer_rsrc_t pre_buf = __builtin_amdgcn_make_buffer_rsrc(a.dpre1, 0, (int)(uint32_t)(samples * H * kElem), kRawBuffer);
+        WFrag<P> whhT[3 * KS], wihT[3 * KS];
 #pragma unroll
-        for (int ks = 0; ks < 3 * KS; ++ks) whhT[ks] = load_wfrag<P>(net.whhT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+        for (int ks = 0; ks < 3 * KS; ++ks) {
+            whhT[ks] = load_wfrag<P>(net.whhT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+            wihT[ks] = load_wfrag<P>(net.wihT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+        }
         {
             const int i = (int)threadIdx.x, gate = i / H, j = i % H;      // 256 threads, 4 H biases
             const float *src = gate == 0 ? net.bias_r : gate == 1 ? net.bias_z : gate == 2 ? net.bias_in : net.bias_hn;
@@ -448,20 +456,31 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
         fetch(set_a, a.t_end - 1, action(a.t_end - 1));
         fetch(set_b, a.t_end - 2, action(a.t_end - 2));
 #pragma unroll
-        for (int ks = 0; ks < 3 * KS; ++ks) settle(whhT[ks]);
+        for (int ks = 0; ks < 3 * KS; ++ks) { settle(whhT[ks]); settle(wihT[ks]); }
         asm volatile("" : "+v"(set_a.w2), "+v"(set_a.gq_raw), "+v"(set_a.fil), "+v"(set_a.u), "+v"(set_a.u_ahead), "+v"(carry));
         asm volatile("" : "+v"(set_b.w2), "+v"(set_b.gq_raw), "+v"(set_b.fil), "+v"(set_b.u), "+v"(set_b.u_ahead));
 
-        auto back_product = [&](int t) {                           // carry += W_hh^T adjoints(t)
+        uint32_t positive = 0;                                     // x > 0 of the slot whose adjoints were formed last
+        auto back_product = [&](int t, uint32_t drop_mask) {       // carry += W_hh^T adjoints(t); dpre1 of slot t
+            f32x4 accx = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int ks = 0; ks < 3 * KS; ++ks) mma16<P>(carry, whhT[ks], operand(da_at(t) + (ks < 2 * KS ? ks : ks + KS) * kFrag));
+            for (int ks = 0; ks < 3 * KS; ++ks) {
+                const Frag<P> di = operand(da_at(t) + ks * kFrag);
+                const Frag<P> dhid = ks < 2 * KS ? di : operand(da_at(t) + (ks + KS) * kFrag);
+                mma16<P>(carry, whhT[ks], dhid);
+                mma16<P>(accx, wihT[ks], di);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) accx[r] = positive >> r & 1u ? accx[r] : 0.0f;
+            store4(accx, pre_buf, (btn0 + (uint32_t)t * N) * H + unit0, drop_mask);
         };
         auto step = [&](const In &in, In &nxt, int t) {
             fetch(nxt, t - 2, in.u_ahead);
             f32x4 fac[Bs::kFactors];
 #pragma unroll
             for (int f = 0; f < Bs::kFactors; ++f) fac[f] = *fac_of(t, f);
-            back_product(t + 1);
+            back_product(t + 1, t + 1 < a.t_end ? drop : kDrop);
+            positive = *bits_of(t);
             const float gq = (valid && in.fil) ? in.gq_raw : 0.0f;
             f32x4 dan, dar, daz, dahn;
 #pragma unroll
@@ -498,14 +517,11 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
             step(set_c, set_b, t);
             if (--t < a.t_begin) break;
         }
-        if (a.t_begin > 0) {
-            back_product(a.t_begin);
-            *reinterpret_cast<f32x4 *>(a.carry + carry_at) = carry;
-        }
+        back_product(a.t_begin, drop);
+        if (a.t_begin > 0) *reinterpret_cast<f32x4 *>(a.carry + carry_at) = carry;
     } else {
         // ---------------------------------------------------------------- gate wave
-        const __amdgpu_buffer_rsrc_t pre_buf = __builtin_amdgcn_make_buffer_rsrc(a.dpre1, 0, (int)(uint32_t)(samples * H * kElem), kRawBuffer);
-        WFrag<P> whh[3][KS], wih[3][KS], wihT[3 * KS];
+        WFrag<P> whh[3][KS], wih[3][KS];
 #pragma unroll
         for (int gate = 0; gate < 3; ++gate)
 #pragma unroll
@@ -514,9 +530,6 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
                 whh[gate][ks] = load_wfrag<P>(net.whh_16 + at);
                 wih[gate][ks] = load_wfrag<P>(net.wih_16 + at);
             }
-#pragma unroll
-        for (int ks = 0; ks < 3 * KS; ++ks) wihT[ks] = load_wfrag<P>(net.wihT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
-
         // x of a one-plane network stays the bf16 that it is in memory: an operand as it lies
         using XRegs = std::conditional_t<P == 1, uint2, f32x4>;
         struct In { f32x4 h; XRegs x; };
@@ -526,7 +539,7 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
             in.h = *reinterpret_cast<const f32x4 *>(a.h_all + at);
             in.x = *reinterpret_cast<const XRegs *>(static_cast<const char *>(a.x_all) + (size_t)at * kElem);
         };
-        uint32_t positive = 0;                                     // x > 0 of the slots put down so far, four bits each
+        uint32_t positive = 0;                                     // x > 0 of the slot put down last
         auto put_down = [&](const In &in, int t) {
             publish(Bs::oH + (t & 1) * KS * kFrag, in.h);
             uint32_t bits = 0;
@@ -540,7 +553,7 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) bits |= in.x[r] > 0.0f ? 1u << r : 0u;
             }
-            positive = positive << 4 | bits;
+            positive = bits;
         };
         auto gates = [&](const In &in, int t) {
             f32x4 acc_r = load_feature4(bias_lds, w, q4), acc_z = load_feature4(bias_lds + H, w, q4);
@@ -565,15 +578,7 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
             }
 #pragma unroll
             for (int f = 0; f < Bs::kFactors; ++f) *fac_of(t, f) = fac[f];
-        };
-        // dpre1 of slot t, whose x was put down `ago` slots before the last
-        auto input_side = [&](int t, int ago, uint32_t drop_mask) {
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int ks = 0; ks < 3 * KS; ++ks) mma16<P>(acc, wihT[ks], operand(da_at(t) + ks * kFrag));
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = positive >> (4 * ago + r) & 1u ? acc[r] : 0.0f;
-            store4(acc, pre_buf, (btn0 + (uint32_t)t * N) * H + unit0, drop_mask);
+            *bits_of(t) = positive;
         };
         In set_a, set_b, set_c;                                    // in turn: slot t-1's, slot t-2's, the one asked for
         fetch(set_c, a.t_end - 1);
@@ -583,8 +588,6 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
         for (int gate = 0; gate < 3; ++gate)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) { settle(whh[gate][ks]); settle(wih[gate][ks]); }
-#pragma unroll
-        for (int ks = 0; ks < 3 * KS; ++ks) settle(wihT[ks]);
         for (In *in : {&set_a, &set_b, &set_c}) {
             asm volatile("" : "+v"(in->h));
             if constexpr (P == 1) asm volatile("" : "+v"(in->x.x), "+v"(in->x.y));
@@ -598,7 +601,6 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
         auto step = [&](const In &at_gates, const In &next, In &asked, int t) {
             fetch(asked, t - 3);
             gates(at_gates, t - 1);
-            input_side(t + 1, 2, t + 1 < a.t_end ? drop : kDrop);
             put_down(next, t - 2);
             lds_barrier();
         };
@@ -610,7 +612,6 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
             step(set_c, set_a, set_b, t);
             if (--t < a.t_begin) break;
         }
-        input_side(a.t_begin, 2, drop);
     }
 }
 
