@@ -39,6 +39,7 @@
 #include <algorithm>
 
 #include "fused16_roles.h"
+#include "grad_chunks.h"
 
 namespace marl {
 
@@ -1212,7 +1213,8 @@ size_t align_up(size_t v) { return (v + 255) / 256 * 256; }
 
 struct Plan {
     size_t off_h, off_x, off_da, off_dpre1, off_dq, off_carry, off_partial, partial_bytes, bytes;
-    int a16, chunks, chunk;
+    int a16;
+    GradChunks cut;
 };
 
 Plan make_plan(const NetFrags &net, int B, int T)
@@ -1221,28 +1223,16 @@ Plan make_plan(const NetFrags &net, int B, int T)
     const size_t adj = net.planes == 1 ? 2 : 4;                    // bytes per stored adjoint
     const size_t R = (size_t)B * net.N, S = (size_t)T + 1, H = net.H;
     p.a16 = (net.A + 15) / 16 * 16;
-    const long M = (long)R * T;
-    // Every chunk's partial sums are written once and read once more, up to 221 KB each, where 32 samples are 60 KB at
-    // most: few chunks for few samples.  Two planes: the products of a launch come in pairs, 128 chunks each, which
-    // are the chip's 256 compute units once, where up to 256 each were one wave and a part of another.  One plane
-    // (products alone in their launch too): 256 once every chunk has 128 samples.  Learner iterations against up to 256
-    // chunks of any size: 64 x 120 x 5 fp32 502 -> 481 us (with 128 chunks), 37 x 83 x 5 bf16 292 -> 280 us (with 120).
-    p.chunks = (int)(net.planes == 2 ? std::min<long>(128, (M + 31) / 32) : std::min<long>(256, (M + 127) / 128));
-    if (p.chunks < 1) p.chunks = 1;
-    p.chunk = (int)(((M + p.chunks - 1) / p.chunks + 63) / 64 * 64);      // whole rounds of two steps of 32 samples
+    p.cut = grad_chunks(net.planes, (long)R, T);
     size_t off = 0;
     p.off_h = off;      off = align_up(off + R * S * H * 4);
     p.off_x = off;      off = align_up(off + R * S * H * adj + 4);         // x: bf16 for a one-plane network
     p.off_da = off;     off = align_up(off + R * T * 4 * H * adj + 4);
     p.off_dpre1 = off;  off = align_up(off + R * T * H * adj + 4);
     p.off_dq = off;     off = align_up(off + R * T * p.a16 * adj + 4);
-    // the four products run together: room for all their partial results
-    // (one-plane networks: or the two halves' chunks, of 64 samples or more, up to 128 each)
-    const long chunks_own = (M + p.chunk - 1) / p.chunk;
-    const long chunks_real = net.planes == 1 ? std::max(chunks_own, std::min<long>(128, M / 128 + 1)) : chunks_own;
-    auto part = [&](size_t P, size_t Qt) { return (size_t)chunks_real * (P > 128 ? 384 : 128) * ((Qt + 15) / 16 * 16) * 4; };
-    // (one-plane networks: twice, for the two halves of the slots whose products run apart, each in up to 256 chunks)
-    const size_t need = (net.planes == 1 ? 2 : 1) * (2 * part(3 * H, H + 1) + part(H, (size_t)net.D + net.N) + part(net.A, H + 1));
+    // room for the partial sums of all four products, whichever way the slots are walked
+    auto part = [&](size_t P, size_t Qt) { return (size_t)p.cut.room * (P > 128 ? 384 : 128) * ((Qt + 15) / 16 * 16) * 4; };
+    const size_t need = 2 * part(3 * H, H + 1) + part(H, (size_t)net.D + net.N) + part(net.A, H + 1);
     p.partial_bytes = need;
     p.off_carry = off;  off = align_up(off + (R + 15) / 16 * 16 * H * 4);
     p.off_partial = off; off = align_up(off + need);
@@ -1525,28 +1515,20 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     // The reverse recurrence is one workgroup per 16 rows: a batch with fewer tiles than compute units leaves the
     // rest of the chip idle for as long as the episodes are.  Then the slots are walked in two launches, and the
     // products over the later half run on a second stream beside the earlier half's recurrence.
-    const int tiles = (B * N + 15) / 16, t_mid = T / 2;
-    bool split = side && side->stream && net.planes == 1 && T >= 16 && 2 * tiles <= 3 * n_cu / 2;
+    const int tiles = (B * N + 15) / 16, t_mid = plan.cut.t_mid;
+    const SampleChunks &cut_late = plan.cut.late, &cut_early = plan.cut.early;
+    bool split = side && side->stream && net.planes == 1 && T >= kForkSlots && 2 * tiles <= 3 * n_cu / 2;
     Four late{}, early{};
-    long m_late = 0, m_early = 0;
     if (split) {
         late = products_of(t_mid, T); early = products_of(0, t_mid);
-        m_late = (long)B * N * (T - t_mid); m_early = (long)B * N * t_mid;
-        for (int i = 0; i < 4 && split; ++i) split = tn_wide_fits(late.p[i], m_late) && tn_wide_fits(early.p[i], m_early);
+        for (int i = 0; i < 4 && split; ++i) split = tn_wide_fits(late.p[i], cut_late.samples) && tn_wide_fits(early.p[i], cut_early.samples);
     }
     if (!split) {
         err = reverse(0, T, stream);
         if (err != hipSuccess) return err;
         const Four all = products_of(0, T);
-        return launch_tn_products(net.planes, all.p, 4, (long)B * N * T, plan.chunk, partial, plan.partial_bytes, stream);
+        return launch_tn_products(net.planes, all.p, 4, plan.cut.whole.samples, plan.cut.whole.chunk, partial, plan.partial_bytes, stream);
     }
-    // the later half's products share the chip with the recurrence, whose workgroups hold half the compute units
-    // or less: half as many chunks (every chunk's partial sums are written once and read once more)
-    auto chunk_of = [](long m, long most) { const long chunks = std::max<long>(1, std::min<long>(most, (m + 31) / 32)); return (int)(((m + chunks - 1) / chunks + 63) / 64 * 64); };
-    // (the earlier half's too: its two GRU products then run side by side, one on each stream, 128 workgroups each;
-    // 256 chunks for the first layer's product, which runs last and alone, changed nothing)
-    const int chunk_late = chunk_of(m_late, 128), chunk_early = chunk_of(m_early, 128);
-    const int chunks_late = (int)((m_late + chunk_late - 1) / chunk_late), chunks_early = (int)((m_early + chunk_early - 1) / chunk_early);
     // a product's partial sums: the later half's chunks, then the earlier half's, summed in that order
     float *part_late[4], *part_early[4];
     TnReduceBatch red{};
@@ -1557,10 +1539,10 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
             const TnProduct &t = late.p[i];
             const size_t p_pad = t.P > 128 ? 384 : 128, qp = (size_t)(t.Q + t.n_extra + 15) / 16 * 16;
             part_late[i] = reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used);
-            part_early[i] = part_late[i] + (size_t)chunks_late * p_pad * qp;
-            used += (size_t)(chunks_late + chunks_early) * p_pad * qp * sizeof(float);
+            part_early[i] = part_late[i] + (size_t)cut_late.chunks * p_pad * qp;
+            used += (size_t)(cut_late.chunks + cut_early.chunks) * p_pad * qp * sizeof(float);
             TnReduceArgs r{};
-            r.partial = part_late[i]; r.chunks = chunks_late + chunks_early; r.P = t.P; r.p_pad = (int)p_pad; r.qp = (int)qp;
+            r.partial = part_late[i]; r.chunks = cut_late.chunks + cut_early.chunks; r.P = t.P; r.p_pad = (int)p_pad; r.qp = (int)qp;
             r.Q = t.Q; r.n_extra = t.n_extra; r.extra_mode = t.extra_mode;
             r.row_shift = t.row_shift; r.w_cols = t.Q; r.ld_w = t.ld_w; r.dst_w = t.dst_w; r.dst_b = t.dst_b;
             red.r[i] = r;
@@ -1571,16 +1553,16 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     err = reverse(t_mid, T, stream);
     if (err == hipSuccess) err = hipEventRecord(side->fork, stream);
     if (err == hipSuccess) err = hipStreamWaitEvent(side->stream, side->fork, 0);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(late.p, 4, m_late, chunk_late, part_late, side->stream);
+    if (err == hipSuccess) err = launch_tn_gemms_wide(late.p, 4, cut_late.samples, cut_late.chunk, part_late, side->stream);
     if (err == hipSuccess) err = reverse(0, t_mid, stream);
     // the earlier half: W_hh's product follows on the second stream (a second fork: it needs the recurrence's end),
     // the other three on the caller's
     if (err == hipSuccess) err = hipEventRecord(side->fork, stream);
     if (err == hipSuccess) err = hipStreamWaitEvent(side->stream, side->fork, 0);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 1, 1, m_early, chunk_early, part_early + 1, side->stream);
+    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 1, 1, cut_early.samples, cut_early.chunk, part_early + 1, side->stream);
     if (err == hipSuccess) err = hipEventRecord(side->join, side->stream);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p, 1, m_early, chunk_early, part_early, stream);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 2, 2, m_early, chunk_early, part_early + 2, stream);
+    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p, 1, cut_early.samples, cut_early.chunk, part_early, stream);
+    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 2, 2, cut_early.samples, cut_early.chunk, part_early + 2, stream);
     if (err == hipSuccess) err = hipStreamWaitEvent(stream, side->join, 0);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(tn_reduce_kernel, dim3((max_total + 255) / 256, 4), dim3(256), 0, stream, red);
