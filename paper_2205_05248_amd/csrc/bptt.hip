@@ -356,6 +356,10 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
 // 220 -> 215 and 281 -> 278 us (figures after the products' chunks had changed).
 // (128 hidden units keep bptt_back_kernel: eight waves already hold 144 registers of weights each, and its one-barrier
 // form took 327 us per hundred slots against 313.)
+// One plane: 126 registers and 68 KB of LDS, two workgroups per compute unit, asked for with the launch bound.  With one
+// (136 registers) a batch of a few more than 256 tiles walked all its slots twice over: gradient of 820 episodes x 199
+// slots x 5 agents (257 tiles) 1080 -> 1055 us, 4096 x 1 x 5 89 -> 85 us.  The fewer instructions per store help few
+// tiles too: 37 x 83 x 5 148 -> 140 us, two planes 64 x 120 x 5 240 -> 233 us.  (Two planes need 192 registers.)
 template <int P> struct BpttSplit {
     static constexpr int H = 64, KS = H / 32, FBK = H / 16, kFrag = P * 1024;
     static constexpr int kFactors = 5;
@@ -365,7 +369,7 @@ template <int P> struct BpttSplit {
 };
 
 template <int P>
-__global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
+__global__ __launch_bounds__(512, P == 1 ? 4 : 2) void bptt_back_split_kernel(BpttArgs a)
 {
     using Bs = BpttSplit<P>;
     constexpr int H = Bs::H, KS = Bs::KS, FBK = Bs::FBK, kFrag = Bs::kFrag;
@@ -461,6 +465,11 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
         asm volatile("" : "+v"(set_a.w2), "+v"(set_a.gq_raw), "+v"(set_a.fil), "+v"(set_a.u), "+v"(set_a.u_ahead), "+v"(carry));
         asm volatile("" : "+v"(set_b.w2), "+v"(set_b.gq_raw), "+v"(set_b.fil), "+v"(set_b.u), "+v"(set_b.u_ahead));
 
+        // Offsets of the stores: the lane's own part, and the slot's, the same in every lane.  The slot's is hidden from the
+        // compiler, which would otherwise step an address of its own for every store of the unrolled loop (ten registers,
+        // with which two workgroups of a one-plane network do not fit a compute unit).
+        const uint32_t da_lane = btn0 * 4 * H + unit0, pre_lane = btn0 * H + unit0, dq_lane = btn0 * a.a16 + unit0;
+        auto rows_before = [&](int t) { uint32_t r = (uint32_t)t * N; asm volatile("" : "+s"(r)); return r; };
         uint32_t positive = 0;                                     // x > 0 of the slot whose adjoints were formed last
         auto back_product = [&](int t, uint32_t drop_mask) {       // carry += W_hh^T adjoints(t); dpre1 of slot t
             f32x4 accx = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -473,7 +482,7 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) accx[r] = positive >> r & 1u ? accx[r] : 0.0f;
-            store4(accx, pre_buf, (btn0 + (uint32_t)t * N) * H + unit0, drop_mask);
+            store4(accx, pre_buf, pre_lane + rows_before(t) * H, drop_mask);
         };
         auto step = [&](const In &in, In &nxt, int t) {
             fetch(nxt, t - 2, in.u_ahead);
@@ -497,15 +506,15 @@ __global__ __launch_bounds__(512, 2) void bptt_back_split_kernel(BpttArgs a)
             publish(da_at(t) + 1 * KS * kFrag, daz);
             publish(da_at(t) + 2 * KS * kFrag, dan);
             publish(da_at(t) + 3 * KS * kFrag, dahn);
-            const uint32_t m = btn0 + (uint32_t)t * N, at = m * 4 * H + unit0;
+            const uint32_t tn = rows_before(t), at = da_lane + tn * 4 * H;
             store4(dan, da_buf, at + 0 * H, drop);
             store4(dar, da_buf, at + 1 * H, drop);
             store4(daz, da_buf, at + 2 * H, drop);
             store4(dahn, da_buf, at + 3 * H, drop);
             f32x4 v;                                               // the adjoint of Q_t, dense
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = (16 * w + 4 * q4 + r == in.u) ? gq : 0.0f;
-            store4(v, dq_buf, m * a.a16 + 16 * w + 4 * q4, drop_dq);
+            for (int r = 0; r < 4; ++r) v[r] = in.u - unit0 == r ? gq : 0.0f;
+            store4(v, dq_buf, dq_lane + tn * a.a16, drop_dq);
             lds_barrier();
         };
         lds_barrier();                                             // biases, zeros, the last slot's x and h

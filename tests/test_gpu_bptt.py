@@ -89,7 +89,9 @@ CASES = [(0, 4, 6, {}), (0, 32, 25, {}), (1, 5, 9, {}), (2, 7, 12, {}), (3, 33, 
          # first two and the last the halves fill more chunks of partial sums together than all slots at once would
          (2, 3, 17, dict(N=5, D=96, dtype="bf16")), (2, 12, 17, dict(N=5, D=96, dtype="bf16")),
          (2, 2, 19, dict(N=5, D=96, dtype="bf16")), (2, 3, 21, dict(N=5, D=96, dtype="bf16")),
-         (2, 12, 61, dict(N=5, D=96, dtype="bf16")), (4, 12, 17, dict(N=5, D=96, A=11))]
+         (2, 12, 61, dict(N=5, D=96, dtype="bf16")), (4, 12, 17, dict(N=5, D=96, A=11)),
+         # more row tiles than compute units: two workgroups of a bf16 network share one, fp32 ones follow one another
+         (2, 823, 5, dict(N=5, D=24, dtype="bf16")), (2, 823, 3, dict(N=5, D=24))]
 
 
 @pytest.mark.parametrize("ci,B,T,over", CASES, ids=lambda v: str(v).replace(" ", ""))
