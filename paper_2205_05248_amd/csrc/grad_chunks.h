@@ -33,11 +33,12 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
     const long M = rows * T;
     // Every chunk's partial sums are written once and read once more, up to 221 KB each, where 32 samples are 60 KB at
     // most: few chunks for few samples.  Two planes: the products of a launch come in pairs, 128 chunks each, which
-    // are the chip's 256 compute units once, where up to 256 each were one wave and a part of another.  One plane
-    // (a GRU product is alone in its launch): 256 once every chunk has 128 samples.  Learner iterations against up to
-    // 256 chunks of any size: 64 x 120 x 5 fp32 502 -> 481 us (with 128 chunks), 37 x 83 x 5 bf16 with 55 observations
-    // 292 -> 280 us (with 120).
-    g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, 128);
+    // are the chip's 256 compute units once, where up to 256 each were one wave and a part of another; learner iteration
+    // of 64 x 120 x 5 502 -> 481 us.  One plane (a GRU product is alone in its launch): up to 256 chunks, of 64 samples
+    // up to 4096 of them, where the steps that follow one another in a chunk are what takes time (gradient at 576 / 720 /
+    // 2400 samples 71 / 182 / 201 us, with chunks of 128 75 / 188 / 202), of 128 or more beyond, where the partial sums
+    // are (6640 / 15360 samples 274 / 130 us, 271 / 110 with 128; 128 hidden units all).
+    g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, M <= 4096 ? 64 : 128);
     g.room = g.whole.chunks;
     if (planes == 1 && T >= kForkSlots) {
         // the later half's products share the chip with the recurrence, whose workgroups hold half the compute units

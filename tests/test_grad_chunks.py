@@ -53,3 +53,10 @@ def test_partial_sums_of_either_walk_fit_the_workspace(cut, planes):
                 needed = sum(-(-samples // chunk) for _, (samples, chunk, _) in walk)
                 assert needed <= room, (planes, rows, T, needed, room)
             assert room <= 256
+
+
+def test_few_samples_of_a_one_plane_network_are_cut_into_short_chunks(cut):
+    """Up to 4096 samples a chunk's own steps are what takes time: none is longer than 64; beyond, none is shorter than 128."""
+    for M in list(range(1, 4500, 7)) + [4096, 4097, 8192, 32768]:
+        whole = cut(1, M, 1)[0][0]
+        assert whole[1] == 64 if M <= 4096 else whole[1] >= 128
