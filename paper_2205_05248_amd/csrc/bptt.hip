@@ -10,9 +10,10 @@
 //                                      pre-activations, and carries dL/dh back through W_hh^T; W_ih^T gives
 //                                      the adjoint of x and, through the ReLU, of fc1's pre-activation.  All
 //                                      four GRU matrices stay on chip: W_hh, W_hh^T and W_ih^T as operand
-//                                      fragments in registers (eight waves, two per SIMD), W_ih in LDS.  The adjoints go to global memory.
-//   bptt_back_split_kernel             the same for 64 hidden units, the recurrence's chain and everything that hangs
-//                                      on nothing behind it on different waves
+//                                      fragments in registers, W_ih in LDS.  The adjoints go to global memory.
+//                                      128 hidden units, bf16.
+//   bptt_back_split_kernel             the same for 64 hidden units, fp32 and bf16: the recurrence's chain and
+//                                      everything that hangs on nothing behind it on different waves
 //   tn_gemm_kernel                     the weight gradients are sums over all (row, slot) samples of outer
 //                                      products adjoint x activation: C[p][q] = sum_m A[m][p] B[m][q], four
 //                                      times (W_ih, W_hh, W1, W2).  The samples are split into chunks, one
@@ -27,7 +28,7 @@
 //                                      turns the staged rows into fragments.
 //   tn_reduce_kernel                   adds the chunks' partial sums in a fixed order and writes the result
 //                                      into the packed gradient vector.
-// A batch with fewer row tiles than compute units leaves most of the chip idle while bptt_back_kernel walks the
+// A batch with fewer row tiles than compute units leaves most of the chip idle while the reverse recurrence walks the
 // slots.  For a bf16 network the slots are therefore walked in two launches (dL/dh handed over in memory), and the
 // products over the later half run on a second stream of the handle's beside the earlier half's recurrence
 // (launch_qnet_grad); the sum over all chunks, later half first, follows on the caller's stream.
@@ -63,46 +64,61 @@ struct BpttArgs {
     float *carry;
 };
 
-template <int H, int P> struct BpttShape {
-    using Sh = Fused16<H, P>;
-    static constexpr int KS = Sh::KS, FBK = Sh::FBK, NBC = Sh::NBC;
+// The wave's block of 16 units as half a fragment in LDS: two adjacent blocks make one k-step, and a wave writes its
+// half of every lane's 16 bytes.
+template <int P>
+__device__ __forceinline__ void publish_block(bf16x8 (*dst)[P][64], int w, int lane, const f32x4 &v)
+{
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    bf16x4 hi, lo;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        hi[r] = (__bf16)v[r];
+        lo[r] = (__bf16)(v[r] - (float)hi[r]);
+    }
+    char *at = reinterpret_cast<char *>(&dst[w / 2][0][lane]) + (w & 1) * 8;
+    *reinterpret_cast<bf16x4 *>(at) = hi;
+    if constexpr (P == 2) *reinterpret_cast<bf16x4 *>(at + 1024) = lo;
+}
+
+// Every global access inside the loops over the slots is unconditional, so that their bodies are straight-line code and
+// the waits for the prefetched inputs count exactly the stores issued after them: rows past the end store through
+// buffer descriptors at an offset beyond the descriptor, which the hardware drops.
+constexpr uint32_t kDrop = 0xFFFFFFF0u;
+
+// Four adjoints of one lane -> element offset `at` of the array behind `buf`, fp32 or, for a one-plane network, bf16.
+template <int P>
+__device__ __forceinline__ void store_adjoints(const f32x4 &v, const __amdgpu_buffer_rsrc_t &buf, uint32_t at, uint32_t drop_mask)
+{
+    if constexpr (P == 1) {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        bf16x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (__bf16)v[i];
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), buf, (at * 2u) | drop_mask, 0, 0);
+    } else {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), buf, (at * 4u) | drop_mask, 0, 0);
+    }
+}
+
+// 128 hidden units, one plane (two planes do not fit on chip).  Eight waves, two per SIMD, so that one wave's waits are
+// another's work; wave w owns block w of sixteen units.
+struct BpttBack {
+    using Sh = Fused16<128, 1>;
+    static constexpr int H = 128, P = 1, NW = 8, KS = Sh::KS, FBK = Sh::FBK;
+    static_assert(FBK == NW, "one block of hidden units per wave");
     // LDS: W_ih, one buffer of h and x fragments and the gate biases where the forward kernel has them;
     // the adjoint fragments (r, z, n: 3 KS k-steps; n hidden side: KS) where it keeps the observations
     static constexpr int oDa = Sh::oObs, oDhn = oDa + 3 * KS * Sh::kFrag, kBytes = oDhn + KS * Sh::kFrag;
 };
 
-// The wave's blocks of 16 units as operand fragments in LDS: two adjacent blocks make one k-step.  A wave with
-// two blocks writes a whole fragment, a wave with one block its half of every lane's 16 bytes.
-template <int P, int NBC>
-__device__ __forceinline__ void publish_blocks(bf16x8 (*dst)[P][64], int w, int lane, const f32x4 (&v)[NBC])
+__global__ __launch_bounds__(64 * BpttBack::NW, BpttBack::NW / 4) void bptt_back_kernel(BpttArgs a)
 {
-    if constexpr (NBC == 2) {
-        const Frag<P> f = frag_of_pair<P>(v[0], v[1]);
-        dst[w][0][lane] = f.hi;
-        if constexpr (P == 2) dst[w][1][lane] = f.lo;
-    } else {
-        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-        bf16x4 hi, lo;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            hi[r] = (__bf16)v[0][r];
-            lo[r] = (__bf16)(v[0][r] - (float)hi[r]);
-        }
-        char *at = reinterpret_cast<char *>(&dst[w / 2][0][lane]) + (w & 1) * 8;
-        *reinterpret_cast<bf16x4 *>(at) = hi;
-        if constexpr (P == 2) *reinterpret_cast<bf16x4 *>(at + 1024) = lo;
-    }
-}
-
-// NW waves share the H / 16 blocks of hidden units; launched for 128 units with eight (two per SIMD, one block each,
-// so that one wave's waits are another's work).
-template <int H, int P, int NW>
-__global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
-{
-    using Sh = Fused16<H, P>;
-    using Bs = BpttShape<H, P>;
-    constexpr int KS = Sh::KS, FBK = Sh::FBK, NBC = FBK / NW;
-    static_assert(NBC == 1 || NBC == 2, "one or two blocks of hidden units per wave");
+    using Bs = BpttBack;
+    using Sh = Bs::Sh;
+    constexpr int H = Bs::H, P = Bs::P, KS = Bs::KS, FBK = Bs::FBK;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     typedef bf16x8 (*FragBuf)[P][64];
     const FragBuf hf = reinterpret_cast<FragBuf>(lds + Sh::oH), xf = reinterpret_cast<FragBuf>(lds + Sh::oX);
@@ -120,40 +136,35 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
     const int b = valid ? row / N : 0, n = valid ? row % N : 0;
 
     {
-        constexpr int kVecs = 3 * FBK * KS * P * 64;
-        for (int i = threadIdx.x; i < kVecs; i += 64 * NW) wih_lds[i] = net.wih_16[i];
+        constexpr int kVecs = 3 * FBK * KS * 64;
+        for (int i = threadIdx.x; i < kVecs; i += 64 * Bs::NW) wih_lds[i] = net.wih_16[i];
     }
     if (w == 0) GruWave<H, P>::stage_gate_biases(lds, net, lane);
 
-    // this wave's hidden units: blocks NBC w + j; forward W_hh rows of the three gates, and the rows of
-    // W_hh^T and W_ih^T that produce its units of dL/dh and dL/dx
-    WFrag<P> whh[3][NBC][KS], whhT[NBC][3 * KS], wihT[NBC][3 * KS];
-    f32x4 bias_hn[NBC];
+    // this wave's hidden units: forward W_hh rows of the three gates, and the rows of W_hh^T and W_ih^T that produce
+    // its units of dL/dh and dL/dx
+    WFrag<P> whh[3][KS], whhT[3 * KS], wihT[3 * KS];
 #pragma unroll
-    for (int j = 0; j < NBC; ++j) {
-        const int blk = NBC * w + j;
+    for (int gate = 0; gate < 3; ++gate)
 #pragma unroll
-        for (int gate = 0; gate < 3; ++gate)
+        for (int ks = 0; ks < KS; ++ks)
+            whh[gate][ks] = load_wfrag<P>(net.whh_16 + ((size_t)(gate * FBK + w) * KS + ks) * 64 + lane);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                whh[gate][j][ks] = load_wfrag<P>(net.whh_16 + ((size_t)((gate * FBK + blk) * KS + ks) * P) * 64 + lane);
-#pragma unroll
-        for (int ks = 0; ks < 3 * KS; ++ks) {
-            whhT[j][ks] = load_wfrag<P>(net.whhT_16 + ((size_t)(blk * 3 * KS + ks) * P) * 64 + lane);
-            wihT[j][ks] = load_wfrag<P>(net.wihT_16 + ((size_t)(blk * 3 * KS + ks) * P) * 64 + lane);
-        }
-        bias_hn[j] = load_feature4(net.bias_hn, blk, q4);
+    for (int ks = 0; ks < 3 * KS; ++ks) {
+        whhT[ks] = load_wfrag<P>(net.whhT_16 + (size_t)(w * 3 * KS + ks) * 64 + lane);
+        wihT[ks] = load_wfrag<P>(net.wihT_16 + (size_t)(w * 3 * KS + ks) * 64 + lane);
     }
+    const f32x4 bias_hn = load_feature4(net.bias_hn, w, q4);
 
-    const int unit0 = 16 * NBC * w + 4 * q4;                       // + 16 j: the lane's four units of block j
+    const int unit0 = 16 * w + 4 * q4;                             // the lane's four units
     const size_t slot_stride = (size_t)N * H;
     const float *h_row = a.h_all + ((size_t)b * S * N + n) * H + unit0;
-    constexpr int kBytesX = P == 1 ? 2 : 4;
-    const char *x_row = static_cast<const char *>(a.x_all) + (((size_t)b * S * N + n) * H + unit0) * kBytesX;
+    constexpr int kElem = 2;                                       // bytes of an x and of a stored adjoint
+    const char *x_row = static_cast<const char *>(a.x_all) + (((size_t)b * S * N + n) * H + unit0) * kElem;
 
     // The inputs of a slot are asked for one iteration before it; the chosen action, whose row of W2 is one
     // of those inputs, one iteration earlier still.  Nothing here is conditional (rows past the end read row 0).
-    struct StepIn { f32x4 hp[NBC], xv[NBC], w2[NBC]; float gq_raw; uint8_t fil; int u; };
+    struct StepIn { f32x4 hp, w2; uint2 x; float gq_raw; uint32_t fil; int u; };
     auto load_action = [&](int t) { return a.actions[((size_t)b * T + t) * N + n]; };
     auto fetch = [&](int t, int u_raw) {
         StepIn in;
@@ -161,54 +172,20 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
         in.u = min(max(u_raw, 0), A - 1);
         in.fil = a.filled[bt];
         in.gq_raw = a.grad_q[bt * N + n];
-#pragma unroll
-        for (int j = 0; j < NBC; ++j) {
-            in.hp[j] = *reinterpret_cast<const f32x4 *>(h_row + (size_t)t * slot_stride + 16 * j);
-            const char *xp = x_row + ((size_t)t * slot_stride + 16 * j) * kBytesX;
-            if constexpr (P == 1) {      // four bf16 values, widened (bf16 is the upper half of an fp32)
-                const uint2 raw = *reinterpret_cast<const uint2 *>(xp);
-                in.xv[j][0] = __uint_as_float(raw.x << 16); in.xv[j][1] = __uint_as_float(raw.x & 0xFFFF0000u);
-                in.xv[j][2] = __uint_as_float(raw.y << 16); in.xv[j][3] = __uint_as_float(raw.y & 0xFFFF0000u);
-            } else {
-                in.xv[j] = *reinterpret_cast<const f32x4 *>(xp);
-            }
-            in.w2[j] = *reinterpret_cast<const f32x4 *>(net.w2_plain + (size_t)in.u * H + unit0 + 16 * j);
-        }
+        in.hp = *reinterpret_cast<const f32x4 *>(h_row + (size_t)t * slot_stride);
+        in.x = *reinterpret_cast<const uint2 *>(x_row + (size_t)t * slot_stride * kElem);
+        in.w2 = *reinterpret_cast<const f32x4 *>(net.w2_plain + (size_t)in.u * H + unit0);
         return in;
     };
 
-    f32x4 dh[NBC];                                                 // dL/dh flowing into the state after slot t
-    float *const carry_row = a.carry + (size_t)(blockIdx.x * 16 + c) * H + unit0;      // rows past the end have room too
-#pragma unroll
-    for (int j = 0; j < NBC; ++j) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dh[j][r] = 0.0f;
-        if (a.t_end < T) dh[j] = *reinterpret_cast<const f32x4 *>(carry_row + 16 * j);
-    }
+    f32x4 dh = {0.0f, 0.0f, 0.0f, 0.0f};                           // dL/dh flowing into the state after slot t
+    float *const carry_row = a.carry + (size_t)row * H + unit0;    // rows past the end have room too
+    if (a.t_end < T) dh = *reinterpret_cast<const f32x4 *>(carry_row);
 
-    // Every global access inside the loop is unconditional, so that the loop body is straight-line code and
-    // the waits for the prefetched inputs count exactly the stores issued after them: rows past the end
-    // store through buffer descriptors at an offset beyond the descriptor, which the hardware drops.
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr uint32_t kDrop = 0xFFFFFFF0u;
     const size_t samples = (size_t)rows * T;
-    constexpr uint32_t kElem = P == 1 ? 2u : 4u;                   // bytes per stored adjoint
     const __amdgpu_buffer_rsrc_t da_buf = __builtin_amdgcn_make_buffer_rsrc(a.da, 0, (int)(uint32_t)(samples * 4 * H * kElem), kRawBuffer);
     const __amdgpu_buffer_rsrc_t pre_buf = __builtin_amdgcn_make_buffer_rsrc(a.dpre1, 0, (int)(uint32_t)(samples * H * kElem), kRawBuffer);
     const __amdgpu_buffer_rsrc_t dq_buf = __builtin_amdgcn_make_buffer_rsrc(a.dq, 0, (int)(uint32_t)(samples * a.a16 * kElem), kRawBuffer);
-    // four adjoints of one lane -> element offset `at` of the array behind `buf` (dropped for rows past the end)
-    auto store4 = [&](const f32x4 &v, const __amdgpu_buffer_rsrc_t &buf, uint32_t at, uint32_t drop_mask) {
-        if constexpr (P == 1) {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            bf16x4 r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = (__bf16)v[i];
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), buf, (at * 2u) | drop_mask, 0, 0);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), buf, (at * 4u) | drop_mask, 0, 0);
-        }
-    };
     uint32_t drop = valid ? 0u : kDrop;
     asm volatile("" : "+v"(drop));
     const uint32_t drop_dq = (16 * w < a.a16) ? drop : kDrop;      // wave w writes block w of the row's dQ
@@ -219,121 +196,94 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void bptt_back_kernel(BpttArgs a)
     // itself (the entry would otherwise add its own, stricter ones, which make every iteration wait for the
     // previous iteration's stores).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int j = 0; j < NBC; ++j) asm volatile("" : "+v"(nxt.hp[j]), "+v"(nxt.xv[j]), "+v"(nxt.w2[j]));
-    asm volatile("" : "+v"(nxt.gq_raw), "+v"(u_ahead));
+    asm volatile("" : "+v"(nxt.hp), "+v"(nxt.x.x), "+v"(nxt.x.y), "+v"(nxt.w2));
+    asm volatile("" : "+v"(nxt.gq_raw), "+v"(nxt.fil), "+v"(u_ahead));
     lds_barrier();                                                 // W_ih and the biases are in LDS
     for (int t = a.t_end - 1; t >= a.t_begin; --t) {
+        // What passes through the empty asm is used here and not earlier: the compiler would widen x and compare `filled`
+        // where they are loaded, and wait there.  The scheduling barriers keep the loads behind the operands' way to LDS
+        // and the stores behind the adjoints', which is what the other waves wait for: gradient of 64 episodes x 200 slots
+        // x 32 agents with 300 observations 1182 -> 1143 us, of 128 x 160 x 5 783 -> 772 us.
         const StepIn in = nxt;
         const int u_next = u_ahead;
+        uint32_t fil = in.fil;
+        uint2 raw = in.x;
+        asm volatile("" : "+v"(fil), "+v"(raw.x), "+v"(raw.y));
+        const float gq = (valid && fil) ? in.gq_raw : 0.0f;
+        // four bf16 values, widened (bf16 is the upper half of an fp32)
+        const f32x4 xv = {__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xFFFF0000u),
+                          __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xFFFF0000u)};
+        publish_block<P>(hf, w, lane, in.hp);
+        publish_block<P>(xf, w, lane, xv);
+        __builtin_amdgcn_sched_barrier(0);
         u_ahead = load_action(max(t - 2, 0));
         nxt = fetch(max(t - 1, 0), u_next);
-        const float gq = (valid && in.fil) ? in.gq_raw : 0.0f;
-        publish_blocks<P, NBC>(hf, w, lane, in.hp);
-        publish_blocks<P, NBC>(xf, w, lane, in.xv);
         lds_barrier();
 
         // the gates of slot t again
-        f32x4 acc_r[NBC], acc_z[NBC], acc_in[NBC], acc_hn[NBC];
-#pragma unroll
-        for (int j = 0; j < NBC; ++j) {
-            acc_r[j] = load_feature4(gb, 0 * FBK + NBC * w + j, q4);
-            acc_z[j] = load_feature4(gb, 1 * FBK + NBC * w + j, q4);
-            acc_in[j] = load_feature4(gb, 2 * FBK + NBC * w + j, q4);
-            acc_hn[j] = bias_hn[j];
-        }
+        f32x4 acc_r = load_feature4(gb, 0 * FBK + w, q4), acc_z = load_feature4(gb, 1 * FBK + w, q4);
+        f32x4 acc_in = load_feature4(gb, 2 * FBK + w, q4), acc_hn = bias_hn;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             Frag<P> hb, xb;
             hb.hi = hf[ks][0][lane];
             xb.hi = xf[ks][0][lane];
-            if constexpr (P == 2) { hb.lo = hf[ks][1][lane]; xb.lo = xf[ks][1][lane]; }
-#pragma unroll
-            for (int j = 0; j < NBC; ++j) {
-                const int blk = NBC * w + j;
-                mma16<P>(acc_r[j], whh[0][j][ks], hb);
-                mma16<P>(acc_z[j], whh[1][j][ks], hb);
-                mma16<P>(acc_hn[j], whh[2][j][ks], hb);
-                mma16<P>(acc_r[j], load_wfrag<P>(wih_lds + ((size_t)((0 * FBK + blk) * KS + ks) * P) * 64 + lane), xb);
-                mma16<P>(acc_z[j], load_wfrag<P>(wih_lds + ((size_t)((1 * FBK + blk) * KS + ks) * P) * 64 + lane), xb);
-                mma16<P>(acc_in[j], load_wfrag<P>(wih_lds + ((size_t)((2 * FBK + blk) * KS + ks) * P) * 64 + lane), xb);
-            }
+            mma16<P>(acc_r, whh[0][ks], hb);
+            mma16<P>(acc_z, whh[1][ks], hb);
+            mma16<P>(acc_hn, whh[2][ks], hb);
+            mma16<P>(acc_r, load_wfrag<P>(wih_lds + ((size_t)(0 * FBK + w) * KS + ks) * 64 + lane), xb);
+            mma16<P>(acc_z, load_wfrag<P>(wih_lds + ((size_t)(1 * FBK + w) * KS + ks) * 64 + lane), xb);
+            mma16<P>(acc_in, load_wfrag<P>(wih_lds + ((size_t)(2 * FBK + w) * KS + ks) * 64 + lane), xb);
         }
 
         // adjoints of the pre-activations
-        f32x4 dar[NBC], daz[NBC], dan[NBC], dahn[NBC], carry[NBC];
+        f32x4 dar, daz, dan, dahn, carry;
 #pragma unroll
-        for (int j = 0; j < NBC; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float rr = sigmoidf_fast(acc_r[j][r]), zz = sigmoidf_fast(acc_z[j][r]);
-                const float nn = tanhf_fast(acc_in[j][r] + rr * acc_hn[j][r]);
-                const float dht = dh[j][r] + gq * in.w2[j][r];             // Q_t[u] = W2[u] . h_t + b2[u]
-                const float dn = dht * (1.0f - zz) * (1.0f - nn * nn);
-                dan[j][r] = dn;
-                dahn[j][r] = dn * rr;
-                dar[j][r] = dn * acc_hn[j][r] * rr * (1.0f - rr);
-                daz[j][r] = dht * (in.hp[j][r] - nn) * zz * (1.0f - zz);
-                carry[j][r] = dht * zz;
-            }
-        const uint32_t m = (uint32_t)((b * T + t) * N + n);          // sample index; the host bounds 4 H samples to 2^30
-        {
-            const uint32_t da_at = m * 4 * H + unit0;
-#pragma unroll
-            for (int j = 0; j < NBC; ++j) {
-                store4(dan[j], da_buf, da_at + 0 * H + 16 * j, drop);
-                store4(dar[j], da_buf, da_at + 1 * H + 16 * j, drop);
-                store4(daz[j], da_buf, da_at + 2 * H + 16 * j, drop);
-                store4(dahn[j], da_buf, da_at + 3 * H + 16 * j, drop);
-            }
-            // the adjoint of Q_t, dense: wave w writes action block w of every row
-            f32x4 v;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = (16 * w + 4 * q4 + r == in.u) ? gq : 0.0f;
-            store4(v, dq_buf, m * a.a16 + 16 * w + 4 * q4, drop_dq);
+        for (int r = 0; r < 4; ++r) {
+            const float rr = sigmoidf_fast(acc_r[r]), zz = sigmoidf_fast(acc_z[r]);
+            const float nn = tanhf_fast(acc_in[r] + rr * acc_hn[r]);
+            const float dht = dh[r] + gq * in.w2[r];               // Q_t[u] = W2[u] . h_t + b2[u]
+            const float dn = dht * (1.0f - zz) * (1.0f - nn * nn);
+            dan[r] = dn;
+            dahn[r] = dn * rr;
+            dar[r] = dn * acc_hn[r] * rr * (1.0f - rr);
+            daz[r] = dht * (in.hp[r] - nn) * zz * (1.0f - zz);
+            carry[r] = dht * zz;
         }
-        publish_blocks<P, NBC>(daf + 0 * KS, w, lane, dar);
-        publish_blocks<P, NBC>(daf + 1 * KS, w, lane, daz);
-        publish_blocks<P, NBC>(daf + 2 * KS, w, lane, dan);
-        publish_blocks<P, NBC>(dhf, w, lane, dahn);
+        publish_block<P>(daf + 0 * KS, w, lane, dar);
+        publish_block<P>(daf + 1 * KS, w, lane, daz);
+        publish_block<P>(daf + 2 * KS, w, lane, dan);
+        publish_block<P>(dhf, w, lane, dahn);
+        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t m = (uint32_t)((b * T + t) * N + n);        // sample index; the host bounds 4 H samples to 2^30
+        const uint32_t da_at = m * 4 * H + unit0;
+        store_adjoints<P>(dan, da_buf, da_at + 0 * H, drop);
+        store_adjoints<P>(dar, da_buf, da_at + 1 * H, drop);
+        store_adjoints<P>(daz, da_buf, da_at + 2 * H, drop);
+        store_adjoints<P>(dahn, da_buf, da_at + 3 * H, drop);
+        f32x4 dq;                                                  // the adjoint of Q_t, dense
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dq[r] = (unit0 + r == in.u) ? gq : 0.0f;
+        store_adjoints<P>(dq, dq_buf, m * a.a16 + unit0, drop_dq);
         lds_barrier();
 
         // back through the two products: dL/dh_{t-1} and dL/dx_t for this wave's units
-        f32x4 accx[NBC];
-#pragma unroll
-        for (int j = 0; j < NBC; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) accx[j][r] = 0.0f;
+        f32x4 accx = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int ks = 0; ks < 3 * KS; ++ks) {
             Frag<P> di, dhid;
             di.hi = daf[ks][0][lane];
-            if constexpr (P == 2) di.lo = daf[ks][1][lane];
-            if (ks < 2 * KS) {
-                dhid = di;
-            } else {
-                dhid.hi = dhf[ks - 2 * KS][0][lane];
-                if constexpr (P == 2) dhid.lo = dhf[ks - 2 * KS][1][lane];
-            }
-#pragma unroll
-            for (int j = 0; j < NBC; ++j) {
-                mma16<P>(carry[j], whhT[j][ks], dhid);
-                mma16<P>(accx[j], wihT[j][ks], di);
-            }
+            if (ks < 2 * KS) dhid = di;
+            else dhid.hi = dhf[ks - 2 * KS][0][lane];
+            mma16<P>(carry, whhT[ks], dhid);
+            mma16<P>(accx, wihT[ks], di);
         }
+        dh = carry;
 #pragma unroll
-        for (int j = 0; j < NBC; ++j) {
-            dh[j] = carry[j];
-            f32x4 dp;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) dp[r] = in.xv[j][r] > 0.0f ? accx[j][r] : 0.0f;
-            store4(dp, pre_buf, m * H + unit0 + 16 * j, drop);
-        }
+        for (int r = 0; r < 4; ++r) accx[r] = xv[r] > 0.0f ? accx[r] : 0.0f;
+        store_adjoints<P>(accx, pre_buf, m * H + unit0, drop);
     }
-    if (a.t_begin > 0) {
-#pragma unroll
-        for (int j = 0; j < NBC; ++j) *reinterpret_cast<f32x4 *>(carry_row + 16 * j) = dh[j];
-    }
+    if (a.t_begin > 0) *reinterpret_cast<f32x4 *>(carry_row) = dh;
 }
 
 // The same for 64 hidden units, cut into two roles.  What bounds it is issue and latency, not memory or the matrix
@@ -387,22 +337,8 @@ __global__ __launch_bounds__(512, P == 1 ? 4 : 2) void bptt_back_split_kernel(Bp
     const int b = valid ? row / N : 0, n = valid ? row % N : 0;
     const int unit0 = 16 * w + 4 * q4;                             // the lane's four units
 
-    // Stores of rows past the end go beyond the descriptor, which drops them: the loops are straight-line code.
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr uint32_t kDrop = 0xFFFFFFF0u, kElem = P == 1 ? 2u : 4u;
+    constexpr uint32_t kElem = P == 1 ? 2u : 4u;                   // bytes per stored adjoint
     const size_t samples = (size_t)rows * T;
-    auto store4 = [&](const f32x4 &v, const __amdgpu_buffer_rsrc_t &buf, uint32_t at, uint32_t drop_mask) {
-        if constexpr (P == 1) {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            bf16x4 r;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) r[i] = (__bf16)v[i];
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), buf, (at * 2u) | drop_mask, 0, 0);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), buf, (at * 4u) | drop_mask, 0, 0);
-        }
-    };
     auto operand = [&](int at) {                                   // at: byte offset of a fragment
         Frag<P> f;
         const FragBuf p = reinterpret_cast<FragBuf>(lds + at);
@@ -410,10 +346,7 @@ __global__ __launch_bounds__(512, P == 1 ? 4 : 2) void bptt_back_split_kernel(Bp
         if constexpr (P == 2) f.lo = p[0][1][lane];
         return f;
     };
-    auto publish = [&](int at, const f32x4 &v) {
-        const f32x4 one[1] = {v};
-        publish_blocks<P, 1>(reinterpret_cast<FragBuf>(lds + at), w, lane, one);
-    };
+    auto publish = [&](int at, const f32x4 &v) { publish_block<P>(reinterpret_cast<FragBuf>(lds + at), w, lane, v); };
     auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
     auto fac_of = [&](int t, int f) { return reinterpret_cast<f32x4 *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + (f * FBK + w) * 1024) + lane; };
     auto bits_of = [&](int t) { return reinterpret_cast<uint32_t *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + Bs::kFactors * FBK * 1024 + w * 256) + lane; };
@@ -482,7 +415,7 @@ __global__ __launch_bounds__(512, P == 1 ? 4 : 2) void bptt_back_split_kernel(Bp
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) accx[r] = positive >> r & 1u ? accx[r] : 0.0f;
-            store4(accx, pre_buf, pre_lane + rows_before(t) * H, drop_mask);
+            store_adjoints<P>(accx, pre_buf, pre_lane + rows_before(t) * H, drop_mask);
         };
         auto step = [&](const In &in, In &nxt, int t) {
             fetch(nxt, t - 2, in.u_ahead);
@@ -507,14 +440,14 @@ __global__ __launch_bounds__(512, P == 1 ? 4 : 2) void bptt_back_split_kernel(Bp
             publish(da_at(t) + 2 * KS * kFrag, dan);
             publish(da_at(t) + 3 * KS * kFrag, dahn);
             const uint32_t tn = rows_before(t), at = da_lane + tn * 4 * H;
-            store4(dan, da_buf, at + 0 * H, drop);
-            store4(dar, da_buf, at + 1 * H, drop);
-            store4(daz, da_buf, at + 2 * H, drop);
-            store4(dahn, da_buf, at + 3 * H, drop);
+            store_adjoints<P>(dan, da_buf, at + 0 * H, drop);
+            store_adjoints<P>(dar, da_buf, at + 1 * H, drop);
+            store_adjoints<P>(daz, da_buf, at + 2 * H, drop);
+            store_adjoints<P>(dahn, da_buf, at + 3 * H, drop);
             f32x4 v;                                               // the adjoint of Q_t, dense
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = in.u - unit0 == r ? gq : 0.0f;
-            store4(v, dq_buf, dq_lane + tn * a.a16, drop_dq);
+            store_adjoints<P>(v, dq_buf, dq_lane + tn * a.a16, drop_dq);
             lds_barrier();
         };
         lds_barrier();                                             // biases, zeros, the last slot's x and h
@@ -1249,25 +1182,13 @@ Plan make_plan(const NetFrags &net, int B, int T)
     return p;
 }
 
-template <int H, int P, int NW>
-hipError_t back_dispatch(const BpttArgs &a, hipStream_t stream)
+template <auto kKernel>
+hipError_t back_dispatch(const BpttArgs &a, size_t lds_bytes, hipStream_t stream)
 {
     const int tiles = (a.B * a.net.N + 15) / 16;
-    hipError_t err = allow_large_lds<bptt_back_kernel<H, P, NW>>(kLdsLimit);
+    hipError_t err = allow_large_lds<kKernel>(kLdsLimit);
     if (err != hipSuccess) return err;
-    constexpr size_t kLds = BpttShape<H, P>::kBytes;
-    hipLaunchKernelGGL((bptt_back_kernel<H, P, NW>), dim3(tiles), dim3(64 * NW), kLds, stream, a);
-    return hipGetLastError();
-}
-
-template <int P>
-hipError_t back_split_dispatch(const BpttArgs &a, hipStream_t stream)
-{
-    const int tiles = (a.B * a.net.N + 15) / 16;
-    hipError_t err = allow_large_lds<bptt_back_split_kernel<P>>(kLdsLimit);
-    if (err != hipSuccess) return err;
-    constexpr size_t kLds = BpttSplit<P>::kBytes;
-    hipLaunchKernelGGL((bptt_back_split_kernel<P>), dim3(tiles), dim3(512), kLds, stream, a);
+    hipLaunchKernelGGL(kKernel, dim3(tiles), dim3(512), lds_bytes, stream, a);
     return hipGetLastError();
 }
 
@@ -1486,9 +1407,9 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     a.carry = reinterpret_cast<float *>(ws + plan.off_carry);
     auto reverse = [&](int t_begin, int t_end, hipStream_t on) {
         a.t_begin = t_begin; a.t_end = t_end;
-        if (H == 64 && net.planes == 2) return back_split_dispatch<2>(a, on);
-        if (H == 64 && net.planes == 1) return back_split_dispatch<1>(a, on);
-        if (H == 128 && net.planes == 1) return back_dispatch<128, 1, 8>(a, on);
+        if (H == 64 && net.planes == 2) return back_dispatch<bptt_back_split_kernel<2>>(a, BpttSplit<2>::kBytes, on);
+        if (H == 64 && net.planes == 1) return back_dispatch<bptt_back_split_kernel<1>>(a, BpttSplit<1>::kBytes, on);
+        if (H == 128 && net.planes == 1) return back_dispatch<bptt_back_kernel>(a, BpttBack::kBytes, on);
         return hipErrorInvalidValue;
     };
 
