@@ -33,12 +33,14 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
     const long M = rows * T;
     // Every chunk's partial sums are written once and read once more, up to 221 KB each, where 32 samples are 60 KB at
     // most: few chunks for few samples.  Two planes: the products of a launch come in pairs, 128 chunks each, which
-    // are the chip's 256 compute units once, where up to 256 each were one wave and a part of another; learner iteration
-    // of 64 x 120 x 5 502 -> 481 us.  One plane (a GRU product is alone in its launch): up to 256 chunks, of 64 samples
-    // up to 4096 of them, where the steps that follow one another in a chunk are what takes time (gradient at 576 / 720 /
-    // 2400 samples 71 / 182 / 201 us, with chunks of 128 75 / 188 / 202), of 128 or more beyond, where the partial sums
-    // are (6640 / 15360 samples 274 / 130 us, 271 / 110 with 128; 128 hidden units all).
-    g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, M <= 4096 ? 64 : 128);
+    // are the chip's 256 compute units once, where up to 256 each were one wave and a part of another (gradient with up to
+    // 256 / 128 chunks, 96 observations: 8400 samples 111 / 100 us, 38400 362 / 341, 102400 405 / 379, 815900 2068 / 2043;
+    // the same below 8192).  One plane (a GRU product is alone in its launch): up to 256 chunks.  Of 64 samples
+    // for the fewest, where the steps that follow one another in a chunk are what takes time, of 128 or more beyond,
+    // where the partial sums are.  Gradient with chunks of 64 / 128, 128 units and 93 observations: 720 samples 95 / 100 us,
+    // 1200 104 / 109, 2250 111 / 113, 2400 131 / 132, 3000 139 / 133, 3600 121 / 120, 4000 144 / 133, 4800 284 / 279,
+    // 9900 297 / 290; 64 units, and 33 and 301 observations, change over between the same 2400 and 3000.
+    g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, M <= 2560 ? 64 : 128);
     g.room = g.whole.chunks;
     if (planes == 1 && T >= kForkSlots) {
         // the later half's products share the chip with the recurrence, whose workgroups hold half the compute units

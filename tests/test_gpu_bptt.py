@@ -85,11 +85,13 @@ CASES = [(0, 4, 6, {}), (0, 32, 25, {}), (1, 5, 9, {}), (2, 7, 12, {}), (3, 33, 
          # bf16 networks over sixteen slots or more: the slots are walked in two launches (an odd count: halves of
          # eight and nine) and the products run per half; the last one's first layer keeps the narrow loads
          (4, 2, 17, {}), (1, 3, 24, dict(dtype="bf16")), (0, 2, 16, dict(N=17, D=33, A=64, dtype="bf16")),
-         # 64 hidden units in two launches of odd halves, every remainder of the unrolled loop on either side; in the
-         # first two and the last the halves fill more chunks of partial sums together than all slots at once would
+         # two launches of unequal halves, for 64 hidden units with every remainder of the unrolled loop on either side;
+         # the halves fill more chunks of partial sums together than all slots at once would
          (2, 3, 17, dict(N=5, D=96, dtype="bf16")), (2, 12, 17, dict(N=5, D=96, dtype="bf16")),
          (2, 2, 19, dict(N=5, D=96, dtype="bf16")), (2, 3, 21, dict(N=5, D=96, dtype="bf16")),
          (2, 12, 61, dict(N=5, D=96, dtype="bf16")), (4, 12, 17, dict(N=5, D=96, A=11)),
+         # one launch, just past the samples up to which a chunk of a bf16 network has 64
+         (2, 37, 14, dict(N=5, D=55, dtype="bf16")),
          # more row tiles than compute units: two workgroups of a bf16 network share one, fp32 ones follow one another
          (2, 823, 5, dict(N=5, D=24, dtype="bf16")), (2, 823, 3, dict(N=5, D=24))]
 

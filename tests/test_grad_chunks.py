@@ -56,7 +56,7 @@ def test_partial_sums_of_either_walk_fit_the_workspace(cut, planes):
 
 
 def test_few_samples_of_a_one_plane_network_are_cut_into_short_chunks(cut):
-    """Up to 4096 samples a chunk's own steps are what takes time: none is longer than 64; beyond, none is shorter than 128."""
-    for M in list(range(1, 4500, 7)) + [4096, 4097, 8192, 32768]:
+    """Up to 2560 samples a chunk's own steps are what takes time: none is longer than 64; beyond, none is shorter than 128."""
+    for M in list(range(1, 4500, 7)) + [2560, 2561, 8192, 32768]:
         whole = cut(1, M, 1)[0][0]
-        assert whole[1] == 64 if M <= 4096 else whole[1] >= 128
+        assert whole[1] == 64 if M <= 2560 else whole[1] >= 128
