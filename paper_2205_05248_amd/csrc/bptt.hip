@@ -287,10 +287,10 @@ __global__ __launch_bounds__(64 * BpttBack::NW, BpttBack::NW / 4) void bptt_back
 }
 
 // The same for 64 hidden units, cut into two roles.  What bounds it is issue and latency, not memory or the matrix
-// cores: four waves in one role issue some 500 instructions each per slot, one wave per SIMD, so that nothing hides
-// a wait (1.9 us per slot, fp32; one barrier per slot instead of two in that form: 1.75 us).  But only
+// cores: four waves in one role issue 508 instructions each per slot (two planes; 326 of them vector arithmetic, 72
+// products), one wave per SIMD, so that nothing hides a wait: 1.97 us per slot, fp32.  But only
 // dL/dh_t -> adjoints -> dL/dh_{t-1} is a chain; the gates of a slot and the adjoint of x hang on nothing behind them.
-// Eight waves, two per SIMD: in the step of slot t
+// Eight waves, two per SIMD, 258 (chain) and 242 (gates) instructions a slot: in the step of slot t
 //
 //   chain waves 0..3  dL/dh_t = carry + W_hh^T adjoints(t+1), beside it W_ih^T adjoints(t+1) -> dpre1 of slot t+1 (the
 //                     same operands, and matrix instructions that do not wait for each other), then slot t's
@@ -300,16 +300,15 @@ __global__ __launch_bounds__(64 * BpttBack::NW, BpttBack::NW / 4) void bptt_back
 //
 // and ONE barrier per slot.  Every LDS buffer is double-buffered on the parity of its slot: written in one step, read
 // in the next, written again only in the one after.  All weights are in registers.  Waves w and w + 4 own the same
-// 16 units, in the same lanes.  Measured on the whole learner iteration (mixer and products included): 64 episodes of
-// 120 slots x 5 agents, fp32, 562 -> 502 us; 4 x 60 x 3 fp32 247 -> 220 us; 37 x 83 x 5 bf16 316 -> 292 us.  With the
-// adjoint of x on the gate waves, which then issue more than the chain does; on the chain waves another 481 -> 468,
-// 220 -> 215 and 281 -> 278 us (figures after the products' chunks had changed).
-// (128 hidden units keep bptt_back_kernel: eight waves already hold 144 registers of weights each, and its one-barrier
-// form took 327 us per hundred slots against 313.)
+// 16 units, in the same lanes.  Kernel trace, us per launch, four waves in one role / split with the adjoint of x on the
+// gate waves, which then issue more than the chain does / on the chain waves / with the stores' offsets as below:
+// 64 episodes x 120 slots x 5 agents fp32 237 / 178 / 165 / 158.  First and last form: 4 x 60 x 3 fp32 115 / 80,
+// 37 x 83 x 5 bf16 116 / 82.
+// (128 hidden units keep bptt_back_kernel: eight waves already hold 144 registers of weights each.)
 // One plane: 126 registers and 68 KB of LDS, two workgroups per compute unit, asked for with the launch bound.  With one
 // (136 registers) a batch of a few more than 256 tiles walked all its slots twice over: gradient of 820 episodes x 199
 // slots x 5 agents (257 tiles) 1080 -> 1055 us, 4096 x 1 x 5 89 -> 85 us.  The fewer instructions per store help few
-// tiles too: 37 x 83 x 5 148 -> 140 us, two planes 64 x 120 x 5 240 -> 233 us.  (Two planes need 192 registers.)
+// tiles too.  (Two planes need 192 registers.)
 template <int P> struct BpttSplit {
     static constexpr int H = 64, KS = H / 32, FBK = H / 16, kFrag = P * 1024;
     static constexpr int kFactors = 5;
