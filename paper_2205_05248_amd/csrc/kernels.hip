@@ -9,7 +9,8 @@
 //                            accumulator layout of the consumer.
 //   recurrent_td_kernel      two-kernel unroll, part 2: one workgroup per 32 (episode, agent) rows
 //                            walks the T+1 slots, adds the hidden half of the gates, applies fc2 and
-//                            emits q_taken / next_max / td_target.
+//                            emits q_taken / next_max / td_target.  (128 hidden units in fp32:
+//                            recurrent16_td_kernel, unroll_recur16.hip.)
 // The default unroll is the fused kernel of unroll_fused.hip; this pair serves the networks that do
 // not fit it.
 #include "mfma_tile.h"
@@ -472,16 +473,22 @@ hipError_t unroll_dispatch(const NetFrags &online, const NetFrags &target, bool 
             if (err != hipSuccess) return err;
         }
     }
-    const dim3 grid((unsigned)tiles, nets), block(64 * RecurrentShape<H, P>::kWaves);
-    const int two = two_nets ? 1 : 0;
+    if constexpr (H == 128 && P == 2) {      // tiles of 16 rows: W_hh in two planes fits the registers of eight waves, not of four
+        const TdArrays td{episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken, next_max, td_target,
+                          q_all, (int)mode, next_action};
+        return launch_recurrent16(online, target, two_nets, gi_on, gi_tg, B, T, td, stream);
+    } else {
+        const dim3 grid((unsigned)tiles, nets), block(64 * RecurrentShape<H, P>::kWaves);
+        const int two = two_nets ? 1 : 0;
 #define MARL_REC(MB, QA)                                                                                             \
-    hipLaunchKernelGGL((recurrent_td_kernel<H, P, MB, QA>), grid, block, 0, stream, online, target, gi_on, gi_tg, two,  \
-                       B, T, episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken,      \
-                       next_max, td_target, q_all, (int)mode, next_action)
-    if (online.mb2 == 1) { if (q_all) MARL_REC(1, true); else MARL_REC(1, false); }
-    else                 { if (q_all) MARL_REC(2, true); else MARL_REC(2, false); }
+        hipLaunchKernelGGL((recurrent_td_kernel<H, P, MB, QA>), grid, block, 0, stream, online, target, gi_on, gi_tg, two,  \
+                           B, T, episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken,      \
+                           next_max, td_target, q_all, (int)mode, next_action)
+        if (online.mb2 == 1) { if (q_all) MARL_REC(1, true); else MARL_REC(1, false); }
+        else                 { if (q_all) MARL_REC(2, true); else MARL_REC(2, false); }
 #undef MARL_REC
-    return hipGetLastError();
+        return hipGetLastError();
+    }
 }
 
 }  // namespace

@@ -81,21 +81,6 @@ __device__ __forceinline__ void compute_role(const NetFrags &net, int fb, int la
     }
 }
 
-// Arrays of the TD step as the epilogue sees them.
-struct TdArrays {
-    const int32_t *episode_index;   // null: the input arrays hold the batch; else batch position b reads episode episode_index[b]
-    int pool_episodes;              // episodes the input arrays hold (listed indices are clamped into it)
-    const uint8_t *avail;
-    const int32_t *actions;
-    const float *reward;
-    const uint8_t *terminated;
-    const uint8_t *filled;
-    float gamma;
-    float *q_taken, *next_max, *td_target, *q_all;
-    int mode;                       // TdMode
-    int32_t *next_action;           // written under kTdSelect, read under kTdValue, unused otherwise
-};
-
 // emit_online: q_taken (and q_all); emit_target: next_max and td_target.  b2_lds: 32 MB2 floats
 // owned by this wavefront.
 template <int H, int P, int MB2, bool QALL>

@@ -70,4 +70,23 @@ __device__ __forceinline__ f32x16 load_gi_block(const char *src, int lane)
     return v;
 }
 
+// Arrays of the TD step as the epilogue sees them.
+struct TdArrays {
+    const int32_t *episode_index;   // null: the input arrays hold the batch; else batch position b reads episode episode_index[b]
+    int pool_episodes;              // episodes the input arrays hold (listed indices are clamped into it)
+    const uint8_t *avail;
+    const int32_t *actions;
+    const float *reward;
+    const uint8_t *terminated;
+    const uint8_t *filled;
+    float gamma;
+    float *q_taken, *next_max, *td_target, *q_all;
+    int mode;                       // TdMode
+    int32_t *next_action;           // written under kTdSelect, read under kTdValue, unused otherwise
+};
+
+// Second kernel of the two-kernel unroll for 128 hidden units in fp32 (unroll_recur16.hip); td.mode: kTdPlain, kTdSelect or kTdValue.
+hipError_t launch_recurrent16(const NetFrags &online, const NetFrags &target, bool two_nets, const char *gi_online, const char *gi_target,
+                              int B, int T, const TdArrays &td, hipStream_t stream);
+
 }  // namespace marl

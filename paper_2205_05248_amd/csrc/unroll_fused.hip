@@ -32,15 +32,13 @@
 // step s was last read in step s-1 and is first read in step s+1.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
-#include "fused16_roles.h"
+#include "unroll16_td.h"
 
 namespace marl {
 
 
-// LDS of a launch: the shared layout, then the staging area of the epilogue's inputs, [2][4][64] words.
-template <int H, int P> constexpr size_t unroll_lds_bytes(int ks1) { return Fused16<H, P>::lds_bytes(ks1) + 2 * 4 * 64 * 4; }
+// LDS of a launch: the shared layout, then the staging area of the epilogue's inputs.
+template <int H, int P> constexpr size_t unroll_lds_bytes(int ks1) { return Fused16<H, P>::lds_bytes(ks1) + kEpiBytes; }
 
 template <int H, int P, int AB, bool QALL, int MODE>
 __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
@@ -79,62 +77,11 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
     // episode of the input arrays: the batch position itself, or the listed episode of a larger pool
     const int bi = episode_index ? min(max(episode_index[b], 0), pool_episodes - 1) : b;
 
-    // ---- the epilogue's per-slot inputs: the taken action, the flags, the reward and the availability bytes
-    // kSelect / kValue: the two single-network launches of the double-estimator target
-    constexpr bool kSelect = MODE == kTdSelect, kValue = MODE == kTdValue, kSave = MODE == kTdSave;
-    // 32-bit element offsets (the host bounds every array to 2^30 elements)
-    const uint32_t btn0 = (uint32_t)(b * T) * N + n;          // outputs [B, T, N]:       + t N
-    const uint32_t qa0 = ((uint32_t)(b * S) * N + n) * A;     // q_all [B, T+1, N, A]:    + t N A
-    const uint32_t act0 = (uint32_t)(bi * T) * N + n;         // actions of the episode:  + t N
-    const uint32_t av0 = ((uint32_t)(bi * S) * N + n) * A;    // avail of the episode:    + t N A
-    const uint32_t bt0 = (uint32_t)(bi * T);                  // per-episode flags:       + t
-    // They are global loads whose latency is longer than a step, and the epilogue's own instruction stream cannot
-    // hide it: its stores and loads are conditional, so any wait it needs covers everything in flight.  The loader
-    // wave fetches them instead, beside the observations and a step earlier, the same number of loads every step
-    // (positions clamped into the arrays, rows past the end read row 0), and hands them over in LDS:
-    // epi[slot & 1][word][lane], words: 0 action, 1 flags (filled(t) | terminated(t-1) << 8 | filled(t-1) << 16),
-    // 2 reward(t-1), 3 the lane's availability slots of slot t (avail_mask16, formed by the loader).
-    // With two networks each workgroup's epilogue uses one half only - the online one the action and filled(t),
-    // the target one the rest - and its loader fetches just that half (WANT_ONLINE / WANT_TARGET).
-    struct SlotIn { int u; uint32_t flags; float reward; uint32_t slots; };
-    struct SlotRaw { int u; uint32_t flags; float reward; uint32_t avail_raw[AB]; };
-    constexpr int kEpiWords = 4;
-    uint32_t *const epi = reinterpret_cast<uint32_t *>(lds + Sh::lds_bytes(ks1));
-    auto fetch_slot = [&](int t, auto wide, auto want_online, auto want_target) {        // t in 0 .. T
-        constexpr bool kOn = decltype(want_online)::value, kTg = decltype(want_target)::value;
-        SlotRaw in{};
-        if constexpr (!kSave) {
-            const uint32_t tq = (uint32_t)min(t, T - 1), tp = (uint32_t)max(t - 1, 0);
-            if constexpr (kValue) in.u = next_action[btn0 + tp * N];
-            else if constexpr (kOn) in.u = actions[act0 + tq * N];
-            if constexpr (kOn) in.flags = (uint32_t)filled[bt0 + tq];
-            if constexpr (kTg) {
-                in.flags |= (uint32_t)terminated[bt0 + tp] << 8 | (uint32_t)filled[bt0 + tp] << 16;
-                in.reward = reward[bt0 + tp];
-                if constexpr (decltype(wide)::value && !kValue)
-                    issue_avail_loads16<AB>(avail + (av0 + (uint32_t)t * N * A), A, q4, in.avail_raw);
-            }
-        }
-        return in;
-    };
-    auto stage_slot = [&](const SlotRaw &in, int t, auto wide, auto want_target) {
-        uint32_t *at = epi + (size_t)(t & 1) * kEpiWords * 64 + lane;
-        at[0] = (uint32_t)in.u;
-        at[64] = in.flags;
-        if constexpr (decltype(want_target)::value) {
-            at[128] = __builtin_bit_cast(uint32_t, in.reward);
-            if constexpr (decltype(wide)::value && !kValue && !kSave) at[192] = avail_mask16<AB>(in.avail_raw, A, q4, valid);
-        }
-    };
-    auto staged_slot = [&](int t) {
-        const uint32_t *at = epi + (size_t)(t & 1) * kEpiWords * 64 + lane;
-        SlotIn in;
-        in.u = (int)at[0];
-        in.flags = at[64];
-        in.reward = __builtin_bit_cast(float, at[128]);
-        in.slots = at[192];
-        return in;
-    };
+    constexpr bool kValue = MODE == kTdValue, kSave = MODE == kTdSave;
+    TdTile16<AB, MODE> tile;
+    tile.init(TdArrays{episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken, next_max, td_target,
+                       q_all, MODE, next_action},
+              net, T, lane, b, bi, n, valid, lds + Sh::lds_bytes(ks1));
 
     // W_ih -> LDS, all waves.  Its first readers start after kFusedLead barriers.
     {
@@ -183,82 +130,8 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         }
     } else if (wave == Sh::kEpilogue) {
         // ---------------------------------------------------------------- epilogue wave
-        const bool emit_online = !is_target && !kValue && !kSave, emit_target = (is_target || !two_nets) && !kSave;
-        float *const b2_lds = reinterpret_cast<float *>(lds + Sh::oB2);
-        WFrag<P> w2[AB][KS];
-#pragma unroll
-        for (int ab = 0; ab < AB; ++ab)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) w2[ab][ks] = load_wfrag<P>(net.w2_16 + ((size_t)(ab * KS + ks) * P) * 64 + lane);
-        if (lane < 16 * AB) b2_lds[lane] = lane < A ? net.b2[lane] : 0.0f;
-        // the weights have arrived before the loop starts: a wait for them inside it would also cover the loop's own loads
-#pragma unroll
-        for (int ab = 0; ab < AB; ++ab)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) settle(w2[ab][ks]);
-        for (int i = 0; i < LEAD; ++i) lds_barrier();
-        for (int it = 0; it <= T + 1; ++it) {
-            if (it >= 1) {
-                const int t = it - 1, cur = it & 1;          // h_t was published during iteration t
-                const SlotIn in = staged_slot(t);
-                const bool on_filled = (in.flags & 0xFFu) != 0, terminated_prev = (in.flags >> 8 & 0xFFu) != 0, tg_filled = (in.flags >> 16 & 0xFFu) != 0;
-                f32x4 qv[AB];
-#pragma unroll
-                for (int ab = 0; ab < AB; ++ab) qv[ab] = load_feature4(b2_lds, ab, q4);
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    Frag<P> hb;
-                    hb.hi = h_lds[cur][ks][0][lane];
-                    if constexpr (P == 2) hb.lo = h_lds[cur][ks][1][lane];
-                    {
-                        f32x4 *accs[AB];
-                        const WFrag<P> *wf[AB];
-#pragma unroll
-                        for (int ab = 0; ab < AB; ++ab) {
-                            accs[ab] = &qv[ab];
-                            wf[ab] = &w2[ab][ks];
-                        }
-                        mma16_across<P, AB>(accs, wf, hb);
-                    }
-                }
-                if (emit_online) {
-                    if constexpr (QALL) {
-                        if (valid) store_q_row16<AB>(q_all + (qa0 + (uint32_t)t * N * A), qv, A, q4);
-                    }
-                    if (t < T) {
-                        const int u = min(max(in.u, 0), A - 1);
-                        const float qu = pick_action_value16<AB>(qv, u, q4);
-                        if (valid && q4 == 0) q_taken[btn0 + (uint32_t)t * N] = on_filled ? qu : 0.0f;
-                    }
-                }
-                if (emit_target && t >= 1) {
-                    const uint32_t o = btn0 + (uint32_t)(t - 1) * N;
-                    float best_q;
-                    if constexpr (kValue) {               // the value of the action the other network chose
-                        const float picked = pick_action_value16<AB>(qv, min(max(in.u, 0), A - 1), q4);
-                        best_q = in.u >= 0 ? picked : 0.0f;      // -1: the other network found no action available
-                    } else {
-                        const uint32_t slots =
-                            A >= 4 ? in.slots
-                                   : avail_mask_small16(avail + (valid ? av0 + (uint32_t)t * N * A : 0u), A, q4, valid);
-                        if constexpr (kSelect) {
-                            int best;
-                            masked_argmax16<AB, true>(qv, slots, q4, best_q, best);
-                            if (valid && q4 == 0) next_action[o] = best;
-                        } else {
-                            best_q = masked_max16<AB>(qv, slots);
-                        }
-                    }
-                    if (!kSelect && valid && q4 == 0) {
-                        const float keep = terminated_prev ? 0.0f : 1.0f;
-                        const float y = in.reward + gamma * keep * best_q;
-                        next_max[o] = tg_filled ? best_q : 0.0f;
-                        td_target[o] = tg_filled ? y : 0.0f;
-                    }
-                }
-            }
-            lds_barrier();
-        }
+        td_epilogue16<H, P, AB, QALL, MODE>(net, tile, !is_target && !kValue && !kSave, (is_target || !two_nets) && !kSave, LEAD, h_lds,
+                                            reinterpret_cast<float *>(lds + Sh::oB2));
     } else if (wave == Sh::kLoader) {
         // ---------------------------------------------------------------- loader wave
         const float *base = obs + ((size_t)bi * S * N + n) * D + 8 * q4;     // the lane's row at slot 0
@@ -268,14 +141,15 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         // Two register sets in turn: a step first issues the loads of the slot it will write in the next step, into
         // the set that step will read, then converts the set loaded a step ago.  The loads have a whole step to arrive.
         ObsRegs<H, P> set_a, set_b;
+        using SlotRaw = typename TdTile16<AB, MODE>::SlotRaw;
         SlotRaw epi_a{}, epi_b{};                    // the epilogue's inputs of a slot, in turn like the observation sets
         auto loader_step = [&](const ObsRegs<H, P> &ready, ObsRegs<H, P> &refill, const SlotRaw &epi_ready, SlotRaw &epi_refill,
                                int s, auto wide, auto want_online, auto want_target) {
             const int ws = s + 2, ls = ws + 1;
             st.load(refill, base + (size_t)min(max(ls, 0), T) * slot_stride);       // every step the same number of loads (the ends load a slot again)
-            epi_refill = fetch_slot(min(max(s + 1, 0), T), wide, want_online, want_target);     // slot s + 1: staged in the next step, read by the epilogue in step s + 2
+            epi_refill = tile.fetch(min(max(s + 1, 0), T), wide, want_online, want_target);     // slot s + 1: staged in the next step, read by the epilogue in step s + 2
             if (ws >= 0 && ws <= T) st.write(ready, obuf + (size_t)((ws & 1) * ks1) * P * 64 + lane);     // registers -> LDS
-            if (s >= 0 && s <= T) stage_slot(epi_ready, s, wide, want_target);
+            if (s >= 0 && s <= T) tile.stage(epi_ready, s, wide, want_target);
             lds_barrier();
         };
         auto loader_loop = [&](auto wide, auto want_online, auto want_target) {
@@ -361,7 +235,6 @@ hipError_t fused_dispatch(const NetFrags &online, const NetFrags &target, bool t
                           float *next_max, float *td_target, float *q_all, hipStream_t stream, TdMode mode,
                           int32_t *next_action, float *h_save, void *x_save)
 {
-    using Sh = Fused16<H, P>;
     const int tiles = (B * online.N + 15) / 16;
     const dim3 grid(two_nets ? (unsigned)((tiles + 7) / 8) * 16u : (unsigned)tiles), block(fused_threads(H));
     const size_t lds = unroll_lds_bytes<H, P>((online.D + 31) / 32);
