@@ -452,11 +452,20 @@ hipError_t unroll_dispatch(const NetFrags &online, const NetFrags &target, bool 
                            int B, int T, const int32_t *episode_index, int pool_episodes, const float *obs, const uint8_t *avail, const int32_t *actions,
                            const float *reward, const uint8_t *terminated, const uint8_t *filled, float gamma,
                            float *q_taken, float *next_max, float *td_target, float *q_all, hipStream_t stream,
-                           hipEvent_t between, TdMode mode, int32_t *next_action)
+                           hipEvent_t between, int n_cu, TdMode mode, int32_t *next_action)
 {
     const int rows = B * online.N, tiles = (rows + 31) / 32;
     const unsigned nets = two_nets ? 2u : 1u;
-    {
+    // 128 hidden units in fp32 have kernels of their own; what is wider than the first of them takes still has front_kernel
+    bool projected = false;
+    if constexpr (H == 128 && P == 2) {
+        if (project16_fits(online)) {
+            const hipError_t err = launch_project16(online, target, two_nets, gi_on, gi_tg, B, T, episode_index, pool_episodes, obs, n_cu, stream);
+            if (err != hipSuccess) return err;
+            projected = true;
+        }
+    }
+    if (!projected) {
         constexpr int NC = front_col_blocks(H, P);
         const long groups = (long)((tiles + NC - 1) / NC) * (T + 1);      // wavefront work items
         FrontArgs a{};
@@ -466,12 +475,12 @@ hipError_t unroll_dispatch(const NetFrags &online, const NetFrags &target, bool 
         const dim3 grid((unsigned)((groups + kFrontWaves - 1) / kFrontWaves) * nets), block(kFrontThreads);
         // the fc2 block count does not enter the projection; one instantiation serves both
         hipLaunchKernelGGL((front_kernel<H, P, 1, false>), grid, block, 0, stream, a);
-        hipError_t err = hipGetLastError();
+        const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
-        if (between) {
-            err = hipEventRecord(between, stream);
-            if (err != hipSuccess) return err;
-        }
+    }
+    if (between) {
+        const hipError_t err = hipEventRecord(between, stream);
+        if (err != hipSuccess) return err;
     }
     if constexpr (H == 128 && P == 2) {      // tiles of 16 rows: W_hh in two planes fits the registers of eight waves, not of four
         const TdArrays td{episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken, next_max, td_target,
@@ -521,7 +530,7 @@ hipError_t launch_unroll_td(const NetFrags &online, const NetFrags &target, bool
                             const float *obs, const uint8_t *avail,
                             const int32_t *actions, const float *reward, const uint8_t *terminated,
                             const uint8_t *filled, float gamma, float *q_taken, float *next_max, float *td_target,
-                            float *q_all, hipStream_t stream, hipEvent_t between, TdMode mode, int32_t *next_action)
+                            float *q_all, hipStream_t stream, hipEvent_t between, int n_cu, TdMode mode, int32_t *next_action)
 {
     if (mode != kTdPlain && (two_nets || !next_action)) return hipErrorInvalidValue;
     char *gi_on = static_cast<char *>(scratch_online), *gi_tg = static_cast<char *>(scratch_target);
@@ -529,7 +538,7 @@ hipError_t launch_unroll_td(const NetFrags &online, const NetFrags &target, bool
     return unroll_dispatch<HH, PP>(online, target, two_nets, gi_on, gi_tg, B, T, episode_index, pool_episodes, obs, \
                                    avail, actions, reward,                                                         \
                                    terminated, filled, gamma, q_taken, next_max, td_target, q_all, stream, between,  \
-                                   mode, next_action)
+                                   n_cu, mode, next_action)
     if (online.H == 64 && online.planes == 2) MARL_UNROLL(64, 2);
     if (online.H == 64 && online.planes == 1) MARL_UNROLL(64, 1);
     if (online.H == 128 && online.planes == 2) MARL_UNROLL(128, 2);

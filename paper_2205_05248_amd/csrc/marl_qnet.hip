@@ -487,11 +487,11 @@ int unroll_call(marl_qnet *online, marl_qnet *target, int32_t B, int32_t T, cons
             err = marl::launch_unroll_td(online->net, online->net, false, scratch_on, scratch_on, B, T,
                                          episode_index, pool_episodes, obs, avail, actions, reward, terminated,
                                          filled, gamma, q_taken, nullptr, nullptr, q_all, stream,
-                                         ev ? ev[1] : nullptr, marl::kTdSelect, next_action);
+                                         ev ? ev[1] : nullptr, online->n_cu, marl::kTdSelect, next_action);
             if (err != hipSuccess) return err;
             err = marl::launch_unroll_td(target->net, target->net, false, scratch_tg, scratch_tg, B, T,
                                          episode_index, pool_episodes, obs, avail, actions, reward, terminated,
-                                         filled, gamma, nullptr, next_max, td_target, nullptr, stream, nullptr,
+                                         filled, gamma, nullptr, next_max, td_target, nullptr, stream, nullptr, online->n_cu,
                                          marl::kTdValue, next_action);
             if (err == hipSuccess && ev) err = hipEventRecord(ev[2], stream);
             return err;
@@ -513,7 +513,7 @@ int unroll_call(marl_qnet *online, marl_qnet *target, int32_t B, int32_t T, cons
         err = marl::launch_unroll_td(online->net, target->net, two, scratch_on, scratch_tg, B, T, episode_index,
                                      pool_episodes, obs, avail,
                                      actions, reward, terminated, filled, gamma, q_taken, next_max, td_target, q_all,
-                                     stream, ev ? ev[1] : nullptr);
+                                     stream, ev ? ev[1] : nullptr, online->n_cu);
         if (err == hipSuccess && ev) err = hipEventRecord(ev[2], stream);
         return err;
     };

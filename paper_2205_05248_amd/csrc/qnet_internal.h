@@ -156,7 +156,7 @@ hipError_t launch_unroll_td(const NetFrags &online, const NetFrags &target, bool
                             const float *obs, const uint8_t *avail,
                             const int32_t *actions, const float *reward, const uint8_t *terminated,
                             const uint8_t *filled, float gamma, float *q_taken, float *next_max, float *td_target,
-                            float *q_all, hipStream_t stream, hipEvent_t between, TdMode mode = kTdPlain,
+                            float *q_all, hipStream_t stream, hipEvent_t between, int n_cu, TdMode mode = kTdPlain,
                             int32_t *next_action = nullptr);
 
 // Fused decision step (act_fused.hip).  `fits` as below; groups_hint = workgroups to spread the

@@ -89,4 +89,9 @@ struct TdArrays {
 hipError_t launch_recurrent16(const NetFrags &online, const NetFrags &target, bool two_nets, const char *gi_online, const char *gi_target,
                               int B, int T, const TdArrays &td, hipStream_t stream);
 
+// First kernel of it (unroll_project16.hip), for networks of these sizes that it takes; else front_kernel.
+bool project16_fits(const NetFrags &net);
+hipError_t launch_project16(const NetFrags &online, const NetFrags &target, bool two_nets, char *gi_online, char *gi_target, int B, int T,
+                            const int32_t *episode_index, int pool_episodes, const float *obs, int n_cu, hipStream_t stream);
+
 }  // namespace marl

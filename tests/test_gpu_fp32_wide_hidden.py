@@ -22,14 +22,17 @@ def _need_gpu():
 
 SHAPES = [
     # B, T, N, D, A
-    (1, 1, 1, 1, 1),         # one row, two slots, fewer actions than a lane holds
-    (1, 2, 16, 20, 3),       # one whole tile, half a record
-    (1, 3, 17, 33, 4),       # one row past a tile
-    (2, 4, 16, 32, 16),      # one whole record
+    (1, 1, 1, 1, 1),         # one row, two slots, fewer actions than a lane holds; observations of less than eight values
+    (1, 2, 16, 8, 3),        # one whole tile, half a record; the fewest observations the weight-stationary projection takes
+    (1, 3, 17, 33, 4),       # one row past a tile; observations one past a k-step
+    (2, 4, 16, 64, 16),      # one whole record
     (3, 5, 11, 55, 17),      # one row past a record; a second action block of one action
-    (5, 6, 13, 96, 48),      # an odd number of tiles
+    (5, 6, 13, 97, 48),      # an odd number of tiles
     (7, 25, 30, 161, 64),    # the most actions, 210 rows
-    (9, 31, 5, 320, 40),
+    (2, 9, 3, 255, 5),       # eight k-steps, one observation short of whole
+    (9, 31, 5, 257, 40),     # ten k-steps with one empty
+    (3, 40, 64, 320, 9),     # the widest; more items than workgroups
+    (4, 7, 5, 321, 9),       # wider: the streaming projection
 ]
 
 
