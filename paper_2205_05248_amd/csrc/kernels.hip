@@ -427,6 +427,44 @@ __global__ __launch_bounds__(64 * recurrent_waves(H), 2) void recurrent_td_kerne
     }
 }
 
+// ------------------------------------------------------------------------------------------ double estimator
+// The value that the target network gives the action the online network chose, one thread per (episode, slot, agent).
+// A pass of its own because the two networks' workgroups run side by side: one launch after the other, each chain
+// leaves the compute units idle that the other could have had.
+__global__ __launch_bounds__(256) void pick_next_q_kernel(NextQ next_q, int B, int T, int N, int A, const int32_t *__restrict__ episode_index,
+                                                          int pool_episodes, const float *__restrict__ reward,
+                                                          const uint8_t *__restrict__ terminated, const uint8_t *__restrict__ filled, float gamma,
+                                                          const int32_t *__restrict__ next_action, float *__restrict__ next_max,
+                                                          float *__restrict__ td_target)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, bt = i / (uint32_t)N;
+    const int n = (int)(i - bt * N), b = (int)(bt / (uint32_t)T), t = (int)(bt - (uint32_t)b * T);
+    if (b >= B) return;
+    const uint32_t row = (uint32_t)b * N + n;
+    const int bi = episode_index ? min(max(episode_index[b], 0), pool_episodes - 1) : b;
+    const uint32_t at = (uint32_t)bi * T + t;
+    const int u = next_action[i];
+    const float picked = next_q.q[(row >> 5) * next_q.tile_stride + (size_t)(t + 1) * next_q.slot_stride + next_q_row(next_q, row) +
+                                  (uint32_t)min(max(u, 0), A - 1) * next_q.action_stride];
+    const float best_q = u >= 0 ? picked : 0.0f;                   // -1: the online network found no action available
+    const float keep = terminated[at] ? 0.0f : 1.0f;
+    const float y = reward[at] + gamma * keep * best_q;
+    next_max[i] = filled[at] ? best_q : 0.0f;
+    td_target[i] = filled[at] ? y : 0.0f;
+}
+
+hipError_t launch_pick_next_q(const NetFrags &net, const NextQ &next_q, int B, int T, const int32_t *episode_index, int pool_episodes,
+                              const float *reward, const uint8_t *terminated, const uint8_t *filled, float gamma, const int32_t *next_action,
+                              float *next_max, float *td_target, hipStream_t stream)
+{
+    const unsigned blocks = ((unsigned)B * T * net.N + 255u) / 256u;      // the host bounds B (T + 1) N max(D, A) to 2^30
+    hipLaunchKernelGGL(pick_next_q_kernel, dim3(blocks), dim3(256), 0, stream, next_q, B, T, net.N, net.A, episode_index, pool_episodes, reward,
+                       terminated, filled, gamma, next_action, next_max, td_target);
+    return hipGetLastError();
+}
+
+bool unroll_td_double_fits(const NetFrags &net) { return net.H == 128 && net.planes == 2; }
+
 // ------------------------------------------------------------------------------------------ launchers
 namespace {
 
@@ -483,9 +521,19 @@ hipError_t unroll_dispatch(const NetFrags &online, const NetFrags &target, bool 
         if (err != hipSuccess) return err;
     }
     if constexpr (H == 128 && P == 2) {      // tiles of 16 rows: W_hh in two planes fits the registers of eight waves, not of four
+        // kTdDouble: the target network's Q values of a slot go where its gate inputs of that slot were.  A record belongs to
+        // two tiles that do not wait for each other, 256 bytes in turn: each keeps to its own, one action in each 256.
+        constexpr size_t kRecordFloats = 3 * (H / 32) * GiLayout<P>::kBlockBytes / sizeof(float);
+        static_assert(64 * 128 <= kRecordFloats, "as many pieces of a tile's own in a record as there are actions at most");
+        NextQ next_q;
+        if (mode == kTdDouble) next_q = {reinterpret_cast<float *>(gi_tg), (size_t)(T + 1) * kRecordFloats, kRecordFloats, 64, 128};
         const TdArrays td{episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken, next_max, td_target,
-                          q_all, (int)mode, next_action};
-        return launch_recurrent16(online, target, two_nets, gi_on, gi_tg, B, T, td, stream);
+                          q_all, (int)mode, next_action, next_q};
+        hipError_t err = launch_recurrent16(online, target, two_nets, gi_on, gi_tg, B, T, td, stream);
+        if (err == hipSuccess && mode == kTdDouble)
+            err = launch_pick_next_q(online, next_q, B, T, episode_index, pool_episodes, reward, terminated, filled, gamma, next_action,
+                                     next_max, td_target, stream);
+        return err;
     } else {
         const dim3 grid((unsigned)tiles, nets), block(64 * RecurrentShape<H, P>::kWaves);
         const int two = two_nets ? 1 : 0;
@@ -532,7 +580,8 @@ hipError_t launch_unroll_td(const NetFrags &online, const NetFrags &target, bool
                             const uint8_t *filled, float gamma, float *q_taken, float *next_max, float *td_target,
                             float *q_all, hipStream_t stream, hipEvent_t between, int n_cu, TdMode mode, int32_t *next_action)
 {
-    if (mode != kTdPlain && (two_nets || !next_action)) return hipErrorInvalidValue;
+    if (mode != kTdPlain && (two_nets != (mode == kTdDouble) || !next_action)) return hipErrorInvalidValue;
+    if (mode == kTdDouble && !unroll_td_double_fits(online)) return hipErrorInvalidValue;
     char *gi_on = static_cast<char *>(scratch_online), *gi_tg = static_cast<char *>(scratch_target);
 #define MARL_UNROLL(HH, PP)                                                                                        \
     return unroll_dispatch<HH, PP>(online, target, two_nets, gi_on, gi_tg, B, T, episode_index, pool_episodes, obs, \

@@ -113,6 +113,52 @@ int ensure_scratch(marl_qnet *q, size_t bytes)
     return MARL_OK;
 }
 
+// The double-estimator call on the fused kernels keeps the target network's Q values for a pass of their own when it
+// can have room for them: not more than this, and not under stream capture, where nothing may be allocated and the graph may
+// be replayed beside anything.  Otherwise the networks run one after the other and need no room.
+constexpr size_t kNextQMost = (size_t)256 << 20;
+
+// next_q_lock held.  Allocation in a mode of its own, so that a capture elsewhere in the process is left alone.
+bool ensure_next_q(marl_qnet *q, size_t bytes)
+{
+    if (bytes > kNextQMost) return false;
+    if (bytes <= q->next_q_bytes) return true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    bool ok = true;
+    if (!q->next_q_done) ok = hipEventCreateWithFlags(&q->next_q_done, hipEventDisableTiming) == hipSuccess;
+    if (ok && q->next_q) {
+        ok = !q->next_q_used || hipEventSynchronize(q->next_q_done) == hipSuccess;
+        if (ok) ok = hipFree(q->next_q) == hipSuccess;
+        if (ok) { q->next_q = nullptr; q->next_q_bytes = 0; }
+    }
+    if (ok) {
+        ok = hipMalloc(&q->next_q, bytes) == hipSuccess;
+        if (ok) q->next_q_bytes = bytes;
+        else q->next_q = nullptr;
+    }
+    if (!ok) (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return ok;
+}
+
+// Whether both networks' workgroups in one launch are better than one network's after the other's.  A workgroup (16 rows of
+// one network) fills a compute unit and takes as long as its chain of slots, so what counts is how often the chip fills:
+// 32 episodes x 120 slots x 8 agents (64 units, 16 tiles) 221 -> 130 us, 128 tiles of 128 units 570 -> 328; but with 160 tiles,
+// twice either way, 229 -> 279, as the second time is nearly empty and the first twice as crowded.
+bool side_by_side(const marl_qnet *q, int B)
+{
+    const int64_t tiles = ((int64_t)B * q->desc.n_agents + 15) / 16, cu = q->n_cu;
+    return (2 * tiles + cu - 1) / cu < 2 * ((tiles + cu - 1) / cu);
+}
+
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // Hands out `count` events for one timed call, or nullptr when the record is full.
 hipEvent_t *take_events(marl_qnet *q, int count, int *rc)
 {
@@ -184,6 +230,10 @@ int marl_qnet_create(const marl_qnet_desc *desc, const float *host_weights, size
     q->staging_done = nullptr;
     q->scratch = nullptr;
     q->scratch_bytes = 0;
+    q->next_q = nullptr;
+    q->next_q_bytes = 0;
+    q->next_q_done = nullptr;
+    q->next_q_used = false;
     q->repack_map = nullptr;
     q->repack_elems = 0;
     q->kernels = MARL_KERNELS_AUTO;
@@ -375,7 +425,11 @@ int marl_qnet_reserve_unroll(marl_qnet *q, int32_t B, int32_t T)
         return MARL_ERR_BAD_DIM;
     DeviceGuard guard(q->desc.device);
     if (!guard.ok) return device_fail(hipErrorInvalidDevice, "hipSetDevice");
-    if (takes_fused_path(q, true)) return MARL_OK;
+    if (takes_fused_path(q, true)) {                       // room for a double-estimator call; without it that call is slower, no more
+        std::lock_guard<std::mutex> hold(q->next_q_lock);
+        if (B > 0 && side_by_side(q, B)) (void)ensure_next_q(q, marl::next_q_bytes(q->net, B, T));
+        return MARL_OK;
+    }
     return ensure_scratch(q, marl::unroll_scratch_bytes(q->net, B, T));
 }
 
@@ -427,7 +481,7 @@ int unroll_call(marl_qnet *online, marl_qnet *target, int32_t B, int32_t T, cons
 
     DeviceGuard guard(a.device);
     if (!guard.ok) return device_fail(hipErrorInvalidDevice, "hipSetDevice");
-    const bool two = online != target && !double_q;      // the double-estimator target runs the networks one after the other
+    const bool two = online != target && !double_q;      // (the double-estimator target has launches of its own)
     // no_alloc: the tiled kernels, with both networks' projections in the device's static array
     const bool fused = !no_alloc && takes_fused_path(online, true);
     int rc = MARL_OK;
@@ -472,8 +526,36 @@ int unroll_call(marl_qnet *online, marl_qnet *target, int32_t B, int32_t T, cons
         if (ev) err = hipEventRecord(ev[0], stream);
         if (err != hipSuccess) return err;
         if (double_q) {
-            // Selection by the online network (q_taken, q_all, next_action), then valuation by the target
-            // network (next_max, td_target); the stream orders the second launch after the first.
+            // Selection by the online network (q_taken, q_all, next_action), valuation by the target network (next_max,
+            // td_target): side by side in one launch where the target's Q values can be kept, else one after the other.
+            if (online != target && !fused && side_by_side(online, B) && marl::unroll_td_double_fits(online->net)) {
+                err = marl::launch_unroll_td(online->net, target->net, true, scratch_on, scratch_tg, B, T, episode_index, pool_episodes,
+                                             obs, avail, actions, reward, terminated, filled, gamma, q_taken, next_max, td_target, q_all,
+                                             stream, ev ? ev[1] : nullptr, online->n_cu, marl::kTdDouble, next_action);
+                if (err == hipSuccess && ev) err = hipEventRecord(ev[2], stream);
+                return err;
+            }
+            if (online != target && fused && side_by_side(online, B) && !capturing(stream)) {
+                std::lock_guard<std::mutex> hold(online->next_q_lock);
+                if (ensure_next_q(online, marl::next_q_bytes(online->net, B, T))) {
+                    const size_t record = (size_t)32 * online->net.A;
+                    const marl::NextQ next_q{static_cast<float *>(online->next_q), record * (T + 1), record, 16, 32};
+                    // a call on another stream may still read what the last one left
+                    if (online->next_q_used) err = hipStreamWaitEvent(stream, online->next_q_done, 0);
+                    if (err == hipSuccess && ev) err = hipEventRecord(ev[1], stream);
+                    if (err == hipSuccess)
+                        err = marl::launch_unroll_fused(online->net, target->net, true, B, T, episode_index, pool_episodes, obs, avail,
+                                                        actions, reward, terminated, filled, gamma, q_taken, nullptr, nullptr, q_all, stream,
+                                                        marl::kTdDouble, next_action, nullptr, nullptr, next_q);
+                    if (err == hipSuccess)
+                        err = marl::launch_pick_next_q(online->net, next_q, B, T, episode_index, pool_episodes, reward, terminated, filled,
+                                                       gamma, next_action, next_max, td_target, stream);
+                    if (err == hipSuccess) err = hipEventRecord(online->next_q_done, stream);
+                    online->next_q_used = true;
+                    if (err == hipSuccess && ev) err = hipEventRecord(ev[2], stream);
+                    return err;
+                }
+            }
             if (fused) {
                 err = marl::launch_unroll_fused(online->net, online->net, false, B, T, episode_index, pool_episodes, obs,
                                                 avail, actions, reward, terminated, filled, gamma, q_taken, nullptr,
@@ -733,11 +815,12 @@ int marl_destroy(marl_qnet *q)
     {
         DeviceGuard guard(q->desc.device);
         for (hipEvent_t e : q->ev_pool) (void)hipEventDestroy(e);
-        for (void *p : {q->dev_weights, q->scratch, static_cast<void *>(q->repack_map)}) {
+        for (void *p : {q->dev_weights, q->scratch, q->next_q, static_cast<void *>(q->repack_map)}) {
             if (!p) continue;
             hipError_t err = hipFree(p);
             if (err != hipSuccess) rc = device_fail(err, "hipFree");        // hipFree waits for the device
         }
+        if (q->next_q_done) (void)hipEventDestroy(q->next_q_done);
         if (q->staging_done) (void)hipEventDestroy(q->staging_done);
         if (q->staging) (void)hipHostFree(q->staging);
         if (q->side.join) (void)hipEventDestroy(q->side.join);

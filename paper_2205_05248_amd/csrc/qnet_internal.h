@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <functional>
+#include <mutex>
 #include <vector>
 
 #include "../../include/marl_qnet.h"
@@ -83,6 +84,13 @@ struct marl_qnet {
     hipEvent_t staging_done;  // recorded after the last upload from `staging`
     void *scratch;            // input-projection buffer of marl_unroll_td, grown on demand
     size_t scratch_bytes;
+    // the target network's Q values of a double-estimator call on the fused kernels (this handle's as `online`), grown on demand;
+    // `next_q_lock` while a call enqueues, next_q_done: the end of the last call that used it
+    std::mutex next_q_lock;
+    void *next_q;
+    size_t next_q_bytes;
+    hipEvent_t next_q_done;
+    bool next_q_used;
     void *static_scratch;     // this device's address of the library's static buffer (marl_unroll_td_static)
     marl::SideStream side;    // second stream of the backward pass, made with the handle
     int n_cu;                          // compute units of the device
@@ -148,8 +156,24 @@ size_t unroll_scratch_bytes(const NetFrags &net, int B, int T);
 // every slot go to x_save / h_save [B, T+1, N, H] for the backward pass (h fp32; x fp32, or bf16 for a one-plane
 // network, whose every use of x rounds it to bf16 anyway): x_save[b, s] = x of slot s,
 // h_save[b, 0] = 0 and h_save[b, s + 1] = the state after slot s (s < T).
+// kTdDouble: both halves of the double estimator in one two-network launch, whose workgroups do not wait for each other: the
+// online network's do as under kTdSelect, the target network's store their Q values (NextQ), and pick_next_q takes the chosen one.
 // kTdKeep: kTdPlain (one or two networks, all TD outputs) whose online network also stores x_save / h_save.
-enum TdMode : int { kTdPlain = 0, kTdSelect = 1, kTdValue = 2, kTdSave = 3, kTdKeep = 4 };
+enum TdMode : int { kTdPlain = 0, kTdSelect = 1, kTdValue = 2, kTdSave = 3, kTdKeep = 4, kTdDouble = 5 };
+
+// Where the target network's Q values of every slot lie under kTdDouble: records of 32 rows, [row tile][slot]; within one
+// the values of an action are action_stride apart, those of the record's two halves of 16 rows half_stride (all in floats).
+struct NextQ {
+    float *q = nullptr;
+    size_t tile_stride = 0, slot_stride = 0;
+    uint32_t half_stride = 0, action_stride = 0;
+};
+__host__ __device__ inline uint32_t next_q_row(const NextQ &x, uint32_t row) { return (row >> 4 & 1u) * x.half_stride + (row & 15u); }
+inline size_t next_q_bytes(const NetFrags &net, int B, int T) { return ((size_t)B * net.N + 31) / 32 * (size_t)(T + 1) * 32 * net.A * sizeof(float); }
+// next_max and td_target from the values at next_action (kernels.hip)
+hipError_t launch_pick_next_q(const NetFrags &net, const NextQ &next_q, int B, int T, const int32_t *episode_index, int pool_episodes,
+                              const float *reward, const uint8_t *terminated, const uint8_t *filled, float gamma, const int32_t *next_action,
+                              float *next_max, float *td_target, hipStream_t stream);
 
 hipError_t launch_unroll_td(const NetFrags &online, const NetFrags &target, bool two_nets, void *scratch_online,
                             void *scratch_target, int B, int T, const int32_t *episode_index, int pool_episodes,
@@ -158,6 +182,9 @@ hipError_t launch_unroll_td(const NetFrags &online, const NetFrags &target, bool
                             const uint8_t *filled, float gamma, float *q_taken, float *next_max, float *td_target,
                             float *q_all, hipStream_t stream, hipEvent_t between, int n_cu, TdMode mode = kTdPlain,
                             int32_t *next_action = nullptr);
+// kTdDouble in these kernels: whether they have it, and the whole step (projection, recurrence, pick_next_q); the target
+// network's Q values take the place of the gate inputs that have been read, in its own scratch.
+bool unroll_td_double_fits(const NetFrags &net);
 
 // Fused decision step (act_fused.hip).  `fits` as below; groups_hint = workgroups to spread the
 // tiles over (0: one per compute unit).
@@ -188,7 +215,7 @@ hipError_t launch_unroll_fused(const NetFrags &online, const NetFrags &target, b
                                const uint8_t *terminated, const uint8_t *filled, float gamma, float *q_taken,
                                float *next_max, float *td_target, float *q_all, hipStream_t stream,
                                TdMode mode = kTdPlain, int32_t *next_action = nullptr, float *h_save = nullptr,
-                               void *x_save = nullptr);
+                               void *x_save = nullptr, const NextQ &next_q = NextQ());
 
 // Products over samples, C[p][q] = sum_m A[m][p] B[m][q] with fp32 operands in global memory (bptt.hip).
 // Row m of an operand lives at base + (m / rows_per_group) * group_stride + (m % rows_per_group) * ld.

@@ -21,7 +21,7 @@ constexpr int kEpiWords = 4;
 constexpr size_t kEpiBytes = 2 * kEpiWords * 64 * 4;
 
 template <int AB, int MODE> struct TdTile16 {
-    static constexpr bool kSelect = MODE == kTdSelect, kValue = MODE == kTdValue, kSave = MODE == kTdSave;
+    static constexpr bool kValue = MODE == kTdValue, kSave = MODE == kTdSave;
     struct SlotIn { int u; uint32_t flags; float reward; uint32_t slots; };
     struct SlotRaw { int u; uint32_t flags; float reward; uint32_t avail_raw[AB]; };
 
@@ -35,6 +35,8 @@ template <int AB, int MODE> struct TdTile16 {
     uint32_t act0;          // actions of the episode:  + t N
     uint32_t av0;           // avail of the episode:    + t N A
     uint32_t bt0;           // per-episode flags:       + t
+    uint32_t next_row;      // the row's place in a record of the target network's Q values
+    size_t next_tile;
 
     // b, n: the lane's row of the batch; bi: the episode of the input arrays that it reads
     __device__ __forceinline__ void init(const TdArrays &arrays, const NetFrags &net, int T_, int lane_, int b, int bi, int n, bool valid_,
@@ -49,6 +51,11 @@ template <int AB, int MODE> struct TdTile16 {
         act0 = (uint32_t)(bi * T) * N + n;
         av0 = ((uint32_t)(bi * S) * N + n) * A;
         bt0 = (uint32_t)(bi * T);
+        if constexpr (MODE == kTdDouble) {
+            const uint32_t row = (uint32_t)b * N + n;
+            next_tile = (row >> 5) * arrays.next_q.tile_stride;
+            next_row = next_q_row(arrays.next_q, row);
+        }
     }
 
     template <class Wide, class WantOnline, class WantTarget>
@@ -97,13 +104,14 @@ template <int AB, int MODE> struct TdTile16 {
 
 // The epilogue wave: fc2 (W2 in registers) on the hidden state that the recurrence published during the step before,
 // and the TD step on the result.  `lead` barriers before slot 0, then T + 2 more.  emit_online: q_taken (and q_all);
-// emit_target: next_max and td_target.
+// emit_target: next_max and td_target, or (kTdSelect, kTdDouble) the index of the best action instead; store_next
+// (kTdDouble): the Q values of every slot but the first.
 template <int H, int P, int AB, bool QALL, int MODE>
 __device__ __forceinline__ void td_epilogue16(const NetFrags &net, const TdTile16<AB, MODE> &tile, bool emit_online, bool emit_target,
-                                              int lead, bf16x8 (*h_lds)[H / 32][P][64], float *b2_lds)
+                                              bool store_next, int lead, bf16x8 (*h_lds)[H / 32][P][64], float *b2_lds)
 {
     constexpr int KS = H / 32;
-    constexpr bool kSelect = MODE == kTdSelect, kValue = MODE == kTdValue;
+    constexpr bool kSelect = MODE == kTdSelect || MODE == kTdDouble, kValue = MODE == kTdValue;
     const int lane = tile.lane, q4 = tile.q4, N = tile.N, A = tile.A, T = tile.T;
     const bool valid = tile.valid;
     const TdArrays &td = tile.td;
@@ -149,6 +157,18 @@ __device__ __forceinline__ void td_epilogue16(const NetFrags &net, const TdTile1
                     const int u = min(max(in.u, 0), A - 1);
                     const float qu = pick_action_value16<AB>(qv, u, q4);
                     if (valid && q4 == 0) td.q_taken[tile.btn0 + (uint32_t)t * N] = on_filled ? qu : 0.0f;
+                }
+            }
+            if constexpr (MODE == kTdDouble) {
+                if (store_next && valid && t >= 1) {
+                    float *const at = td.next_q.q + tile.next_tile + (size_t)t * td.next_q.slot_stride + tile.next_row;
+#pragma unroll
+                    for (int ab = 0; ab < AB; ++ab)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int action = 16 * ab + 4 * q4 + r;
+                            if (action < A) at[(uint32_t)action * td.next_q.action_stride] = qv[ab][r];
+                        }
                 }
             }
             if (emit_target && t >= 1) {

@@ -82,10 +82,12 @@ struct TdArrays {
     float gamma;
     float *q_taken, *next_max, *td_target, *q_all;
     int mode;                       // TdMode
-    int32_t *next_action;           // written under kTdSelect, read under kTdValue, unused otherwise
+    int32_t *next_action;           // written under kTdSelect and kTdDouble, read under kTdValue, unused otherwise
+    NextQ next_q;                   // kTdDouble
 };
 
-// Second kernel of the two-kernel unroll for 128 hidden units in fp32 (unroll_recur16.hip); td.mode: kTdPlain, kTdSelect or kTdValue.
+// Second kernel of the two-kernel unroll for 128 hidden units in fp32 (unroll_recur16.hip); td.mode: kTdPlain, kTdSelect,
+// kTdValue or kTdDouble.
 hipError_t launch_recurrent16(const NetFrags &online, const NetFrags &target, bool two_nets, const char *gi_online, const char *gi_target,
                               int B, int T, const TdArrays &td, hipStream_t stream);
 

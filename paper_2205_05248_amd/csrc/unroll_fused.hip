@@ -47,7 +47,7 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
     const uint8_t *__restrict__ avail, const int32_t *__restrict__ actions, const float *__restrict__ reward,
     const uint8_t *__restrict__ terminated, const uint8_t *__restrict__ filled, float gamma,
     float *__restrict__ q_taken, float *__restrict__ next_max, float *__restrict__ td_target, float *__restrict__ q_all,
-    int32_t *__restrict__ next_action, float *__restrict__ h_save, void *__restrict__ x_save)
+    int32_t *__restrict__ next_action, float *__restrict__ h_save, void *__restrict__ x_save, NextQ next_q)
 {
     using Sh = Fused16<H, P>;
     constexpr int FBK = Sh::FBK, KS = Sh::KS, LEAD = kFusedLead;
@@ -77,10 +77,10 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
     // episode of the input arrays: the batch position itself, or the listed episode of a larger pool
     const int bi = episode_index ? min(max(episode_index[b], 0), pool_episodes - 1) : b;
 
-    constexpr bool kValue = MODE == kTdValue, kSave = MODE == kTdSave;
+    constexpr bool kValue = MODE == kTdValue, kSave = MODE == kTdSave, kDouble = MODE == kTdDouble;
     TdTile16<AB, MODE> tile;
     tile.init(TdArrays{episode_index, pool_episodes, avail, actions, reward, terminated, filled, gamma, q_taken, next_max, td_target,
-                       q_all, MODE, next_action},
+                       q_all, MODE, next_action, next_q},
               net, T, lane, b, bi, n, valid, lds + Sh::lds_bytes(ks1));
 
     // W_ih -> LDS, all waves.  Its first readers start after kFusedLead barriers.
@@ -130,7 +130,8 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         }
     } else if (wave == Sh::kEpilogue) {
         // ---------------------------------------------------------------- epilogue wave
-        td_epilogue16<H, P, AB, QALL, MODE>(net, tile, !is_target && !kValue && !kSave, (is_target || !two_nets) && !kSave, LEAD, h_lds,
+        td_epilogue16<H, P, AB, QALL, MODE>(net, tile, !is_target && !kValue && !kSave, (kDouble ? !is_target : is_target || !two_nets) && !kSave,
+                                            kDouble && is_target, LEAD, h_lds,
                                             reinterpret_cast<float *>(lds + Sh::oB2));
     } else if (wave == Sh::kLoader) {
         // ---------------------------------------------------------------- loader wave
@@ -163,8 +164,9 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         using Yes = std::true_type;
         using No = std::false_type;
         // which half the workgroup's epilogue uses (see emit_online / emit_target there)
-        const bool need_online = !is_target && !kValue, need_target = is_target || !two_nets;
-        if (A >= 4) {
+        const bool need_online = !is_target && !kValue, need_target = kDouble ? !is_target : is_target || !two_nets;
+        if (kDouble && is_target) loader_loop(No{}, No{}, No{});
+        else if (A >= 4) {
             if (need_online && need_target) loader_loop(Yes{}, Yes{}, Yes{});
             else if (need_online) loader_loop(Yes{}, Yes{}, No{});
             else loader_loop(Yes{}, No{}, Yes{});
@@ -233,7 +235,7 @@ hipError_t fused_dispatch(const NetFrags &online, const NetFrags &target, bool t
                           const int32_t *episode_index, int pool_episodes, const float *obs, const uint8_t *avail, const int32_t *actions, const float *reward,
                           const uint8_t *terminated, const uint8_t *filled, float gamma, float *q_taken,
                           float *next_max, float *td_target, float *q_all, hipStream_t stream, TdMode mode,
-                          int32_t *next_action, float *h_save, void *x_save)
+                          int32_t *next_action, float *h_save, void *x_save, const NextQ &next_q)
 {
     const int tiles = (B * online.N + 15) / 16;
     const dim3 grid(two_nets ? (unsigned)((tiles + 7) / 8) * 16u : (unsigned)tiles), block(fused_threads(H));
@@ -248,12 +250,13 @@ hipError_t fused_dispatch(const NetFrags &online, const NetFrags &target, bool t
         launch_kernel(kernel, grid, block, lds, stream, online, target, two, B, T, episode_index, pool_episodes,      \
                            obs, avail, actions,                                                                      \
                            reward, terminated, filled, gamma, q_taken, next_max, td_target, q_all, next_action,     \
-                           h_save, x_save);                                                                         \
+                           h_save, x_save, next_q);                                                                 \
     } while (0)
 #define MARL_FUSED_Q(ABLK)                                                                                          \
     do {                                                                                                            \
         if (mode == kTdSave) MARL_FUSED(ABLK, false, kTdSave);                                                      \
         else if (mode == kTdKeep) { if (q_all) MARL_FUSED(ABLK, true, kTdKeep); else MARL_FUSED(ABLK, false, kTdKeep); } \
+        else if (mode == kTdDouble) { if (q_all) MARL_FUSED(ABLK, true, kTdDouble); else MARL_FUSED(ABLK, false, kTdDouble); } \
         else if (mode == kTdValue) MARL_FUSED(ABLK, false, kTdValue);                                               \
         else if (mode == kTdSelect) { if (q_all) MARL_FUSED(ABLK, true, kTdSelect); else MARL_FUSED(ABLK, false, kTdSelect); } \
         else if (q_all) MARL_FUSED(ABLK, true, kTdPlain);                                                           \
@@ -292,14 +295,15 @@ hipError_t launch_unroll_fused(const NetFrags &online, const NetFrags &target, b
                                const int32_t *episode_index, int pool_episodes, const float *obs, const uint8_t *avail, const int32_t *actions, const float *reward,
                                const uint8_t *terminated, const uint8_t *filled, float gamma, float *q_taken,
                                float *next_max, float *td_target, float *q_all, hipStream_t stream, TdMode mode,
-                               int32_t *next_action, float *h_save, void *x_save)
+                               int32_t *next_action, float *h_save, void *x_save, const NextQ &next_q)
 {
     if ((mode == kTdSelect || mode == kTdValue) && (two_nets || !next_action)) return hipErrorInvalidValue;
+    if (mode == kTdDouble && (!two_nets || !next_action || !next_q.q)) return hipErrorInvalidValue;
     if (mode == kTdSave && (two_nets || !h_save || !x_save)) return hipErrorInvalidValue;
     if (mode == kTdKeep && (!h_save || !x_save)) return hipErrorInvalidValue;
 #define MARL_GO(HH, PP)                                                                                             \
     return fused_dispatch<HH, PP>(online, target, two_nets, B, T, episode_index, pool_episodes, obs, avail, actions, reward, terminated, filled,  \
-                                  gamma, q_taken, next_max, td_target, q_all, stream, mode, next_action, h_save, x_save)
+                                  gamma, q_taken, next_max, td_target, q_all, stream, mode, next_action, h_save, x_save, next_q)
     if (online.H == 64 && online.planes == 2) MARL_GO(64, 2);
     if (online.H == 64 && online.planes == 1) MARL_GO(64, 1);
     if (online.H == 128 && online.planes == 1) MARL_GO(128, 1);

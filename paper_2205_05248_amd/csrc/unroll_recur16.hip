@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel
 {
     using Sh = Recur16;
     constexpr int H = Sh::H, P = Sh::P, KS = Sh::KS, LEAD = Sh::kLead;
-    constexpr bool kValue = MODE == kTdValue;
+    constexpr bool kValue = MODE == kTdValue, kDouble = MODE == kTdDouble;
     __shared__ bf16x8 h_lds[2][KS][P][64];
     __shared__ __attribute__((aligned(16))) char epi_lds[kEpiBytes];
     __shared__ __attribute__((aligned(16))) float b2_lds[64];
@@ -154,7 +154,8 @@ __global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel
     TdTile16<AB, MODE> tile;
     tile.init(td, net, T, lane, b, bi, n, valid, epi_lds);
     if (wave == Sh::kEpilogue) {
-        td_epilogue16<H, P, AB, QALL, MODE>(net, tile, !is_target && !kValue, is_target || !two_nets, LEAD, h_lds, b2_lds);
+        td_epilogue16<H, P, AB, QALL, MODE>(net, tile, !is_target && !kValue, kDouble ? !is_target : is_target || !two_nets,
+                                            kDouble && is_target, LEAD, h_lds, b2_lds);
         return;
     }
     using SlotRaw = typename TdTile16<AB, MODE>::SlotRaw;
@@ -174,8 +175,9 @@ __global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel
     };
     using Yes = std::true_type;
     using No = std::false_type;
-    const bool need_online = !is_target && !kValue, need_target = is_target || !two_nets;
-    if (A >= 4) {
+    const bool need_online = !is_target && !kValue, need_target = kDouble ? !is_target : is_target || !two_nets;
+    if (kDouble && is_target) loader_loop(No{}, No{}, No{});
+    else if (A >= 4) {
         if (need_online && need_target) loader_loop(Yes{}, Yes{}, Yes{});
         else if (need_online) loader_loop(Yes{}, Yes{}, No{});
         else loader_loop(Yes{}, No{}, Yes{});
@@ -190,13 +192,15 @@ hipError_t launch_recurrent16(const NetFrags &online, const NetFrags &target, bo
                               int B, int T, const TdArrays &td, hipStream_t stream)
 {
     if (online.H != Recur16::H || online.planes != Recur16::P) return hipErrorInvalidValue;
+    if (td.mode == kTdDouble && (!two_nets || !td.next_q.q)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((B * online.N + 15) / 16), two_nets ? 2u : 1u), block(64 * Recur16::kWaves);
     const int two = two_nets ? 1 : 0;
 #define MARL_REC16(ABLK, QA, MD)                                                                                               \
     hipLaunchKernelGGL((recurrent16_td_kernel<ABLK, QA, MD>), grid, block, 0, stream, online, target, gi_online, gi_target, two, B, T, td)
 #define MARL_REC16_Q(ABLK)                                                                                                     \
     do {                                                                                                                       \
-        if (td.mode == kTdValue) MARL_REC16(ABLK, false, kTdValue);                                                            \
+        if (td.mode == kTdDouble) { if (td.q_all) MARL_REC16(ABLK, true, kTdDouble); else MARL_REC16(ABLK, false, kTdDouble); } \
+        else if (td.mode == kTdValue) MARL_REC16(ABLK, false, kTdValue);                                                            \
         else if (td.mode == kTdSelect) { if (td.q_all) MARL_REC16(ABLK, true, kTdSelect); else MARL_REC16(ABLK, false, kTdSelect); } \
         else if (td.mode != kTdPlain) return hipErrorInvalidValue;                                                             \
         else if (td.q_all) MARL_REC16(ABLK, true, kTdPlain);                                                                   \
