@@ -3,6 +3,7 @@
 // offsets of the LDS buffers.
 #pragma once
 #include <atomic>
+#include <type_traits>
 
 #include "mfma16_tile.h"
 #include "unroll_common.h"
@@ -29,7 +30,34 @@ constexpr int kFusedLead = 3;         // steps before slot 0 enters the recurren
 constexpr int kLdsLimit = 160 * 1024;
 constexpr int kRawBuffer = 0x00020000;       // descriptor word 3: untyped 32-bit data, no swizzle, offsets checked against the size
 
-template <int H, int P> struct Fused16 {
+// k-steps that the first layer's product takes: those of the observations, rounded up to a number the roles are compiled for.
+// Their loops over the k-steps are straight-line code (with_k_steps below): a branch around a load makes the compiler wait
+// for everything in flight, and the loader, whose k-steps were counted at run time, waited out a trip to memory in
+// every step of the unroll; it was the last wave at the barrier in each.
+__host__ __device__ constexpr int obs_k_steps(int planes, int D)
+{
+    const int ks1 = (D + 31) / 32;
+    if (ks1 <= 4 || planes == 2) return ks1;                        // two planes: 5 at most
+    return (ks1 + 1) / 2 * 2;
+}
+
+template <int P, class F>
+__device__ __forceinline__ void with_k_steps(int ks1, F f)
+{
+    switch (ks1) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    default:
+        if constexpr (P == 2) f(std::integral_constant<int, 5>{});
+        else if (ks1 == 6) f(std::integral_constant<int, 6>{});
+        else if (ks1 == 8) f(std::integral_constant<int, 8>{});
+        else f(std::integral_constant<int, 10>{});
+    }
+}
+
+template <int H, int P, bool WIH_IN_REGS = false> struct Fused16 {
     static constexpr int FBK = H / 16;                 // feature blocks of the hidden layer
     static constexpr int KS = H / 32;                  // k-steps over the hidden layer
     static constexpr int NC = 4;                       // compute waves
@@ -40,12 +68,17 @@ template <int H, int P> struct Fused16 {
     static constexpr int kKs1Max = 10 / P;             // observation k-steps: W1 fragments of an fc1 wave within 160 registers (H = 128), 80 (H = 64)
     static constexpr int kFrag = P * 1024;             // bytes of one fragment (all planes)
     // LDS layout (byte offsets)
+    // WIH_IN_REGS: W_ih in the compute waves' registers, beside W_hh (64 hidden units: 96 of them in two planes), as are the gate
+    // biases: a wave issues a 16-byte LDS read every 29 clocks at best, and these were 15 of the 23 reads of a wave and slot.
+    static constexpr bool kWihInRegs = WIH_IN_REGS;
+    static constexpr int kWihVecs = kWihInRegs ? 0 : 3 * FBK * KS * P * 64;     // 16-byte vectors of W_ih in LDS
     static constexpr int oWih = 0;                                  // [3 FBK][KS][P][64] bf16x8
-    static constexpr int oH = oWih + 3 * FBK * KS * kFrag;          // [2][KS][P][64] bf16x8
+    static constexpr int oH = oWih + kWihVecs * 16;                 // [2][KS][P][64] bf16x8
     static constexpr int oX = oH + 2 * KS * kFrag;                  // [2][KS][P][64] bf16x8
     static constexpr int oGBias = oX + 2 * KS * kFrag;              // [3 H] floats: b_ir + b_hr, b_iz + b_hz, b_in
     static constexpr int oB2 = oGBias + 3 * H * 4;                  // [64] floats
     static constexpr int oObs = oB2 + 256;                          // [2][ks1][P][64] bf16x8
+    // (ks1 here and below: obs_k_steps of the network)
     static constexpr size_t lds_bytes(int ks1) { return (size_t)oObs + (size_t)2 * ks1 * kFrag; }
     // decision step only, after the observations: the incoming hidden state as operand fragments
     // [2][KS][P][64] bf16x8, then in fp32 by feature block [2][FBK][64] float4

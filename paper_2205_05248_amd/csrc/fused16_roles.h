@@ -22,12 +22,27 @@ template <int P> __device__ __forceinline__ void settle(const WFrag<P> &w)
     if constexpr (P == 2) asm volatile("" ::"v"(w.lo));
 }
 
-template <int H, int P> struct GruWave {
-    using Sh = Fused16<H, P>;
+// Eight 16-bit values moved up by s places (0 <= s <= 8), zeros below.
+__device__ __forceinline__ bf16x8 shift_up(const bf16x8 &v, int s)
+{
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2 a = __builtin_bit_cast(u64x2, v);
+    const int low = 16 * (s & 3);
+    const uint64_t first = a[0] << low, spill = low ? a[0] >> (64 - low) : 0;
+    u64x2 r;
+    r[0] = s < 4 ? first : 0;
+    r[1] = s < 4 ? (a[1] << low) | spill : (s < 8 ? first : 0);
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+template <int H, int P, bool REGS = false> struct GruWave {
+    using Sh = Fused16<H, P, REGS>;
     static constexpr int FBK = Sh::FBK, KS = Sh::KS, NBC = Sh::NBC;
     typedef bf16x8 (*FragBuf)[KS][P][64];
+    static constexpr bool kRegs = REGS;
     WFrag<P> whh[3][NBC][KS];
-    f32x4 bias_hn[NBC];
+    WFrag<P> wih[kRegs ? 3 : 1][kRegs ? NBC : 1][kRegs ? KS : 1];      // (in LDS otherwise, as are the gate biases)
+    f32x4 bias_hn[NBC], bias_g[kRegs ? 3 : 1][NBC];
 
     // w = index of the compute wave: feature blocks NBC w .. NBC w + NBC - 1, all three gates
     __device__ __forceinline__ void load(const NetFrags &net, int w, int lane, int q4)
@@ -41,6 +56,17 @@ template <int H, int P> struct GruWave {
                     whh[gate][j][ks] = load_wfrag<P>(net.whh_16 + ((size_t)((gate * FBK + NBC * w + j) * KS + ks) * P) * 64 + lane);
 #pragma unroll
         for (int j = 0; j < NBC; ++j) bias_hn[j] = load_feature4(net.bias_hn, NBC * w + j, q4);
+        if constexpr (kRegs) {
+#pragma unroll
+            for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+                for (int j = 0; j < NBC; ++j) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+                        wih[gate][j][ks] = load_wfrag<P>(net.wih_16 + ((size_t)((gate * FBK + NBC * w + j) * KS + ks) * P) * 64 + lane);
+                    bias_g[gate][j] = load_feature4(gate == 0 ? net.bias_r : gate == 1 ? net.bias_z : net.bias_in, NBC * w + j, q4);
+                }
+        }
     }
 
     __device__ __forceinline__ void settle_weights() const
@@ -53,6 +79,16 @@ template <int H, int P> struct GruWave {
                 for (int ks = 0; ks < KS; ++ks) settle(whh[gate][j][ks]);
 #pragma unroll
         for (int j = 0; j < NBC; ++j) asm volatile("" ::"v"(bias_hn[j]));
+        if constexpr (kRegs) {
+#pragma unroll
+            for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+                for (int j = 0; j < NBC; ++j) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) settle(wih[gate][j][ks]);
+                    asm volatile("" ::"v"(bias_g[gate][j]));
+                }
+        }
     }
 
     // Gate biases (b_ir + b_hr, b_iz + b_hz, b_in) -> LDS, by one wave; read after a barrier.
@@ -71,6 +107,36 @@ template <int H, int P> struct GruWave {
     __device__ __forceinline__ void step(char *lds, int w, int lane, int q4, const bf16x8 (*h_src)[P][64],
                                          const bf16x8 (*x_src)[P][64], f32x4 (&hv)[NBC]) const
     {
+        if constexpr (kRegs) {
+            Frag<P> hb[KS], x[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                x[ks].hi = x_src[ks][0][lane];
+                if constexpr (P == 2) x[ks].lo = x_src[ks][1][lane];
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                hb[ks].hi = h_src[ks][0][lane];
+                if constexpr (P == 2) hb[ks].lo = h_src[ks][1][lane];
+            }
+#pragma unroll
+            for (int j = 0; j < NBC; ++j) {
+                f32x4 acc_r = bias_g[0][j], acc_z = bias_g[1][j], acc_in = bias_g[2][j], acc_hn = bias_hn[j];
+                f32x4 *const acc_x[3] = {&acc_r, &acc_z, &acc_in}, *const acc_h[3] = {&acc_r, &acc_z, &acc_hn};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const WFrag<P> *const wx[3] = {&wih[0][j][ks], &wih[1][j][ks], &wih[2][j][ks]};
+                    mma16_across<P, 3>(acc_x, wx, x[ks]);
+                }
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const WFrag<P> *const wh[3] = {&whh[0][j][ks], &whh[1][j][ks], &whh[2][j][ks]};
+                    mma16_across<P, 3>(acc_h, wh, hb[ks]);
+                }
+                hv[j] = gru_blend4(acc_r, acc_z, acc_in, acc_hn, hv[j]);
+            }
+            return;
+        }
         const float *gb = reinterpret_cast<const float *>(lds + Sh::oGBias);
         // W_ih fragments of this wave: two per-lane base addresses (an LDS access encodes at most
         // 64 KB of constant offset, the matrix may be larger) that already contain the wave's own
@@ -185,6 +251,30 @@ template <int H, int P> struct Fc1Wave {
                 if (ks < ks1) settle(w1[j][ks]);
     }
 
+    // The same for step_k: the weights of the k-steps past the network's own are zero, and those of the last eight
+    // observations are where ObsStageK puts these.
+    __device__ __forceinline__ void load_k(const NetFrags &net, int f, int lane)
+    {
+        const int D = net.D, ks1 = (D + 31) / 32;
+#pragma unroll
+        for (int j = 0; j < NBF; ++j)
+#pragma unroll
+            for (int ks = 0; ks < KM; ++ks) {
+                w1[j][ks] = load_wfrag<P>(net.w1_16 + ((size_t)((f * NBF + j) * ks1 + min(ks, ks1 - 1)) * P) * 64 + lane);
+                const int shift = ks < ks1 ? (D >= 8 ? min(max(32 * ks + 8 * (lane >> 4) - (D - 8), 0), 8) : 0) : 8;
+                w1[j][ks].hi = shift_up(w1[j][ks].hi, shift);
+                if constexpr (P == 2) w1[j][ks].lo = shift_up(w1[j][ks].lo, shift);
+            }
+    }
+
+    __device__ __forceinline__ void settle_weights_k() const
+    {
+#pragma unroll
+        for (int j = 0; j < NBF; ++j)
+#pragma unroll
+            for (int ks = 0; ks < KM; ++ks) settle(w1[j][ks]);
+    }
+
     static __device__ __forceinline__ void load_bias(const NetFrags &net, int f, int n, int q4, f32x4 (&b1v)[NBF])
     {
 #pragma unroll
@@ -192,11 +282,8 @@ template <int H, int P> struct Fc1Wave {
     }
 
     // One item: observation fragments obs_src[ks] (LDS) -> x fragments of this wave's blocks in x_dst.
-    // SAVE: x also goes to elements 16 block + 0..3 of x_row (the caller has added the lane's 4 q; null: no store):
-    // fp32 for a two-plane network, bf16 for a one-plane network (the rounding every reader of x applies anyway).
-    template <bool SAVE = false>
     __device__ __forceinline__ void step(const bf16x8 *obs_src, int ks1, int f, int lane, const f32x4 (&b1v)[NBF],
-                                         bf16x8 (*x_dst)[P][64], void *x_row = nullptr) const
+                                         bf16x8 (*x_dst)[P][64]) const
     {
         auto obs_frag = [&](int ks) {
             const bf16x8 *src = obs_src + (size_t)(ks * P) * 64 + lane;
@@ -233,20 +320,69 @@ template <int H, int P> struct Fc1Wave {
         for (int j = 0; j < NBF; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[j][r] = fmaxf(acc[j][r] + b1v[j][r], 0.0f);
+#pragma unroll
+        for (int jj = 0; jj < NBF / 2; ++jj) {
+            const Frag<P> fr = frag_of_pair<P>(acc[2 * jj], acc[2 * jj + 1]);
+            x_dst[f * (NBF / 2) + jj][0][lane] = fr.hi;
+            if constexpr (P == 2) x_dst[f * (NBF / 2) + jj][1][lane] = fr.lo;
+        }
+    }
+
+    // The same, straight-line, over KN = obs_k_steps fragments; after load_k.
+    // SAVE: x also goes to byte x_at (+ the block's) of *x_buf, fp32 for a two-plane network, bf16 for a one-plane network (the
+    // rounding every reader of x applies anyway).  The store is unconditional; x_drop, all ones, puts it beyond the buffer, which
+    // drops it.
+    template <int KN, bool SAVE = false>
+    __device__ __forceinline__ void step_k(const bf16x8 *obs_src, int f, int lane, const f32x4 (&b1v)[NBF], bf16x8 (*x_dst)[P][64],
+                                         const __amdgpu_buffer_rsrc_t *x_buf = nullptr, uint32_t x_at = 0, uint32_t x_drop = 0) const
+    {
+        auto obs_frag = [&](int ks) {
+            const bf16x8 *src = obs_src + (size_t)(ks * P) * 64 + lane;
+            Frag<P> fr;
+            fr.hi = src[0];
+            if constexpr (P == 2) fr.lo = src[64];
+            return fr;
+        };
+        f32x4 acc[NBF];
+#pragma unroll
+        for (int j = 0; j < NBF; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][r] = 0.0f;
+        // observation fragments are read two k-steps ahead of their MFMAs (LDS latency)
+        Frag<P> bq[3];
+        bq[0] = obs_frag(0);
+        if constexpr (KN > 1) bq[1] = obs_frag(1);
+#pragma unroll
+        for (int ks = 0; ks < KN; ++ks) {
+            if (ks + 2 < KN) bq[(ks + 2) % 3] = obs_frag(ks + 2);
+            f32x4 *accs[NBF];
+            const WFrag<P> *wf[NBF];
+#pragma unroll
+            for (int j = 0; j < NBF; ++j) {
+                accs[j] = &acc[j];
+                wf[j] = &w1[j][ks];
+            }
+            mma16_across<P, NBF>(accs, wf, bq[ks % 3]);
+        }
+#pragma unroll
+        for (int j = 0; j < NBF; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][r] = fmaxf(acc[j][r] + b1v[j][r], 0.0f);
         if constexpr (SAVE) {
-            if (x_row)
 #pragma unroll
-                for (int j = 0; j < NBF; ++j) {
-                    if constexpr (P == 1) {
-                        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-                        bf16x4 v;
+            for (int j = 0; j < NBF; ++j) {
+                if constexpr (P == 1) {
+                    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    bf16x4 v;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = (__bf16)acc[j][r];
-                        *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(x_row) + 16 * (f * NBF + j)) = v;
-                    } else {
-                        *reinterpret_cast<f32x4 *>(static_cast<float *>(x_row) + 16 * (f * NBF + j)) = acc[j];
-                    }
+                    for (int r = 0; r < 4; ++r) v[r] = (__bf16)acc[j][r];
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), *x_buf, (x_at + 32u * (f * NBF + j)) | x_drop, 0, 0);
+                } else {
+                    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j]), *x_buf, (x_at + 64u * (f * NBF + j)) | x_drop, 0, 0);
                 }
+            }
         }
 #pragma unroll
         for (int jj = 0; jj < NBF / 2; ++jj) {
@@ -311,6 +447,51 @@ template <int H, int P> struct ObsStage {
         for (int k = 0; k < KM - 1; ++k)
             if (k < nfull) put(dst + (k * P) * 64, r.stage[k]);
         put(dst + (nfull * P) * 64, r.last);
+    }
+};
+
+// The same with the k-steps (KN: obs_k_steps) known at compile time, for the unroll's loader.  Where a lane's eight floats would
+// pass the row's end it holds the row's last eight instead, and the weights are shifted to match (Fc1Wave::load_k), so that
+// every load is a wide one.  Rows of less than eight floats (SHORT) are fetched element by element, positions past the end from the
+// last one, whose weights are zero.  (In the decision step, whose loader and fc1 waves have more to address per item, this form
+// was slower: 2048 x 32 rows of 300 observations 45.0 -> 58.0 us.)
+template <int KN> struct ObsRegsK { float v[KN][8]; };
+
+template <int P, int KN, bool SHORT> struct ObsStageK {
+    int off[SHORT ? 8 : KN];
+
+    __device__ __forceinline__ void init(int D, int q4)
+    {
+#pragma unroll
+        for (int i = 0; i < (SHORT ? 8 : KN); ++i) off[i] = SHORT ? min(8 * q4 + i, D - 1) : min(32 * i + 8 * q4, D - 8);
+    }
+
+    __device__ __forceinline__ void load(ObsRegsK<KN> &r, const float *row) const
+    {
+        if constexpr (SHORT) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) r.v[0][i] = row[off[i]];
+        } else {
+#pragma unroll
+            for (int k = 0; k < KN; ++k) {
+                f32x4 lo4, hi4;
+                __builtin_memcpy(&lo4, row + off[k], 16);
+                __builtin_memcpy(&hi4, row + off[k] + 4, 16);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { r.v[k][i] = lo4[i]; r.v[k][4 + i] = hi4[i]; }
+            }
+        }
+    }
+
+    // dst = this lane's slot in the item's first fragment
+    __device__ __forceinline__ void write(const ObsRegsK<KN> &r, bf16x8 *dst) const
+    {
+#pragma unroll
+        for (int k = 0; k < KN; ++k) {
+            const Frag<P> f = to_frag<P>(r.v[k]);
+            dst[(k * P) * 64] = f.hi;
+            if constexpr (P == 2) dst[(k * P + 1) * 64] = f.lo;
+        }
     }
 };
 

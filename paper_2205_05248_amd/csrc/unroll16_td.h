@@ -15,15 +15,15 @@ namespace marl {
 // (positions clamped into the arrays, rows past the end read row 0), and hands them over in LDS:
 // epi[slot & 1][word][lane], words: 0 action, 1 flags (filled(t) | terminated(t-1) << 8 | filled(t-1) << 16),
 // 2 reward(t-1), 3 the lane's availability slots of slot t (avail_mask16, formed by the loader).
-// With two networks each workgroup's epilogue uses one half only - the online one the action and filled(t),
-// the target one the rest - and its loader fetches just that half (want_online / want_target).
+// (With two networks each workgroup's epilogue uses one half only; all of it is fetched, as the loader is not what a step
+// waits for.)  wide: at least four actions, whose availability is read four bytes at a time.
 constexpr int kEpiWords = 4;
 constexpr size_t kEpiBytes = 2 * kEpiWords * 64 * 4;
 
 template <int AB, int MODE> struct TdTile16 {
     static constexpr bool kValue = MODE == kTdValue, kSave = MODE == kTdSave;
     struct SlotIn { int u; uint32_t flags; float reward; uint32_t slots; };
-    struct SlotRaw { int u; uint32_t flags; float reward; uint32_t avail_raw[AB]; };
+    struct SlotRaw { int u; uint32_t filled, terminated_prev, filled_prev; float reward; uint32_t avail_raw[AB]; };
 
     TdArrays td;
     uint32_t *epi;
@@ -58,35 +58,35 @@ template <int AB, int MODE> struct TdTile16 {
         }
     }
 
-    template <class Wide, class WantOnline, class WantTarget>
-    __device__ __forceinline__ SlotRaw fetch(int t, Wide, WantOnline, WantTarget) const        // t in 0 .. T
+    template <class Wide>
+    __device__ __forceinline__ SlotRaw fetch(int t, Wide) const        // t in 0 .. T
     {
-        constexpr bool kOn = WantOnline::value, kTg = WantTarget::value;
         SlotRaw in{};
         if constexpr (!kSave) {
             const uint32_t tq = (uint32_t)min(t, T - 1), tp = (uint32_t)max(t - 1, 0);
-            if constexpr (kValue) in.u = td.next_action[btn0 + tp * N];
-            else if constexpr (kOn) in.u = td.actions[act0 + tq * N];
-            if constexpr (kOn) in.flags = (uint32_t)td.filled[bt0 + tq];
-            if constexpr (kTg) {
-                in.flags |= (uint32_t)td.terminated[bt0 + tp] << 8 | (uint32_t)td.filled[bt0 + tp] << 16;
-                in.reward = td.reward[bt0 + tp];
-                if constexpr (Wide::value && !kValue)
-                    issue_avail_loads16<AB>(td.avail + (av0 + (uint32_t)t * N * A), A, q4, in.avail_raw);
-            }
+            in.u = kValue ? td.next_action[btn0 + tp * N] : td.actions[act0 + tq * N];
+            in.filled = td.filled[bt0 + tq];
+            in.terminated_prev = td.terminated[bt0 + tp];
+            in.filled_prev = td.filled[bt0 + tp];
+            in.reward = td.reward[bt0 + tp];
+            if constexpr (Wide::value && !kValue) issue_avail_loads16<AB>(td.avail + (av0 + (uint32_t)t * N * A), A, q4, in.avail_raw);
         }
         return in;
     }
 
-    template <class Wide, class WantTarget>
-    __device__ __forceinline__ void stage(const SlotRaw &in, int t, Wide, WantTarget) const
+    template <class Wide>
+    __device__ __forceinline__ void stage(const SlotRaw &in, int t, Wide) const
     {
-        uint32_t *at = epi + (size_t)(t & 1) * kEpiWords * 64 + lane;
-        at[0] = (uint32_t)in.u;
-        at[64] = in.flags;
-        if constexpr (WantTarget::value) {
+        if constexpr (!kSave) {
+            uint32_t *at = epi + (size_t)(t & 1) * kEpiWords * 64 + lane;
+            // The flags pass through the empty asm so that they are put together here: done where they are loaded, the loader
+            // waited for them there, a trip to memory in every step.
+            uint32_t filled = in.filled, terminated_prev = in.terminated_prev, filled_prev = in.filled_prev;
+            asm volatile("" : "+v"(filled), "+v"(terminated_prev), "+v"(filled_prev));
+            at[0] = (uint32_t)in.u;
+            at[64] = filled | terminated_prev << 8 | filled_prev << 16;
             at[128] = __builtin_bit_cast(uint32_t, in.reward);
-            if constexpr (Wide::value && !kValue && !kSave) at[192] = avail_mask16<AB>(in.avail_raw, A, q4, valid);
+            if constexpr (Wide::value && !kValue) at[192] = avail_mask16<AB>(in.avail_raw, A, q4, valid);
         }
     }
 

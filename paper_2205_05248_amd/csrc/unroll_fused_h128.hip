@@ -1,0 +1,8 @@
+// Fused unroll: the instantiations for 128 hidden units, bf16 weights (see unroll_fused_kernel.h).
+#include "unroll_fused_kernel.h"
+
+namespace marl {
+
+hipError_t launch_unroll_fused_h128(const FusedCall &call) { return fused_dispatch<128, 1>(call); }
+
+}  // namespace marl

@@ -35,19 +35,6 @@ struct ProjectArgs {
     uint32_t magic;                      // ceil(2^32 / N): row / N is a multiplication, exact below 2^26 rows
 };
 
-// Eight 16-bit values moved up by s places (0 <= s <= 8), zeros below.
-__device__ __forceinline__ bf16x8 shift_up(const bf16x8 &v, int s)
-{
-    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-    const u64x2 a = __builtin_bit_cast(u64x2, v);
-    u64x2 r;
-    const int low = 16 * (s & 3);
-    const uint64_t lo = s < 4 ? a[0] << low : 0, spill = low ? a[0] >> (64 - low) : 0;
-    r[0] = lo;
-    r[1] = s < 4 ? (a[1] << low) | spill : (s < 8 ? a[0] << low : 0);
-    return __builtin_bit_cast(bf16x8, r);
-}
-
 }  // namespace
 
 // KM: k-steps over the observations, the network's own rounded up (weights of the rest zero).

@@ -160,10 +160,10 @@ __global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel
     }
     using SlotRaw = typename TdTile16<AB, MODE>::SlotRaw;
     SlotRaw epi_a{}, epi_b{};
-    auto loader_loop = [&](auto wide, auto want_online, auto want_target) {
+    auto loader_loop = [&](auto wide) {
         auto loader_step = [&](const SlotRaw &ready, SlotRaw &refill, int s) {
-            refill = tile.fetch(min(max(s + 1, 0), T), wide, want_online, want_target);
-            if (s >= 0 && s <= T) tile.stage(ready, s, wide, want_target);
+            refill = tile.fetch(min(max(s + 1, 0), T), wide);
+            tile.stage(ready, s, wide);
             lds_barrier();
         };
         int s = -LEAD;
@@ -173,19 +173,8 @@ __global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel
         }
         if (s <= T + 1) loader_step(epi_a, epi_b, s);
     };
-    using Yes = std::true_type;
-    using No = std::false_type;
-    const bool need_online = !is_target && !kValue, need_target = kDouble ? !is_target : is_target || !two_nets;
-    if (kDouble && is_target) loader_loop(No{}, No{}, No{});
-    else if (A >= 4) {
-        if (need_online && need_target) loader_loop(Yes{}, Yes{}, Yes{});
-        else if (need_online) loader_loop(Yes{}, Yes{}, No{});
-        else loader_loop(Yes{}, No{}, Yes{});
-    } else {
-        if (need_online && need_target) loader_loop(No{}, Yes{}, Yes{});
-        else if (need_online) loader_loop(No{}, Yes{}, No{});
-        else loader_loop(No{}, No{}, Yes{});
-    }
+    if (A >= 4) loader_loop(std::true_type{});
+    else loader_loop(std::false_type{});
 }
 
 hipError_t launch_recurrent16(const NetFrags &online, const NetFrags &target, bool two_nets, const char *gi_online, const char *gi_target,

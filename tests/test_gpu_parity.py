@@ -411,6 +411,22 @@ def test_odd_shapes(shape, path):
     net.close(); target.close()
 
 
+@pytest.mark.parametrize("H,dtype", [(64, "fp32"), (64, "bf16"), (128, "bf16")])
+@pytest.mark.parametrize("D", [1, 7, 8, 9, 39, 63, 65, 96, 127, 129, 161, 193, 225, 257, 289, 313])
+def test_unroll_observation_widths(D, H, dtype):
+    """The fused unroll reads the last eight observations of a row from the row's end and runs a number of k-steps that may be
+    rounded up: widths around eight, around whole k-steps and in every such number; 19 rows, T odd and even."""
+    if dtype == "fp32" and D > 160:
+        pytest.skip("wider than the fused kernels take in two planes")
+    cfg = dict(wl.config(0), N=19, D=D, A=5, H=H, dtype=dtype, B=1, T=4 + D % 2)
+    net, w = make_net(cfg)
+    target, w_tg = make_net(cfg, 1)
+    assert net.kernels_in_use(binding.ENTRY_UNROLL_TD) == binding.KERNELS_FUSED16
+    u = wl.make_unroll_inputs(cfg)
+    pu.compare_unroll(pu.gpu_unroll(net, target, cfg, u), oracle_unroll(cfg, w, w_tg, u), pu.TOL[dtype])
+    net.close(); target.close()
+
+
 # Shapes the descriptor admits that only the tiled kernels take: fp32 weights with 128 hidden units, and
 # observations up to the widest the library accepts.
 TILED_ONLY_SHAPES = [
