@@ -565,12 +565,13 @@ struct TnGemmArgs {
     int extra_mode;     // columns appended to B: kExtraOnes (one column of ones), kExtraAgent (N one-hot columns of m % N)
     int n_extra, N;
     int qp;             // Q + n_extra rounded up to 16: row pitch of the result
+    int pp;             // rows of a partial result (partial_rows)
     int chunk;          // samples per workgroup along the contraction, a multiple of 32
     // elements from a row to the next: inside a group, and from a group's last row to the next group's first
     // (A's rows are one group: the adjoint arrays are)
     unsigned next_a, next_b, wrap_b;
     unsigned wrap_a;    // tn_gemm_wide_kernel only: A in groups too
-    float *partial;     // [chunks][128 or 384 rows][qp]
+    float *partial;     // [chunks][pp][qp]
 };
 
 constexpr int kTnThreads = 512;        // eight waves: two per SIMD
@@ -578,7 +579,9 @@ constexpr int kTnBatchMax = 16;        // products of one shape launched togethe
 struct TnGemmBatch { TnGemmArgs g[kTnBatchMax]; };
 
 // One workgroup per chunk of samples computes the whole result, so that every operand element is read from
-// memory once.  Wave w owns result row blocks w, w + 8, .. (PBW of them) and all QBN column blocks.  P: bf16
+// memory once.  Wave w owns result row blocks w, w + 8, .. (PBW of them at most) and all column blocks (QBN at most).  Shapes
+// (launch_shape): what is staged is sized by PBW and QBN, so the products of 64 hidden units, 192 x 65 and 64 x (D + N), have
+// their own; in those of 128 units, 384 x 144 and 128 x 336, half of what they staged and multiplied was padding.  P: bf16
 // planes per operand, the network's own: 2 = every value as bf16 high part + bf16 of the remainder, three MFMAs
 // per product; 1 = values rounded to bf16, one MFMA.
 // ABF: A's elements are bf16 (the adjoints of a bf16 network), else fp32.  BBF: the same for B's (its saved x).
@@ -600,6 +603,7 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_kernel(const TnGemmBatc
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sg = w & 3, half = w >> 2;                           // the wave stages samples 8 sg + 0..7 of every other column set
     const int n_qb = g.qp / 16;
+    [[maybe_unused]] const bool last_block = 16 * (w + 8 * (PBW - 1)) < g.P;        // whether the wave's last row block exists
     const int m_begin = (int)blockIdx.x * g.chunk, m_end = min(g.M, m_begin + g.chunk);     // M < 2^30
     // The 32 samples of a step are eight consecutive ones from each quarter of the chunk: wave group sg walks
     // through its own quarter, so that the rows it reads follow one another from the first step to the last and
@@ -815,15 +819,24 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_kernel(const TnGemmBatc
                     if constexpr (P == 2) af[k].lo = *reinterpret_cast<const bf16x8 *>(mine + plane_bytes + 16 * (w + 8 * k) * kPitch);
                 }
             }
+            // (PBW == 2: the first of a wave's row blocks exists, as P is more than 128, the second may not)
+            auto product = [&](auto row_blocks) {
 #pragma unroll
-            for (int j = 0; j < QBN; ++j)
-                if (j < n_qb) {
-                    Frag<P> bf;
-                    bf.hi = *reinterpret_cast<const bf16x8 *>(mine + (kPp + 16 * j) * kPitch);
-                    if constexpr (P == 2) bf.lo = *reinterpret_cast<const bf16x8 *>(mine + plane_bytes + (kPp + 16 * j) * kPitch);
+                for (int j = 0; j < QBN; ++j)
+                    if (j < n_qb) {
+                        Frag<P> bf;
+                        bf.hi = *reinterpret_cast<const bf16x8 *>(mine + (kPp + 16 * j) * kPitch);
+                        if constexpr (P == 2) bf.lo = *reinterpret_cast<const bf16x8 *>(mine + plane_bytes + (kPp + 16 * j) * kPitch);
 #pragma unroll
-                    for (int k = 0; k < PBW; ++k) mma16<P>(acc[k][j], af[k], bf);
-                }
+                        for (int k = 0; k < decltype(row_blocks)::value; ++k) mma16<P>(acc[k][j], af[k], bf);
+                    }
+            };
+            if constexpr (PBW == 2) {          // (with three row blocks a wave, the accumulators of two ways through spill)
+                if (last_block) product(std::integral_constant<int, PBW>{});
+                else product(std::integral_constant<int, PBW - 1>{});
+            } else {
+                product(std::integral_constant<int, PBW>{});
+            }
         };
         // Rounds of kDepth steps; steps past the end of the chunk add zeros.  The compiler's wait at the head of
         // the loop is for everything asked for so far, whatever the order of the round.  Where two staging
@@ -862,12 +875,12 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_kernel(const TnGemmBatc
     else run(std::true_type{});
 
     // C layout: lane (c, q4) holds result[16 block + 4 q4 + r][16 j + c]
-    float *out = g.partial + (size_t)blockIdx.x * kPp * g.qp;
+    float *out = g.partial + (size_t)blockIdx.x * g.pp * g.qp;
 #pragma unroll
     for (int k = 0; k < PBW; ++k)
 #pragma unroll
         for (int j = 0; j < QBN; ++j)
-            if (j < n_qb)
+            if (j < n_qb && (PBW == 3 || 16 * (w + 8 * k) < g.P))
 #pragma unroll
                 for (int r = 0; r < 4; ++r) out[(size_t)(16 * (w + 8 * k) + 4 * q4 + r) * g.qp + 16 * j + c] = acc[k][j][r];
 }
@@ -905,6 +918,10 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
     constexpr int kRB = kSplitColumns ? 8 : PBW, kCB = kSplitColumns ? (QBN + 7) / 8 : QBN;
     auto row_block = [&](int k) { return kSplitColumns ? k : w + 8 * k; };
     auto col_block = [&](int j) { return kSplitColumns ? w + 8 * j : j; };
+    // whether the wave's last row block exists, or (split columns) more than the first half of them do
+    // (the accumulators of the larger shapes leave no room for two ways through)
+    constexpr bool kMayBeShort = PBW == 2 || (kSplitColumns && kCB <= 2);
+    [[maybe_unused]] const bool all_blocks = kSplitColumns ? g.P > 64 : 16 * (w + 8 * (PBW - 1)) < g.P;
     f32x4 acc[kRB][kCB];
 #pragma unroll
     for (int k = 0; k < kRB; ++k)
@@ -1037,14 +1054,29 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
             WFrag<1> af[kRB];
 #pragma unroll
             for (int k = 0; k < kRB; ++k) af[k].hi = fragment(buf, kAPitch, 16 * row_block(k));
+            if constexpr (kMayBeShort) {
+                auto product = [&](auto row_blocks) {
 #pragma unroll
-            for (int j = 0; j < kCB; ++j)
-                if (col_block(j) < n_qb) {
-                    Frag<1> bf;
-                    bf.hi = fragment(buf + 32 * kAPitch, kBPitch, 16 * col_block(j));
+                    for (int j = 0; j < kCB; ++j)
+                        if (col_block(j) < n_qb) {
+                            Frag<1> bf;
+                            bf.hi = fragment(buf + 32 * kAPitch, kBPitch, 16 * col_block(j));
 #pragma unroll
-                    for (int k = 0; k < kRB; ++k) mma16<1>(acc[k][j], af[k], bf);
-                }
+                            for (int k = 0; k < decltype(row_blocks)::value; ++k) mma16<1>(acc[k][j], af[k], bf);
+                        }
+                };
+                if (all_blocks) product(std::integral_constant<int, kRB>{});
+                else product(std::integral_constant<int, kSplitColumns ? kRB / 2 : kRB - 1>{});
+            } else {
+#pragma unroll
+                for (int j = 0; j < kCB; ++j)
+                    if (col_block(j) < n_qb) {
+                        Frag<1> bf;
+                        bf.hi = fragment(buf + 32 * kAPitch, kBPitch, 16 * col_block(j));
+#pragma unroll
+                        for (int k = 0; k < kRB; ++k) mma16<1>(acc[k][j], af[k], bf);
+                    }
+            }
         };
 #pragma unroll
         for (int d = 0; d < kDepth; ++d) fetch(rv[d]);
@@ -1068,12 +1100,12 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
     else run(std::true_type{});
 
     // C layout: lane (c, q4) holds result[16 block + 4 q4 + r][16 j + c]
-    float *out = g.partial + (size_t)blockIdx.x * kPp * g.qp;
+    float *out = g.partial + (size_t)blockIdx.x * g.pp * g.qp;
 #pragma unroll
     for (int k = 0; k < kRB; ++k)
 #pragma unroll
         for (int j = 0; j < kCB; ++j)
-            if (col_block(j) < n_qb)
+            if (col_block(j) < n_qb && (PBW == 3 || 16 * row_block(k) < g.P))
 #pragma unroll
                 for (int r = 0; r < 4; ++r) out[(size_t)(16 * row_block(k) + 4 * q4 + r) * g.qp + 16 * col_block(j) + c] = acc[k][j][r];
 }
@@ -1152,6 +1184,9 @@ namespace {
 
 size_t align_up(size_t v) { return (v + 255) / 256 * 256; }
 
+// Rows of a product's partial result: P rounded up to 16, or the whole tile of the largest shape.
+int partial_rows(int P) { return P > 256 ? 384 : (P + 15) / 16 * 16; }
+
 struct Plan {
     size_t off_h, off_x, off_da, off_dpre1, off_dq, off_carry, off_partial, partial_bytes, bytes;
     int a16;
@@ -1172,7 +1207,7 @@ Plan make_plan(const NetFrags &net, int B, int T)
     p.off_dpre1 = off;  off = align_up(off + R * T * H * adj + 4);
     p.off_dq = off;     off = align_up(off + R * T * p.a16 * adj + 4);
     // room for the partial sums of all four products, whichever way the slots are walked
-    auto part = [&](size_t P, size_t Qt) { return (size_t)p.cut.room * (P > 128 ? 384 : 128) * ((Qt + 15) / 16 * 16) * 4; };
+    auto part = [&](size_t P, size_t Qt) { return (size_t)p.cut.room * partial_rows((int)P) * ((Qt + 15) / 16 * 16) * 4; };
     const size_t need = 2 * part(3 * H, H + 1) + part(H, (size_t)net.D + net.N) + part(net.A, H + 1);
     p.partial_bytes = need;
     p.off_carry = off;  off = align_up(off + (R + 15) / 16 * 16 * H * 4);
@@ -1196,8 +1231,87 @@ hipError_t back_dispatch(const BpttArgs &a, size_t lds_bytes, hipStream_t stream
 size_t tn_partial_bytes(long M, int chunk, int P, int q_total)
 {
     const size_t chunks = (size_t)((M + chunk - 1) / chunk);
-    return chunks * (P > 128 ? 384 : 128) * (size_t)((q_total + 15) / 16 * 16) * sizeof(float);
+    return chunks * (size_t)partial_rows(P) * (size_t)((q_total + 15) / 16 * 16) * sizeof(float);
 }
+
+namespace {
+
+// What a product needs of its kernel: rows 3 (up to 384), 2 (256) or 1 (128), and whether its B is bf16.
+int row_class(int P) { return P > 256 ? 3 : P > 128 ? 2 : 1; }
+
+// Fills a product's kernel arguments; false where no kernel takes it.
+bool tn_args(const TnProduct &t, long M, int chunk, float *partial, TnGemmArgs *out)
+{
+    TnGemmArgs g{};
+    g.a = t.a; g.b = t.b; g.M = (int)M; g.P = t.P; g.Q = t.Q; g.extra_mode = t.extra_mode; g.n_extra = t.n_extra;
+    g.N = t.N > 0 ? t.N : 1;
+    g.qp = (t.Q + t.n_extra + 15) / 16 * 16;
+    g.pp = partial_rows(t.P);
+    g.chunk = chunk;
+    g.partial = partial;
+    // steps from row to row in elements, 32 bits each; an operand that is one group never takes the second
+    auto steps = [&](const RowMap &m, unsigned *next, unsigned *wrap) {
+        const long n = (long)m.ld;
+        const long w = m.rows_per_group >= M ? n : m.group_stride - (long)(m.rows_per_group - 1) * m.ld;
+        if (n < 0 || w < 0 || n >= (1L << 31) || w >= (1L << 31)) return false;
+        *next = (unsigned)n; *wrap = (unsigned)w;
+        return true;
+    };
+    if (!steps(t.a, &g.next_a, &g.wrap_a) || !steps(t.b, &g.next_b, &g.wrap_b)) return false;
+    *out = g;
+    return t.P > 128 ? t.P <= 384 && g.qp <= 144 : g.qp <= 336 && !t.b.bf16;
+}
+
+TnReduceArgs reduce_args(const TnProduct &t, const float *partial, int chunks)
+{
+    TnReduceArgs r{};
+    r.partial = partial; r.chunks = chunks; r.P = t.P; r.p_pad = partial_rows(t.P); r.qp = (t.Q + t.n_extra + 15) / 16 * 16;
+    r.Q = t.Q; r.n_extra = t.n_extra; r.extra_mode = t.extra_mode;
+    r.row_shift = t.row_shift; r.w_cols = t.Q; r.ld_w = t.ld_w; r.dst_w = t.dst_w; r.dst_b = t.dst_b;
+    return r;
+}
+
+// Products that go together in one launch.
+struct TnLaunch {
+    TnGemmBatch batch{};
+    int count = 0, max_qp = 0;
+    void add(const TnGemmArgs &g) { batch.g[count++] = g; max_qp = std::max(max_qp, g.qp); }
+};
+
+template <auto kKernel>
+hipError_t launch_tn(const TnLaunch &l, int chunks, size_t lds, hipStream_t stream)
+{
+    const hipError_t err = allow_large_lds<kKernel>(kLdsLimit);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kKernel, dim3(chunks, l.count), dim3(kTnThreads), lds, stream, l.batch);
+    return hipGetLastError();
+}
+
+template <int PBW, int QBN, bool BBF>
+hipError_t launch_tn_shape(const TnLaunch &l, int planes, bool wide_loads, int chunks, hipStream_t stream)
+{
+    if (wide_loads) return launch_tn<tn_gemm_wide_kernel<PBW, QBN, BBF>>(l, chunks, tn_wide_lds<PBW, QBN>(), stream);
+    const size_t lds = (size_t)2 * (128 * PBW + l.max_qp) * 80;      // 80 bytes per staged column; two planes, or two buffers of one
+    if constexpr (!BBF)
+        if (planes == 2) return launch_tn<tn_gemm_kernel<PBW, QBN, 2, false>>(l, chunks, lds, stream);
+    return launch_tn<tn_gemm_kernel<PBW, QBN, 1, true, BBF>>(l, chunks, lds, stream);
+}
+
+// rows: row_class of all of them.  wide_loads: every one fits tn_gemm_wide_kernel.
+hipError_t launch_shape(const TnLaunch &l, int rows, bool b_bf16, int planes, bool wide_loads, int chunks, hipStream_t stream)
+{
+    if (l.count == 0) return hipSuccess;
+    if (rows == 1) return l.max_qp <= 176 ? launch_tn_shape<1, 11, false>(l, planes, wide_loads, chunks, stream)
+                                          : launch_tn_shape<1, 21, false>(l, planes, wide_loads, chunks, stream);
+    if (rows == 3) return b_bf16 ? launch_tn_shape<3, 9, true>(l, planes, wide_loads, chunks, stream)
+                                 : launch_tn_shape<3, 9, false>(l, planes, wide_loads, chunks, stream);
+    if (l.max_qp <= 80) return b_bf16 ? launch_tn_shape<2, 5, true>(l, planes, wide_loads, chunks, stream)
+                                      : launch_tn_shape<2, 5, false>(l, planes, wide_loads, chunks, stream);
+    return b_bf16 ? launch_tn_shape<2, 9, true>(l, planes, wide_loads, chunks, stream)
+                  : launch_tn_shape<2, 9, false>(l, planes, wide_loads, chunks, stream);
+}
+
+}  // namespace
 
 // Launches the products of `list` (all over the same M samples, chunks of `chunk`): those of one shape go
 // together in one launch (up to kTnBatchMax), then their partial sums are reduced, again in one launch.
@@ -1207,101 +1321,38 @@ hipError_t launch_tn_products(int planes, const TnProduct *list, int count, long
     const int chunks = (int)((M + chunk - 1) / chunk);
     int done = 0;
     while (done < count) {
-        TnGemmBatch wide{}, narrow{};
+        TnLaunch rows[3];
         TnReduceBatch red{};
-        int n_wide = 0, n_narrow = 0, n_red = 0, max_q_wide = 0, max_q_narrow = 0, max_total = 0;
+        int n_red = 0, max_total = 0;
         size_t used = 0;
         int taken = done;
-        bool a_in_groups = false;
+        bool a_in_groups = false, wide_loads = planes == 1 && list[done].a.bf16;
         for (; taken < count; ++taken) {
             const TnProduct &t = list[taken];
             TnGemmArgs g{};
-            g.a = t.a; g.b = t.b; g.M = (int)M; g.P = t.P; g.Q = t.Q; g.extra_mode = t.extra_mode; g.n_extra = t.n_extra;
-            g.N = t.N > 0 ? t.N : 1;
-            g.qp = (t.Q + t.n_extra + 15) / 16 * 16;
-            g.chunk = chunk;
-            // steps from row to row in elements, 32 bits each; an operand that is one group never takes the second
-            auto steps = [&](const RowMap &m, unsigned *next, unsigned *wrap) {
-                const long n = (long)m.ld;
-                const long w = m.rows_per_group >= M ? n : m.group_stride - (long)(m.rows_per_group - 1) * m.ld;
-                if (n < 0 || w < 0 || n >= (1L << 31) || w >= (1L << 31)) return false;
-                *next = (unsigned)n; *wrap = (unsigned)w;
-                return true;
-            };
-            if (!steps(t.a, &g.next_a, &g.wrap_a) || !steps(t.b, &g.next_b, &g.wrap_b)) return hipErrorInvalidValue;
+            if (!tn_args(t, M, chunk, reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used), &g)) return hipErrorInvalidValue;
             // A in groups: the wide kernel only
             if (t.a.rows_per_group < M && !(planes == 1 && tn_wide_fits(t, M))) return hipErrorInvalidValue;
-            a_in_groups = a_in_groups || t.a.rows_per_group < M;
             // bf16 adjoints are read 16 bytes (eight columns) at a time
             if (t.a.bf16 && (reinterpret_cast<uintptr_t>(t.a.base) % 16 != 0 || t.a.ld % 8 != 0 || t.a.ld < (t.P + 7) / 8 * 8)) return hipErrorInvalidValue;
-            // two shapes: up to 384 rows x 144 columns (the GRU matrices), up to 128 rows x 336 columns (fc1, fc2)
-            const bool is_wide = t.P > 128;
-            if ((is_wide && (t.P > 384 || g.qp > 144)) || (!is_wide && g.qp > 336)) return hipErrorInvalidValue;
-            if ((t.a.bf16 != 0) != (list[0].a.bf16 != 0) || (t.a.bf16 && planes != 1)) return hipErrorInvalidValue;
-            // B in bf16: the wide shape of a one-plane network with bf16 adjoints only; such products go in launches of their own
-            if (t.b.bf16 && !(is_wide && t.a.bf16)) return hipErrorInvalidValue;
+            // A's elements: bf16 for one plane, fp32 for two
+            if ((t.a.bf16 != 0) != (planes == 1)) return hipErrorInvalidValue;
+            // B in bf16: such products go in launches of their own
             if ((t.b.bf16 != 0) != (list[done].b.bf16 != 0)) break;
             const size_t bytes = tn_partial_bytes(M, chunk, t.P, t.Q + t.n_extra);
             if (bytes > partial_bytes) return hipErrorInvalidValue;
-            if (used + bytes > partial_bytes || (is_wide ? n_wide : n_narrow) == kTnBatchMax || n_red == kTnBatchMax) break;
-            g.partial = reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used);
+            if (used + bytes > partial_bytes || n_red == kTnBatchMax) break;
             used += bytes;
-            if (is_wide) { wide.g[n_wide++] = g; max_q_wide = std::max(max_q_wide, g.qp); }
-            else         { narrow.g[n_narrow++] = g; max_q_narrow = std::max(max_q_narrow, g.qp); }
-            TnReduceArgs r{};
-            r.partial = g.partial; r.chunks = chunks; r.P = t.P; r.p_pad = is_wide ? 384 : 128; r.qp = g.qp;
-            r.Q = t.Q; r.n_extra = t.n_extra; r.extra_mode = t.extra_mode;
-            r.row_shift = t.row_shift; r.w_cols = t.Q; r.ld_w = t.ld_w; r.dst_w = t.dst_w; r.dst_b = t.dst_b;
-            red.r[n_red++] = r;
+            a_in_groups = a_in_groups || t.a.rows_per_group < M;
+            wide_loads = wide_loads && tn_wide_fits(t, M);
+            rows[row_class(t.P) - 1].add(g);
+            red.r[n_red++] = reduce_args(t, g.partial, chunks);
             max_total = std::max(max_total, t.P * (t.Q + t.n_extra));
         }
+        if (a_in_groups && !wide_loads) return hipErrorInvalidValue;
         hipError_t err = hipSuccess;
-#define MARL_TN(PBW, QBN, PL, ABF, BATCH, COUNT, PPAD, MAXQ) MARL_TN2(PBW, QBN, PL, ABF, false, BATCH, COUNT, PPAD, MAXQ)
-#define MARL_TN2(PBW, QBN, PL, ABF, BBF, BATCH, COUNT, PPAD, MAXQ)                                       \
-    do {                                                                                                 \
-        const size_t lds = (size_t)(PL == 1 ? 2 : 1) * PL * (PPAD + MAXQ) * 80;      /* 80 bytes per staged column and plane */ \
-        err = allow_large_lds<tn_gemm_kernel<PBW, QBN, PL, ABF, BBF>>(kLdsLimit);                        \
-        if (err != hipSuccess) return err;                                                               \
-        hipLaunchKernelGGL((tn_gemm_kernel<PBW, QBN, PL, ABF, BBF>), dim3(chunks, COUNT), dim3(kTnThreads), lds, stream, BATCH); \
-        err = hipGetLastError();                                                                         \
-        if (err != hipSuccess) return err;                                                               \
-    } while (0)
-        // the element type of A is the same for every product of a call (bf16 adjoints only with one plane)
-        const bool a_bf16 = list[done].a.bf16 != 0;
-        bool all_wide = planes == 1 && a_bf16;
-        for (int i = done; i < taken && all_wide; ++i) all_wide = tn_wide_fits(list[i], M);
-        if (a_in_groups && !all_wide) return hipErrorInvalidValue;
-#define MARL_TN_WIDE(PBW, QBN, BBF, BATCH, COUNT)                                                         \
-    do {                                                                                                 \
-        err = allow_large_lds<tn_gemm_wide_kernel<PBW, QBN, BBF>>(kLdsLimit);                            \
-        if (err != hipSuccess) return err;                                                               \
-        const size_t lds_wide = tn_wide_lds<PBW, QBN>();                                                 \
-        hipLaunchKernelGGL((tn_gemm_wide_kernel<PBW, QBN, BBF>), dim3(chunks, COUNT), dim3(kTnThreads), lds_wide, stream, BATCH); \
-        err = hipGetLastError();                                                                         \
-        if (err != hipSuccess) return err;                                                               \
-    } while (0)
-        if (all_wide) {
-            if (n_wide) {
-                if (list[done].b.bf16) MARL_TN_WIDE(3, 9, true, wide, n_wide);
-                else MARL_TN_WIDE(3, 9, false, wide, n_wide);
-            }
-            if (n_narrow) MARL_TN_WIDE(1, 21, false, narrow, n_narrow);
-            n_wide = n_narrow = 0;
-        }
-#undef MARL_TN_WIDE
-        if (n_wide) {
-            if (planes == 2) MARL_TN(3, 9, 2, false, wide, n_wide, 384, max_q_wide);
-            else if (a_bf16 && list[done].b.bf16) MARL_TN2(3, 9, 1, true, true, wide, n_wide, 384, max_q_wide);
-            else if (a_bf16) MARL_TN(3, 9, 1, true, wide, n_wide, 384, max_q_wide);
-            else MARL_TN(3, 9, 1, false, wide, n_wide, 384, max_q_wide);
-        }
-        if (n_narrow) {
-            if (planes == 2) MARL_TN(1, 21, 2, false, narrow, n_narrow, 128, max_q_narrow);
-            else if (a_bf16) MARL_TN(1, 21, 1, true, narrow, n_narrow, 128, max_q_narrow);
-            else MARL_TN(1, 21, 1, false, narrow, n_narrow, 128, max_q_narrow);
-        }
-#undef MARL_TN
-#undef MARL_TN2
+        for (int k = 3; k >= 1 && err == hipSuccess; --k) err = launch_shape(rows[k - 1], k, list[done].b.bf16 != 0, planes, wide_loads, chunks, stream);
+        if (err != hipSuccess) return err;
         hipLaunchKernelGGL(tn_reduce_kernel, dim3((max_total + 255) / 256, n_red), dim3(256), 0, stream, red);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
@@ -1318,51 +1369,23 @@ hipError_t launch_tn_products(int planes, const TnProduct *list, int count, long
     return hipSuccess;
 }
 
-
 // The products of `list` (every one fits the wide kernel; same M and chunk), without the sum of their chunks:
 // product i's partial sums go to partial[i].  One launch per shape and element type of B.
 hipError_t launch_tn_gemms_wide(const TnProduct *list, int count, long M, int chunk, float *const *partial, hipStream_t stream)
 {
     const int chunks = (int)((M + chunk - 1) / chunk);
-    TnGemmBatch batch[3]{};             // wide with bf16 B, wide, narrow
-    int n[3] = {0, 0, 0};
+    TnLaunch rows[3][2];                // by row class and element type of B
     for (int i = 0; i < count; ++i) {
         const TnProduct &t = list[i];
         TnGemmArgs g{};
-        g.a = t.a; g.b = t.b; g.M = (int)M; g.P = t.P; g.Q = t.Q; g.extra_mode = t.extra_mode; g.n_extra = t.n_extra;
-        g.N = t.N > 0 ? t.N : 1;
-        g.qp = (t.Q + t.n_extra + 15) / 16 * 16;
-        g.chunk = chunk;
-        auto steps = [&](const RowMap &m, unsigned *next, unsigned *wrap) {
-            const long nx = (long)m.ld;
-            const long w = m.rows_per_group >= M ? nx : m.group_stride - (long)(m.rows_per_group - 1) * m.ld;
-            if (nx < 0 || w < 0 || nx >= (1L << 31) || w >= (1L << 31)) return false;
-            *next = (unsigned)nx; *wrap = (unsigned)w;
-            return true;
-        };
-        if (!tn_wide_fits(t, M) || !steps(t.a, &g.next_a, &g.wrap_a) || !steps(t.b, &g.next_b, &g.wrap_b)) return hipErrorInvalidValue;
-        const bool is_wide = t.P > 128;
-        if ((is_wide && (t.P > 384 || g.qp > 144)) || (!is_wide && g.qp > 336) || (t.b.bf16 && !is_wide)) return hipErrorInvalidValue;
-        g.partial = partial[i];
-        const int kind = is_wide ? (t.b.bf16 ? 0 : 1) : 2;
-        if (n[kind] == kTnBatchMax) return hipErrorInvalidValue;
-        batch[kind].g[n[kind]++] = g;
+        TnLaunch &l = rows[row_class(t.P) - 1][t.b.bf16 ? 1 : 0];
+        if (!tn_wide_fits(t, M) || !tn_args(t, M, chunk, partial[i], &g) || l.count == kTnBatchMax) return hipErrorInvalidValue;
+        l.add(g);
     }
     hipError_t err = hipSuccess;
-#define MARL_TN_WIDE(PBW, QBN, BBF, KIND)                                                                 \
-    if (n[KIND]) {                                                                                       \
-        err = allow_large_lds<tn_gemm_wide_kernel<PBW, QBN, BBF>>(kLdsLimit);                            \
-        if (err != hipSuccess) return err;                                                               \
-        const size_t lds_wide = tn_wide_lds<PBW, QBN>();                                                 \
-        hipLaunchKernelGGL((tn_gemm_wide_kernel<PBW, QBN, BBF>), dim3(chunks, n[KIND]), dim3(kTnThreads), lds_wide, stream, batch[KIND]); \
-        err = hipGetLastError();                                                                         \
-        if (err != hipSuccess) return err;                                                               \
-    }
-    MARL_TN_WIDE(3, 9, true, 0)
-    MARL_TN_WIDE(3, 9, false, 1)
-    MARL_TN_WIDE(1, 21, false, 2)
-#undef MARL_TN_WIDE
-    return hipSuccess;
+    for (int k = 3; k >= 1; --k)
+        for (int b = 1; b >= 0 && err == hipSuccess; --b) err = launch_shape(rows[k - 1][b], k, b != 0, 1, true, chunks, stream);
+    return err;
 }
 
 bool qnet_grad_fits(const NetFrags &net)
@@ -1466,15 +1489,11 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
         size_t used = 0;
         for (int i = 0; i < 4; ++i) {
             const TnProduct &t = late.p[i];
-            const size_t p_pad = t.P > 128 ? 384 : 128, qp = (size_t)(t.Q + t.n_extra + 15) / 16 * 16;
+            const size_t p_pad = (size_t)partial_rows(t.P), qp = (size_t)(t.Q + t.n_extra + 15) / 16 * 16;
             part_late[i] = reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used);
             part_early[i] = part_late[i] + (size_t)cut_late.chunks * p_pad * qp;
             used += (size_t)(cut_late.chunks + cut_early.chunks) * p_pad * qp * sizeof(float);
-            TnReduceArgs r{};
-            r.partial = part_late[i]; r.chunks = cut_late.chunks + cut_early.chunks; r.P = t.P; r.p_pad = (int)p_pad; r.qp = (int)qp;
-            r.Q = t.Q; r.n_extra = t.n_extra; r.extra_mode = t.extra_mode;
-            r.row_shift = t.row_shift; r.w_cols = t.Q; r.ld_w = t.ld_w; r.dst_w = t.dst_w; r.dst_b = t.dst_b;
-            red.r[i] = r;
+            red.r[i] = reduce_args(t, part_late[i], cut_late.chunks + cut_early.chunks);
             max_total = std::max(max_total, t.P * (t.Q + t.n_extra));
         }
         if (used > plan.partial_bytes) return hipErrorInvalidValue;

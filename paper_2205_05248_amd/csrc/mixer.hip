@@ -26,6 +26,7 @@
 
 #include "../../include/marl_mixer.h"
 #include "fused16.h"
+#include "grad_chunks.h"
 #include "qnet_internal.h"
 
 struct marl_mixer {
@@ -895,8 +896,19 @@ hipError_t mixer_back_stream_dispatch(int mb, const MixerBackArgs &a, hipStream_
     }
 }
 
+// The products of the four state matrices and of v2, by the rows of their results: tall ones (Hw1's, when it has more than 128
+// rows), cut into 384 rows and 128 state columns, the rest into 128 rows and 320.  Both lists run as launches of their own.
+struct ProductCut { int tall, flat; };
+ProductCut mixer_products(const marl_mixer_desc &d)
+{
+    const int rows = d.n_agents * d.embed, S = d.state_dim;
+    const int flat = 3 * ((S + 319) / 320) + 1;
+    if (rows > 128) return {(rows + 383) / 384 * ((S + 127) / 128), flat};
+    return {0, flat + (S + 319) / 320};
+}
+
 struct MixerGradPlan {
-    int ldd, chunk;
+    int ldd, chunk_tall, chunk_flat;
     size_t off_dgen, off_partial, partial_bytes, bytes;
 };
 
@@ -907,13 +919,18 @@ MixerGradPlan mixer_grad_plan(const marl_mixer_desc &d, int B, int T)
     const int F = (d.n_agents + 3) * d.embed;
     // whole 16-byte pieces, and eight columns from the last product's first one on (it takes the last embed + 1)
     p.ldd = F + (d.embed + 1 + 7) / 8 * 8;
-    // few samples (B T, not B T N) and many products that run side by side: chunks of about 256 transitions
-    const long chunks = std::max<long>(1, std::min<long>(256, R / 256));
-    p.chunk = (int)(((R + chunks - 1) / chunks + 63) / 64 * 64);
+    // One workgroup per product and chunk, one per compute unit: as many chunks as let a launch fill the chip once, of 64
+    // transitions (two steps) at least.  Chunks of 256 transitions whatever the number of products left all but 30 compute units idle
+    // on 7680 transitions of 160 x 120 weights (31 + 21 us for the products), one chunk in all on 240.
+    const ProductCut cut = mixer_products(d);
+    auto chunk_of = [&](int products) { return cut_samples(R, std::max(1, 256 / std::max(1, products)), 64).chunk; };
+    p.chunk_tall = chunk_of(cut.tall);
+    p.chunk_flat = chunk_of(cut.flat);
     size_t off = 0;
     p.off_dgen = off;    off = (off + (size_t)R * p.ldd * 4 + 255) / 256 * 256;
-    // room for sixteen of the largest partial results: the products run sixteen at a time
-    p.partial_bytes = 16 * tn_partial_bytes(R, p.chunk, 384, 144);
+    // room for all partial results of a list, or for sixteen, as many as run at a time
+    p.partial_bytes = std::max(std::min(cut.tall, 16) * tn_partial_bytes(R, p.chunk_tall, 384, 144),
+                               std::min(cut.flat, 16) * tn_partial_bytes(R, p.chunk_flat, 128, 336));
     p.off_partial = off; off = (off + p.partial_bytes + 255) / 256 * 256;
     p.bytes = off;
     return p;
@@ -988,7 +1005,7 @@ int marl_mixer_grad(marl_mixer *m, int32_t B, int32_t T, const float *state, con
     const marl::RowMap states{state, (long)(T + 1) * S, T, S, 0};
     // one matrix: rows [r0, r0 + P) of it are adjoint columns [col0 + r0, ..); state columns in slices, the
     // column of ones (the bias) rides with the last slice
-    std::vector<marl::TnProduct> products;
+    std::vector<marl::TnProduct> tall, flat;
     auto matrix = [&](int col0, int rows_total, float *dst_w, float *dst_b) {
         const bool wide = rows_total > 128;
         const int p_step = wide ? 384 : 128, q_step = wide ? 128 : 320;
@@ -999,7 +1016,7 @@ int marl_mixer_grad(marl_mixer *m, int32_t B, int32_t T, const float *state, con
                 marl::RowMap ar = plain, br = states;
                 ar.base = dgen + (size_t)(col0 + r0) * elem;
                 br.base = state + k0;
-                products.push_back({ar, br, P, Q, last ? marl::kExtraOnes : marl::kExtraNone, last ? 1 : 0, 1, 0, S,
+                (wide ? tall : flat).push_back({ar, br, P, Q, last ? marl::kExtraOnes : marl::kExtraNone, last ? 1 : 0, 1, 0, S,
                                     dst_w + (size_t)r0 * S + k0, dst_b + r0});
             }
     };
@@ -1010,9 +1027,11 @@ int marl_mixer_grad(marl_mixer *m, int32_t B, int32_t T, const float *state, con
     {        // v2 and c2: the last M + 1 adjoint columns against the column of ones alone
         marl::RowMap ar = plain;
         ar.base = dgen + (size_t)F * elem;
-        products.push_back({ar, states, M + 1, 0, marl::kExtraOnes, 1, 1, 0, 1, gv2, gv2});
+        flat.push_back({ar, states, M + 1, 0, marl::kExtraOnes, 1, 1, 0, 1, gv2, gv2});
     }
-    err = marl::launch_tn_products(m->planes, products.data(), (int)products.size(), R, plan.chunk, partial, plan.partial_bytes, stream);
+    err = marl::launch_tn_products(m->planes, tall.data(), (int)tall.size(), R, plan.chunk_tall, partial, plan.partial_bytes, stream);
+    if (err == hipSuccess)
+        err = marl::launch_tn_products(m->planes, flat.data(), (int)flat.size(), R, plan.chunk_flat, partial, plan.partial_bytes, stream);
     if (err != hipSuccess) return marl::report_device_error(err, "marl_mixer_grad products");
     return MARL_OK;
 }
