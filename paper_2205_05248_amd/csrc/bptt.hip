@@ -911,16 +911,16 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
     const int n_steps = (m_end - m_begin + 31) / 32;
 
     // Which blocks of the result a wave owns.  Three row blocks (w, w + 8, w + 16) and every column block where the
-    // result is tall: a fragment of B then feeds three products.  Where it is 128 rows by up to 336 columns, all
-    // eight row blocks and every eighth column block (w, w + 8, w + 16): 11 fragments per step for 24 products,
-    // where one row block and all 21 column blocks would read 22 for 21 - and a wave can only issue so many LDS reads.
-    constexpr bool kSplitColumns = PBW == 1;
-    constexpr int kRB = kSplitColumns ? 8 : PBW, kCB = kSplitColumns ? (QBN + 7) / 8 : QBN;
-    auto row_block = [&](int k) { return kSplitColumns ? k : w + 8 * k; };
-    auto col_block = [&](int j) { return kSplitColumns ? w + 8 * j : j; };
-    // whether the wave's last row block exists, or (split columns) more than the first half of them do
+    // result is tall: a fragment of B then feeds three products.  Where it is 128 rows, all eight row blocks and every
+    // eighth column block (w, w + 8) of up to 176 columns; of up to 336 columns, half the row blocks and every fourth column
+    // block: 10 fragments per step for 24 products, and 16 registers less of them than with all row blocks and every eighth
+    // column block, which spilled 25.
+    constexpr bool kSplitColumns = PBW == 1, kHalves = kSplitColumns && QBN > 16;
+    constexpr int kRB = kHalves ? 4 : kSplitColumns ? 8 : PBW, kCB = kHalves ? (QBN + 3) / 4 : kSplitColumns ? (QBN + 7) / 8 : QBN;
+    auto row_block = [&](int k) { return kHalves ? 4 * (w >> 2) + k : kSplitColumns ? k : w + 8 * k; };
+    auto col_block = [&](int j) { return kHalves ? (w & 3) + 4 * j : kSplitColumns ? w + 8 * j : j; };
     // (the accumulators of the larger shapes leave no room for two ways through)
-    constexpr bool kMayBeShort = PBW == 2 || (kSplitColumns && kCB <= 2);
+    constexpr bool kMayBeShort = PBW == 2 || (kSplitColumns && !kHalves);
     [[maybe_unused]] const bool all_blocks = kSplitColumns ? g.P > 64 : 16 * (w + 8 * (PBW - 1)) < g.P;
     f32x4 acc[kRB][kCB];
 #pragma unroll
@@ -992,6 +992,8 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
         auto deposit = [&](char *buf, Staged &from) {
             uint32_t keep = 0xFFFFFFFFu;       // samples past the chunk's end count for nothing: A's values are cleared, B's may stay
             if constexpr (ENDS) keep = staged_sample < share_end ? 0xFFFFFFFFu : 0u;
+            // where the sample's row of appended columns has its 1: the column of ones, its agent's column, or nowhere
+            const int one_at = g.extra_mode == kExtraAgent ? g.Q + (int)agent : g.extra_mode == kExtraOnes ? g.Q : -8;
 #pragma unroll
             for (int i = 0; i < kALoads; ++i) {
                 uint4 v = from.a[i];
@@ -1006,22 +1008,14 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
                 const int piece = first_piece + 16 * i, col = kColsB * piece;
                 // a piece past B's own columns is made up: the column of ones, or the one-hot columns of the sample's agent
                 const bool made_up = col >= g.Q;
-                uint32_t word[kColsB / 2];
-#pragma unroll
-                for (int e = 0; e < kColsB / 2; ++e) {
-                    uint32_t pair[2];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int extra = col + 2 * e + h - g.Q;            // which appended column, if any
-                        const bool one = extra >= 0 && extra < g.n_extra && (g.extra_mode == kExtraOnes || (unsigned)extra == agent);
-                        pair[h] = one ? 0x3F80u : 0u;
-                    }
-                    word[e] = pair[0] | (pair[1] << 16);
-                }
+                // (the one 1 of its columns, if it has it: `one` columns on from the piece's first)
+                const int one = one_at - col;
+                const uint64_t bf16_one = 0x3F80ull << (16 * (one & 3));
+                const uint64_t low = (unsigned)one < 4u ? bf16_one : 0, high = kColsB == 8 && (unsigned)(one - 4) < 4u ? bf16_one : 0;
                 // a spare load (a piece past the staged columns) goes to the padding at the end of the row
                 const int at = piece < pieces_b ? b_lds + 32 * kColsB * i : b_spare;
                 if constexpr (BBF) {
-                    const uint4 out = made_up && piece < pieces_b ? make_uint4(word[0], word[1], word[2], word[3]) : v;
+                    const uint4 out = made_up && piece < pieces_b ? make_uint4((uint32_t)low, (uint32_t)(low >> 32), (uint32_t)high, (uint32_t)(high >> 32)) : v;
                     *reinterpret_cast<uint4 *>(buf + at) = out;
                 } else {
                     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -1029,7 +1023,7 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
                     r[0] = (__bf16)__uint_as_float(v.x); r[1] = (__bf16)__uint_as_float(v.y);
                     r[2] = (__bf16)__uint_as_float(v.z); r[3] = (__bf16)__uint_as_float(v.w);
                     const uint2 real = __builtin_bit_cast(uint2, r);
-                    const uint2 out = made_up && piece < pieces_b ? make_uint2(word[0], word[1]) : real;
+                    const uint2 out = made_up && piece < pieces_b ? make_uint2((uint32_t)low, (uint32_t)(low >> 32)) : real;
                     *reinterpret_cast<uint2 *>(buf + at) = out;
                 }
             }
