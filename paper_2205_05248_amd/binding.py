@@ -173,22 +173,41 @@ def marl_destroy(handle):
     check(load().marl_destroy(ctypes.c_void_p(handle)))
 
 
-def _dev(t, dtype, shape, name, optional=False):
+# The smallest calls wait for the host, and most of that is what follows, eight to fourteen times a call: the types are looked up
+# once, a shape is compared as it is (torch.Size is a tuple), addresses and the stream are plain integers, which the
+# argument types turn into pointers.
+_torch, _dtypes, _raw_stream = None, None, None
+
+
+def _bind_torch():
+    global _torch, _dtypes, _raw_stream
     import torch
+    _dtypes = {"f32": torch.float32, "u8": torch.uint8, "i32": torch.int32}
+    # the stream's address without an object around it, where this torch has it
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+
+
+def _dev(t, dtype, shape, name, optional=False):
     if t is None:
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    want = {"f32": torch.float32, "u8": torch.uint8, "i32": torch.int32}[dtype]
-    if t.dtype != want or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
+    if _torch is None:
+        _bind_torch()
+    if t.dtype is not _dtypes[dtype] or t.shape != shape or not t.is_contiguous() or not t.is_cuda:
         raise ValueError(f"{name}: expected contiguous device {dtype} tensor of shape {tuple(shape)}, "
                          f"got {t.dtype} {tuple(t.shape)} on {t.device}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream of the current device."""
+    if _torch is None:
+        _bind_torch()
+    if _raw_stream is None:
+        return _torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_torch.cuda.current_device())
 
 
 def marl_act_step(handle, dims, obs, avail, h_in, reset, step_t, epsilon, seed, h_out, action, q_out=None):
@@ -196,7 +215,7 @@ def marl_act_step(handle, dims, obs, avail, h_in, reset, step_t, epsilon, seed, 
     N, D, A, H = dims
     E = obs.shape[0]
     check(load().marl_act_step(
-        ctypes.c_void_p(handle), E,
+        handle, E,
         _dev(obs, "f32", (E, N, D), "obs"), _dev(avail, "u8", (E, N, A), "avail"),
         _dev(h_in, "f32", (E, N, H), "h_in"), _dev(reset, "u8", (E,), "reset", optional=True),
         _dev(step_t, "i32", (E,), "step_t"), float(epsilon), int(seed) & 0xFFFFFFFFFFFFFFFF,
@@ -211,7 +230,7 @@ def marl_act_step_indexed(handle, dims, env_index, obs, avail, h_in, reset, step
     E = obs.shape[0]
     n_listed = int(env_index.shape[0])
     check(load().marl_act_step_indexed(
-        ctypes.c_void_p(handle), E, _dev(env_index, "i32", (n_listed,), "env_index"), n_listed,
+        handle, E, _dev(env_index, "i32", (n_listed,), "env_index"), n_listed,
         _dev(obs, "f32", (E, N, D), "obs"), _dev(avail, "u8", (E, N, A), "avail"),
         _dev(h_in, "f32", (E, N, H), "h_in"), _dev(reset, "u8", (E,), "reset", optional=True),
         _dev(step_t, "i32", (E,), "step_t"), float(epsilon), int(seed) & 0xFFFFFFFFFFFFFFFF,
@@ -244,7 +263,7 @@ def marl_unroll_td(online, target, dims, obs, avail, actions, reward, terminated
     B, T = obs.shape[0], obs.shape[1] - 1
     entry = load().marl_unroll_td_static if static else load().marl_unroll_td
     check(entry(
-        ctypes.c_void_p(online), ctypes.c_void_p(target), B, T,
+        online, target, B, T,
         _dev(obs, "f32", (B, T + 1, N, D), "obs"), _dev(avail, "u8", (B, T + 1, N, A), "avail"),
         _dev(actions, "i32", (B, T, N), "actions"), _dev(reward, "f32", (B, T), "reward"),
         _dev(terminated, "u8", (B, T), "terminated"), _dev(filled, "u8", (B, T), "filled"), float(gamma),
@@ -295,7 +314,7 @@ def marl_unroll_td_indexed(online, target, dims, episode_index, obs, avail, acti
     pool, T = obs.shape[0], obs.shape[1] - 1
     B = int(episode_index.shape[0])
     check(load().marl_unroll_td_indexed(
-        ctypes.c_void_p(online), ctypes.c_void_p(target), pool, _dev(episode_index, "i32", (B,), "episode_index"), B, T,
+        online, target, pool, _dev(episode_index, "i32", (B,), "episode_index"), B, T,
         _dev(obs, "f32", (pool, T + 1, N, D), "obs"), _dev(avail, "u8", (pool, T + 1, N, A), "avail"),
         _dev(actions, "i32", (pool, T, N), "actions"), _dev(reward, "f32", (pool, T), "reward"),
         _dev(terminated, "u8", (pool, T), "terminated"), _dev(filled, "u8", (pool, T), "filled"), float(gamma),
@@ -311,7 +330,7 @@ def marl_unroll_td_double(online, target, dims, obs, avail, actions, reward, ter
     pool, T = obs.shape[0], obs.shape[1] - 1
     B = pool if episode_index is None else int(episode_index.shape[0])
     check(load().marl_unroll_td_double(
-        ctypes.c_void_p(online), ctypes.c_void_p(target), pool,
+        online, target, pool,
         _dev(episode_index, "i32", (B,), "episode_index", optional=True), B, T,
         _dev(obs, "f32", (pool, T + 1, N, D), "obs"), _dev(avail, "u8", (pool, T + 1, N, A), "avail"),
         _dev(actions, "i32", (pool, T, N), "actions"), _dev(reward, "f32", (pool, T), "reward"),
@@ -335,7 +354,7 @@ def marl_qnet_grad(handle, dims, obs, actions, filled, grad_q_taken, workspace, 
     n_params = (D + N) * H + H + 6 * H * H + 6 * H + A * H + A
     fn = load().marl_qnet_grad_kept if kept else load().marl_qnet_grad
     check(fn(
-        ctypes.c_void_p(handle), B, T, _dev(obs, "f32", (B, T + 1, N, D), "obs"),
+        handle, B, T, _dev(obs, "f32", (B, T + 1, N, D), "obs"),
         _dev(actions, "i32", (B, T, N), "actions"), _dev(filled, "u8", (B, T), "filled"),
         _dev(grad_q_taken, "f32", (B, T, N), "grad_q_taken"), _dev(workspace, "u8", (workspace.numel(),), "workspace"),
         int(workspace.numel()), _dev(grad_weights, "f32", (n_params,), "grad_weights"), _stream()))
@@ -367,13 +386,13 @@ class QNet:
 
     def rmsprop_step(self, weights, grad_weights, sq_avg, lr, alpha=0.99, eps=1e-5):
         n = weights.numel()
-        check(load().marl_qnet_rmsprop_step(ctypes.c_void_p(self.handle), _dev(weights, "f32", (n,), "weights"),
+        check(load().marl_qnet_rmsprop_step(self.handle, _dev(weights, "f32", (n,), "weights"),
                                             _dev(grad_weights, "f32", (n,), "grad_weights"), _dev(sq_avg, "f32", (n,), "sq_avg"),
                                             float(lr), float(alpha), float(eps), _stream()))
 
     def sgd_step(self, weights, grad_weights, lr):
         n = weights.numel()
-        check(load().marl_qnet_sgd_step(ctypes.c_void_p(self.handle), _dev(weights, "f32", (n,), "weights"),
+        check(load().marl_qnet_sgd_step(self.handle, _dev(weights, "f32", (n,), "weights"),
                                         _dev(grad_weights, "f32", (n,), "grad_weights"), float(lr), _stream()))
 
     def grad_workspace_bytes(self, B, T):
@@ -388,7 +407,7 @@ class QNet:
         B, T = obs.shape[0], obs.shape[1] - 1
         tgt = self if target is None else target
         check(load().marl_unroll_td_keep(
-            ctypes.c_void_p(self.handle), ctypes.c_void_p(tgt.handle), B, T, _dev(obs, "f32", (B, T + 1, N, D), "obs"),
+            self.handle, tgt.handle, B, T, _dev(obs, "f32", (B, T + 1, N, D), "obs"),
             _dev(avail, "u8", (B, T + 1, N, A), "avail"), _dev(actions, "i32", (B, T, N), "actions"),
             _dev(reward, "f32", (B, T), "reward"), _dev(terminated, "u8", (B, T), "terminated"),
             _dev(filled, "u8", (B, T), "filled"), float(gamma), _dev(q_taken, "f32", (B, T, N), "q_taken"),
@@ -462,7 +481,7 @@ def marl_mixer_td(online, target, dims, state, q_taken, next_max, reward, termin
     N, M, S = dims
     B, T = int(state.shape[0]), int(state.shape[1]) - 1
     check(load().marl_mixer_td(
-        ctypes.c_void_p(online), ctypes.c_void_p(target) if target else None, B, T,
+        online, target if target else None, B, T,
         _dev(state, "f32", (B, T + 1, S), "state"), _dev(q_taken, "f32", (B, T, N), "q_taken"),
         _dev(next_max, "f32", (B, T, N), "next_max"), _dev(reward, "f32", (B, T), "reward"),
         _dev(terminated, "u8", (B, T), "terminated"), _dev(filled, "u8", (B, T), "filled"), float(gamma),
@@ -482,18 +501,18 @@ class Mixer:
 
     def rmsprop_step(self, weights, grad_weights, sq_avg, lr, alpha=0.99, eps=1e-5):
         n = weights.numel()
-        check(load().marl_mixer_rmsprop_step(ctypes.c_void_p(self.handle), _dev(weights, "f32", (n,), "weights"),
+        check(load().marl_mixer_rmsprop_step(self.handle, _dev(weights, "f32", (n,), "weights"),
                                              _dev(grad_weights, "f32", (n,), "grad_weights"), _dev(sq_avg, "f32", (n,), "sq_avg"),
                                              float(lr), float(alpha), float(eps), _stream()))
 
     def sgd_step(self, weights, grad_weights, lr):
         n = weights.numel()
-        check(load().marl_mixer_sgd_step(ctypes.c_void_p(self.handle), _dev(weights, "f32", (n,), "weights"),
+        check(load().marl_mixer_sgd_step(self.handle, _dev(weights, "f32", (n,), "weights"),
                                          _dev(grad_weights, "f32", (n,), "grad_weights"), float(lr), _stream()))
 
     def grad_workspace_bytes(self, B, T):
         n = ctypes.c_size_t(0)
-        check(load().marl_mixer_grad_workspace_bytes(ctypes.c_void_p(self.handle), int(B), int(T), ctypes.byref(n)))
+        check(load().marl_mixer_grad_workspace_bytes(self.handle, int(B), int(T), ctypes.byref(n)))
         return int(n.value)
 
     def grad(self, state, q_taken, grad_q_total, workspace, grad_q_taken, grad_weights):
@@ -501,7 +520,7 @@ class Mixer:
         B, T = q_taken.shape[0], q_taken.shape[1]
         n_params = (N * M + 3 * M) * (S + 1) + M + 1
         check(load().marl_mixer_grad(
-            ctypes.c_void_p(self.handle), B, T, _dev(state, "f32", (B, T + 1, S), "state"),
+            self.handle, B, T, _dev(state, "f32", (B, T + 1, S), "state"),
             _dev(q_taken, "f32", (B, T, N), "q_taken"), _dev(grad_q_total, "f32", (B, T), "grad_q_total"),
             _dev(workspace, "u8", (workspace.numel(),), "workspace"), int(workspace.numel()),
             _dev(grad_q_taken, "f32", (B, T, N), "grad_q_taken"), _dev(grad_weights, "f32", (n_params,), "grad_weights"),

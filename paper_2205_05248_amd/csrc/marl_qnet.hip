@@ -53,16 +53,19 @@ size_t param_count(const marl_qnet_desc *d)
     return Din * H + H + 2 * 3 * H * H + 2 * 3 * H + A * H + A;
 }
 
+// Makes a device current for the calling thread and the one before current again (usually the same: nothing is set then).
 struct DeviceGuard {
     int prev = -1;
-    bool ok = false;
+    bool ok = false, moved = false;
     explicit DeviceGuard(int dev)
     {
-        if (hipGetDevice(&prev) == hipSuccess && hipSetDevice(dev) == hipSuccess) ok = true;
+        if (hipGetDevice(&prev) != hipSuccess) return;
+        moved = prev != dev;
+        ok = !moved || hipSetDevice(dev) == hipSuccess;
     }
     ~DeviceGuard()
     {
-        if (ok && prev >= 0) (void)hipSetDevice(prev);
+        if (ok && moved && prev >= 0) (void)hipSetDevice(prev);
     }
 };
 

@@ -537,9 +537,14 @@ size_t mixer_params(const marl_mixer_desc *d)
 
 struct MixerDeviceGuard {
     int prev = -1;
-    bool ok = false;
-    explicit MixerDeviceGuard(int dev) { ok = hipGetDevice(&prev) == hipSuccess && hipSetDevice(dev) == hipSuccess; }
-    ~MixerDeviceGuard() { if (ok && prev >= 0) (void)hipSetDevice(prev); }
+    bool ok = false, moved = false;
+    explicit MixerDeviceGuard(int dev)
+    {
+        if (hipGetDevice(&prev) != hipSuccess) return;
+        moved = prev != dev;
+        ok = !moved || hipSetDevice(dev) == hipSuccess;
+    }
+    ~MixerDeviceGuard() { if (ok && moved && prev >= 0) (void)hipSetDevice(prev); }
 };
 
 }  // namespace
