@@ -15,8 +15,9 @@ namespace marl {
 // (positions clamped into the arrays, rows past the end read row 0), and hands them over in LDS:
 // epi[slot & 1][word][lane], words: 0 action, 1 flags (filled(t) | terminated(t-1) << 8 | filled(t-1) << 16),
 // 2 reward(t-1), 3 the lane's availability slots of slot t (avail_mask16, formed by the loader).
-// (With two networks each workgroup's epilogue uses one half only; all of it is fetched, as the loader is not what a step
-// waits for.)  wide: at least four actions, whose availability is read four bytes at a time.
+// With two networks each workgroup's epilogue uses one half only: both are fetched (a load left out by a branch would make
+// the waits for the others inexact), but the target's half is put together only where it is wanted.
+// wide: at least four actions, whose availability is read four bytes at a time.
 constexpr int kEpiWords = 4;
 constexpr size_t kEpiBytes = 2 * kEpiWords * 64 * 4;
 
@@ -75,7 +76,7 @@ template <int AB, int MODE> struct TdTile16 {
     }
 
     template <class Wide>
-    __device__ __forceinline__ void stage(const SlotRaw &in, int t, Wide) const
+    __device__ __forceinline__ void stage(const SlotRaw &in, int t, Wide, bool want_target) const
     {
         if constexpr (!kSave) {
             uint32_t *at = epi + (size_t)(t & 1) * kEpiWords * 64 + lane;
@@ -85,8 +86,10 @@ template <int AB, int MODE> struct TdTile16 {
             asm volatile("" : "+v"(filled), "+v"(terminated_prev), "+v"(filled_prev));
             at[0] = (uint32_t)in.u;
             at[64] = filled | terminated_prev << 8 | filled_prev << 16;
-            at[128] = __builtin_bit_cast(uint32_t, in.reward);
-            if constexpr (Wide::value && !kValue) at[192] = avail_mask16<AB>(in.avail_raw, A, q4, valid);
+            if (want_target) {
+                at[128] = __builtin_bit_cast(uint32_t, in.reward);
+                if constexpr (Wide::value && !kValue) at[192] = avail_mask16<AB>(in.avail_raw, A, q4, valid);
+            }
         }
     }
 

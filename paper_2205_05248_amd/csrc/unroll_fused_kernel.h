@@ -146,6 +146,7 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         const float *base = obs + ((size_t)bi * S * N + n) * D;              // the lane's row at slot 0
         const size_t slot_stride = (size_t)N * D;
         using SlotRaw = typename TdTile16<AB, MODE>::SlotRaw;
+        const bool want_target = kDouble ? !is_target : is_target || !two_nets;
         auto loader_loop = [&](auto k_steps, auto is_short, auto wide) {
             constexpr int KN = decltype(k_steps)::value;
             ObsStageK<P, KN, decltype(is_short)::value> st;
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
                 epi_refill = tile.fetch(min(max(s + 1, 0), T), wide);        // slot s + 1: staged in the next step, read by the epilogue in step s + 2
                 __builtin_amdgcn_sched_barrier(0);
                 st.write(ready, obuf + (size_t)((ws & 1) * KN) * P * 64 + lane);     // registers -> LDS
-                tile.stage(epi_ready, s, wide);
+                tile.stage(epi_ready, s, wide, want_target);
                 lds_barrier();
             };
             int s = -LEAD;

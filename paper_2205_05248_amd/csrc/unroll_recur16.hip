@@ -160,10 +160,11 @@ __global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel
     }
     using SlotRaw = typename TdTile16<AB, MODE>::SlotRaw;
     SlotRaw epi_a{}, epi_b{};
+    const bool want_target = kDouble ? !is_target : is_target || !two_nets;
     auto loader_loop = [&](auto wide) {
         auto loader_step = [&](const SlotRaw &ready, SlotRaw &refill, int s) {
             refill = tile.fetch(min(max(s + 1, 0), T), wide);
-            tile.stage(ready, s, wide);
+            tile.stage(ready, s, wide, want_target);
             lds_barrier();
         };
         int s = -LEAD;
