@@ -251,28 +251,31 @@ template <int H, int P> struct Fc1Wave {
                 if (ks < ks1) settle(w1[j][ks]);
     }
 
-    // The same for step_k: the weights of the k-steps past the network's own are zero, and those of the last eight
-    // observations are where ObsStageK puts these.
-    __device__ __forceinline__ void load_k(const NetFrags &net, int f, int lane)
+    // The same for step_k<KN>: the weights of a k-step past the network's own are zero, and those of the last eight
+    // observations are where ObsStageK puts these.  Only a k-step that has them, or lies past them, is moved: with all the
+    // k-steps that a wave has room for loaded and moved, the first slot waited for 1700 instructions of this (2 k-steps at 128
+    // bf16 units, 100 slots: 104.6 us, now 100.0).
+    template <int KN> __device__ __forceinline__ void load_k(const NetFrags &net, int f, int lane)
     {
-        const int D = net.D, ks1 = (D + 31) / 32;
+        const int D = net.D, ks1 = (D + 31) / 32;                       // KN or KN - 1
 #pragma unroll
         for (int j = 0; j < NBF; ++j)
 #pragma unroll
-            for (int ks = 0; ks < KM; ++ks) {
+            for (int ks = 0; ks < KN; ++ks)
                 w1[j][ks] = load_wfrag<P>(net.w1_16 + ((size_t)((f * NBF + j) * ks1 + min(ks, ks1 - 1)) * P) * 64 + lane);
-                const int shift = ks < ks1 ? (D >= 8 ? min(max(32 * ks + 8 * (lane >> 4) - (D - 8), 0), 8) : 0) : 8;
+#pragma unroll
+        for (int ks = KN < 2 ? 0 : KN - 2; ks < KN; ++ks) {
+            const int shift = ks < ks1 ? (D >= 8 ? min(max(32 * ks + 8 * (lane >> 4) - (D - 8), 0), 8) : 0) : 8;
+#pragma unroll
+            for (int j = 0; j < NBF; ++j) {
                 w1[j][ks].hi = shift_up(w1[j][ks].hi, shift);
                 if constexpr (P == 2) w1[j][ks].lo = shift_up(w1[j][ks].lo, shift);
             }
-    }
-
-    __device__ __forceinline__ void settle_weights_k() const
-    {
+        }
 #pragma unroll
         for (int j = 0; j < NBF; ++j)
 #pragma unroll
-            for (int ks = 0; ks < KM; ++ks) settle(w1[j][ks]);
+            for (int ks = 0; ks < KN; ++ks) settle(w1[j][ks]);
     }
 
     static __device__ __forceinline__ void load_bias(const NetFrags &net, int f, int n, int q4, f32x4 (&b1v)[NBF])

@@ -35,7 +35,8 @@
 // cycle counters every wave works 1700 to 2050 of a step's 2080 clocks, the loader all of them).  The loader waited out a
 // trip to memory in each step until its loads were straight-line code and the flags it fetches were put together where
 // they are staged; with that and W_ih in registers for 64 units, 32 episodes x 120 slots x 8 agents 103.3 -> 96.7 us,
-// 64 x 200 x 32 with 128 units 279 -> 275 us, keeping activations 370 -> 335 us.
+// 64 x 200 x 32 with 128 units 279 -> 275 us, keeping activations 370 -> 335 us.  (With the target half of the TD inputs put
+// together only where it is read, and the first layer's weights prepared per k-step: 91.6 and 259 us.)
 #include <hip/hip_runtime.h>
 
 #pragma once
@@ -183,10 +184,8 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         // ---------------------------------------------------------------- fc1 wave
         const int f = wave - Sh::kFc1;
         Fc1Wave<H, P> fc1;
-        fc1.load_k(net, f, lane);
         f32x4 b1v[Sh::NBF];
         Fc1Wave<H, P>::load_bias(net, f, n, q4, b1v);
-        fc1.settle_weights_k();
 #pragma unroll
         for (int j = 0; j < Sh::NBF; ++j) asm volatile("" ::"v"(b1v[j]));
         const float *touch_row = obs + ((size_t)bi * S * N + n) * D;
@@ -212,6 +211,7 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         asm volatile("" : "+v"(x_drop));
         auto fc1_loop = [&](auto k_steps) {
             constexpr int KN = decltype(k_steps)::value;
+            fc1.template load_k<KN>(net, f, lane);
             auto fc1_step = [&](int s) {
                 const int slot = s + 1;
                 if (slot >= 0 && slot <= T) {
