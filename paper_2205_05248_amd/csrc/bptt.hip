@@ -1137,30 +1137,75 @@ struct TnReduceArgs {
 };
 struct TnReduceBatch { TnReduceArgs r[kTnBatchMax]; };
 
-__global__ void tn_reduce_kernel(const TnReduceBatch batch)
+// A result is four running sums over interleaved chunks (j, j + 4, ...), added in a fixed order.
+// kWaves = 1: one thread has all four, sixteen loads in flight.  What bounds it where the results are few is the trips to
+// memory of that thread, eight for 128 chunks (9.9 us a launch on 64 episodes x 120 slots x 5 agents, 64 units, for 15 MB).
+// kWaves = 4: four waves share 64 results, one sum each; iterations there 408 -> 404 us, 37 x 83 x 5 bf16 232 -> 228.
+// Four only up to kReduceFew results a launch (one wave per SIMD of the chip): with 147,000 (64 x 200 x 32, 128 units) the
+// loads of one thread per result already fill the memory path (iteration 1350 us, with four waves 1352).  The four
+// products of 128 units together have more results than that (99,000 and the first layer's), those of 64 units fewer.
+constexpr int kReduceThreads = 256;
+constexpr long kReduceFew = 65536;
+
+template <int kWaves>
+__global__ __launch_bounds__(kReduceThreads) void tn_reduce_kernel(const TnReduceBatch batch)
 {
+    constexpr int kResults = kReduceThreads / kWaves, kSums = 4 / kWaves;        // results of a workgroup, sums of a thread
     const TnReduceArgs g = batch.r[blockIdx.y];
     const int cols = g.Q + g.n_extra;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= g.P * cols) return;
+    if ((int)blockIdx.x * kResults >= g.P * cols) return;                        // the whole workgroup
+    const int part = threadIdx.x / kResults, lane = threadIdx.x % kResults;
+    const int at = blockIdx.x * kResults + lane;
+    const int idx = min(at, g.P * cols - 1);
     const int p = idx / cols, q = idx % cols;
-    const int row = (p + g.row_shift) % g.P;
-    // four running sums over interleaved chunks keep sixteen loads in flight; the order is fixed
     const float *src = g.partial + (size_t)p * g.qp + q;
     const size_t step = (size_t)g.p_pad * g.qp;
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    int ch = 0;
-    for (; ch + 16 <= g.chunks; ch += 16) {
+    float s[kSums] = {};
+    int ch = part;
+    for (; ch + kWaves * 15 < g.chunks; ch += kWaves * 16) {
         float v[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = src[(size_t)(ch + i) * step];
+        for (int i = 0; i < 16; ++i) v[i] = src[(size_t)(ch + kWaves * i) * step];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i & 3] += v[i];
+        for (int i = 0; i < 16; ++i) s[i % kSums] += v[i];
     }
-    for (; ch < g.chunks; ++ch) s[ch & 3] += src[(size_t)ch * step];
-    const float total = (s[0] + s[1]) + (s[2] + s[3]);
+    for (; ch < g.chunks; ch += kWaves * 8) {                                    // the rest, eight at a time
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = src[(size_t)min(ch + kWaves * i, g.chunks - 1) * step];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s[i % kSums] += ch + kWaves * i < g.chunks ? v[i] : 0.0f;
+    }
+    float total;
+    if constexpr (kWaves == 4) {
+        __shared__ float sums[4][kResults];
+        sums[part][lane] = s[0];
+        __syncthreads();
+        if (part != 0) return;
+        total = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
+    } else {
+        total = (s[0] + s[1]) + (s[2] + s[3]);
+    }
+    if (at >= g.P * cols) return;
+    const int row = (p + g.row_shift) % g.P;
     if (q < g.Q || g.extra_mode == kExtraAgent) g.dst_w[(size_t)row * g.ld_w + q] = total;
     else g.dst_b[row] = total;
+}
+
+hipError_t launch_reduce(const TnReduceBatch &batch, int count, hipStream_t stream)
+{
+    long results = 0;
+    int most = 0;
+    for (int i = 0; i < count; ++i) {
+        const int n = batch.r[i].P * (batch.r[i].Q + batch.r[i].n_extra);
+        results += n;
+        most = std::max(most, n);
+    }
+    if (results <= kReduceFew)
+        hipLaunchKernelGGL(tn_reduce_kernel<4>, dim3((most + kReduceThreads / 4 - 1) / (kReduceThreads / 4), count), dim3(kReduceThreads), 0, stream, batch);
+    else
+        hipLaunchKernelGGL(tn_reduce_kernel<1>, dim3((most + kReduceThreads - 1) / kReduceThreads, count), dim3(kReduceThreads), 0, stream, batch);
+    return hipGetLastError();
 }
 
 // kExtraAgent: the bias gradient is the sum of the agent columns just written.
@@ -1317,7 +1362,7 @@ hipError_t launch_tn_products(int planes, const TnProduct *list, int count, long
     while (done < count) {
         TnLaunch rows[3];
         TnReduceBatch red{};
-        int n_red = 0, max_total = 0;
+        int n_red = 0;
         size_t used = 0;
         int taken = done;
         bool a_in_groups = false, wide_loads = planes == 1 && list[done].a.bf16;
@@ -1341,14 +1386,12 @@ hipError_t launch_tn_products(int planes, const TnProduct *list, int count, long
             wide_loads = wide_loads && tn_wide_fits(t, M);
             rows[row_class(t.P) - 1].add(g);
             red.r[n_red++] = reduce_args(t, g.partial, chunks);
-            max_total = std::max(max_total, t.P * (t.Q + t.n_extra));
         }
         if (a_in_groups && !wide_loads) return hipErrorInvalidValue;
         hipError_t err = hipSuccess;
         for (int k = 3; k >= 1 && err == hipSuccess; --k) err = launch_shape(rows[k - 1], k, list[done].b.bf16 != 0, planes, wide_loads, chunks, stream);
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(tn_reduce_kernel, dim3((max_total + 255) / 256, n_red), dim3(256), 0, stream, red);
-        err = hipGetLastError();
+        err = launch_reduce(red, n_red, stream);
         if (err != hipSuccess) return err;
         for (int i = done; i < taken; ++i)
             if (list[i].extra_mode == kExtraAgent) {
@@ -1478,7 +1521,6 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     // a product's partial sums: the later half's chunks, then the earlier half's, summed in that order
     float *part_late[4], *part_early[4];
     TnReduceBatch red{};
-    int max_total = 0;
     {
         size_t used = 0;
         for (int i = 0; i < 4; ++i) {
@@ -1488,7 +1530,6 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
             part_early[i] = part_late[i] + (size_t)cut_late.chunks * p_pad * qp;
             used += (size_t)(cut_late.chunks + cut_early.chunks) * p_pad * qp * sizeof(float);
             red.r[i] = reduce_args(t, part_late[i], cut_late.chunks + cut_early.chunks);
-            max_total = std::max(max_total, t.P * (t.Q + t.n_extra));
         }
         if (used > plan.partial_bytes) return hipErrorInvalidValue;
     }
@@ -1507,8 +1548,7 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 2, 2, cut_early.samples, cut_early.chunk, part_early + 2, stream);
     if (err == hipSuccess) err = hipStreamWaitEvent(stream, side->join, 0);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(tn_reduce_kernel, dim3((max_total + 255) / 256, 4), dim3(256), 0, stream, red);
-    err = hipGetLastError();
+    err = launch_reduce(red, 4, stream);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(bias_from_columns_kernel, dim3((H + 255) / 256), dim3(256), 0, stream, gW1, H, D + N, D, N, gb1);
     return hipGetLastError();
