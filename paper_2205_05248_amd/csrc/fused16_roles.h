@@ -333,11 +333,10 @@ template <int H, int P> struct Fc1Wave {
 
     // The same, straight-line, over KN = obs_k_steps fragments; after load_k.
     // SAVE: x also goes to byte x_at (+ the block's) of *x_buf, fp32 for a two-plane network, bf16 for a one-plane network (the
-    // rounding every reader of x applies anyway).  The store is unconditional; x_drop, all ones, puts it beyond the buffer, which
-    // drops it.
+    // rounding every reader of x applies anyway).  The store is unconditional; an x_at beyond the buffer drops it.
     template <int KN, bool SAVE = false>
     __device__ __forceinline__ void step_k(const bf16x8 *obs_src, int f, int lane, const f32x4 (&b1v)[NBF], bf16x8 (*x_dst)[P][64],
-                                         const __amdgpu_buffer_rsrc_t *x_buf = nullptr, uint32_t x_at = 0, uint32_t x_drop = 0) const
+                                         const __amdgpu_buffer_rsrc_t *x_buf = nullptr, uint32_t x_at = 0) const
     {
         auto obs_frag = [&](int ks) {
             const bf16x8 *src = obs_src + (size_t)(ks * P) * 64 + lane;
@@ -380,10 +379,10 @@ template <int H, int P> struct Fc1Wave {
                     bf16x4 v;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) v[r] = (__bf16)acc[j][r];
-                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), *x_buf, (x_at + 32u * (f * NBF + j)) | x_drop, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), *x_buf, x_at + 32u * (f * NBF) + 32u * j, 0, 0);
                 } else {
                     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j]), *x_buf, (x_at + 64u * (f * NBF + j)) | x_drop, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j]), *x_buf, x_at + 64u * (f * NBF) + 64u * j, 0, 0);
                 }
             }
         }
@@ -458,42 +457,81 @@ template <int H, int P> struct ObsStage {
 // every load is a wide one.  Rows of less than eight floats (SHORT) are fetched element by element, positions past the end from the
 // last one, whose weights are zero.  (In the decision step, whose loader and fc1 waves have more to address per item, this form
 // was slower: 2048 x 32 rows of 300 observations 45.0 -> 58.0 us.)
+// What a lane holds twice meets zero weights the second time, which is nothing added unless it is infinite (or rounds to infinity):
+// 0 x inf is NaN.  With one plane `write` therefore puts the row's last value in its place, which is what the decision step's
+// loader has there, and zeros where a k-step lies past the network's own: the same rows give the same x in either.  With two
+// planes the remainder of an infinity is NaN already, and so is every x of its row, whatever its weight.
 template <int KN> struct ObsRegsK { float v[KN][8]; };
 
 template <int P, int KN, bool SHORT> struct ObsStageK {
-    int off[SHORT ? 8 : KN];
+    static constexpr bool kRounded = P == 1 && KN > 4;                   // KN may be one more than the network's own k-steps
+    static constexpr int kInside = SHORT ? 0 : KN - (kRounded ? 2 : 1);  // k-steps that end inside every such row
+    static constexpr bool kFills = P == 1 && !SHORT;
+    int q8, off[SHORT ? 8 : KN - kInside];           // from the lane's first observation on: of an element (SHORT), of the last k-steps
+    uint32_t own[kFills ? 4 : 1];                    // in the network's last k-step: ones over the elements that the lane holds once
+    bool past;                                       // the last k-step lies past the network's own
 
     __device__ __forceinline__ void init(int D, int q4)
     {
+        q8 = 8 * q4;
 #pragma unroll
-        for (int i = 0; i < (SHORT ? 8 : KN); ++i) off[i] = SHORT ? min(8 * q4 + i, D - 1) : min(32 * i + 8 * q4, D - 8);
+        for (int i = 0; i < (SHORT ? 8 : KN - kInside); ++i) off[i] = (SHORT ? min(q8 + i, D - 1) : min(32 * (kInside + i) + q8, D - 8)) - q8;
+        past = kRounded && 32 * (KN - 1) >= D;
+        if constexpr (kFills) {
+            const int from = 32 * (past ? KN - 2 : KN - 1) + q8, twice = from - min(from, D - 8);      // the first so many
+#pragma unroll
+            for (int i = 0; i < 4; ++i) own[i] = twice <= 2 * i ? 0xFFFFFFFFu : twice == 2 * i + 1 ? 0xFFFF0000u : 0u;
+        }
     }
 
     __device__ __forceinline__ void load(ObsRegsK<KN> &r, const float *row) const
     {
+        const float *const at = row + q8;
         if constexpr (SHORT) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) r.v[0][i] = row[off[i]];
+            for (int i = 0; i < 8; ++i) r.v[0][i] = at[off[i]];
         } else {
 #pragma unroll
             for (int k = 0; k < KN; ++k) {
+                const float *const from = k < kInside ? at + 32 * k : at + off[max(k - kInside, 0)];
                 f32x4 lo4, hi4;
-                __builtin_memcpy(&lo4, row + off[k], 16);
-                __builtin_memcpy(&hi4, row + off[k] + 4, 16);
+                __builtin_memcpy(&lo4, from, 16);
+                __builtin_memcpy(&hi4, from + 4, 16);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { r.v[k][i] = lo4[i]; r.v[k][4 + i] = hi4[i]; }
             }
         }
     }
 
+    // The row's last value in place of what the lane holds twice.
+    __device__ __forceinline__ bf16x8 filled(const bf16x8 &v) const
+    {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 word = __builtin_bit_cast(u32x4, v);
+        const uint32_t last = (word[3] >> 16) * 0x10001u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) word[i] = (word[i] & own[i]) | (last & ~own[i]);
+        return __builtin_bit_cast(bf16x8, word);
+    }
+
     // dst = this lane's slot in the item's first fragment
     __device__ __forceinline__ void write(const ObsRegsK<KN> &r, bf16x8 *dst) const
     {
+        Frag<P> f[KN];
+#pragma unroll
+        for (int k = 0; k < KN; ++k) f[k] = to_frag<P>(r.v[k]);
+        if constexpr (kFills) {
+            if (kRounded && past) {
+                f[kRounded ? KN - 2 : 0].hi = filled(f[kRounded ? KN - 2 : 0].hi);
+                f[KN - 1].hi = bf16x8{};
+            } else {
+                f[KN - 1].hi = filled(f[KN - 1].hi);
+            }
+        }
 #pragma unroll
         for (int k = 0; k < KN; ++k) {
-            const Frag<P> f = to_frag<P>(r.v[k]);
-            dst[(k * P) * 64] = f.hi;
-            if constexpr (P == 2) dst[(k * P + 1) * 64] = f.lo;
+            dst[(k * P) * 64] = f[k].hi;
+            if constexpr (P == 2) dst[(k * P + 1) * 64] = f[k].lo;
         }
     }
 };

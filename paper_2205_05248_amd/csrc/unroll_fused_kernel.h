@@ -206,9 +206,8 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
         constexpr uint32_t kElem = P == 1 ? 2u : 4u;
         const __amdgpu_buffer_rsrc_t x_buf =
             __builtin_amdgcn_make_buffer_rsrc(x_save, 0, kStores ? (int)((uint32_t)rows * S * H * kElem) : 0, kRawBuffer);
-        const uint32_t x_row = (((uint32_t)b * S * N + n) * H + 4 * q4) * kElem, x_slot = (uint32_t)N * H * kElem;
-        uint32_t x_drop = valid && !is_target ? 0u : 0xFFFFFFF0u;
-        asm volatile("" : "+v"(x_drop));
+        // (rows that are not kept: beyond the buffer, in any slot)
+        const uint32_t x_row = valid && !is_target ? (((uint32_t)b * S * N + n) * H + 4 * q4) * kElem : 0x80000000u, x_slot = (uint32_t)N * H * kElem;
         auto fc1_loop = [&](auto k_steps) {
             constexpr int KN = decltype(k_steps)::value;
             fc1.template load_k<KN>(net, f, lane);
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(fused_threads(H), 2) void unroll_fused_kernel(
                 const int slot = s + 1;
                 if (slot >= 0 && slot <= T) {
                     const bf16x8 *const o = obuf + (size_t)((slot & 1) * KN) * P * 64;
-                    if constexpr (kStores) fc1.template step_k<KN, true>(o, f, lane, b1v, x_lds[slot & 1], &x_buf, x_row + (uint32_t)slot * x_slot, x_drop);
+                    if constexpr (kStores) fc1.template step_k<KN, true>(o, f, lane, b1v, x_lds[slot & 1], &x_buf, x_row + (uint32_t)slot * x_slot);
                     else fc1.template step_k<KN>(o, f, lane, b1v, x_lds[slot & 1]);
                 }
                 lds_barrier();
