@@ -30,9 +30,13 @@ struct Recur16 {
 
 }  // namespace
 
+// The gate inputs carry no __restrict__: under kTdDouble the target network's Q values go where they were (td.next_q.q is
+// gi_target).  A workgroup stores to its half of the record of slot t in step t + 1.  Its recurrence waves have asked for the gate
+// inputs there in step t - 1 and used them in step t, before the barrier that ends it; what reads the record later (the last slot
+// again in step T, the touches past the end) uses nothing of it.
 template <int AB, bool QALL, int MODE>
-__global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel(NetFrags online, NetFrags target, const char *__restrict__ gi_online,
-                                                                                 const char *__restrict__ gi_target, int two_nets, int B, int T,
+__global__ __launch_bounds__(64 * Recur16::kWaves, 3) void recurrent16_td_kernel(NetFrags online, NetFrags target, const char *gi_online,
+                                                                                 const char *gi_target, int two_nets, int B, int T,
                                                                                  TdArrays td)
 {
     using Sh = Recur16;
