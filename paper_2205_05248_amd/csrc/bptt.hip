@@ -1275,11 +1275,8 @@ size_t tn_partial_bytes(long M, int chunk, int P, int q_total)
 
 namespace {
 
-// What a product needs of its kernel: rows 3 (up to 384), 2 (256) or 1 (128), and whether its B is bf16.
-int row_class(int P) { return P > 256 ? 3 : P > 128 ? 2 : 1; }
-
 // Fills a product's kernel arguments; false where no kernel takes it.
-bool tn_args(const TnProduct &t, long M, int chunk, float *partial, TnGemmArgs *out)
+bool tn_args(int planes, const TnProduct &t, long M, int chunk, float *partial, TnGemmArgs *out)
 {
     TnGemmArgs g{};
     g.a = t.a; g.b = t.b; g.M = (int)M; g.P = t.P; g.Q = t.Q; g.extra_mode = t.extra_mode; g.n_extra = t.n_extra;
@@ -1298,7 +1295,7 @@ bool tn_args(const TnProduct &t, long M, int chunk, float *partial, TnGemmArgs *
     };
     if (!steps(t.a, &g.next_a, &g.wrap_a) || !steps(t.b, &g.next_b, &g.wrap_b)) return false;
     *out = g;
-    return t.P > 128 ? t.P <= 384 && g.qp <= 144 : g.qp <= 336 && !t.b.bf16;
+    return has_product_kernel(planes, t.a.bf16 != 0, t.b.bf16 != 0, t.P, g.qp);
 }
 
 TnReduceArgs reduce_args(const TnProduct &t, const float *partial, int chunks)
@@ -1369,13 +1366,11 @@ hipError_t launch_tn_products(int planes, const TnProduct *list, int count, long
         for (; taken < count; ++taken) {
             const TnProduct &t = list[taken];
             TnGemmArgs g{};
-            if (!tn_args(t, M, chunk, reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used), &g)) return hipErrorInvalidValue;
+            if (!tn_args(planes, t, M, chunk, reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used), &g)) return hipErrorInvalidValue;
             // A in groups: the wide kernel only
             if (t.a.rows_per_group < M && !(planes == 1 && tn_wide_fits(t, M))) return hipErrorInvalidValue;
             // bf16 adjoints are read 16 bytes (eight columns) at a time
             if (t.a.bf16 && (reinterpret_cast<uintptr_t>(t.a.base) % 16 != 0 || t.a.ld % 8 != 0 || t.a.ld < (t.P + 7) / 8 * 8)) return hipErrorInvalidValue;
-            // A's elements: bf16 for one plane, fp32 for two
-            if ((t.a.bf16 != 0) != (planes == 1)) return hipErrorInvalidValue;
             // B in bf16: such products go in launches of their own
             if ((t.b.bf16 != 0) != (list[done].b.bf16 != 0)) break;
             const size_t bytes = tn_partial_bytes(M, chunk, t.P, t.Q + t.n_extra);
@@ -1416,7 +1411,7 @@ hipError_t launch_tn_gemms_wide(const TnProduct *list, int count, long M, int ch
         const TnProduct &t = list[i];
         TnGemmArgs g{};
         TnLaunch &l = rows[row_class(t.P) - 1][t.b.bf16 ? 1 : 0];
-        if (!tn_wide_fits(t, M) || !tn_args(t, M, chunk, partial[i], &g) || l.count == kTnBatchMax) return hipErrorInvalidValue;
+        if (!tn_wide_fits(t, M) || !tn_args(1, t, M, chunk, partial[i], &g) || l.count == kTnBatchMax) return hipErrorInvalidValue;
         l.add(g);
     }
     hipError_t err = hipSuccess;

@@ -1,10 +1,23 @@
-// How the backward pass cuts the samples of its weight-gradient products into chunks, one workgroup and one set of
-// partial sums each.  Host arithmetic only, in one place for the launches and for the workspace that they write to.
+// Which weight-gradient products there are kernels for, and how the backward pass cuts the samples of its products into chunks,
+// one workgroup and one set of partial sums each.  Host arithmetic only, in one place for the launches and for the workspace
+// that they write to.
 #pragma once
 
 #include <algorithm>
 
 namespace marl {
+
+// What a product needs of its kernel: rows 3 (up to 384), 2 (256) or 1 (128).
+inline int row_class(int P) { return P > 256 ? 3 : P > 128 ? 2 : 1; }
+
+// Whether there is a kernel for a product of P rows and `columns` columns (appended ones included, padded to 16).  The kernels
+// read an operand as the elements that they are compiled for: A (the adjoints) is bf16 in a one-plane network and fp32 in
+// one of two planes, B (states, activations) fp32, or bf16 beside bf16 adjoints in the shapes above 128 rows.
+inline bool has_product_kernel(int planes, bool a_bf16, bool b_bf16, int P, int columns)
+{
+    if (a_bf16 != (planes == 1) || (b_bf16 && !(a_bf16 && P > 128))) return false;
+    return P > 128 ? P <= 384 && columns <= 144 : columns <= 336;
+}
 
 // chunk: samples of every chunk but the last, whole rounds of two steps of 32
 struct SampleChunks { long samples; int chunk, chunks; };
