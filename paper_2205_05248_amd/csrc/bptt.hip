@@ -575,7 +575,7 @@ struct TnGemmArgs {
 };
 
 constexpr int kTnThreads = 512;        // eight waves: two per SIMD
-constexpr int kTnBatchMax = 16;        // products of one shape launched together (blockIdx.y picks one)
+constexpr int kTnBatchMax = kProductsPerLaunch;        // products of one shape launched together (blockIdx.y picks one)
 struct TnGemmBatch { TnGemmArgs g[kTnBatchMax]; };
 
 // One workgroup per chunk of samples computes the whole result, so that every operand element is read from

@@ -29,6 +29,48 @@ inline SampleChunks cut_samples(long samples, long most_chunks, long least_sampl
     return {samples, (int)chunk, (int)((samples + chunk - 1) / chunk)};
 }
 
+// A list of products is launched so many at a time, each with a set of chunks.
+constexpr int kProductsPerLaunch = 16;
+
+// count things in as few and as equal parts as hold `most` of them at most: part i has size(i), from first(i) on.
+struct EvenParts {
+    int count, parts;
+    int size(int i) const { return count / parts + (i < count % parts ? 1 : 0); }
+    int first(int i) const { return count / parts * i + (i < count % parts ? i : count % parts); }
+};
+inline EvenParts even_parts(int count, int most) { return {count, std::max(1, (count + most - 1) / most)}; }
+
+// The rows of a matrix of more than 128, in blocks of 16: parts of at most 384 rows, as few as there can be with all of one
+// row class, whose products then go together in one launch.  1024 rows as 384 + 384 + 256, or 528 as 272 + 256, are two
+// launches in a row that share out the compute units among all the products and then use a part of them each.  Mixer gradient, slices
+// of 384 and the rest / these: 32 agents x 32, state 256, 6400 transitions fp32 148 / 126 us, 12800 bf16 114 / 100; 33 x 16, state
+// 400, 182 / 152 and 127 / 110.
+inline EvenParts tall_slices(int rows)
+{
+    EvenParts s = even_parts((rows + 15) / 16, 24);
+    while (row_class(16 * s.size(0)) != row_class(16 * s.size(s.parts - 1))) ++s.parts;
+    return s;
+}
+
+// The mixer's products: those of its largest matrix, if it is taller than 128 rows (128 state columns each), and those of the
+// others (320 columns) and of v2.
+constexpr int kTallColumns = 128, kFlatColumns = 320;
+struct MixerProducts { int tall, flat; };
+inline MixerProducts mixer_products(int largest_rows, int state_dim)
+{
+    const int per_flat = (state_dim + kFlatColumns - 1) / kFlatColumns, flat = 3 * per_flat + 1;
+    if (largest_rows <= 128) return {0, flat + per_flat};
+    return {tall_slices(largest_rows).parts * ((state_dim + kTallColumns - 1) / kTallColumns), flat};
+}
+
+// The mixer's chunks, for a launch of `products`.  One workgroup per product and chunk, one per compute unit: as many chunks as
+// let the launch fill the chip once, of 64 transitions (two steps) at least.  Chunks of 256 transitions whatever the number of
+// products left all but 30 compute units idle on 7680 transitions of 160 x 120 weights (31 + 21 us for the products), one chunk
+// in all on 240.  What counts is the products of the launch, not of the list: 24 products of ten chunks each, in launches of
+// sixteen and eight, were slower than with chunks of 256 (32 agents x 64, state 512, 6400 transitions fp32: chunks of 256 472 us,
+// ten chunks 542, two launches of 12 x 21 chunks 432).
+inline SampleChunks mixer_chunks(long transitions, int products) { return cut_samples(transitions, 256 / products, 64); }
+
 // The reverse recurrence may walk the slots in two launches from this many on (one-plane networks).
 constexpr int kForkSlots = 16;
 

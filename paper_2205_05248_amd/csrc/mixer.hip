@@ -901,19 +901,8 @@ hipError_t mixer_back_stream_dispatch(int mb, const MixerBackArgs &a, hipStream_
     }
 }
 
-// The products of the four state matrices and of v2, by the rows of their results: tall ones (Hw1's, when it has more than 128
-// rows), cut into 384 rows and 128 state columns, the rest into 128 rows and 320.  Both lists run as launches of their own.
-struct ProductCut { int tall, flat; };
-ProductCut mixer_products(const marl_mixer_desc &d)
-{
-    const int rows = d.n_agents * d.embed, S = d.state_dim;
-    const int flat = 3 * ((S + 319) / 320) + 1;
-    if (rows > 128) return {(rows + 383) / 384 * ((S + 127) / 128), flat};
-    return {0, flat + (S + 319) / 320};
-}
-
 struct MixerGradPlan {
-    int ldd, chunk_tall, chunk_flat;
+    int ldd;
     size_t off_dgen, off_partial, partial_bytes, bytes;
 };
 
@@ -924,18 +913,17 @@ MixerGradPlan mixer_grad_plan(const marl_mixer_desc &d, int B, int T)
     const int F = (d.n_agents + 3) * d.embed;
     // whole 16-byte pieces, and eight columns from the last product's first one on (it takes the last embed + 1)
     p.ldd = F + (d.embed + 1 + 7) / 8 * 8;
-    // One workgroup per product and chunk, one per compute unit: as many chunks as let a launch fill the chip once, of 64
-    // transitions (two steps) at least.  Chunks of 256 transitions whatever the number of products left all but 30 compute units idle
-    // on 7680 transitions of 160 x 120 weights (31 + 21 us for the products), one chunk in all on 240.
-    const ProductCut cut = mixer_products(d);
-    auto chunk_of = [&](int products) { return cut_samples(R, std::max(1, 256 / std::max(1, products)), 64).chunk; };
-    p.chunk_tall = chunk_of(cut.tall);
-    p.chunk_flat = chunk_of(cut.flat);
     size_t off = 0;
     p.off_dgen = off;    off = (off + (size_t)R * p.ldd * 4 + 255) / 256 * 256;
-    // room for all partial results of a list, or for sixteen, as many as run at a time
-    p.partial_bytes = std::max(std::min(cut.tall, 16) * tn_partial_bytes(R, p.chunk_tall, 384, 144),
-                               std::min(cut.flat, 16) * tn_partial_bytes(R, p.chunk_flat, 128, 336));
+    // room for the partial results of the launch that has the most
+    const MixerProducts products = mixer_products(d.n_agents * d.embed, d.state_dim);
+    auto room = [&](int count, int rows, int columns) {
+        const EvenParts launches = even_parts(count, kProductsPerLaunch);
+        for (int n : {launches.size(0), launches.size(launches.parts - 1)})
+            if (n > 0) p.partial_bytes = std::max(p.partial_bytes, n * tn_partial_bytes(R, mixer_chunks(R, n).chunk, rows, columns));
+    };
+    room(products.tall, 16 * tall_slices(d.n_agents * d.embed).size(0), kTallColumns + 1);
+    room(products.flat, 128, kFlatColumns + 1);
     p.off_partial = off; off = (off + p.partial_bytes + 255) / 256 * 256;
     p.bytes = off;
     return p;
@@ -1013,10 +1001,11 @@ int marl_mixer_grad(marl_mixer *m, int32_t B, int32_t T, const float *state, con
     std::vector<marl::TnProduct> tall, flat;
     auto matrix = [&](int col0, int rows_total, float *dst_w, float *dst_b) {
         const bool wide = rows_total > 128;
-        const int p_step = wide ? 384 : 128, q_step = wide ? 128 : 320;
-        for (int r0 = 0; r0 < rows_total; r0 += p_step)
+        const int q_step = wide ? marl::kTallColumns : marl::kFlatColumns;
+        const marl::EvenParts slices = wide ? marl::tall_slices(rows_total) : marl::EvenParts{(rows_total + 15) / 16, 1};
+        for (int i = 0; i < slices.parts; ++i)
             for (int k0 = 0; k0 < S; k0 += q_step) {
-                const int P = std::min(p_step, rows_total - r0), Q = std::min(q_step, S - k0);
+                const int r0 = 16 * slices.first(i), P = std::min(16 * slices.size(i), rows_total - r0), Q = std::min(q_step, S - k0);
                 const bool last = k0 + q_step >= S;
                 marl::RowMap ar = plain, br = states;
                 ar.base = dgen + (size_t)(col0 + r0) * elem;
@@ -1034,9 +1023,14 @@ int marl_mixer_grad(marl_mixer *m, int32_t B, int32_t T, const float *state, con
         ar.base = dgen + (size_t)F * elem;
         flat.push_back({ar, states, M + 1, 0, marl::kExtraOnes, 1, 1, 0, 1, gv2, gv2});
     }
-    err = marl::launch_tn_products(m->planes, tall.data(), (int)tall.size(), R, plan.chunk_tall, partial, plan.partial_bytes, stream);
-    if (err == hipSuccess)
-        err = marl::launch_tn_products(m->planes, flat.data(), (int)flat.size(), R, plan.chunk_flat, partial, plan.partial_bytes, stream);
+    for (const std::vector<marl::TnProduct> *list : {&tall, &flat}) {
+        const marl::EvenParts launches = marl::even_parts((int)list->size(), marl::kProductsPerLaunch);
+        for (int i = 0; i < launches.parts && err == hipSuccess; ++i) {
+            const int n = launches.size(i);
+            if (n > 0) err = marl::launch_tn_products(m->planes, list->data() + launches.first(i), n, R, marl::mixer_chunks(R, n).chunk, partial,
+                                                      plan.partial_bytes, stream);
+        }
+    }
     if (err != hipSuccess) return marl::report_device_error(err, "marl_mixer_grad products");
     return MARL_OK;
 }

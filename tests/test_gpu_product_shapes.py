@@ -34,18 +34,14 @@ def test_first_layer_gradient_around_a_tile(N, D, H, dtype):
     net.close()
 
 
-# agents x hidden units: the rows of the largest product; state sizes: its columns, whole slices and one past them
-@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("N,M,S", [(8, 16, 64), (9, 16, 64), (9, 16, 65), (16, 16, 79), (16, 16, 80), (17, 16, 128), (24, 16, 129),
-                                   (25, 16, 48), (2, 64, 176), (3, 64, 177)])
-def test_mixer_gradient_around_a_tile(N, M, S, dtype):
-    """On 155 transitions one switch (the sign of a generated weight, an offset unit) within the forward error of zero is worth
-    more than the cap that the comparison sets on the oracle's ambiguity budget.  The inputs are the first, of twenty, whose
-    budget is within the cap; that is decided by the oracle alone."""
-    cfg = dict(wl.config(0), N=N, S=S, B=5, T=31)
-    dims = (N, M, S)
+def compare_mixer_gradient(dims, dtype, B, T):
+    """One switch (the sign of a generated weight, an offset unit) within the forward error of zero may be worth more than the
+    cap that the comparison sets on the oracle's ambiguity budget, where there are few transitions.  The inputs are the first, of
+    twenty, whose budget is within the cap; that is decided by the oracle alone."""
+    N, M, S = dims
+    cfg = dict(wl.config(0), N=N, S=S, B=B, T=T)
     m = wl.make_mixer_inputs(cfg)
-    e = np.abs(np.random.default_rng([12, N, S]).normal(size=(5, 31))).astype(np.float32) * m["filled"]
+    e = np.abs(np.random.default_rng([12, N, S]).normal(size=(B, T))).astype(np.float32) * m["filled"]
     for seed in range(20):
         w = wl.pack_mixer(dims, {k: np.random.default_rng([seed, i]).uniform(-1, 1, shp) / np.sqrt(max(shp[-1], 1) if len(shp) == 2 else 4)
                                  for i, (k, (_, _, shp)) in enumerate(wl.mixer_slices(*dims).items())})
@@ -53,4 +49,22 @@ def test_mixer_gradient_around_a_tile(N, M, S, dtype):
                                    e.astype(np.float64), switch_band=mixer.SWITCH_BAND[dtype], inputs_as_bf16=dtype == "bf16")
         if all(budget[a:b].max() <= mixer.BUDGET_CAP * np.abs(want[a:b]).max() for a, b, _ in wl.mixer_slices(*dims).values()):
             break
+    else:
+        pytest.fail("no inputs within the budget's cap")
     mixer._compare_mixer_gradient("N%d M%d S%d" % dims, dims, w, dtype, m, e)
+
+
+# agents x hidden units: the rows of the largest product; state sizes: its columns, whole slices and one past them
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("N,M,S", [(8, 16, 64), (9, 16, 64), (9, 16, 65), (16, 16, 79), (16, 16, 80), (17, 16, 128), (24, 16, 129),
+                                   (25, 16, 48), (2, 64, 176), (3, 64, 177)])
+def test_mixer_gradient_around_a_tile(N, M, S, dtype):
+    compare_mixer_gradient((N, M, S), dtype, 5, 31)
+
+
+# Lists of products: rows of one class only if cut into one slice more (528, 784), even slices of unequal blocks (800, 1024); more
+# than sixteen tall products, in two launches and in three of unequal size; seventeen flat ones.  Several chunks of transitions each.
+@pytest.mark.parametrize("N,M,S,dtype", [(33, 16, 129, "fp32"), (49, 16, 100, "bf16"), (25, 32, 128, "bf16"), (32, 32, 132, "bf16"),
+                                         (51, 32, 400, "fp32"), (32, 64, 300, "bf16"), (57, 64, 420, "bf16"), (8, 16, 1000, "bf16")])
+def test_mixer_gradient_of_many_products(N, M, S, dtype):
+    compare_mixer_gradient((N, M, S), dtype, 9, 57)
