@@ -183,8 +183,8 @@ int marl_act_step_indexed(marl_qnet *q, int32_t E, const int32_t *env_index, int
  * handle for intermediate activations, grown (never shrunk) when a call needs
  * more than any earlier call; growing synchronises the device.
  * marl_qnet_reserve_unroll sizes it ahead of time so that later calls up to
- * that size allocate nothing (for handles on the fused path: the room of marl_unroll_td_double,
- * so far as there is memory; their other calls need none).
+ * that size allocate nothing (it does nothing for handles on the fused path, which need none but
+ * for marl_unroll_td_double, whose first call of a size makes its own).
  */
 int marl_unroll_td(marl_qnet *online, marl_qnet *target, int32_t B, int32_t T,
                    const float *obs, const uint8_t *avail, const int32_t *actions,
@@ -258,8 +258,8 @@ int marl_unroll_td_indexed(marl_qnet *online, marl_qnet *target, int32_t pool_ep
  * `online` and `target` may be the same handle, and the result then equals marl_unroll_td's.
  * Where the batch leaves compute units free, two handles on the fused16 kernels run side by side,
  * the target network's Q values kept until the choice is made: in a buffer of `online`'s of about
- * 4 B (T+1) N A bytes, 256 MB at most, allocated by marl_qnet_reserve_unroll or by the first call
- * that needs it.  Under stream capture, beyond that size, without memory, and in the tile32 family
+ * 4 B (T+1) N A bytes, 256 MB at most, allocated by the first call that needs it (growing it waits
+ * for the last call that used it) and kept until marl_destroy.  Under stream capture, beyond that size, without memory, and in the tile32 family
  * (but for 128 hidden units in fp32, which have room in their scratch) the networks run one after
  * the other.  The choice of a* is made in
  * fp32 on the library's Q values: where two available actions are within rounding of each other

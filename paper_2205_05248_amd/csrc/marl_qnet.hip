@@ -428,11 +428,7 @@ int marl_qnet_reserve_unroll(marl_qnet *q, int32_t B, int32_t T)
         return MARL_ERR_BAD_DIM;
     DeviceGuard guard(q->desc.device);
     if (!guard.ok) return device_fail(hipErrorInvalidDevice, "hipSetDevice");
-    if (takes_fused_path(q, true)) {                       // room for a double-estimator call; without it that call is slower, no more
-        std::lock_guard<std::mutex> hold(q->next_q_lock);
-        if (B > 0 && side_by_side(q, B)) (void)ensure_next_q(q, marl::next_q_bytes(q->net, B, T));
-        return MARL_OK;
-    }
+    if (takes_fused_path(q, true)) return MARL_OK;         // (the double-estimator call makes room itself: most learners make no such call)
     return ensure_scratch(q, marl::unroll_scratch_bytes(q->net, B, T));
 }
 

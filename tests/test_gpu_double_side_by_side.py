@@ -104,3 +104,32 @@ def test_one_handle_on_two_streams():
             for k in NAMES:
                 assert torch.equal(out[k], want[k]), k
     net.close(); target.close()
+
+
+def test_room_is_made_by_the_call_that_needs_it_and_given_back():
+    """Reserving for the unroll, and unrolling, take no memory for a call that may never come; 64 episodes of the scale-up take 66 MB
+    for the double estimator, once."""
+    cfg = dict(wl.config(4), B=64, T=200)
+    N, D, A, H = wl.dims(cfg)
+    u = wl.make_unroll_inputs(cfg)
+    d, out = pu.to_dev(u, KEYS), blank(cfg, 64)
+    need = 4 * 64 * 201 * N * A
+    assert 60 << 20 <= need <= 256 << 20
+    net, _ = make_net(cfg)
+    target, _ = make_net(cfg, 1)
+    net.unroll_td(target, *(d[k] for k in KEYS), u["gamma"], *(out[k] for k in NAMES[:3]), out["q_all"])      # (whatever a first launch takes)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    before = free()
+    for handle in (net.handle, target.handle):
+        binding.marl_qnet_reserve_unroll(handle, 64, 200)
+    net.unroll_td(target, *(d[k] for k in KEYS), u["gamma"], *(out[k] for k in NAMES[:3]), out["q_all"])
+    assert before - free() < need // 2
+    for _ in range(2):
+        call(net, target, d, u["gamma"], out)
+        assert need // 2 < before - free() < 2 * need
+    net.close(); target.close()
+    assert before - free() < need // 2
