@@ -1,6 +1,7 @@
 """The double-estimator call whose two networks run side by side: the same bits as the two launches one after the other,
 which is what a captured call runs, over row counts around a tile (16) and a record (32), the fewest and most actions
-and all networks of the fused kernels; and calls of one handle on two streams at once."""
+and all networks of the fused kernels; which of the two ways a call goes, by the room that one of them takes; and calls of one
+handle on two streams at once."""
 import numpy as np
 import pytest
 import torch
@@ -82,6 +83,37 @@ def test_side_by_side_gives_the_bits_of_one_after_the_other(shape):
     net.close(); target.close()
 
 
+def test_room_grows_while_an_earlier_call_is_in_flight():
+    """A small batch on one stream, then one that needs more room on another, with nothing waited for in between."""
+    cfg = dict(wl.config(1), T=60)
+    N, D, A, H = wl.dims(cfg)
+    streams = torch.cuda.Stream(), torch.cuda.Stream()
+    sizes = (6, 40)
+    assert all(2 * ((B * N + 15) // 16) <= 256 for B in sizes)              # side by side, either one
+    (first, _), (target, _) = make_net(cfg), make_net(cfg, 1)
+    batches = []
+    for s, B in enumerate(sizes):
+        u = wl.make_unroll_inputs(cfg, B=B, T=60, stream=s)
+        d, want = pu.to_dev(u, KEYS), blank(cfg, B)
+        call(first, target, d, u["gamma"], want)
+        batches.append((u, d, want))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        net, _ = make_net(cfg)                                              # room for nothing yet
+        got = [blank(cfg, B) for B in sizes] + [blank(cfg, sizes[0])]
+        torch.cuda.synchronize()
+        for turn, out in enumerate(got):
+            u, d, _ = batches[turn % 2]
+            with torch.cuda.stream(streams[turn % 2]):
+                call(net, target, d, u["gamma"], out)
+        torch.cuda.synchronize()
+        for turn, out in enumerate(got):
+            for k in NAMES:
+                assert torch.equal(out[k], batches[turn % 2][2][k]), (turn, k)
+        net.close()
+    first.close(); target.close()
+
+
 def test_one_handle_on_two_streams():
     """Batches of different sizes enqueued in turn on two streams with nothing waited for in between."""
     cfg = dict(wl.config(1), T=30)
@@ -106,30 +138,45 @@ def test_one_handle_on_two_streams():
     net.close(); target.close()
 
 
-def test_room_is_made_by_the_call_that_needs_it_and_given_back():
-    """Reserving for the unroll, and unrolling, take no memory for a call that may never come; 64 episodes of the scale-up take 66 MB
-    for the double estimator, once."""
-    cfg = dict(wl.config(4), B=64, T=200)
-    N, D, A, H = wl.dims(cfg)
+# B, T, N, D, A, H, dtype, whether its networks run side by side
+ROOMS = [(64, 200, 32, 30, 40, 128, "bf16", True),        # 128 tiles of 16 rows: both networks fill the chip once
+         (100, 200, 20, 30, 40, 64, "bf16", True),        # 125
+         (100, 200, 20, 30, 40, 64, "fp32", True),
+         (128, 200, 20, 30, 40, 64, "bf16", False)]       # 160: twice the chip either way
+
+
+@pytest.mark.parametrize("shape", ROOMS, ids=lambda s: "B%d_T%d_N%d_D%d_A%d_H%d_%s_%s" % s)
+def test_room_is_made_by_the_call_that_needs_it_and_given_back(shape):
+    """The target's Q values, over 60 MB here, have their room made in the way through a call that runs both networks side by side,
+    and nowhere else: not by reserving, by the plain unroll, by a captured call, or where the networks run one after the other."""
+    B, T, N, D, A, H, dtype, side_by_side = shape
+    cfg = dict(wl.config(0), B=B, T=T, N=N, D=D, A=A, H=H, dtype=dtype)
     u = wl.make_unroll_inputs(cfg)
-    d, out = pu.to_dev(u, KEYS), blank(cfg, 64)
-    need = 4 * 64 * 201 * N * A
+    d, out = pu.to_dev(u, KEYS), blank(cfg, B)
+    need = 4 * B * (T + 1) * N * A
     assert 60 << 20 <= need <= 256 << 20
-    net, _ = make_net(cfg)
-    target, _ = make_net(cfg, 1)
-    net.unroll_td(target, *(d[k] for k in KEYS), u["gamma"], *(out[k] for k in NAMES[:3]), out["q_all"])      # (whatever a first launch takes)
+    plain = lambda: net.unroll_td(target, *(d[k] for k in KEYS), u["gamma"], *(out[k] for k in NAMES[:3]), out["q_all"])
+    stream = torch.cuda.Stream()
+
+    def captured():
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            call(net, target, d, u["gamma"], out)
 
     def free():
         torch.cuda.synchronize()
         return torch.cuda.mem_get_info()[0]
 
+    net, _ = make_net(cfg)
+    target, _ = make_net(cfg, 1)
+    plain(); captured()                                    # whatever first launches and a first capture take
     before = free()
     for handle in (net.handle, target.handle):
-        binding.marl_qnet_reserve_unroll(handle, 64, 200)
-    net.unroll_td(target, *(d[k] for k in KEYS), u["gamma"], *(out[k] for k in NAMES[:3]), out["q_all"])
+        binding.marl_qnet_reserve_unroll(handle, B, T)
+    plain(); captured()
     assert before - free() < need // 2
     for _ in range(2):
         call(net, target, d, u["gamma"], out)
-        assert need // 2 < before - free() < 2 * need
+        assert (need // 2 < before - free() < 2 * need) if side_by_side else before - free() < need // 2
     net.close(); target.close()
     assert before - free() < need // 2
