@@ -465,20 +465,22 @@ template <int KN> struct ObsRegsK { float v[KN][8]; };
 
 template <int P, int KN, bool SHORT> struct ObsStageK {
     static constexpr bool kRounded = P == 1 && KN > 4;                   // KN may be one more than the network's own k-steps
-    static constexpr int kInside = SHORT ? 0 : KN - (kRounded ? 2 : 1);  // k-steps that end inside every such row
     static constexpr bool kFills = P == 1 && !SHORT;
-    int q8, off[SHORT ? 8 : KN - kInside];           // from the lane's first observation on: of an element (SHORT), of the last k-steps
+    // k-steps that end inside every such row, read at constant offsets: their registers are what the fill needs
+    static constexpr int kInside = kFills ? KN - (kRounded ? 2 : 1) : 0;
+    int q8, off[SHORT ? 8 : KN - kInside];           // kFills: the lane's first observation; from there on, of an element (SHORT) or the other k-steps
     uint32_t own[kFills ? 4 : 1];                    // in the network's last k-step: ones over the elements that the lane holds once
     bool past;                                       // the last k-step lies past the network's own
 
     __device__ __forceinline__ void init(int D, int q4)
     {
-        q8 = 8 * q4;
+        const int first = 8 * q4;
+        q8 = kFills ? first : 0;
 #pragma unroll
-        for (int i = 0; i < (SHORT ? 8 : KN - kInside); ++i) off[i] = (SHORT ? min(q8 + i, D - 1) : min(32 * (kInside + i) + q8, D - 8)) - q8;
+        for (int i = 0; i < (SHORT ? 8 : KN - kInside); ++i) off[i] = (SHORT ? min(first + i, D - 1) : min(32 * (kInside + i) + first, D - 8)) - q8;
         past = kRounded && 32 * (KN - 1) >= D;
         if constexpr (kFills) {
-            const int from = 32 * (past ? KN - 2 : KN - 1) + q8, twice = from - min(from, D - 8);      // the first so many
+            const int from = 32 * (past ? KN - 2 : KN - 1) + first, twice = from - min(from, D - 8);      // the first so many
 #pragma unroll
             for (int i = 0; i < 4; ++i) own[i] = twice <= 2 * i ? 0xFFFFFFFFu : twice == 2 * i + 1 ? 0xFFFF0000u : 0u;
         }
@@ -486,7 +488,7 @@ template <int P, int KN, bool SHORT> struct ObsStageK {
 
     __device__ __forceinline__ void load(ObsRegsK<KN> &r, const float *row) const
     {
-        const float *const at = row + q8;
+        const float *const at = kFills ? row + q8 : row;
         if constexpr (SHORT) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) r.v[0][i] = at[off[i]];
@@ -517,21 +519,25 @@ template <int P, int KN, bool SHORT> struct ObsStageK {
     // dst = this lane's slot in the item's first fragment
     __device__ __forceinline__ void write(const ObsRegsK<KN> &r, bf16x8 *dst) const
     {
-        Frag<P> f[KN];
-#pragma unroll
-        for (int k = 0; k < KN; ++k) f[k] = to_frag<P>(r.v[k]);
         if constexpr (kFills) {
-            if (kRounded && past) {
-                f[kRounded ? KN - 2 : 0].hi = filled(f[kRounded ? KN - 2 : 0].hi);
-                f[KN - 1].hi = bf16x8{};
-            } else {
-                f[KN - 1].hi = filled(f[KN - 1].hi);
-            }
-        }
+            bf16x8 f[KN];
 #pragma unroll
-        for (int k = 0; k < KN; ++k) {
-            dst[(k * P) * 64] = f[k].hi;
-            if constexpr (P == 2) dst[(k * P + 1) * 64] = f[k].lo;
+            for (int k = 0; k < KN; ++k) f[k] = to_frag<1>(r.v[k]).hi;
+            if (kRounded && past) {
+                f[kRounded ? KN - 2 : 0] = filled(f[kRounded ? KN - 2 : 0]);
+                f[KN - 1] = bf16x8{};
+            } else {
+                f[KN - 1] = filled(f[KN - 1]);
+            }
+#pragma unroll
+            for (int k = 0; k < KN; ++k) dst[k * 64] = f[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < KN; ++k) {
+                const Frag<P> f = to_frag<P>(r.v[k]);
+                dst[(k * P) * 64] = f.hi;
+                if constexpr (P == 2) dst[(k * P + 1) * 64] = f.lo;
+            }
         }
     }
 };
