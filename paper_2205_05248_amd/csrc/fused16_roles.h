@@ -251,10 +251,16 @@ template <int H, int P> struct Fc1Wave {
                 if (ks < ks1) settle(w1[j][ks]);
     }
 
-    // The same for step_k<KN>: the weights of a k-step past the network's own are zero, and those of the last eight
-    // observations are where ObsStageK puts these.  Only a k-step that has them, or lies past them, is moved: with all the
-    // k-steps that a wave has room for loaded and moved, the first slot waited for 1700 instructions of this (2 k-steps at 128
-    // bf16 units, 100 slots: 104.6 us, now 100.0).
+    // The same for step_k<KN>: weights where ObsStageK puts the observations.  A lane whose eight would pass the row's end holds
+    // the row's last eight: those that are its own at their weights, those that another lane has too (all of them in a k-step
+    // past the network's own) at next to nothing.  Not at zero: 0 x inf is NaN, which the ReLU makes 0, where the row's x is
+    // infinite (0 where the weight is negative).  The smallest normal number of the weight's sign, 2^-126 (but 0 for a weight of
+    // 0, whose sums stay 0), keeps an infinity what it is and is lost in the sum of finite values.  (With two planes zero does: the remainder of an infinity is NaN, and
+    // with it every x of the row.)  Filling those places in the loader instead, with a value of the row that counts anyway, made
+    // the loader's step longer, and so every slot: 24 episodes x 60 slots x 5 agents, 64 units, 33 observations 32.8 -> 33.6 us, 150
+    // observations 37.4 -> 46.0.
+    // Only a k-step that may have such lanes is looked at: with all the k-steps that a wave has room for loaded and moved, the
+    // first slot waited for 1700 instructions of this (2 k-steps at 128 bf16 units, 100 slots: 104.6 us, now 100.0).
     template <int KN> __device__ __forceinline__ void load_k(const NetFrags &net, int f, int lane)
     {
         const int D = net.D, ks1 = (D + 31) / 32;                       // KN or KN - 1
@@ -263,13 +269,57 @@ template <int H, int P> struct Fc1Wave {
 #pragma unroll
             for (int ks = 0; ks < KN; ++ks)
                 w1[j][ks] = load_wfrag<P>(net.w1_16 + ((size_t)((f * NBF + j) * ks1 + min(ks, ks1 - 1)) * P) * 64 + lane);
+        if constexpr (P == 2) {
 #pragma unroll
-        for (int ks = KN < 2 ? 0 : KN - 2; ks < KN; ++ks) {
-            const int shift = ks < ks1 ? (D >= 8 ? min(max(32 * ks + 8 * (lane >> 4) - (D - 8), 0), 8) : 0) : 8;
+            for (int ks = KN < 2 ? 0 : KN - 2; ks < KN; ++ks) {
+                const int shift = ks < ks1 ? (D >= 8 ? min(max(32 * ks + 8 * (lane >> 4) - (D - 8), 0), 8) : 0) : 8;
 #pragma unroll
-            for (int j = 0; j < NBF; ++j) {
-                w1[j][ks].hi = shift_up(w1[j][ks].hi, shift);
-                if constexpr (P == 2) w1[j][ks].lo = shift_up(w1[j][ks].lo, shift);
+                for (int j = 0; j < NBF; ++j) {
+                    w1[j][ks].hi = shift_up(w1[j][ks].hi, shift);
+                    w1[j][ks].lo = shift_up(w1[j][ks].lo, shift);
+                }
+            }
+        } else {
+            // the weights of the row's last eight, from the five pairs that they lie in (a lane's eight are four pairs)
+            uint32_t pair[NBF][5];
+            const char *const block = reinterpret_cast<const char *>(net.w1_16 + (size_t)(f * NBF) * ks1 * 64);
+            const uint32_t block_bytes = (uint32_t)ks1 * 1024;
+            const int first_pair = max(D - 8, 0) / 2;
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                const uint32_t at = (uint32_t)min(first_pair + i, 16 * ks1 - 1);
+                const uint32_t offset = (at >> 2) * 256 + (at & 3) * 4 + 16 * (lane & 15);      // (an eight of the row: 256 bytes of its block)
+#pragma unroll
+                for (int j = 0; j < NBF; ++j) pair[j][i] = *reinterpret_cast<const uint32_t *>(block + j * block_bytes + offset);
+            }
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+            // of the eight that a lane has in the network's last k-step, the first so many are another lane's too; past that k-step, all
+            const int from = 32 * (ks1 - 1) + 8 * (lane >> 4), twice = D >= 8 ? from - min(from, D - 8) : 0;
+            const bool past = KN > 4 && ks1 < KN;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t own = twice <= 2 * i ? 0xFFFFFFFFu : twice == 2 * i + 1 ? 0xFFFF0000u : 0u;
+#pragma unroll
+                for (int j = 0; j < NBF; ++j) {
+                    const uint32_t last = __builtin_amdgcn_alignbit(pair[j][i + 1], pair[j][i], 16 * (D & 1));
+                    const uint32_t tiny = (last & 0x80008000u) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, last & 0x7FFF7FFFu), u16x2{0x0080, 0x0080}));
+                    const uint32_t mixed = (last & own) | (tiny & ~own);
+                    auto put = [&](bf16x8 &v, uint32_t word) {
+                        u32x4 w = __builtin_bit_cast(u32x4, v);
+                        w[i] = word;
+                        v = __builtin_bit_cast(bf16x8, w);
+                    };
+                    auto has = [&](const bf16x8 &v) { return __builtin_bit_cast(u32x4, v)[i]; };
+                    bf16x8 &end = w1[j][KN - 1].hi, &before = w1[j][KN > 4 ? KN - 2 : 0].hi;
+                    if constexpr (KN > 4) {
+                        const uint32_t at_before = has(before), at_end = has(end);
+                        put(before, past && twice > 0 ? mixed : at_before);
+                        put(end, past ? tiny : twice > 0 ? mixed : at_end);
+                    } else {
+                        put(end, twice > 0 ? mixed : has(end));
+                    }
+                }
             }
         }
 #pragma unroll
@@ -453,91 +503,46 @@ template <int H, int P> struct ObsStage {
 };
 
 // The same with the k-steps (KN: obs_k_steps) known at compile time, for the unroll's loader.  Where a lane's eight floats would
-// pass the row's end it holds the row's last eight instead, and the weights are shifted to match (Fc1Wave::load_k), so that
+// pass the row's end it holds the row's last eight instead, and the weights match (Fc1Wave::load_k), so that
 // every load is a wide one.  Rows of less than eight floats (SHORT) are fetched element by element, positions past the end from the
 // last one, whose weights are zero.  (In the decision step, whose loader and fc1 waves have more to address per item, this form
 // was slower: 2048 x 32 rows of 300 observations 45.0 -> 58.0 us.)
-// What a lane holds twice meets zero weights the second time, which is nothing added unless it is infinite (or rounds to infinity):
-// 0 x inf is NaN.  With one plane `write` therefore puts the row's last value in its place, which is what the decision step's
-// loader has there, and zeros where a k-step lies past the network's own: the same rows give the same x in either.  With two
-// planes the remainder of an infinity is NaN already, and so is every x of its row, whatever its weight.
 template <int KN> struct ObsRegsK { float v[KN][8]; };
 
 template <int P, int KN, bool SHORT> struct ObsStageK {
-    static constexpr bool kRounded = P == 1 && KN > 4;                   // KN may be one more than the network's own k-steps
-    static constexpr bool kFills = P == 1 && !SHORT;
-    // k-steps that end inside every such row, read at constant offsets: their registers are what the fill needs
-    static constexpr int kInside = kFills ? KN - (kRounded ? 2 : 1) : 0;
-    int q8, off[SHORT ? 8 : KN - kInside];           // kFills: the lane's first observation; from there on, of an element (SHORT) or the other k-steps
-    uint32_t own[kFills ? 4 : 1];                    // in the network's last k-step: ones over the elements that the lane holds once
-    bool past;                                       // the last k-step lies past the network's own
+    int off[SHORT ? 8 : KN];
 
     __device__ __forceinline__ void init(int D, int q4)
     {
-        const int first = 8 * q4;
-        q8 = kFills ? first : 0;
 #pragma unroll
-        for (int i = 0; i < (SHORT ? 8 : KN - kInside); ++i) off[i] = (SHORT ? min(first + i, D - 1) : min(32 * (kInside + i) + first, D - 8)) - q8;
-        past = kRounded && 32 * (KN - 1) >= D;
-        if constexpr (kFills) {
-            const int from = 32 * (past ? KN - 2 : KN - 1) + first, twice = from - min(from, D - 8);      // the first so many
-#pragma unroll
-            for (int i = 0; i < 4; ++i) own[i] = twice <= 2 * i ? 0xFFFFFFFFu : twice == 2 * i + 1 ? 0xFFFF0000u : 0u;
-        }
+        for (int i = 0; i < (SHORT ? 8 : KN); ++i) off[i] = SHORT ? min(8 * q4 + i, D - 1) : min(32 * i + 8 * q4, D - 8);
     }
 
     __device__ __forceinline__ void load(ObsRegsK<KN> &r, const float *row) const
     {
-        const float *const at = kFills ? row + q8 : row;
         if constexpr (SHORT) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) r.v[0][i] = at[off[i]];
+            for (int i = 0; i < 8; ++i) r.v[0][i] = row[off[i]];
         } else {
 #pragma unroll
             for (int k = 0; k < KN; ++k) {
-                const float *const from = k < kInside ? at + 32 * k : at + off[max(k - kInside, 0)];
                 f32x4 lo4, hi4;
-                __builtin_memcpy(&lo4, from, 16);
-                __builtin_memcpy(&hi4, from + 4, 16);
+                __builtin_memcpy(&lo4, row + off[k], 16);
+                __builtin_memcpy(&hi4, row + off[k] + 4, 16);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { r.v[k][i] = lo4[i]; r.v[k][4 + i] = hi4[i]; }
             }
         }
     }
 
-    // The row's last value in place of what the lane holds twice.
-    __device__ __forceinline__ bf16x8 filled(const bf16x8 &v) const
-    {
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        u32x4 word = __builtin_bit_cast(u32x4, v);
-        const uint32_t last = (word[3] >> 16) * 0x10001u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) word[i] = (word[i] & own[i]) | (last & ~own[i]);
-        return __builtin_bit_cast(bf16x8, word);
-    }
-
     // dst = this lane's slot in the item's first fragment
     __device__ __forceinline__ void write(const ObsRegsK<KN> &r, bf16x8 *dst) const
     {
-        if constexpr (kFills) {
-            bf16x8 f[KN];
 #pragma unroll
-            for (int k = 0; k < KN; ++k) f[k] = to_frag<1>(r.v[k]).hi;
-            if (kRounded && past) {
-                f[kRounded ? KN - 2 : 0] = filled(f[kRounded ? KN - 2 : 0]);
-                f[KN - 1] = bf16x8{};
-            } else {
-                f[KN - 1] = filled(f[KN - 1]);
-            }
-#pragma unroll
-            for (int k = 0; k < KN; ++k) dst[k * 64] = f[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < KN; ++k) {
-                const Frag<P> f = to_frag<P>(r.v[k]);
-                dst[(k * P) * 64] = f.hi;
-                if constexpr (P == 2) dst[(k * P + 1) * 64] = f.lo;
-            }
+        for (int k = 0; k < KN; ++k) {
+            const Frag<P> f = to_frag<P>(r.v[k]);
+            dst[(k * P) * 64] = f.hi;
+            if constexpr (P == 2) dst[(k * P + 1) * 64] = f.lo;
         }
     }
 };
