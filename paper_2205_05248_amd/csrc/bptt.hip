@@ -914,7 +914,7 @@ __global__ __launch_bounds__(kTnThreads, 2) void tn_gemm_wide_kernel(const TnGem
     // result is tall: a fragment of B then feeds three products.  Where it is 128 rows, all eight row blocks and every
     // eighth column block (w, w + 8) of up to 176 columns; of up to 336 columns, half the row blocks and every fourth column
     // block: 10 fragments per step for 24 products, and 16 registers less of them than with all row blocks and every eighth
-    // column block, which spilled 25.
+    // column block, which spilled 25 (this one spills one).
     constexpr bool kSplitColumns = PBW == 1, kHalves = kSplitColumns && QBN > 16;
     constexpr int kRB = kHalves ? 4 : kSplitColumns ? 8 : PBW, kCB = kHalves ? (QBN + 3) / 4 : kSplitColumns ? (QBN + 7) / 8 : QBN;
     auto row_block = [&](int k) { return kHalves ? 4 * (w >> 2) + k : kSplitColumns ? k : w + 8 * k; };

@@ -36,7 +36,7 @@
 // trip to memory in each step until its loads were straight-line code and the flags it fetches were put together where
 // they are staged; with that and W_ih in registers for 64 units, 32 episodes x 120 slots x 8 agents 103.3 -> 96.7 us,
 // 64 x 200 x 32 with 128 units 279 -> 275 us, keeping activations 370 -> 335 us.  (With the target half of the TD inputs put
-// together only where it is read, and the first layer's weights prepared per k-step: 91.6 and 259 us.)
+// together only where it is read, and the first layer's weights prepared per k-step: 92 and 256 to 268 us, box to box.)
 #include <hip/hip_runtime.h>
 
 #pragma once

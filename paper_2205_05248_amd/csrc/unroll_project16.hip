@@ -1,11 +1,11 @@
 // Input projection of the two-kernel unroll for 128 hidden units in fp32: x = ReLU(W1 o + b1[agent]) and the gate inputs
 // W_ih x + b of every (episode, slot, agent), into the scratch buffer that the recurrence reads (unroll_recur16.hip).
 //
-// The rows do not depend on each other; what bounds it is how often the weights (384 KB with 300 observations, two planes)
+// The rows do not depend on each other; what bounds it is how often the weights (352 KB with 300 observations, two planes)
 // travel.  front_kernel (kernels.hip) streams them through LDS once per 128 rows, a barrier per 24 KB: 27 us for the 21,655
 // rows of 61 episodes x 70 slots x 5 agents, whatever their width.  Here they stay in registers: eight waves, each with its block of
-// 16 units of both layers (80 registers of W1 at most, 96 of W_ih), one workgroup per compute unit and network, which
-// takes a run of items (16 rows of one slot).  One LDS-only barrier per item; in the step of item i a wave
+// 16 units of both layers (80 registers of W1 at most, 96 of W_ih), one workgroup per compute unit, the networks taking
+// turns, which takes a run of items (16 rows of one slot).  One LDS-only barrier per item; in the step of item i a wave
 //   puts its part of item i+1's observations down as operand fragments and asks for its part of item i+2's,
 //   forms its block of x of item i, and its block of the gate inputs of item i-1.
 // Every global access is unconditional (the ends load an item again), so that the waits count exactly.

@@ -7,8 +7,13 @@
 // what tiles of 32 rows with 32 hidden units per wave asked for: that form spilled.  A wave reads its own gate inputs
 // from memory, a slot ahead, and adds them after the products, so that the loads have a slot and the products to
 // arrive; a wave of its own touches the lines a few slots earlier, so that they come from L2.  No LDS for them, and
-// one LDS-only barrier per slot.  Double-estimator targets of 61 episodes x 70 slots x 5 agents (both networks in turn, two
-// projections of 27 us included): 543 -> 209 us, 3.4 -> 1.1 us a slot.
+// one LDS-only barrier per slot.  Double-estimator targets of 61 episodes x 70 slots x 5 agents: 543 us with the form on 32 rows, 209
+// with this one (one network after the other, two projections of 27 us included), 118 with both networks in one launch,
+// of which the recurrence is 91, 1.3 us a slot.
+//
+// Eleven waves leave a wave 168 registers, too few for the epilogue of 49 to 64 actions: 10 to 13 registers of its wave spill,
+// 39 and 56 where it also keeps the target's Q values (with 33 to 48 actions 2 and 4 there).  The case above with 48 / 49 actions:
+// 150 / 218 us, and 171 / 350 with q_all; 629 / 628 and 729 / 733 with the form on 32 rows.
 //
 // Wave roles, in the step of slot s:  0..7 the recurrence of slot s;  8 fc2 and the TD step of slot s-1;  9 the
 // per-slot inputs of the TD step of slot s;  10 the touches of slot s + 1 + kTouchAhead.
