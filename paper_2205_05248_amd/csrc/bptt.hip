@@ -4,16 +4,14 @@
 //   unroll_fused_kernel<.., kTdSave>   (unroll_fused.hip) forward pass of the online network that keeps x and
 //                                      h of every slot in global memory, [B, T+1, N, H]: h in fp32, x in fp32
 //                                      or, for a bf16 network, in bf16 (what every reader rounds it to)
-//   bptt_back_kernel                   one workgroup per 16 (episode, agent) rows walks the slots backwards.
+//   bptt_back_roles_kernel             one workgroup per 16 (episode, agent) rows walks the slots backwards.
 //                                      Per slot it recomputes the gates from x_t and h_{t-1} (two MFMA
 //                                      products, as the forward pass), forms the adjoints of the four gate
-//                                      pre-activations, and carries dL/dh back through W_hh^T; W_ih^T gives
-//                                      the adjoint of x and, through the ReLU, of fc1's pre-activation.  All
-//                                      four GRU matrices stay on chip: W_hh, W_hh^T and W_ih^T as operand
-//                                      fragments in registers, W_ih in LDS.  The adjoints go to global memory.
-//                                      128 hidden units, bf16.
-//   bptt_back_split_kernel             the same for 64 hidden units, fp32 and bf16: the recurrence's chain and
-//                                      everything that hangs on nothing behind it on different waves
+//                                      pre-activations, and carries dL/dh back through W_hh^T.  The adjoints
+//                                      go to global memory.  The recurrence's chain and everything that hangs
+//                                      on nothing behind it are on different waves.  128 hidden units, bf16.
+//   bptt_back_split_kernel             the same for 64 hidden units, fp32 and bf16; here W_ih^T and, through the
+//                                      ReLU, the adjoint of fc1's pre-activation are part of it
 //   tn_gemm_kernel                     the weight gradients are sums over all (row, slot) samples of outer
 //                                      products adjoint x activation: C[p][q] = sum_m A[m][p] B[m][q], four
 //                                      times (W_ih, W_hh, W1, W2).  The samples are split into chunks, one
@@ -26,6 +24,8 @@
 //   tn_gemm_wide_kernel                the same products for a bf16 network: both operands are fetched 16 bytes
 //                                      at a time and staged as they lie in memory; the transposing LDS read
 //                                      turns the staged rows into fragments.
+//   gru_products_kernel                the products of W_ih and W_hh of 128 units, bf16, and, from the same read
+//                                      of the adjoints, the adjoint of fc1's pre-activation.
 //   tn_reduce_kernel                   adds the chunks' partial sums in a fixed order and writes the result
 //                                      into the packed gradient vector.
 // A batch with fewer row tiles than compute units leaves most of the chip idle while the reverse recurrence walks the
@@ -54,7 +54,8 @@ struct BpttArgs {
     const void *x_all;           // [B, T+1, N, H]   x of slot s; fp32, or bf16 for a one-plane network
     // The adjoints, fp32 for fp32 networks and bf16 for bf16 networks (whose products round them to bf16 anyway:
     // stored rounded, they cost half the traffic to write here and to read in the weight-gradient products)
-    void *da;                    // [B, T, N, 4H]   adjoints of the gate pre-activations: n (input side), r, z, n (hidden side)
+    void *da;                    // [B, T, N, 4H]   adjoints of the gate pre-activations: n (input side), r, z, n (hidden side);
+                                 //                 128 units: a gate's units in the order of an operand's k-steps
     void *dpre1;                 // [B, T, N, H]    adjoint of fc1's pre-activation
     void *dq;                    // [B, T, N, a16]  adjoint of Q, dense (one non-zero per row)
     // The launch walks slots t_end - 1 .. t_begin.  One launch takes all of them (0, T); two take the later and
@@ -103,187 +104,299 @@ __device__ __forceinline__ void store_adjoints(const f32x4 &v, const __amdgpu_bu
     }
 }
 
-// 128 hidden units, one plane (two planes do not fit on chip).  Eight waves, two per SIMD, so that one wave's waits are
-// another's work; wave w owns block w of sixteen units.
-struct BpttBack {
-    using Sh = Fused16<128, 1>;
-    static constexpr int H = 128, P = 1, NW = 8, KS = Sh::KS, FBK = Sh::FBK;
-    static_assert(FBK == NW, "one block of hidden units per wave");
-    // LDS: W_ih, one buffer of h and x fragments and the gate biases where the forward kernel has them;
-    // the adjoint fragments (r, z, n: 3 KS k-steps; n hidden side: KS) where it keeps the observations
-    static constexpr int oDa = Sh::oObs, oDhn = oDa + 3 * KS * Sh::kFrag, kBytes = oDhn + KS * Sh::kFrag;
+// 128 hidden units, one plane (two planes do not fit on chip), cut into two roles.  Only dL/dh_t -> adjoints -> dL/dh_{t-1}
+// is a chain; the gates of a slot hang on nothing behind them.  Twelve waves, three per SIMD, 168 registers each: in the step
+// of slot t
+//
+//   gate waves 0..7    (16 units each, W_hh and W_ih in registers) the gates of slot t-1 -> five factors per unit, in LDS; the
+//                      adjoint of Q; x and h of slot t-2 to LDS as operand, the loads of slot t-3
+//   chain waves 8..11  (32 units each, W_hh^T in registers) dL/dh_t = carry + W_hh^T adjoints(t+1), then slot t's adjoints from
+//                      its factors, to LDS as operand and to memory; nothing that they wait for comes from memory
+//
+// and ONE barrier per slot.  Every LDS buffer is double-buffered on the parity of its slot: written in one step, read in the
+// next, written again only in the one after.  The adjoint of fc1's pre-activation, which nothing in the chain hangs on either,
+// is formed from the stored adjoints where the W_ih product reads them (gru_products_kernel): its weights have no room here.
+//
+// What bounds it: instruction issue on the SIMDs (265 vector and 72 matrix instructions each per slot) and the address unit,
+// 40 accesses to memory per slot.  A hundred slots of 64 episodes x 32 agents, kernel trace: one role of eight waves with two
+// barriers a slot, which formed that adjoint too, 249 us; this with the chain's stores half as wide, and the rows' scalars read
+// by every gate wave 192; the adjoints stored as operands lie, 16 bytes a lane, and the scalars read by the chain 160.  The
+// gates' products a slot ahead of their factors, so that one wave's vector instructions meet another's matrix instructions:
+// 206 before those two changes, more registers than there are.  Both roles' registers are full: what is asked for is asked for
+// little by little (sched_barrier), or the weights spill.
+struct BpttRoles {
+    static constexpr int H = 128, KS = H / 32, FBK = H / 16, kFrag = 1024, kGate = FBK, kChain = KS, kThreads = 64 * (kGate + kChain);
+    static constexpr int kFactors = 5;
+    static constexpr int oH = 0, oX = oH + 2 * KS * kFrag, oDa = oX + 2 * KS * kFrag, kDaBytes = 3 * KS * kFrag;      // r, z, n hidden side
+    static constexpr int oFac = oDa + 2 * kDaBytes, kFacBytes = kFactors * FBK * 1024;
+    static constexpr int oBias = oFac + 2 * kFacBytes;             // biases r, z, n input side, n hidden side
+    static constexpr int oHf = oBias + 4 * H * 4, kHfBytes = FBK * 1024;              // h in fp32, for the blend
+    // W2, whose row of the chosen action the chain adds: bf16 (what the table holds exactly), rows 32 bytes past a multiple of 256
+    static constexpr int oW2 = oHf + 2 * kHfBytes, kW2Pitch = 2 * H + 32;
+    static constexpr int lds_bytes(int A) { return oW2 + A * kW2Pitch; }
 };
 
-__global__ __launch_bounds__(64 * BpttBack::NW, BpttBack::NW / 4) void bptt_back_kernel(BpttArgs a)
+__global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) void bptt_back_roles_kernel(BpttArgs a)
 {
-    using Bs = BpttBack;
-    using Sh = Bs::Sh;
-    constexpr int H = Bs::H, P = Bs::P, KS = Bs::KS, FBK = Bs::FBK;
+    using Bs = BpttRoles;
+    constexpr int H = Bs::H, KS = Bs::KS, FBK = Bs::FBK, kFrag = Bs::kFrag;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    typedef bf16x8 (*FragBuf)[P][64];
-    const FragBuf hf = reinterpret_cast<FragBuf>(lds + Sh::oH), xf = reinterpret_cast<FragBuf>(lds + Sh::oX);
-    const FragBuf daf = reinterpret_cast<FragBuf>(lds + Bs::oDa), dhf = reinterpret_cast<FragBuf>(lds + Bs::oDhn);
-    bf16x8 *const wih_lds = reinterpret_cast<bf16x8 *>(lds + Sh::oWih);
-    const float *gb = reinterpret_cast<const float *>(lds + Sh::oGBias);
+    typedef bf16x8 (*FragBuf)[1][64];
+    float *const bias_lds = reinterpret_cast<float *>(lds + Bs::oBias);
 
     const NetFrags &net = a.net;
     const int lane = threadIdx.x & 63, q4 = lane >> 4, c = lane & 15;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int N = net.N, A = net.A, T = a.T, S = T + 1;
     const int rows = a.B * N;
     const int row = blockIdx.x * 16 + c;
     const bool valid = row < rows;
     const int b = valid ? row / N : 0, n = valid ? row % N : 0;
 
-    {
-        constexpr int kVecs = 3 * FBK * KS * 64;
-        for (int i = threadIdx.x; i < kVecs; i += 64 * Bs::NW) wih_lds[i] = net.wih_16[i];
-    }
-    if (w == 0) GruWave<H, P>::stage_gate_biases(lds, net, lane);
-
-    // this wave's hidden units: forward W_hh rows of the three gates, and the rows of W_hh^T and W_ih^T that produce
-    // its units of dL/dh and dL/dx
-    WFrag<P> whh[3][KS], whhT[3 * KS], wihT[3 * KS];
-#pragma unroll
-    for (int gate = 0; gate < 3; ++gate)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            whh[gate][ks] = load_wfrag<P>(net.whh_16 + ((size_t)(gate * FBK + w) * KS + ks) * 64 + lane);
-#pragma unroll
-    for (int ks = 0; ks < 3 * KS; ++ks) {
-        whhT[ks] = load_wfrag<P>(net.whhT_16 + (size_t)(w * 3 * KS + ks) * 64 + lane);
-        wihT[ks] = load_wfrag<P>(net.wihT_16 + (size_t)(w * 3 * KS + ks) * 64 + lane);
-    }
-    const f32x4 bias_hn = load_feature4(net.bias_hn, w, q4);
-
-    const int unit0 = 16 * w + 4 * q4;                             // the lane's four units
-    const size_t slot_stride = (size_t)N * H;
-    const float *h_row = a.h_all + ((size_t)b * S * N + n) * H + unit0;
-    constexpr int kElem = 2;                                       // bytes of an x and of a stored adjoint
-    const char *x_row = static_cast<const char *>(a.x_all) + (((size_t)b * S * N + n) * H + unit0) * kElem;
-
-    // The inputs of a slot are asked for one iteration before it; the chosen action, whose row of W2 is one
-    // of those inputs, one iteration earlier still.  Nothing here is conditional (rows past the end read row 0).
-    struct StepIn { f32x4 hp, w2; uint2 x; float gq_raw; uint32_t fil; int u; };
-    auto load_action = [&](int t) { return a.actions[((size_t)b * T + t) * N + n]; };
-    auto fetch = [&](int t, int u_raw) {
-        StepIn in;
-        const size_t bt = (size_t)b * T + t;
-        in.u = min(max(u_raw, 0), A - 1);
-        in.fil = a.filled[bt];
-        in.gq_raw = a.grad_q[bt * N + n];
-        in.hp = *reinterpret_cast<const f32x4 *>(h_row + (size_t)t * slot_stride);
-        in.x = *reinterpret_cast<const uint2 *>(x_row + (size_t)t * slot_stride * kElem);
-        in.w2 = *reinterpret_cast<const f32x4 *>(net.w2_plain + (size_t)in.u * H + unit0);
-        return in;
-    };
-
-    f32x4 dh = {0.0f, 0.0f, 0.0f, 0.0f};                           // dL/dh flowing into the state after slot t
-    float *const carry_row = a.carry + (size_t)row * H + unit0;    // rows past the end have room too
-    if (a.t_end < T) dh = *reinterpret_cast<const f32x4 *>(carry_row);
-
     const size_t samples = (size_t)rows * T;
-    const __amdgpu_buffer_rsrc_t da_buf = __builtin_amdgcn_make_buffer_rsrc(a.da, 0, (int)(uint32_t)(samples * 4 * H * kElem), kRawBuffer);
-    const __amdgpu_buffer_rsrc_t pre_buf = __builtin_amdgcn_make_buffer_rsrc(a.dpre1, 0, (int)(uint32_t)(samples * H * kElem), kRawBuffer);
-    const __amdgpu_buffer_rsrc_t dq_buf = __builtin_amdgcn_make_buffer_rsrc(a.dq, 0, (int)(uint32_t)(samples * a.a16 * kElem), kRawBuffer);
-    uint32_t drop = valid ? 0u : kDrop;
-    asm volatile("" : "+v"(drop));
-    const uint32_t drop_dq = (16 * w < a.a16) ? drop : kDrop;      // wave w writes block w of the row's dQ
+    auto operand = [&](int at) {                                   // at: byte offset of a fragment
+        Frag<1> f;
+        f.hi = *(reinterpret_cast<const bf16x8 *>(lds + at) + lane);
+        return f;
+    };
+    auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
+    auto fac_of = [&](int t, int f, int blk) { return reinterpret_cast<f32x4 *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + (f * FBK + blk) * 1024) + lane; };
+    const uint32_t bt0 = (uint32_t)b * T, btn0 = bt0 * N + n;      // the host bounds 4 H samples to 2^30
+    // A store's offset: the lane's own part (past every array, where the store is to be dropped), and the slot's, the same in
+    // every lane.
+    constexpr uint32_t kPast = 0x80000000u;
 
-    StepIn nxt = fetch(a.t_end - 1, load_action(a.t_end - 1));
-    int u_ahead = load_action(max(a.t_end - 2, 0));
-    // Nothing may be in flight when the loop is entered: the waits inside it are then the ones of the loop
-    // itself (the entry would otherwise add its own, stricter ones, which make every iteration wait for the
-    // previous iteration's stores).
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    asm volatile("" : "+v"(nxt.hp), "+v"(nxt.x.x), "+v"(nxt.x.y), "+v"(nxt.w2));
-    asm volatile("" : "+v"(nxt.gq_raw), "+v"(nxt.fil), "+v"(u_ahead));
-    lds_barrier();                                                 // W_ih and the biases are in LDS
-    for (int t = a.t_end - 1; t >= a.t_begin; --t) {
-        // What passes through the empty asm is used here and not earlier: the compiler would widen x and compare `filled`
-        // where they are loaded, and wait there.  The scheduling barriers keep the loads behind the operands' way to LDS
-        // and the stores behind the adjoints', which is what the other waves wait for: gradient of 64 episodes x 200 slots
-        // x 32 agents with 300 observations 1182 -> 1143 us, of 128 x 160 x 5 783 -> 772 us.
-        const StepIn in = nxt;
-        const int u_next = u_ahead;
-        uint32_t fil = in.fil;
-        uint2 raw = in.x;
-        asm volatile("" : "+v"(fil), "+v"(raw.x), "+v"(raw.y));
-        const float gq = (valid && fil) ? in.gq_raw : 0.0f;
-        // four bf16 values, widened (bf16 is the upper half of an fp32)
-        const f32x4 xv = {__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xFFFF0000u),
-                          __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xFFFF0000u)};
-        publish_block<P>(hf, w, lane, in.hp);
-        publish_block<P>(xf, w, lane, xv);
-        __builtin_amdgcn_sched_barrier(0);
-        u_ahead = load_action(max(t - 2, 0));
-        nxt = fetch(max(t - 1, 0), u_next);
-        lds_barrier();
-
-        // the gates of slot t again
-        f32x4 acc_r = load_feature4(gb, 0 * FBK + w, q4), acc_z = load_feature4(gb, 1 * FBK + w, q4);
-        f32x4 acc_in = load_feature4(gb, 2 * FBK + w, q4), acc_hn = bias_hn;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            Frag<P> hb, xb;
-            hb.hi = hf[ks][0][lane];
-            xb.hi = xf[ks][0][lane];
-            mma16<P>(acc_r, whh[0][ks], hb);
-            mma16<P>(acc_z, whh[1][ks], hb);
-            mma16<P>(acc_hn, whh[2][ks], hb);
-            mma16<P>(acc_r, load_wfrag<P>(wih_lds + ((size_t)(0 * FBK + w) * KS + ks) * 64 + lane), xb);
-            mma16<P>(acc_z, load_wfrag<P>(wih_lds + ((size_t)(1 * FBK + w) * KS + ks) * 64 + lane), xb);
-            mma16<P>(acc_in, load_wfrag<P>(wih_lds + ((size_t)(2 * FBK + w) * KS + ks) * 64 + lane), xb);
-        }
-
-        // adjoints of the pre-activations
-        f32x4 dar, daz, dan, dahn, carry;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float rr = sigmoidf_fast(acc_r[r]), zz = sigmoidf_fast(acc_z[r]);
-            const float nn = tanhf_fast(acc_in[r] + rr * acc_hn[r]);
-            const float dht = dh[r] + gq * in.w2[r];               // Q_t[u] = W2[u] . h_t + b2[u]
-            const float dn = dht * (1.0f - zz) * (1.0f - nn * nn);
-            dan[r] = dn;
-            dahn[r] = dn * rr;
-            dar[r] = dn * acc_hn[r] * rr * (1.0f - rr);
-            daz[r] = dht * (in.hp[r] - nn) * zz * (1.0f - zz);
-            carry[r] = dht * zz;
-        }
-        publish_block<P>(daf + 0 * KS, w, lane, dar);
-        publish_block<P>(daf + 1 * KS, w, lane, daz);
-        publish_block<P>(daf + 2 * KS, w, lane, dan);
-        publish_block<P>(dhf, w, lane, dahn);
-        __builtin_amdgcn_sched_barrier(0);
-        const uint32_t m = (uint32_t)((b * T + t) * N + n);        // sample index; the host bounds 4 H samples to 2^30
-        const uint32_t da_at = m * 4 * H + unit0;
-        store_adjoints<P>(dan, da_buf, da_at + 0 * H, drop);
-        store_adjoints<P>(dar, da_buf, da_at + 1 * H, drop);
-        store_adjoints<P>(daz, da_buf, da_at + 2 * H, drop);
-        store_adjoints<P>(dahn, da_buf, da_at + 3 * H, drop);
-        f32x4 dq;                                                  // the adjoint of Q_t, dense
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dq[r] = (unit0 + r == in.u) ? gq : 0.0f;
-        store_adjoints<P>(dq, dq_buf, m * a.a16 + unit0, drop_dq);
-        lds_barrier();
-
-        // back through the two products: dL/dh_{t-1} and dL/dx_t for this wave's units
-        f32x4 accx = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int ks = 0; ks < 3 * KS; ++ks) {
-            Frag<P> di, dhid;
-            di.hi = daf[ks][0][lane];
-            if (ks < 2 * KS) dhid = di;
-            else dhid.hi = dhf[ks - 2 * KS][0][lane];
-            mma16<P>(carry, whhT[ks], dhid);
-            mma16<P>(accx, wihT[ks], di);
-        }
-        dh = carry;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) accx[r] = xv[r] > 0.0f ? accx[r] : 0.0f;
-        store_adjoints<P>(accx, pre_buf, m * H + unit0, drop);
+    for (int i = threadIdx.x; i < 4 * H; i += Bs::kThreads) {
+        const int gate = i / H, j = i % H;
+        const float *src = gate == 0 ? net.bias_r : gate == 1 ? net.bias_z : gate == 2 ? net.bias_in : net.bias_hn;
+        bias_lds[i] = src[j];
     }
-    if (a.t_begin > 0) *reinterpret_cast<f32x4 *>(carry_row) = dh;
+    for (int i = threadIdx.x; i < A * H; i += Bs::kThreads)
+        *reinterpret_cast<__bf16 *>(lds + Bs::oW2 + (i / H) * Bs::kW2Pitch + 2 * (i % H)) = (__bf16)net.w2_plain[i];
+    // no adjoints behind the last slot: the first step's products add nothing
+    for (int i = threadIdx.x; i < Bs::kDaBytes / 16; i += Bs::kThreads) reinterpret_cast<uint4 *>(lds + da_at(a.t_end))[i] = make_uint4(0, 0, 0, 0);
+
+    if (wave >= Bs::kGate) {
+        // ---------------------------------------------------------------- chain wave
+        const int w = wave - Bs::kGate;                            // blocks 2 w and 2 w + 1 of sixteen units: one k-step of an operand
+        const int unit0 = 32 * w + 4 * q4;                         // the lane's units: these four and those sixteen further on
+        const __amdgpu_buffer_rsrc_t da_buf = __builtin_amdgcn_make_buffer_rsrc(a.da, 0, (int)(uint32_t)(samples * 4 * H * 2), kRawBuffer);
+        WFrag<1> whhT[2][3 * KS];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int ks = 0; ks < 3 * KS; ++ks) whhT[j][ks] = load_wfrag<1>(net.whhT_16 + (size_t)((2 * w + j) * 3 * KS + ks) * 64 + lane);
+        const uint32_t carry_at = (uint32_t)row * H + unit0;       // rows past the end have room too
+        f32x4 carry[2] = {};
+        if (a.t_end < T)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) carry[j] = *reinterpret_cast<const f32x4 *>(a.carry + carry_at + 16 * j);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int ks = 0; ks < 3 * KS; ++ks) settle(whhT[j][ks]);
+            asm volatile("" : "+v"(carry[j]));
+        }
+        // The adjoints lie in memory as in LDS, in the order of an operand's k-steps: the lane's eight units side by side.
+        const uint32_t da_lane = valid ? btn0 * 4 * H * 2 + 64 * w + 16 * q4 : kPast, da_slot = (uint32_t)N * 4 * H * 2;
+        // wave w writes block w of the row's dQ
+        const __amdgpu_buffer_rsrc_t dq_buf = __builtin_amdgcn_make_buffer_rsrc(a.dq, 0, (int)(uint32_t)(samples * a.a16 * 2), kRawBuffer);
+        const int action0 = 16 * w + 4 * q4;
+        const uint32_t dq_lane = valid && 16 * w < a.a16 ? (btn0 * a.a16 + action0) * 2 : kPast, dq_slot = (uint32_t)N * a.a16 * 2;
+        // What a slot's rows add from outside, asked for two steps ahead into two sets in turn.
+        struct In { float gq_raw; uint8_t fil; int u; };
+        auto fetch = [&](In &in, int t) {
+            const uint32_t ts = (uint32_t)max(t, 0), sample = btn0 + ts * N;
+            in.fil = a.filled[bt0 + ts];
+            in.gq_raw = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.grad_q) + sample * 4u);
+            in.u = *reinterpret_cast<const int *>(reinterpret_cast<const char *>(a.actions) + sample * 4u);
+        };
+        auto arrived = [](In &in) {
+            asm volatile("" ::"v"((uint32_t)in.fil));
+            asm volatile("" : "+v"(in.gq_raw), "+v"(in.u));
+        };
+        // carry += W_hh^T adjoints(t).  Two k-steps are asked for while the two before are multiplied; left to itself the compiler
+        // waits out every pair of reads.
+        auto back_product = [&](int t) {
+            Frag<1> d[2][2];
+            auto request = [&](int pair) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) d[pair % 2][i] = operand(da_at(t) + (2 * pair + i) * kFrag);
+            };
+            constexpr int kPairs = 3 * KS / 2;
+            request(0);
+#pragma unroll
+            for (int pair = 0; pair < kPairs; ++pair) {
+                if (pair + 1 < kPairs) request(pair + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) mma16<1>(carry[j], whhT[j][2 * pair + i], d[pair % 2][i]);
+            }
+        };
+        auto step = [&](In &in, int t, bool ask) {                 // (ask: known where it is called)
+            // (What passes through the empty asm is used here and not earlier: the compiler would widen `filled` where it is
+            // loaded, and wait there.)
+            uint32_t fil = in.fil;
+            int u = in.u;
+            float gq = in.gq_raw;
+            asm volatile("" : "+v"(fil), "+v"(u), "+v"(gq));
+            gq = (valid && fil) ? gq : 0.0f;
+            u = min(max(u, 0), A - 1);
+            back_product(t + 1);
+            f32x4 dan[2], dar[2], daz[2], dahn[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                f32x4 fac[Bs::kFactors];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int f = 0; f < Bs::kFactors; ++f) fac[f] = *fac_of(t, f, 2 * w + j);
+                const uint2 w2 = *reinterpret_cast<const uint2 *>(lds + Bs::oW2 + u * Bs::kW2Pitch + 2 * (unit0 + 16 * j));
+                const f32x4 w2v = {__uint_as_float(w2.x << 16), __uint_as_float(w2.x & 0xFFFF0000u),
+                                   __uint_as_float(w2.y << 16), __uint_as_float(w2.y & 0xFFFF0000u)};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float dht = carry[j][r] + gq * w2v[r];   // Q_t[u] = W2[u] . h_t + b2[u]
+                    dan[j][r] = dht * fac[0][r];
+                    dahn[j][r] = dan[j][r] * fac[1][r];
+                    dar[j][r] = dan[j][r] * fac[2][r];
+                    daz[j][r] = dht * fac[3][r];
+                    carry[j][r] = dht * fac[4][r];
+                }
+            }
+            const uint32_t slot_at = (uint32_t)t * da_slot;
+            const f32x4 (*const parts[4])[2] = {&dar, &daz, &dahn, &dan};
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const bf16x8 v = frag_of_pair<1>((*parts[g])[0], (*parts[g])[1]).hi;
+                if (g < 3) *(reinterpret_cast<bf16x8 *>(lds + da_at(t) + (g * KS + w) * kFrag) + lane) = v;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), da_buf, da_lane + (g + 1) % 4 * 2 * H, slot_at, 0);      // n, r, z, n hidden side
+            }
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            bf16x4 dq;                                             // the adjoint of Q_t, dense
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dq[r] = (__bf16)(u - action0 == r ? gq : 0.0f);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, dq), dq_buf, dq_lane, (uint32_t)t * dq_slot, 0);
+            if (ask) fetch(in, t - 2);
+            lds_barrier();
+        };
+        // Two steps a round; an odd one comes first, from a set of its own.  (A way out of the middle of the loop the compiler leads
+        // through the loop's end, and what was asked for last on that way is then waited for at the head of every round.)
+        const int odd = (a.t_end - a.t_begin) & 1;
+        In first, set_a, set_b;
+        fetch(first, a.t_end - 1);
+        fetch(set_a, a.t_end - 1 - odd);
+        fetch(set_b, a.t_end - 2 - odd);
+        arrived(first);
+        arrived(set_a);
+        arrived(set_b);
+        __builtin_amdgcn_s_setprio(2);                             // a SIMD's issue slots go to the chain first
+        lds_barrier();                                             // biases, W2, zeros, the last slot's x and h
+        lds_barrier();                                             // its factors
+        if (odd) step(first, a.t_end - 1, false);
+        for (int t = a.t_end - 1 - odd; t >= a.t_begin; t -= 2) {
+            step(set_a, t, true);
+            __builtin_amdgcn_sched_barrier(0);
+            step(set_b, t - 1, true);
+        }
+        if (a.t_begin > 0) {
+            back_product(a.t_begin);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(a.carry + carry_at + 16 * j) = carry[j];
+        }
+    } else {
+        // ---------------------------------------------------------------- gate wave
+        const int w = wave, unit0 = 16 * w + 4 * q4;               // the lane's four units
+        WFrag<1> whh[3][KS], wih[3][KS];
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const size_t at = (size_t)((gate * FBK + w) * KS + ks) * 64 + lane;
+                whh[gate][ks] = load_wfrag<1>(net.whh_16 + at);
+                wih[gate][ks] = load_wfrag<1>(net.wih_16 + at);
+            }
+        // x stays the bf16 that it is in memory: an operand as it lies
+        struct In { f32x4 h; uint2 x; };
+        const uint32_t saved0 = ((uint32_t)b * S * N + n) * H + unit0;
+        auto fetch = [&](In &in, int t) {
+            const uint32_t at = saved0 + (uint32_t)max(t, 0) * (uint32_t)(N * H);
+            in.h = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(a.h_all) + at * 4u);
+            in.x = *reinterpret_cast<const uint2 *>(static_cast<const char *>(a.x_all) + at * 2u);
+        };
+        auto arrived = [](In &in) { asm volatile("" : "+v"(in.h), "+v"(in.x.x), "+v"(in.x.y)); };
+        auto h_of = [&](int t) { return reinterpret_cast<f32x4 *>(lds + Bs::oHf + (t & 1) * Bs::kHfBytes + w * 1024) + lane; };
+        auto put_down = [&](const In &in, int t) {
+            publish_block<1>(reinterpret_cast<FragBuf>(lds + Bs::oH + (t & 1) * KS * kFrag), w, lane, in.h);
+            *h_of(t) = in.h;
+            *reinterpret_cast<uint2 *>(lds + Bs::oX + (t & 1) * KS * kFrag + (w / 2) * kFrag + lane * 16 + (w & 1) * 8) = in.x;
+        };
+        auto gates = [&](int t) {
+            f32x4 acc_r = load_feature4(bias_lds, w, q4), acc_z = load_feature4(bias_lds + H, w, q4);
+            f32x4 acc_in = load_feature4(bias_lds + 2 * H, w, q4), acc_hn = load_feature4(bias_lds + 3 * H, w, q4);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const Frag<1> hb = operand(Bs::oH + ((t & 1) * KS + ks) * kFrag), xb = operand(Bs::oX + ((t & 1) * KS + ks) * kFrag);
+                mma16<1>(acc_r, whh[0][ks], hb);
+                mma16<1>(acc_z, whh[1][ks], hb);
+                mma16<1>(acc_hn, whh[2][ks], hb);
+                mma16<1>(acc_r, wih[0][ks], xb);
+                mma16<1>(acc_z, wih[1][ks], xb);
+                mma16<1>(acc_in, wih[2][ks], xb);
+            }
+            const f32x4 hp = *h_of(t);
+            f32x4 fac[Bs::kFactors];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float rr = sigmoidf_fast(acc_r[r]), zz = sigmoidf_fast(acc_z[r]);
+                const float nn = tanhf_fast(acc_in[r] + rr * acc_hn[r]);
+                fac[0][r] = (1.0f - zz) * (1.0f - nn * nn);        // dL/dh_t -> n
+                fac[1][r] = rr;                                    // n -> n hidden side
+                fac[2][r] = acc_hn[r] * rr * (1.0f - rr);          // n -> r
+                fac[3][r] = (hp[r] - nn) * zz * (1.0f - zz);       // dL/dh_t -> z
+                fac[4][r] = zz;                                    // dL/dh_t -> what passes the cell by
+            }
+#pragma unroll
+            for (int f = 0; f < Bs::kFactors; ++f) *fac_of(t, f, w) = fac[f];
+        };
+        // in turn: slot t-2's, the one asked for; an odd step comes first, as the chain's
+        const int odd = (a.t_end - a.t_begin) & 1;
+        In first, set_a, set_b;
+        fetch(first, a.t_end - 1);
+        fetch(set_a, a.t_end - 2);
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) { settle(whh[gate][ks]); settle(wih[gate][ks]); }
+        arrived(first);
+        put_down(first, a.t_end - 1);
+        fetch(first, a.t_end - 3);
+        fetch(set_b, a.t_end - 3 - odd);
+        lds_barrier();
+        gates(a.t_end - 1);
+        arrived(set_a);
+        put_down(set_a, a.t_end - 2);
+        lds_barrier();
+        auto step = [&](const In &next, int t) {
+            gates(t - 1);
+            put_down(next, t - 2);
+            lds_barrier();
+        };
+        arrived(first);
+        arrived(set_b);
+        if (odd) step(first, a.t_end - 1);
+        for (int t = a.t_end - 1 - odd; t >= a.t_begin; t -= 2) {
+            fetch(set_a, t - 3);
+            __builtin_amdgcn_sched_barrier(0);
+            step(set_b, t);
+            fetch(set_b, t - 4);
+            __builtin_amdgcn_sched_barrier(0);
+            step(set_a, t - 1);
+        }
+    }
 }
 
 // The same for 64 hidden units, cut into two roles.  What bounds it is issue and latency, not memory or the matrix
@@ -304,7 +417,6 @@ __global__ __launch_bounds__(64 * BpttBack::NW, BpttBack::NW / 4) void bptt_back
 // gate waves, which then issue more than the chain does / on the chain waves / with the stores' offsets as below:
 // 64 episodes x 120 slots x 5 agents fp32 237 / 178 / 165 / 158.  First and last form: 4 x 60 x 3 fp32 115 / 80,
 // 37 x 83 x 5 bf16 116 / 82.
-// (128 hidden units keep bptt_back_kernel: eight waves already hold 144 registers of weights each.)
 // One plane: 126 registers and 68 KB of LDS, two workgroups per compute unit, asked for with the launch bound.  With one
 // (136 registers) a batch of a few more than 256 tiles walked all its slots twice over: gradient of 820 episodes x 199
 // slots x 5 agents (257 tiles) 1080 -> 1055 us, 4096 x 1 x 5 89 -> 85 us.  The fewer instructions per store help few
@@ -1124,6 +1236,248 @@ bool tn_wide_fits(const TnProduct &t, long M)
     return true;
 }
 
+// The products of the two GRU matrices of 128 units, one plane, and the adjoint of fc1's pre-activation, from the stored
+// adjoints: W_ih  sum da[n, r, z]^T [x | 1],  W_hh  sum da[r, z, n_h]^T [h_{t-1} | 1],  dpre1 = (x > 0) W_ih^T da[n, r, z].
+// Four workgroups share a chunk of samples, each with half the columns of one of the two products, those of W_ih with dpre1's
+// units of the same half beside it: the four read the same adjoints at about the same time, on one XCD, so that they come from
+// memory once.  All of a product's columns in one workgroup leave no registers for dpre1's weights.
+struct GruProductArgs {
+    const bf16x8 *wihT;
+    const char *da, *x, *h;        // rows of the window's first sample: adjoints [4 H] bf16, x [H] bf16, h_{t-1} [H] fp32
+    char *dpre1;                   // its row of [H] bf16
+    uint32_t dpre1_bytes;          // from there to the array's end
+    float *partial[2];             // [chunks][384][144] of W_ih, W_hh
+    int M, chunk, chunks;          // samples, samples of a chunk (a multiple of 64)
+    // A window's samples come in groups, the rows of an episode; `adj` and `act` rows from a group's first to the next one's.
+    uint32_t group, adj_group, act_group;
+    // 32 rows on: whole groups and rows of one
+    uint32_t step_rows, adj_step, act_step;
+};
+
+constexpr int kGruRows = 384, kGruColumns = 144;                   // of a partial result
+constexpr int kGruShare = 4;                                       // workgroups of a chunk
+
+struct GruTile {
+    static constexpr int H = 128, KS = H / 32;
+    static constexpr int kAPitch = 3 * H * 2 + 48;                 // 12 words past a multiple of 64: as in tn_gemm_wide_kernel
+    static constexpr int kBPitch = 64 * 2 + 16;                    // four rows' 32 bytes in different banks here too
+    static constexpr int oB = 32 * kAPitch, kBufBytes = oB + 32 * kBPitch;
+    static constexpr int oDp = 2 * kBufBytes, kDpPitch = 64 * 2 + 16, kDpBytes = 32 * kDpPitch;
+    static constexpr int kBytes = oDp + 2 * kDpBytes;
+};
+
+// WIH: the W_ih product and dpre1; else the W_hh product.
+template <bool WIH>
+__device__ __forceinline__ void gru_products(const GruProductArgs &g, int chunk_index, int half, char *lds)
+{
+    using Tl = GruTile;
+    constexpr int H = Tl::H, KS = Tl::KS;
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, q4 = lane >> 4, c = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m_begin = chunk_index * g.chunk, m_end = min(g.M, m_begin + g.chunk);
+    const int n_steps = (m_end - m_begin + 31) / 32;
+
+    // Thread (row of the step, piece): three times 16 bytes of the sample's adjoints, four columns of x or h.
+    const int k_row = (int)threadIdx.x >> 4, piece = (int)threadIdx.x & 15;
+    int sample = m_begin + k_row;                                  // the sample the next loads take
+    uint32_t in_group, adj_row, act_row;                           // where its rows are
+    {
+        const uint32_t first = (uint32_t)min(sample, g.M - 1), group = first / g.group;
+        in_group = first - group * g.group;
+        adj_row = group * g.adj_group + in_group;
+        act_row = group * g.act_group + in_group;
+    }
+    const char *const da = g.da + (WIH ? 0 : 2 * H);               // columns n, r, z or r, z, n of the hidden side
+    const char *const act = WIH ? g.x + 128 * half : g.h + 256 * half;
+    const uint32_t dp_column = 128u * half + 8u * piece;
+    const __amdgpu_buffer_rsrc_t dp_buf = __builtin_amdgcn_make_buffer_rsrc(g.dpre1, 0, WIH ? (int)g.dpre1_bytes : 0, kRawBuffer);
+
+    typedef std::conditional_t<WIH, uint2, uint4> BRegs;
+    struct Staged { uint4 a[3]; BRegs b; uint32_t dp_at; };        // dp_at: where the sample's dpre1 goes, kDrop past the chunk's end
+    auto fetch = [&](Staged &into) {
+        into.dp_at = sample < m_end ? adj_row * (2u * H) + dp_column : kDrop;
+        const uint32_t a_at = adj_row * (8u * H) + 16u * piece, b_at = act_row * ((WIH ? 2u : 4u) * H) + (WIH ? 8u : 16u) * piece;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) into.a[i] = *reinterpret_cast<const uint4 *>(da + 256 * i + a_at);
+        into.b = *reinterpret_cast<const BRegs *>(act + b_at);
+        // 32 rows on; past the last sample its row stays (what is fetched there again does not count).  Masks: of conditions the
+        // compiler makes branches, and a branch between loads makes every wait a full one.
+        uint32_t go = sample + 32 < g.M ? 0xFFFFFFFFu : 0u, wraps = in_group + g.step_rows >= g.group ? 0xFFFFFFFFu : 0u;
+        asm volatile("" : "+v"(go), "+v"(wraps));
+        adj_row += go & (g.adj_step + (wraps & (g.adj_group - g.group)));
+        act_row += go & (g.act_step + (wraps & (g.act_group - g.group)));
+        in_group += go & (g.step_rows - (wraps & g.group));
+        sample += 32;
+    };
+    const int a_lds = k_row * Tl::kAPitch + 16 * piece, b_lds = Tl::oB + k_row * Tl::kBPitch + 8 * piece;
+    // what the thread has to do with dpre1 of the steps staged last: where it goes, which of its four units were on
+    uint32_t dp_at[2] = {kDrop, kDrop}, dp_on[2][2] = {};
+    auto deposit = [&](int which, Staged &from) {
+        char *const buf = lds + which * Tl::kBufBytes;
+        const uint32_t keep = from.dp_at != kDrop ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            uint4 v = from.a[i];
+            asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+            v.x &= keep; v.y &= keep; v.z &= keep; v.w &= keep;
+            *reinterpret_cast<uint4 *>(buf + a_lds + 256 * i) = v;
+        }
+        if constexpr (WIH) {
+            uint2 v = from.b;
+            asm volatile("" : "+v"(v.x), "+v"(v.y));
+            *reinterpret_cast<uint2 *>(buf + b_lds) = v;
+            auto on = [](uint32_t two) {
+                return (__uint_as_float(two << 16) > 0.0f ? 0xFFFFu : 0u) | (__uint_as_float(two & 0xFFFF0000u) > 0.0f ? 0xFFFF0000u : 0u);
+            };
+            dp_on[which][0] = on(v.x);
+            dp_on[which][1] = on(v.y);
+            dp_at[which] = from.dp_at;
+        } else {
+            uint4 v = from.b;
+            asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+            bf16x4 r;
+            r[0] = (__bf16)__uint_as_float(v.x); r[1] = (__bf16)__uint_as_float(v.y);
+            r[2] = (__bf16)__uint_as_float(v.z); r[3] = (__bf16)__uint_as_float(v.w);
+            *reinterpret_cast<bf16x4 *>(buf + b_lds) = r;
+        }
+    };
+    auto store_dpre1 = [&]() {                                     // of the two steps multiplied last
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            uint2 v = *reinterpret_cast<const uint2 *>(lds + Tl::oDp + which * Tl::kDpBytes + k_row * Tl::kDpPitch + 8 * piece);
+            const u32x2 out = {v.x & dp_on[which][0], v.y & dp_on[which][1]};
+            __builtin_amdgcn_raw_buffer_store_b64(out, dp_buf, dp_at[which], 0, 0);
+        }
+    };
+
+    // Wave w: row blocks w, w + 8, w + 16 of the result, all four column blocks, and the column of ones (its fragment is the same
+    // for every sample: no operand to stage).  dpre1: units of block w % 4 of the half, samples 16 (w / 4) .. + 15 of the step.
+    f32x4 acc[3][5] = {};
+    WFrag<1> wihT[WIH ? 3 * KS : 1];
+    const int dp_block = w & 3, dp_half = w >> 2;
+    if constexpr (WIH) {
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) wihT[ks] = load_wfrag<1>(g.wihT + (size_t)((4 * half + dp_block) * 3 * KS + ks) * 64 + lane);
+    }
+    Frag<1> ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones.hi[i] = (__bf16)(c == 0 ? 1.0f : 0.0f);
+
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    typedef s16x4 __attribute__((address_space(3))) *LdsQuad;
+    auto fragment = [&](const char *rows, int pitch, int first_col) {      // the transposing read, as in tn_gemm_wide_kernel
+        const char *at = rows + (8 * q4 + (c >> 2)) * pitch + (first_col + 4 * (c & 3)) * 2;
+        const s16x4 first = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)(at));
+        const s16x4 second = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsQuad)(at + 4 * pitch));
+        return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(first, second, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto multiply = [&](int which) {
+        const char *const buf = lds + which * Tl::kBufBytes;
+        WFrag<1> af[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) af[k].hi = fragment(buf, Tl::kAPitch, 16 * (w + 8 * k));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            Frag<1> bf;
+            bf.hi = fragment(buf + Tl::oB, Tl::kBPitch, 16 * j);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) mma16<1>(acc[k][j], af[k], bf);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) mma16<1>(acc[k][4], af[k], ones);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (WIH) {
+            // the adjoints of a sample are an operand as they lie; the weights' fragments take the gates in the order r, z, n
+            const char *const sample_row = buf + (16 * dp_half + c) * Tl::kAPitch + 16 * q4;
+            f32x4 dp = {0.0f, 0.0f, 0.0f, 0.0f};
+            Frag<1> d[2][KS];                                      // a gate's four k-steps, asked for while the one before is multiplied
+            auto request = [&](int gate) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    d[gate % 2][ks].hi = *reinterpret_cast<const bf16x8 *>(sample_row + ((gate + 1) % 3 * KS + ks) * 64);
+                }
+            };
+            request(0);
+#pragma unroll
+            for (int gate = 0; gate < 3; ++gate) {
+                if (gate < 2) request(gate + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) mma16<1>(dp, wihT[gate * KS + ks], d[gate % 2][ks]);
+            }
+            bf16x4 r;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = (__bf16)dp[i];
+            *reinterpret_cast<bf16x4 *>(lds + Tl::oDp + which * Tl::kDpBytes + (16 * dp_half + c) * Tl::kDpPitch + (16 * dp_block + 4 * q4) * 2) = r;
+        }
+    };
+
+    // Rounds of two steps: stage both, ask for two more, multiply both.  The loads are two rounds ahead, in four register sets
+    // (W_ih: one round, in two; its weights have taken the room).
+    constexpr int kAhead = WIH ? 1 : 2;
+    Staged set_a, set_b, set_c, set_d;
+    for (Staged *set : {&set_a, &set_b, &set_c, &set_d}) {
+        if (kAhead == 1 && set == &set_c) break;
+        fetch(*set);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (WIH) {
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) settle(wihT[ks]);
+    }
+    auto round = [&](Staged &one, Staged &two) {
+        if constexpr (WIH) store_dpre1();
+        deposit(0, one);
+        deposit(1, two);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(one);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(two);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
+        multiply(0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        lds_barrier();                                             // every wave is done reading before the next round writes
+    };
+    for (int s = 0; s < n_steps;) {
+        round(set_a, set_b);
+        s += 2;
+        if constexpr (kAhead == 2) {
+            if (s >= n_steps) break;
+            round(set_c, set_d);
+            s += 2;
+        }
+    }
+    if constexpr (WIH) store_dpre1();
+
+    // C layout: lane (c, q4) holds the result's rows at positions 16 block + 4 q4 + r of the stored adjoints, columns 16 j + c.
+    // Position 32 s + 8 p + 4 b + r of a gate is its unit 32 s + 16 b + 4 p + r.
+    const int unit = 32 * (w >> 1) + 16 * (q4 & 1) + 4 * (2 * (w & 1) + (q4 >> 1));
+    float *const out = g.partial[WIH ? 0 : 1] + (size_t)chunk_index * kGruRows * kGruColumns;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+            if (j < 4 || half == 1)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    out[(size_t)(H * k + unit + r) * kGruColumns + (j < 4 ? 64 * half + 16 * j : H) + c] = acc[k][j][r];
+}
+
+__global__ __launch_bounds__(kTnThreads, 2) void gru_products_kernel(const GruProductArgs g)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    // Workgroup -> (chunk, share): consecutive workgroups go round the eight XCDs, so the four of a chunk are eight apart.
+    const int chunk_index = (int)(blockIdx.x / (8 * kGruShare)) * 8 + (int)(blockIdx.x & 7), share = (int)(blockIdx.x >> 3) & (kGruShare - 1);
+    if (chunk_index >= g.chunks) return;
+    if (share < 2) gru_products<true>(g, chunk_index, share & 1, lds);
+    else gru_products<false>(g, chunk_index, share & 1, lds);
+}
+
 // Sum of the chunks, in a fixed order, into the packed gradient vector.  Result row p goes to row
 // (p + row_shift) % P of the destination matrix (the adjoint array lists the gates as n, r, z, the
 // parameters as r, z, n); columns < Q go to dst_w[row * ld_w + column]; the appended column of ones
@@ -1256,12 +1610,12 @@ Plan make_plan(const NetFrags &net, int B, int T)
 }
 
 template <auto kKernel>
-hipError_t back_dispatch(const BpttArgs &a, size_t lds_bytes, hipStream_t stream)
+hipError_t back_dispatch(const BpttArgs &a, int threads, size_t lds_bytes, hipStream_t stream)
 {
     const int tiles = (a.B * a.net.N + 15) / 16;
     hipError_t err = allow_large_lds<kKernel>(kLdsLimit);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kKernel, dim3(tiles), dim3(512), lds_bytes, stream, a);
+    hipLaunchKernelGGL(kKernel, dim3(tiles), dim3(threads), lds_bytes, stream, a);
     return hipGetLastError();
 }
 
@@ -1420,6 +1774,30 @@ hipError_t launch_tn_gemms_wide(const TnProduct *list, int count, long M, int ch
     return err;
 }
 
+// The GRU matrices' products and dpre1 over the samples of slots [t0, t1), 128 units and one plane; without the sum of the chunks.
+hipError_t launch_gru_products(const BpttArgs &a, int t0, int t1, const SampleChunks &cut, float *partial_ih, float *partial_hh, hipStream_t stream)
+{
+    const NetFrags &net = a.net;
+    const size_t H = net.H, N = net.N, T = a.T, first = (size_t)t0 * N;
+    GruProductArgs g{};
+    g.wihT = net.wihT_16;
+    g.da = static_cast<const char *>(a.da) + first * 4 * H * 2;
+    g.x = static_cast<const char *>(a.x_all) + first * H * 2;
+    g.h = reinterpret_cast<const char *>(a.h_all + first * H);
+    g.dpre1 = static_cast<char *>(a.dpre1) + first * H * 2;
+    g.dpre1_bytes = (uint32_t)((a.B * T * N - first) * H * 2);
+    g.partial[0] = partial_ih; g.partial[1] = partial_hh;
+    g.M = (int)cut.samples; g.chunk = cut.chunk; g.chunks = cut.chunks;
+    g.group = (uint32_t)((t1 - t0) * N); g.adj_group = (uint32_t)(T * N); g.act_group = (uint32_t)((T + 1) * N);
+    const uint32_t groups = 32 / g.group;
+    g.step_rows = 32 % g.group;
+    g.adj_step = groups * g.adj_group + g.step_rows; g.act_step = groups * g.act_group + g.step_rows;
+    const hipError_t err = allow_large_lds<gru_products_kernel>(kLdsLimit);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(gru_products_kernel, dim3((cut.chunks + 7) / 8 * 8 * kGruShare), dim3(kTnThreads), GruTile::kBytes, stream, g);
+    return hipGetLastError();
+}
+
 bool qnet_grad_fits(const NetFrags &net)
 {
     return unroll_fused_fits(net) && net.D + net.N <= 336;        // the widest product the gradient kernel stages
@@ -1459,11 +1837,12 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     a.net = net; a.B = B; a.T = T; a.a16 = plan.a16; a.actions = actions; a.filled = filled; a.grad_q = grad_q;
     a.h_all = h_all; a.x_all = x_all; a.da = da; a.dpre1 = dpre1; a.dq = dq;
     a.carry = reinterpret_cast<float *>(ws + plan.off_carry);
+    const bool roles = H == 128 && net.planes == 1;
     auto reverse = [&](int t_begin, int t_end, hipStream_t on) {
         a.t_begin = t_begin; a.t_end = t_end;
-        if (H == 64 && net.planes == 2) return back_dispatch<bptt_back_split_kernel<2>>(a, BpttSplit<2>::kBytes, on);
-        if (H == 64 && net.planes == 1) return back_dispatch<bptt_back_split_kernel<1>>(a, BpttSplit<1>::kBytes, on);
-        if (H == 128 && net.planes == 1) return back_dispatch<bptt_back_kernel>(a, BpttBack::kBytes, on);
+        if (H == 64 && net.planes == 2) return back_dispatch<bptt_back_split_kernel<2>>(a, 512, BpttSplit<2>::kBytes, on);
+        if (H == 64 && net.planes == 1) return back_dispatch<bptt_back_split_kernel<1>>(a, 512, BpttSplit<1>::kBytes, on);
+        if (roles) return back_dispatch<bptt_back_roles_kernel>(a, BpttRoles::kThreads, BpttRoles::lds_bytes(A), on);
         return hipErrorInvalidValue;
     };
 
@@ -1511,7 +1890,18 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
         err = reverse(0, T, stream);
         if (err != hipSuccess) return err;
         const Four all = products_of(0, T);
-        return launch_tn_products(net.planes, all.p, 4, plan.cut.whole.samples, plan.cut.whole.chunk, partial, plan.partial_bytes, stream);
+        int done = 0;
+        if (roles) {
+            const SampleChunks &cut = plan.cut.gru_whole;
+            float *const parts[2] = {partial, partial + (size_t)cut.chunks * kGruRows * kGruColumns};
+            err = launch_gru_products(a, 0, T, cut, parts[0], parts[1], stream);
+            if (err != hipSuccess) return err;
+            TnReduceBatch red{};
+            for (; done < 2; ++done) red.r[done] = reduce_args(all.p[done], parts[done], cut.chunks);
+            err = launch_reduce(red, 2, stream);
+            if (err != hipSuccess) return err;
+        }
+        return launch_tn_products(net.planes, all.p + done, 4 - done, plan.cut.whole.samples, plan.cut.whole.chunk, partial, plan.partial_bytes, stream);
     }
     // a product's partial sums: the later half's chunks, then the earlier half's, summed in that order
     float *part_late[4], *part_early[4];
@@ -1521,26 +1911,36 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
         for (int i = 0; i < 4; ++i) {
             const TnProduct &t = late.p[i];
             const size_t p_pad = (size_t)partial_rows(t.P), qp = (size_t)(t.Q + t.n_extra + 15) / 16 * 16;
+            const int n_late = (roles && i < 2 ? plan.cut.gru_late : cut_late).chunks, n_early = (roles && i < 2 ? plan.cut.gru_early : cut_early).chunks;
             part_late[i] = reinterpret_cast<float *>(reinterpret_cast<char *>(partial) + used);
-            part_early[i] = part_late[i] + (size_t)cut_late.chunks * p_pad * qp;
-            used += (size_t)(cut_late.chunks + cut_early.chunks) * p_pad * qp * sizeof(float);
-            red.r[i] = reduce_args(t, part_late[i], cut_late.chunks + cut_early.chunks);
+            part_early[i] = part_late[i] + (size_t)n_late * p_pad * qp;
+            used += (size_t)(n_late + n_early) * p_pad * qp * sizeof(float);
+            red.r[i] = reduce_args(t, part_late[i], n_late + n_early);
         }
         if (used > plan.partial_bytes) return hipErrorInvalidValue;
     }
     err = reverse(t_mid, T, stream);
     if (err == hipSuccess) err = hipEventRecord(side->fork, stream);
     if (err == hipSuccess) err = hipStreamWaitEvent(side->stream, side->fork, 0);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(late.p, 4, cut_late.samples, cut_late.chunk, part_late, side->stream);
-    if (err == hipSuccess) err = reverse(0, t_mid, stream);
-    // the earlier half: W_hh's product follows on the second stream (a second fork: it needs the recurrence's end),
-    // the other three on the caller's
-    if (err == hipSuccess) err = hipEventRecord(side->fork, stream);
-    if (err == hipSuccess) err = hipStreamWaitEvent(side->stream, side->fork, 0);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 1, 1, cut_early.samples, cut_early.chunk, part_early + 1, side->stream);
-    if (err == hipSuccess) err = hipEventRecord(side->join, side->stream);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p, 1, cut_early.samples, cut_early.chunk, part_early, stream);
-    if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 2, 2, cut_early.samples, cut_early.chunk, part_early + 2, stream);
+    if (roles) {
+        if (err == hipSuccess) err = launch_gru_products(a, t_mid, T, plan.cut.gru_late, part_late[0], part_late[1], side->stream);
+        if (err == hipSuccess) err = launch_tn_gemms_wide(late.p + 2, 2, cut_late.samples, cut_late.chunk, part_late + 2, side->stream);
+        if (err == hipSuccess) err = hipEventRecord(side->join, side->stream);
+        if (err == hipSuccess) err = reverse(0, t_mid, stream);
+        if (err == hipSuccess) err = launch_gru_products(a, 0, t_mid, plan.cut.gru_early, part_early[0], part_early[1], stream);
+        if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 2, 2, cut_early.samples, cut_early.chunk, part_early + 2, stream);
+    } else {
+        if (err == hipSuccess) err = launch_tn_gemms_wide(late.p, 4, cut_late.samples, cut_late.chunk, part_late, side->stream);
+        if (err == hipSuccess) err = reverse(0, t_mid, stream);
+        // the earlier half: W_hh's product follows on the second stream (a second fork: it needs the recurrence's end),
+        // the other three on the caller's
+        if (err == hipSuccess) err = hipEventRecord(side->fork, stream);
+        if (err == hipSuccess) err = hipStreamWaitEvent(side->stream, side->fork, 0);
+        if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 1, 1, cut_early.samples, cut_early.chunk, part_early + 1, side->stream);
+        if (err == hipSuccess) err = hipEventRecord(side->join, side->stream);
+        if (err == hipSuccess) err = launch_tn_gemms_wide(early.p, 1, cut_early.samples, cut_early.chunk, part_early, stream);
+        if (err == hipSuccess) err = launch_tn_gemms_wide(early.p + 2, 2, cut_early.samples, cut_early.chunk, part_early + 2, stream);
+    }
     if (err == hipSuccess) err = hipStreamWaitEvent(stream, side->join, 0);
     if (err != hipSuccess) return err;
     err = launch_reduce(red, 4, stream);

@@ -78,6 +78,8 @@ struct GradChunks {
     SampleChunks whole;            // one launch of the recurrence, products over all slots
     int t_mid;                     // two launches: slots [t_mid, T), then [0, t_mid)
     SampleChunks late, early;
+    // the same three for the GRU matrices of 128 units, one plane (gru_products_kernel: four workgroups a chunk)
+    SampleChunks gru_whole, gru_late, gru_early;
     int room;                      // most chunks whose partial sums lie in the workspace together
 };
 
@@ -97,6 +99,8 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
     // 9900 297 / 290; 64 units, and 33 and 301 observations, change over between the same 2400 and 3000.
     g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, M <= 2560 ? 64 : 128);
     g.room = g.whole.chunks;
+    auto cut_gru = [](long samples) { return cut_samples(samples, 64, 64); };
+    g.gru_whole = cut_gru(M);
     if (planes == 1 && T >= kForkSlots) {
         // the later half's products share the chip with the recurrence, whose workgroups hold half the compute units
         // or less: half as many chunks.  The earlier half's too: its two GRU products then run side by side, one on
@@ -105,6 +109,8 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
         g.t_mid = T / 2;
         g.late = cut_samples(rows * (T - g.t_mid), 128, 32);
         g.early = cut_samples(rows * g.t_mid, 128, 32);
+        g.gru_late = cut_gru(rows * (T - g.t_mid));
+        g.gru_early = cut_gru(rows * g.t_mid);
         g.room = std::max(g.room, g.late.chunks + g.early.chunks);
     }
     return g;
