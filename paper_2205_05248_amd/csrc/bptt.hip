@@ -272,7 +272,10 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
             for (int g = 0; g < 4; ++g) {
                 const bf16x8 v = frag_of_pair<1>((*parts[g])[0], (*parts[g])[1]).hi;
                 if (g < 3) *(reinterpret_cast<bf16x8 *>(lds + da_at(t) + (g * KS + w) * kFrag) + lane) = v;
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), da_buf, da_lane + (g + 1) % 4 * 2 * H, slot_at, 0);      // n, r, z, n hidden side
+                // n, r, z, n hidden side.  (The slot's part in the lanes' offset, not in the scalar one: behind a 16-byte store with
+                // a scalar offset the compiler lets the next instruction overwrite the registers that are being stored, and values
+                // of the next instruction's have been stored here.)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), da_buf, da_lane + slot_at + (g + 1) % 4 * 2 * H, 0, 0);
             }
             typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
             typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
