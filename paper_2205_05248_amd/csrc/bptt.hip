@@ -12,6 +12,7 @@
 //                                      on nothing behind it are on different waves.  128 hidden units, bf16.
 //   bptt_back_split_kernel             the same for 64 hidden units, fp32 and bf16; here W_ih^T and, through the
 //                                      ReLU, the adjoint of fc1's pre-activation are part of it
+//   bptt_back_split8_kernel            the same on tiles of eight rows, for batches that leave compute units free
 //   tn_gemm_kernel                     the weight gradients are sums over all (row, slot) samples of outer
 //                                      products adjoint x activation: C[p][q] = sum_m A[m][p] B[m][q], four
 //                                      times (W_ih, W_hh, W1, W2).  The samples are split into chunks, one
@@ -669,6 +670,397 @@ __global__ __launch_bounds__(512, P == 1 ? 4 : 2) void bptt_back_split_kernel(Bp
             step(set_c, set_a, set_b, t);
             if (--t < a.t_begin) break;
         }
+    }
+}
+
+// The same two roles on tiles of eight rows, for batches that leave compute units free.
+//
+// An operand's sixteen columns are the eight rows twice: two planes, the high parts and the remainders side by side (c < 8,
+// c >= 8), so that W_hi and W_lo take one product each, two instead of three, and the sum of a row's two columns is the whole (W_lo
+// times the remainder with it); one plane, the same values twice.  Either way lane (c, q4) then has two of the four units 4 q4 .. +
+// 3, those of its side (c / 8), to go on with: half the vector instructions per lane.
+//
+// What goes to memory and comes from it goes through LDS, and waves of their own move it, two rows each, a row's lanes side by
+// side: an access whose neighbouring lanes are different rows, as an operand has them, takes the address unit 64 clocks, one whose
+// neighbours lie side by side 8 to 16, and the kernel above has 48 of them a slot (3,000 clocks; a slot took 2,900).  In the
+// step of slot t
+//
+//   chain waves 0..3  as above; adjoints(t) and the adjoint of fc1's pre-activation of slot t+1 to LDS, nothing to memory
+//   gate waves 4..7   the gates of slot t-1 -> factors
+//   movers 8..11      x and h of slot t-2 to LDS, its rows' scalars, its adjoint of Q to memory; what the chain left in the step
+//                     before to memory; the loads of slot t-3
+//
+// Kernel trace, us per launch: 64 episodes x 120 slots x 5 agents fp32 156 on tiles of 16; of 8 with the accesses as there 111, moved
+// by the gate waves 111 (then what a step waits for), by waves of their own 103; 37 x 83 x 5 bf16 82, 56, 63, 46.  Eight gate waves,
+// every four with every other slot, as long as they also fetched: 140, 66.
+template <int P> struct BpttSplit8 {
+    static constexpr int H = 64, KS = H / 32, FBK = H / 16, kThreads = 3 * 256, kElem = P == 1 ? 2 : 4;      // bytes per stored adjoint
+    static constexpr int kColumns = P == 2 ? 16 : 8, kFrag = 4 * kColumns * 16;          // of an operand that are kept
+    static constexpr int kFactors = 5, kPair = FBK * 512;                                // two floats of every lane and block
+    static constexpr int oH = 0, oX = oH + 2 * KS * kFrag, oDa = oX + 2 * KS * kFrag, kDaBytes = 4 * KS * kFrag;
+    static constexpr int oFac = oDa + 2 * kDaBytes, kFacBytes = kFactors * kPair;
+    // row by row, the pitches 64 bytes past a multiple of 256: h in fp32, for the blend; the adjoints and dpre1 as they are stored
+    static constexpr int oHf = oFac + 2 * kFacBytes, kHfPitch = H * 4 + 64, kHfBytes = 8 * kHfPitch;
+    static constexpr int oOut = oHf + 2 * kHfBytes, kOutPitch = 4 * H * kElem + 64, kOutBytes = 8 * kOutPitch;
+    static constexpr int oPre = oOut + 2 * kOutBytes, kPrePitch = (H * kElem + 255) / 256 * 256 + 64, kPreBytes = 8 * kPrePitch;
+    static constexpr int oBias = oPre + 2 * kPreBytes;             // r, z, n input side, n hidden side; zeros
+    static constexpr int oRow = oBias + 5 * H * 4, kRowBytes = 8 * 8;                    // per row: dL/dq_taken, its action; of four slots
+    // W2, whose row of the chosen action the chain adds; bf16 for a one-plane network (what the table holds exactly)
+    static constexpr int oW2 = oRow + 4 * kRowBytes, kW2Pitch = H * kElem + 4 * kElem;
+    static constexpr int lds_bytes(int A) { return oW2 + (A * kW2Pitch + 15) / 16 * 16; }
+};
+
+template <int P>
+__global__ __launch_bounds__(BpttSplit8<P>::kThreads, BpttSplit8<P>::kThreads / 256) void bptt_back_split8_kernel(BpttArgs a)
+{
+    using Bs = BpttSplit8<P>;
+    constexpr int H = Bs::H, KS = Bs::KS, FBK = Bs::FBK, kFrag = Bs::kFrag, kElem = Bs::kElem;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float *const bias_lds = reinterpret_cast<float *>(lds + Bs::oBias);
+
+    const NetFrags &net = a.net;
+    const int lane = threadIdx.x & 63, q4 = lane >> 4, c = lane & 15, side = c >> 3, r8 = c & 7;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3;
+    const int N = net.N, A = net.A, T = a.T, S = T + 1;
+    const int rows = a.B * N, row0 = blockIdx.x * 8;
+    const int unit0 = 16 * w + 4 * q4 + 2 * side;                  // the two units of the lane's in a product's result
+
+    struct Pair { float v[2]; };
+    // Where an operand keeps column `col` of lane quarter `quarter` in k-step ks: the columns change places from quarter to quarter
+    // and k-step to k-step, or the writers, who have a row's units side by side, would all meet in one bank.
+    auto column_at = [](int ks, int quarter, int col) { return (quarter * Bs::kColumns + (col ^ (quarter + 4 * (ks & 1)))) * 16; };
+    const int operand_at[2] = {column_at(0, q4, c & (Bs::kColumns - 1)), column_at(1, q4, c & (Bs::kColumns - 1))};
+    auto operand = [&](int at, int ks) { return *reinterpret_cast<const bf16x8 *>(lds + at + ks * kFrag + operand_at[ks & 1]); };
+    // two units as their part of an operand; `where`: publish_at of them
+    auto publish_at = [&](int row, int unit) { return (unit >> 5) * kFrag + column_at(unit >> 5, (unit & 15) >> 2, row) + (unit >> 4 & 1) * 8 + (unit & 3) * 2; };
+    auto publish = [&](int where, const Pair &x) {
+        bf16x2 hi;
+        hi[0] = (__bf16)x.v[0]; hi[1] = (__bf16)x.v[1];
+        *reinterpret_cast<bf16x2 *>(lds + where) = hi;
+        if constexpr (P == 2) {
+            bf16x2 lo;
+            lo[0] = (__bf16)(x.v[0] - (float)hi[0]); lo[1] = (__bf16)(x.v[1] - (float)hi[1]);
+            *reinterpret_cast<bf16x2 *>(lds + (where ^ (8 * 16))) = lo;      // column + 8
+        }
+    };
+    // A row's two columns, of which this lane holds one -> the two units of the lane's side.  (Bits, for of a choice between
+    // elements the compiler makes a search for the element, three instructions.)
+    uint32_t upper = side ? 0xFFFFFFFFu : 0u;
+    asm volatile("" : "+v"(upper));
+    auto mine = [&](const f32x4 &acc) {
+        Pair x;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t first = __float_as_uint(acc[i]), second = __float_as_uint(acc[2 + i]);
+            x.v[i] = __uint_as_float(first ^ (upper & (second ^ first)));
+            if constexpr (P == 2) {
+                const uint32_t other = second ^ (upper & (first ^ second));                // what the lane of the other column is to have
+                x.v[i] += __uint_as_float(__builtin_amdgcn_update_dpp(0, other, 0x128, 0xF, 0xF, true));      // row_ror:8
+            }
+        }
+        return x;
+    };
+    auto product = [&](f32x4 &acc, const WFrag<P> &wf, const bf16x8 &d) {
+        if constexpr (P == 2) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.lo, d, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.hi, d, acc, 0, 0, 0);
+    };
+    auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
+    auto fac_of = [&](int t, int f) { return reinterpret_cast<f32x2 *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + f * Bs::kPair + w * 512) + lane; };
+    auto row_of = [&](int t, int r) { return reinterpret_cast<uint2 *>(lds + Bs::oRow + (t & 3) * Bs::kRowBytes) + r; };
+    for (int i = threadIdx.x; i < A * H; i += Bs::kThreads) {
+        char *const at = lds + Bs::oW2 + (i / H) * Bs::kW2Pitch + (i % H) * kElem;
+        if constexpr (P == 1) *reinterpret_cast<__bf16 *>(at) = (__bf16)net.w2_plain[i];
+        else *reinterpret_cast<float *>(at) = net.w2_plain[i];
+    }
+
+    if (wave < 4) {
+        // ---------------------------------------------------------------- chain wave
+        WFrag<P> whhT[3 * KS], wihT[3 * KS];
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) {
+            whhT[ks] = load_wfrag<P>(net.whhT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+            wihT[ks] = load_wfrag<P>(net.wihT_16 + ((size_t)(w * 3 * KS + ks) * P) * 64 + lane);
+        }
+        {
+            const int i = (int)threadIdx.x, gate = i / H, j = i % H;      // 256 threads, 4 H biases
+            const float *src = gate == 0 ? net.bias_r : gate == 1 ? net.bias_z : gate == 2 ? net.bias_in : net.bias_hn;
+            bias_lds[i] = src[j];
+            if (i < H) bias_lds[4 * H + i] = 0.0f;
+            static_assert(4 * H == 256, "one bias per thread of the chain waves");
+        }
+        // no adjoints behind the last slot: the first step's products add nothing
+        for (int i = threadIdx.x; i < Bs::kDaBytes / 16; i += 256) reinterpret_cast<uint4 *>(lds + da_at(a.t_end))[i] = make_uint4(0, 0, 0, 0);
+
+        const uint32_t carry_at = (uint32_t)(row0 + r8) * H + unit0;      // rows past the end have room too (16 is a multiple of 8)
+        Pair carry = {};
+        if (a.t_end < T) {
+            carry.v[0] = a.carry[carry_at];
+            carry.v[1] = a.carry[carry_at + 1];
+        }
+#pragma unroll
+        for (int ks = 0; ks < 3 * KS; ++ks) { settle(whhT[ks]); settle(wihT[ks]); }
+        asm volatile("" : "+v"(carry.v[0]), "+v"(carry.v[1]));
+
+        const int mine_at = publish_at(r8, unit0);
+        // what is to be stored, for the gate waves
+        auto leave = [&](int at, const Pair &x) {
+            if constexpr (P == 1) {
+                bf16x2 v;
+                v[0] = (__bf16)x.v[0]; v[1] = (__bf16)x.v[1];
+                *reinterpret_cast<bf16x2 *>(lds + at + unit0 * kElem) = v;
+            } else {
+                *reinterpret_cast<f32x2 *>(lds + at + unit0 * kElem) = f32x2{x.v[0], x.v[1]};
+            }
+        };
+        auto back_product = [&](int t) {                           // carry += W_hh^T adjoints(t); dpre1 of slot t, before the ReLU
+            f32x4 acch = {0.0f, 0.0f, 0.0f, 0.0f}, accx = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < 3 * KS; ++ks) {
+                const bf16x8 di = operand(da_at(t), ks), dhid = ks < 2 * KS ? di : operand(da_at(t), ks + KS);
+                product(acch, whhT[ks], dhid);
+                product(accx, wihT[ks], di);
+            }
+            const Pair h = mine(acch);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) carry.v[i] += h.v[i];
+            leave(Bs::oPre + (t & 1) * Bs::kPreBytes + r8 * Bs::kPrePitch, mine(accx));
+        };
+        auto step = [&](int t) {
+            const uint2 about = *row_of(t, r8);
+            const float gq = __uint_as_float(about.x);
+            const char *const w2_at = lds + Bs::oW2 + (int)about.y * Bs::kW2Pitch + unit0 * kElem;
+            f32x2 w2;
+            if constexpr (P == 1) {
+                const uint32_t two = *reinterpret_cast<const uint32_t *>(w2_at);
+                w2 = f32x2{__uint_as_float(two << 16), __uint_as_float(two & 0xFFFF0000u)};
+            } else {
+                w2 = *reinterpret_cast<const f32x2 *>(w2_at);
+            }
+            f32x2 fac[Bs::kFactors];
+#pragma unroll
+            for (int f = 0; f < Bs::kFactors; ++f) fac[f] = *fac_of(t, f);
+            back_product(t + 1);
+            Pair dan, dar, daz, dahn;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float dht = carry.v[i] + gq * w2[i];         // Q_t[u] = W2[u] . h_t + b2[u]
+                dan.v[i] = dht * fac[0][i];
+                dahn.v[i] = dan.v[i] * fac[1][i];
+                dar.v[i] = dan.v[i] * fac[2][i];
+                daz.v[i] = dht * fac[3][i];
+                carry.v[i] = dht * fac[4][i];
+            }
+            publish(da_at(t) + 0 * KS * kFrag + mine_at, dar);
+            publish(da_at(t) + 1 * KS * kFrag + mine_at, daz);
+            publish(da_at(t) + 2 * KS * kFrag + mine_at, dan);
+            publish(da_at(t) + 3 * KS * kFrag + mine_at, dahn);
+            const int out = Bs::oOut + (t & 1) * Bs::kOutBytes + r8 * Bs::kOutPitch;
+            leave(out + 0 * H * kElem, dan);
+            leave(out + 1 * H * kElem, dar);
+            leave(out + 2 * H * kElem, daz);
+            leave(out + 3 * H * kElem, dahn);
+            lds_barrier();
+        };
+        lds_barrier();                                             // biases, zeros, the last slot's x and h
+        lds_barrier();                                             // its factors
+        for (int t = a.t_end - 1; t >= a.t_begin; --t) step(t);
+        back_product(a.t_begin);
+        lds_barrier();                                             // the last dpre1
+        if (a.t_begin > 0) {
+            a.carry[carry_at] = carry.v[0];
+            a.carry[carry_at + 1] = carry.v[1];
+        }
+    } else if (wave < 8) {
+        // ---------------------------------------------------------------- gate wave
+        WFrag<P> whh[3][KS], wih[3][KS];
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const size_t at = ((size_t)((gate * FBK + w) * KS + ks) * P) * 64 + lane;
+                whh[gate][ks] = load_wfrag<P>(net.whh_16 + at);
+                wih[gate][ks] = load_wfrag<P>(net.wih_16 + at);
+            }
+        // (two planes: the bias of a unit in one of a row's two columns)
+        const float *const bias = P == 2 && side ? bias_lds + 4 * H : bias_lds + 16 * w + 4 * q4;
+        const int bias_step = P == 2 && side ? 0 : H;
+        auto gates = [&](int t) {
+            f32x4 acc_r = *reinterpret_cast<const f32x4 *>(bias), acc_z = *reinterpret_cast<const f32x4 *>(bias + bias_step);
+            f32x4 acc_in = *reinterpret_cast<const f32x4 *>(bias + 2 * bias_step), acc_hn = *reinterpret_cast<const f32x4 *>(bias + 3 * bias_step);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const bf16x8 hb = operand(Bs::oH + (t & 1) * KS * kFrag, ks), xb = operand(Bs::oX + (t & 1) * KS * kFrag, ks);
+                product(acc_r, whh[0][ks], hb);
+                product(acc_z, whh[1][ks], hb);
+                product(acc_hn, whh[2][ks], hb);
+                product(acc_in, wih[2][ks], xb);
+                product(acc_r, wih[0][ks], xb);
+                product(acc_z, wih[1][ks], xb);
+            }
+            const f32x2 hp = *reinterpret_cast<const f32x2 *>(lds + Bs::oHf + (t & 1) * Bs::kHfBytes + r8 * Bs::kHfPitch + unit0 * 4);
+            const Pair pr = mine(acc_r), pz = mine(acc_z), pin = mine(acc_in), phn = mine(acc_hn);
+            f32x2 fac[Bs::kFactors];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float rr = sigmoidf_fast(pr.v[i]), zz = sigmoidf_fast(pz.v[i]);
+                const float nn = tanhf_fast(pin.v[i] + rr * phn.v[i]);
+                fac[0][i] = (1.0f - zz) * (1.0f - nn * nn);        // dL/dh_t -> n
+                fac[1][i] = rr;                                    // n -> n hidden side
+                fac[2][i] = phn.v[i] * rr * (1.0f - rr);           // n -> r
+                fac[3][i] = (hp[i] - nn) * zz * (1.0f - zz);       // dL/dh_t -> z
+                fac[4][i] = zz;                                    // dL/dh_t -> what passes the cell by
+            }
+#pragma unroll
+            for (int f = 0; f < Bs::kFactors; ++f) *fac_of(t, f) = fac[f];
+        };
+#pragma unroll
+        for (int gate = 0; gate < 3; ++gate)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) { settle(whh[gate][ks]); settle(wih[gate][ks]); }
+        lds_barrier();
+        gates(a.t_end - 1);
+        lds_barrier();
+        for (int t = a.t_end - 1; t >= a.t_begin; --t) {
+            gates(t - 1);
+            lds_barrier();
+        }
+        lds_barrier();
+    } else {
+        // ---------------------------------------------------------------- mover
+        // What this wave moves: rows 2 w and 2 w + 1, half its lanes each, two units a lane.
+        const int mr = 2 * w + (lane >> 5), j = lane & 31, mrow = row0 + mr;
+        const bool valid = mrow < rows;
+        const int b = valid ? mrow / N : 0, n = valid ? mrow % N : 0;
+        const uint32_t bt0 = (uint32_t)b * T, btn0 = bt0 * N + n;  // the host bounds 4 H samples to 2^30
+        const size_t samples = (size_t)rows * T;
+        auto buffer = [&](void *p, size_t per_sample) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(uint32_t)(samples * per_sample * kElem), kRawBuffer); };
+        const __amdgpu_buffer_rsrc_t da_buf = buffer(a.da, 4 * H), dq_buf = buffer(a.dq, a.a16), pre_buf = buffer(a.dpre1, H);
+        // A store's offset: the lane's own part (past every array, where the store is to be dropped), and the slot's, the same in
+        // every lane.  da: two planes, a row per access, 16 bytes a lane; one plane, both rows.
+        constexpr uint32_t kPast = 0x80000000u;
+        uint32_t da_lane[P];
+        int da_from[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int r = P == 2 ? 2 * w + i : mr, piece = P == 2 ? lane : j;
+            const bool there = row0 + r < rows;
+            const int rb = there ? (row0 + r) / N : 0, rn = there ? (row0 + r) % N : 0;
+            da_lane[i] = there ? ((uint32_t)rb * T * N + rn) * 4 * H * kElem + 16 * piece : kPast;
+            da_from[i] = Bs::oOut + r * Bs::kOutPitch + 16 * piece;
+        }
+        const uint32_t pre_lane = valid ? (btn0 * H + 2 * j) * kElem : kPast, dq_lane = valid && 2 * j < a.a16 ? (btn0 * a.a16 + 2 * j) * kElem : kPast;
+        const uint32_t da_slot = (uint32_t)N * 4 * H * kElem, pre_slot = (uint32_t)N * H * kElem, dq_slot = (uint32_t)N * a.a16 * kElem;
+        auto store2 = [](const Pair &x, const __amdgpu_buffer_rsrc_t &buf, uint32_t lane_at, uint32_t slot_at) {
+            if constexpr (P == 1) {
+                bf16x2 v;
+                v[0] = (__bf16)x.v[0]; v[1] = (__bf16)x.v[1];
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), buf, lane_at, slot_at, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(x.v[0]), __float_as_uint(x.v[1])}, buf, lane_at, slot_at, 0);
+            }
+        };
+        uint32_t positive = 0;                                     // x > 0 of the lane's units, slots put down last in the low bits
+        // what the chain left in the step of slot t: adjoints(t), dpre1 of slot t+1
+        auto store_pre = [&](int t, int age) {                     // age: slots put down since that one
+            const int from = Bs::oPre + (t & 1) * Bs::kPreBytes + mr * Bs::kPrePitch + 2 * j * kElem;
+            const uint32_t at = t < a.t_end ? pre_lane : kPast, slot_at = (uint32_t)min(t, T - 1) * pre_slot, on = positive >> (2 * age);
+            if constexpr (P == 1) {
+                const uint32_t v = *reinterpret_cast<const uint32_t *>(lds + from);
+                __builtin_amdgcn_raw_buffer_store_b32(v & ((on & 1u ? 0xFFFFu : 0u) | (on & 2u ? 0xFFFF0000u : 0u)), pre_buf, at, slot_at, 0);
+            } else {
+                const f32x2 v = *reinterpret_cast<const f32x2 *>(lds + from);
+                store2(Pair{on & 1u ? v[0] : 0.0f, on & 2u ? v[1] : 0.0f}, pre_buf, at, slot_at);
+            }
+        };
+        auto store_left = [&](int t) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(lds + da_from[i] + (t & 1) * Bs::kOutBytes);
+                // (the slot's part not as a scalar offset: see the 16-byte stores of bptt_back_roles_kernel)
+                __builtin_amdgcn_raw_buffer_store_b128(v, da_buf, t < a.t_end ? da_lane[i] + (uint32_t)t * da_slot : kPast, 0, 0);
+            }
+        };
+
+        using XRegs = std::conditional_t<P == 1, uint32_t, f32x2>;
+        struct In { f32x2 h; XRegs x; float gq_raw; uint8_t fil; int u; };
+        const uint32_t saved0 = ((uint32_t)b * S * N + n) * H + 2 * j;
+        auto fetch = [&](In &in, int t) {
+            const uint32_t ts = (uint32_t)max(t, 0), at = saved0 + ts * (uint32_t)(N * H), sample = btn0 + ts * N;
+            in.h = *reinterpret_cast<const f32x2 *>(reinterpret_cast<const char *>(a.h_all) + at * 4u);
+            in.x = *reinterpret_cast<const XRegs *>(static_cast<const char *>(a.x_all) + at * (uint32_t)kElem);
+            in.fil = a.filled[bt0 + ts];
+            in.gq_raw = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.grad_q) + sample * 4u);
+            in.u = *reinterpret_cast<const int *>(reinterpret_cast<const char *>(a.actions) + sample * 4u);
+        };
+        auto arrived = [](In &in) {
+            asm volatile("" : "+v"(in.h), "+v"(in.x));
+            asm volatile("" ::"v"((uint32_t)in.fil));
+            asm volatile("" : "+v"(in.gq_raw), "+v"(in.u));
+        };
+        const int moved_at = publish_at(mr, 2 * j);
+        auto put_down = [&](const In &in, int t) {
+            publish(Bs::oH + (t & 1) * KS * kFrag + moved_at, Pair{in.h[0], in.h[1]});
+            *reinterpret_cast<f32x2 *>(lds + Bs::oHf + (t & 1) * Bs::kHfBytes + mr * Bs::kHfPitch + 8 * j) = in.h;
+            if constexpr (P == 1) {                                // x stays the bf16 that it is in memory: an operand as it lies
+                *reinterpret_cast<uint32_t *>(lds + Bs::oX + (t & 1) * KS * kFrag + moved_at) = in.x;
+                positive = positive << 2 | (__uint_as_float(in.x << 16) > 0.0f ? 1u : 0u) | (__uint_as_float(in.x & 0xFFFF0000u) > 0.0f ? 2u : 0u);
+            } else {
+                publish(Bs::oX + (t & 1) * KS * kFrag + moved_at, Pair{in.x[0], in.x[1]});
+                positive = positive << 2 | (in.x[0] > 0.0f ? 1u : 0u) | (in.x[1] > 0.0f ? 2u : 0u);
+            }
+            // (What passes through the empty asm is used here and not earlier: the compiler would widen `filled` where it is
+            // loaded, and wait there.)
+            uint32_t fil = in.fil;
+            int u = in.u;
+            float gq = in.gq_raw;
+            asm volatile("" : "+v"(fil), "+v"(u), "+v"(gq));
+            gq = valid && fil ? gq : 0.0f;
+            u = min(max(u, 0), A - 1);
+            *row_of(t, mr) = make_uint2(__float_as_uint(gq), (uint32_t)u);      // (every lane of the row has the same to say)
+            // the adjoint of Q_t, dense
+            store2(Pair{u == 2 * j ? gq : 0.0f, u == 2 * j + 1 ? gq : 0.0f}, dq_buf, t >= a.t_begin ? dq_lane : kPast, (uint32_t)max(t, 0) * dq_slot);
+        };
+        // In turn: slot t-2's, the one asked for.  Two steps a round; an odd one comes first, from a set of its own.  (A way out of
+        // the middle of the loop the compiler leads through the loop's end, and what was asked for last on that way is then waited
+        // for at the head of every round.)
+        const int odd = (a.t_end - a.t_begin) & 1;
+        In first, set_a, set_b;
+        fetch(first, a.t_end - 1);
+        fetch(set_a, a.t_end - 2);
+        arrived(first);
+        put_down(first, a.t_end - 1);
+        fetch(first, a.t_end - 3);
+        fetch(set_b, a.t_end - 3 - odd);
+        lds_barrier();
+        arrived(set_a);
+        put_down(set_a, a.t_end - 2);
+        lds_barrier();
+        // In the step of slot t slots down to t-1 are put down: slot t+2 is three before the last.
+        auto step = [&](const In &next, int t) {
+            store_left(t + 1);
+            store_pre(t + 2, 3);
+            put_down(next, t - 2);
+            lds_barrier();
+        };
+        arrived(first);
+        arrived(set_b);
+        if (odd) step(first, a.t_end - 1);
+        for (int t = a.t_end - 1 - odd; t >= a.t_begin; t -= 2) {
+            fetch(set_a, t - 3);
+            __builtin_amdgcn_sched_barrier(0);
+            step(set_b, t);
+            fetch(set_b, t - 4);
+            __builtin_amdgcn_sched_barrier(0);
+            step(set_a, t - 1);
+        }
+        store_left(a.t_begin);
+        store_pre(a.t_begin + 1, 3);
+        lds_barrier();
+        store_pre(a.t_begin, 2);
     }
 }
 
@@ -1613,9 +2005,9 @@ Plan make_plan(const NetFrags &net, int B, int T)
 }
 
 template <auto kKernel>
-hipError_t back_dispatch(const BpttArgs &a, int threads, size_t lds_bytes, hipStream_t stream)
+hipError_t back_dispatch(const BpttArgs &a, int tile_rows, int threads, size_t lds_bytes, hipStream_t stream)
 {
-    const int tiles = (a.B * a.net.N + 15) / 16;
+    const int tiles = (a.B * a.net.N + tile_rows - 1) / tile_rows;
     hipError_t err = allow_large_lds<kKernel>(kLdsLimit);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kKernel, dim3(tiles), dim3(threads), lds_bytes, stream, a);
@@ -1841,11 +2233,14 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     a.h_all = h_all; a.x_all = x_all; a.da = da; a.dpre1 = dpre1; a.dq = dq;
     a.carry = reinterpret_cast<float *>(ws + plan.off_carry);
     const bool roles = H == 128 && net.planes == 1;
+    bool eights = false;                                           // 64 units: tiles of eight rows
     auto reverse = [&](int t_begin, int t_end, hipStream_t on) {
         a.t_begin = t_begin; a.t_end = t_end;
-        if (H == 64 && net.planes == 2) return back_dispatch<bptt_back_split_kernel<2>>(a, 512, BpttSplit<2>::kBytes, on);
-        if (H == 64 && net.planes == 1) return back_dispatch<bptt_back_split_kernel<1>>(a, 512, BpttSplit<1>::kBytes, on);
-        if (roles) return back_dispatch<bptt_back_roles_kernel>(a, BpttRoles::kThreads, BpttRoles::lds_bytes(A), on);
+        if (H == 64 && net.planes == 2) return eights ? back_dispatch<bptt_back_split8_kernel<2>>(a, 8, BpttSplit8<2>::kThreads, BpttSplit8<2>::lds_bytes(A), on)
+                                                      : back_dispatch<bptt_back_split_kernel<2>>(a, 16, 512, BpttSplit<2>::kBytes, on);
+        if (H == 64 && net.planes == 1) return eights ? back_dispatch<bptt_back_split8_kernel<1>>(a, 8, BpttSplit8<1>::kThreads, BpttSplit8<1>::lds_bytes(A), on)
+                                                      : back_dispatch<bptt_back_split_kernel<1>>(a, 16, 512, BpttSplit<1>::kBytes, on);
+        if (roles) return back_dispatch<bptt_back_roles_kernel>(a, 16, BpttRoles::kThreads, BpttRoles::lds_bytes(A), on);
         return hipErrorInvalidValue;
     };
 
@@ -1889,6 +2284,11 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
         late = products_of(t_mid, T); early = products_of(0, t_mid);
         for (int i = 0; i < 4 && split; ++i) split = tn_wide_fits(late.p[i], cut_late.samples) && tn_wide_fits(early.p[i], cut_early.samples);
     }
+    // Tiles of eight rows where each has a compute unit of its own; beside products on the second stream, where enough are left for
+    // those (three eighths).  Learner iteration, us, tiles of 16 / of 8, 60 slots: fp32 2048 rows 368 / 343, 1536 328 / 301, 35 220 /
+    // 192; bf16 in two launches 1920 rows 257 / 262, 1536 245 / 248, 1200 238 / 236, 800 219 / 206, 200 x 200 slots 420 / 330, in
+    // one (15 slots) 2048 rows 149 / 144.
+    eights = (B * N + 7) / 8 <= (split ? n_cu * 5 / 8 : n_cu);
     if (!split) {
         err = reverse(0, T, stream);
         if (err != hipSuccess) return err;
