@@ -109,31 +109,32 @@ __device__ __forceinline__ void store_adjoints(const f32x4 &v, const __amdgpu_bu
 // is a chain; the gates of a slot hang on nothing behind them.  Twelve waves, three per SIMD, 168 registers each: in the step
 // of slot t
 //
-//   gate waves 0..7    (16 units each, W_hh and W_ih in registers) the gates of slot t-1 -> five factors per unit, in LDS; the
-//                      adjoint of Q; x and h of slot t-2 to LDS as operand, the loads of slot t-3
+//   gate waves 0..7    (16 units each, W_hh and W_ih in registers) the gates of slot t-1 -> five factors per unit, in LDS; moving two
+//                      rows each, what the chain left in LDS in the step before to memory, x and h of slot t-2 to LDS as operand, the
+//                      loads of slot t-3
 //   chain waves 8..11  (32 units each, W_hh^T in registers) dL/dh_t = carry + W_hh^T adjoints(t+1), then slot t's adjoints from
-//                      its factors, to LDS as operand and to memory; nothing that they wait for comes from memory
+//                      its factors, to LDS as operand; to memory what LDS has no room for, n's and the adjoint of Q
 //
 // and ONE barrier per slot.  Every LDS buffer is double-buffered on the parity of its slot: written in one step, read in the
 // next, written again only in the one after.  The adjoint of fc1's pre-activation, which nothing in the chain hangs on either,
 // is formed from the stored adjoints where the W_ih product reads them (gru_products_kernel): its weights have no room here.
 //
-// What bounds it: instruction issue on the SIMDs (265 vector and 72 matrix instructions each per slot) and the address unit,
-// 40 accesses to memory per slot.  A hundred slots of 64 episodes x 32 agents, kernel trace: one role of eight waves with two
-// barriers a slot, which formed that adjoint too, 249 us; this with the chain's stores half as wide, and the rows' scalars read
-// by every gate wave 192; the adjoints stored as operands lie, 16 bytes a lane, and the scalars read by the chain 160.  The
-// gates' products a slot ahead of their factors, so that one wave's vector instructions meet another's matrix instructions:
-// 206 before those two changes, more registers than there are.  Both roles' registers are full: what is asked for is asked for
-// little by little (sched_barrier), or the weights spill.
+// What bounds it: instruction issue on the SIMDs, some 290 vector and 72 matrix instructions each per slot, which overlap only
+// where waves are in different parts of their step: gate waves 4..7 move first and multiply then, the others the other way round.
+// A hundred slots of 64 episodes x 32 agents, kernel trace: one role of eight waves with two barriers a slot, which formed that
+// adjoint too, 249 us; two roles, stores of 8 bytes a lane, and the rows' scalars read by every gate wave 192; adjoints stored as
+// operands lie, 16 bytes a lane, and the scalars read by the chain 160; the gate waves' accesses row by row 154; their two
+// orders 145.  The gates' products a slot ahead of their factors in all gate waves: 206 instead of 192, more registers than there
+// are.  Both roles' registers are full: what is asked for is asked for little by little (sched_barrier), or the weights spill.
 struct BpttRoles {
     static constexpr int H = 128, KS = H / 32, FBK = H / 16, kFrag = 1024, kGate = FBK, kChain = KS, kThreads = 64 * (kGate + kChain);
     static constexpr int kFactors = 5;
     static constexpr int oH = 0, oX = oH + 2 * KS * kFrag, oDa = oX + 2 * KS * kFrag, kDaBytes = 3 * KS * kFrag;      // r, z, n hidden side
     static constexpr int oFac = oDa + 2 * kDaBytes, kFacBytes = kFactors * FBK * 1024;
     static constexpr int oBias = oFac + 2 * kFacBytes;             // biases r, z, n input side, n hidden side
-    static constexpr int oHf = oBias + 4 * H * 4, kHfBytes = FBK * 1024;              // h in fp32, for the blend
-    // W2, whose row of the chosen action the chain adds: bf16 (what the table holds exactly), rows 32 bytes past a multiple of 256
-    static constexpr int oW2 = oHf + 2 * kHfBytes, kW2Pitch = 2 * H + 32;
+    static constexpr int oHf = oBias + 4 * H * 4, kHfPitch = H * 4 + 16, kHfBytes = 16 * kHfPitch;      // h in fp32, row by row, for the blend
+    // W2, whose row of the chosen action the chain adds: bf16 (what the table holds exactly)
+    static constexpr int oW2 = oHf + 2 * kHfBytes, kW2Pitch = 2 * H + 16;
     static constexpr int lds_bytes(int A) { return oW2 + A * kW2Pitch; }
 };
 
@@ -142,7 +143,6 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
     using Bs = BpttRoles;
     constexpr int H = Bs::H, KS = Bs::KS, FBK = Bs::FBK, kFrag = Bs::kFrag;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    typedef bf16x8 (*FragBuf)[1][64];
     float *const bias_lds = reinterpret_cast<float *>(lds + Bs::oBias);
 
     const NetFrags &net = a.net;
@@ -155,9 +155,13 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
     const int b = valid ? row / N : 0, n = valid ? row % N : 0;
 
     const size_t samples = (size_t)rows * T;
-    auto operand = [&](int at) {                                   // at: byte offset of a fragment
+    // Where an operand keeps column `col` of lane quarter `quarter` in k-step ks: the columns change places from quarter to quarter
+    // and k-step to k-step, or those who have a row's units side by side would all meet in one bank.
+    auto column_at = [](int ks, int quarter, int col) { return quarter * 256 + (((col ^ quarter) * 16) ^ ((ks & 3) * 64)); };
+    const int lane_at = column_at(0, q4, c);
+    auto operand = [&](int at, int ks) {                           // at: byte offset of the first fragment
         Frag<1> f;
-        f.hi = *(reinterpret_cast<const bf16x8 *>(lds + at) + lane);
+        f.hi = *reinterpret_cast<const bf16x8 *>(lds + at + ks * kFrag + (lane_at ^ ((ks & 3) * 64)));
         return f;
     };
     auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
@@ -222,7 +226,7 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
             Frag<1> d[2][2];
             auto request = [&](int pair) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i) d[pair % 2][i] = operand(da_at(t) + (2 * pair + i) * kFrag);
+                for (int i = 0; i < 2; ++i) d[pair % 2][i] = operand(da_at(t), 2 * pair + i);
             };
             constexpr int kPairs = 3 * KS / 2;
             request(0);
@@ -266,18 +270,15 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
                     carry[j][r] = dht * fac[4][r];
                 }
             }
-            const uint32_t slot_at = (uint32_t)t * da_slot;
-            const f32x4 (*const parts[4])[2] = {&dar, &daz, &dahn, &dan};
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const f32x4 (*const parts[3])[2] = {&dar, &daz, &dahn};
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const bf16x8 v = frag_of_pair<1>((*parts[g])[0], (*parts[g])[1]).hi;
-                if (g < 3) *(reinterpret_cast<bf16x8 *>(lds + da_at(t) + (g * KS + w) * kFrag) + lane) = v;
-                // n, r, z, n hidden side.  (The slot's part in the lanes' offset, not in the scalar one: behind a 16-byte store with
-                // a scalar offset the compiler lets the next instruction overwrite the registers that are being stored, and values
-                // of the next instruction's have been stored here.)
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), da_buf, da_lane + slot_at + (g + 1) % 4 * 2 * H, 0, 0);
-            }
+            for (int g = 0; g < 3; ++g)
+                *reinterpret_cast<bf16x8 *>(lds + da_at(t) + (g * KS + w) * kFrag + (lane_at ^ (w * 64))) = frag_of_pair<1>((*parts[g])[0], (*parts[g])[1]).hi;
+            // (the other three go to memory from LDS, for n is no room there.  The slot's part in the lanes' offset, not in the scalar
+            // one: behind a 16-byte store with a scalar offset the compiler lets the next instruction overwrite the registers that
+            // are being stored, and values of the next instruction's have been stored here.)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, frag_of_pair<1>(dan[0], dan[1]).hi), da_buf, da_lane + (uint32_t)t * da_slot, 0, 0);
             typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
             typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
             bf16x4 dq;                                             // the adjoint of Q_t, dense
@@ -313,7 +314,25 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
         }
     } else {
         // ---------------------------------------------------------------- gate wave
-        const int w = wave, unit0 = 16 * w + 4 * q4;               // the lane's four units
+        const int w = wave, unit0 = 16 * w + 4 * q4;               // the lane's four units of a product's result
+        // What this wave moves: rows 2 w and 2 w + 1, half its lanes each, four units a lane: an access whose neighbouring lanes are
+        // different rows, as an operand has them, takes the address unit 64 clocks, one of neighbours side by side 16.
+        const int mr = 2 * w + (lane >> 5), j = lane & 31, mrow = blockIdx.x * 16 + mr;
+        const bool there = mrow < rows;
+        const int mb = there ? mrow / N : 0, mn = there ? mrow % N : 0;
+        const __amdgpu_buffer_rsrc_t da_buf = __builtin_amdgcn_make_buffer_rsrc(a.da, 0, (int)(uint32_t)(samples * 4 * H * 2), kRawBuffer);
+        // r and z of the row, 16 bytes a lane; n of the hidden side on half the lanes
+        const uint32_t da_lane = there ? ((uint32_t)mb * T * N + mn) * 4 * H * 2 + 2 * H + 16 * j : kPast, da_slot = (uint32_t)N * 4 * H * 2;
+        const uint32_t last_lane = there && j < 16 ? da_lane + 2 * 2 * H : kPast;
+        const int piece_at = column_at(j >> 2 & 3, j & 3, mr);     // of 16 bytes j % 16 of a part, in its fragments
+        auto store_left = [&](int t) {                             // adjoints(t), left in LDS by the chain
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const char *const from = lds + da_at(t) + (j >> 2 & 3) * kFrag + piece_at;
+            const u32x4 rz = *reinterpret_cast<const u32x4 *>(from + (j >> 4) * KS * kFrag), nh = *reinterpret_cast<const u32x4 *>(from + 2 * KS * kFrag);
+            const uint32_t slot_at = (uint32_t)t * da_slot;
+            __builtin_amdgcn_raw_buffer_store_b128(rz, da_buf, t < a.t_end ? da_lane + slot_at : kPast, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(nh, da_buf, t < a.t_end ? last_lane + slot_at : kPast, 0, 0);
+        };
         WFrag<1> whh[3][KS], wih[3][KS];
 #pragma unroll
         for (int gate = 0; gate < 3; ++gate)
@@ -325,25 +344,29 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
             }
         // x stays the bf16 that it is in memory: an operand as it lies
         struct In { f32x4 h; uint2 x; };
-        const uint32_t saved0 = ((uint32_t)b * S * N + n) * H + unit0;
+        const uint32_t saved0 = ((uint32_t)mb * S * N + mn) * H + 4 * j;
         auto fetch = [&](In &in, int t) {
             const uint32_t at = saved0 + (uint32_t)max(t, 0) * (uint32_t)(N * H);
             in.h = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(a.h_all) + at * 4u);
             in.x = *reinterpret_cast<const uint2 *>(static_cast<const char *>(a.x_all) + at * 2u);
         };
         auto arrived = [](In &in) { asm volatile("" : "+v"(in.h), "+v"(in.x.x), "+v"(in.x.y)); };
-        auto h_of = [&](int t) { return reinterpret_cast<f32x4 *>(lds + Bs::oHf + (t & 1) * Bs::kHfBytes + w * 1024) + lane; };
+        const int moved_at = (j >> 3) * kFrag + column_at(j >> 3, j & 3, mr) + (j >> 2 & 1) * 8;      // block j / 4, quarter j % 4
         auto put_down = [&](const In &in, int t) {
-            publish_block<1>(reinterpret_cast<FragBuf>(lds + Bs::oH + (t & 1) * KS * kFrag), w, lane, in.h);
-            *h_of(t) = in.h;
-            *reinterpret_cast<uint2 *>(lds + Bs::oX + (t & 1) * KS * kFrag + (w / 2) * kFrag + lane * 16 + (w & 1) * 8) = in.x;
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            bf16x4 hb;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) hb[r] = (__bf16)in.h[r];
+            *reinterpret_cast<bf16x4 *>(lds + Bs::oH + (t & 1) * KS * kFrag + moved_at) = hb;
+            *reinterpret_cast<uint2 *>(lds + Bs::oX + (t & 1) * KS * kFrag + moved_at) = in.x;
+            *reinterpret_cast<f32x4 *>(lds + Bs::oHf + (t & 1) * Bs::kHfBytes + mr * Bs::kHfPitch + 16 * j) = in.h;
         };
         auto gates = [&](int t) {
             f32x4 acc_r = load_feature4(bias_lds, w, q4), acc_z = load_feature4(bias_lds + H, w, q4);
             f32x4 acc_in = load_feature4(bias_lds + 2 * H, w, q4), acc_hn = load_feature4(bias_lds + 3 * H, w, q4);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const Frag<1> hb = operand(Bs::oH + ((t & 1) * KS + ks) * kFrag), xb = operand(Bs::oX + ((t & 1) * KS + ks) * kFrag);
+                const Frag<1> hb = operand(Bs::oH + (t & 1) * KS * kFrag, ks), xb = operand(Bs::oX + (t & 1) * KS * kFrag, ks);
                 mma16<1>(acc_r, whh[0][ks], hb);
                 mma16<1>(acc_z, whh[1][ks], hb);
                 mma16<1>(acc_hn, whh[2][ks], hb);
@@ -351,7 +374,7 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
                 mma16<1>(acc_z, wih[1][ks], xb);
                 mma16<1>(acc_in, wih[2][ks], xb);
             }
-            const f32x4 hp = *h_of(t);
+            const f32x4 hp = *reinterpret_cast<const f32x4 *>(lds + Bs::oHf + (t & 1) * Bs::kHfBytes + c * Bs::kHfPitch + unit0 * 4);
             f32x4 fac[Bs::kFactors];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -385,8 +408,10 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
         put_down(set_a, a.t_end - 2);
         lds_barrier();
         auto step = [&](const In &next, int t) {
-            gates(t - 1);
+            if (w < 4) gates(t - 1);                               // (a SIMD has one wave of either order)
+            store_left(t + 1);
             put_down(next, t - 2);
+            if (w >= 4) gates(t - 1);
             lds_barrier();
         };
         arrived(first);
@@ -400,6 +425,7 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
             __builtin_amdgcn_sched_barrier(0);
             step(set_a, t - 1);
         }
+        store_left(a.t_begin);
     }
 }
 
