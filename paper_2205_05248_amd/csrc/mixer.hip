@@ -1081,9 +1081,8 @@ int mixer_update(marl_mixer *m, float *weights, const float *grad_weights, float
         m->table_entries = F + M + 1;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    hipError_t err = marl::launch_sgd_and_fragments(weights, grad_weights, lr, n_params, m->repack_map, m->frag_elems, m->image, stream, rule);
-    if (err == hipSuccess)
-        err = marl::launch_copy_refresh(weights, m->repack_map + m->frag_elems, m->table_entries, const_cast<float *>(m->bias), stream);
+    const hipError_t err = marl::launch_sgd_and_image(weights, grad_weights, lr, n_params, m->repack_map, m->frag_elems, m->image,
+                                                      m->repack_map + m->frag_elems, m->table_entries, const_cast<float *>(m->bias), stream, rule);
     if (err != hipSuccess) return marl::report_device_error(err, "mixer update launch");
     return MARL_OK;
 }

@@ -86,16 +86,18 @@ __device__ __forceinline__ void repack_frag_element(const float *w, const int32_
     image[e] = (uint16_t)out;
 }
 
-__global__ void repack_frag_kernel(const float *w, const int32_t *map, uint16_t *image, size_t n)
+// A mixer's whole image from its updated weights in one launch: the first frag_blocks workgroups rebuild the fragment part, the
+// others the fp32 tables, plain copies of parameters: dst[i] = w[src[i]].  (Two launches: 2 to 3 us more per update, whatever the
+// sizes; a learner iteration of 4 episodes x 60 slots x 3 agents is a hundred and sixty.)
+__global__ void repack_mixer_kernel(const float *w, const int32_t *map, uint16_t *image, size_t n, unsigned frag_blocks,
+                                    const int32_t *src, float *dst, size_t entries)
 {
-    repack_frag_element(w, map, image, n, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
-}
-
-// fp32 tables that are plain copies of parameters: dst[i] = w[src[i]]
-__global__ void copy_map_kernel(const float *w, const int32_t *src, float *dst, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = w[src[i]];
+    if (blockIdx.x < frag_blocks) {
+        repack_frag_element(w, map, image, n, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
+    } else {
+        const size_t i = (size_t)(blockIdx.x - frag_blocks) * blockDim.x + threadIdx.x;
+        if (i < entries) dst[i] = w[src[i]];
+    }
 }
 
 struct TableArgs {
@@ -218,22 +220,18 @@ bool repack_map_reproduces_packer(const marl_qnet_desc &desc, const float *weigh
     return same;
 }
 
-hipError_t launch_sgd_and_fragments(float *weights, const float *grad, float lr, size_t n_params, const int32_t *map_dev,
-                                    size_t map_elems, void *image_dev, hipStream_t stream, const UpdateRule &rule)
+hipError_t launch_sgd_and_image(float *weights, const float *grad, float lr, size_t n_params, const int32_t *map_dev, size_t map_elems,
+                                void *image_dev, const int32_t *table_src_dev, size_t table_entries, float *table_dev, hipStream_t stream,
+                                const UpdateRule &rule)
 {
     const dim3 grid((unsigned)((n_params + 255) / 256));
     if (rule.sq_avg) hipLaunchKernelGGL(rmsprop_kernel, grid, dim3(256), 0, stream, weights, grad, rule.sq_avg, lr, rule.alpha, rule.eps, n_params);
     else hipLaunchKernelGGL(sgd_kernel, grid, dim3(256), 0, stream, weights, grad, lr, n_params);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(repack_frag_kernel, dim3((unsigned)((map_elems + 255) / 256)), dim3(256), 0, stream, weights, map_dev,
-                       static_cast<uint16_t *>(image_dev), map_elems);
-    return hipGetLastError();
-}
-
-hipError_t launch_copy_refresh(const float *weights, const int32_t *src_dev, size_t n, float *dst, hipStream_t stream)
-{
-    hipLaunchKernelGGL(copy_map_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, weights, src_dev, dst, n);
+    const unsigned frag_blocks = (unsigned)((map_elems + 255) / 256), table_blocks = (unsigned)((table_entries + 255) / 256);
+    hipLaunchKernelGGL(repack_mixer_kernel, dim3(frag_blocks + table_blocks), dim3(256), 0, stream, weights, map_dev,
+                       static_cast<uint16_t *>(image_dev), map_elems, frag_blocks, table_src_dev, table_dev, table_entries);
     return hipGetLastError();
 }
 
