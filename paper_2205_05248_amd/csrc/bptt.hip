@@ -2316,13 +2316,15 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
     // one (15 slots) 2048 rows 149 / 144.
     eights = (B * N + 7) / 8 <= (split ? n_cu * 5 / 8 : n_cu);
     if (!split) {
+        const SampleChunks &cut = plan.cut.gru_whole;
+        const size_t part = (size_t)cut.chunks * kGruRows * kGruColumns;
+        if (roles && 2 * part * sizeof(float) > plan.partial_bytes) return hipErrorInvalidValue;
         err = reverse(0, T, stream);
         if (err != hipSuccess) return err;
         const Four all = products_of(0, T);
         int done = 0;
         if (roles) {
-            const SampleChunks &cut = plan.cut.gru_whole;
-            float *const parts[2] = {partial, partial + (size_t)cut.chunks * kGruRows * kGruColumns};
+            float *const parts[2] = {partial, partial + part};
             err = launch_gru_products(a, 0, T, cut, parts[0], parts[1], stream);
             if (err != hipSuccess) return err;
             TnReduceBatch red{};

@@ -100,8 +100,7 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
     g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, M <= 2560 ? 64 : 128);
     g.room = g.whole.chunks;
     // 64 chunks of four workgroups each are the chip's compute units once.
-    auto cut_gru = [](long samples) { return cut_samples(samples, 64, 64); };
-    g.gru_whole = cut_gru(M);
+    auto cut_gru = [](long samples, long most) { return cut_samples(samples, std::min(64L, most), 64); };
     if (planes == 1 && T >= kForkSlots) {
         // the later half's products share the chip with the recurrence, whose workgroups hold half the compute units
         // or less: half as many chunks.  The earlier half's too: its two GRU products then run side by side, one on
@@ -114,9 +113,12 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
         // episodes x 200 slots x 32 agents 1196 us for the learner iteration, with 32 1191; 64 x 120 x 8 466 / 458, 9 x 200 x 32
         // 698 / 688)
         g.gru_late = cut_samples(rows * (T - g.t_mid), 32, 64);
-        g.gru_early = cut_gru(rows * g.t_mid);
+        g.gru_early = cut_gru(rows * g.t_mid, 64);
         g.room = std::max(g.room, g.late.chunks + g.early.chunks);
     }
+    // No more than there is room for, or a workspace that holds the other products' partial sums would not hold these: fewer than
+    // kForkSlots slots and 2561 to 4096 samples, half as many chunks, of 128 samples, as the other products have.
+    g.gru_whole = cut_gru(M, g.room);
     return g;
 }
 

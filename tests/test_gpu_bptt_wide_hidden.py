@@ -33,3 +33,24 @@ def test_gradient_at_the_edges_of_the_wide_backward_pass(B, T, N, D, A):
     bptt.compare(cfg, got, *bptt.oracle_grad(cfg, w, u, g))
     assert (bptt.gpu_grad(net, cfg, u, g) == got).all()
     net.close()
+
+
+GUARD_BYTES = 32 << 20             # more than the partial sums of both GRU products, 64 chunks of 384 x 144 each, take
+
+
+@pytest.mark.parametrize("B,T,N,D,A", [(197, 13, 1, 8, 5), (64, 10, 5, 12, 6), (270, 5, 3, 12, 6), (273, 15, 1, 8, 64), (4, 16, 41, 8, 5)])
+def test_nothing_is_written_behind_the_workspace(B, T, N, D, A):
+    """One launch and 2561 to 4096 samples, where the GRU products would take more chunks than the other products and the
+    workspace's end is theirs; the last shape in two launches."""
+    cfg = dict(wl.config(4), N=N, D=D, A=A, H=128, dtype="bf16", B=B, T=T)
+    w = wl.make_weights(cfg, 0)
+    u = wl.make_unroll_inputs(cfg, B=B, T=T)
+    # one sign: the sums grow with the samples as the oracle's ambiguity budget does
+    g = np.abs(np.random.default_rng([B, T, N]).normal(size=(B, T, N))).astype(np.float32)
+    net = binding.QNet(wl.dims(cfg), w, "bf16")
+    need = net.grad_workspace_bytes(B, T)
+    block = torch.full((need + GUARD_BYTES,), 0xA5, dtype=torch.uint8, device="cuda")
+    got = bptt.gpu_grad(net, cfg, u, g, workspace=block[:need])
+    assert (block[need:] == 0xA5).all()
+    bptt.compare(cfg, got, *bptt.oracle_grad(cfg, w, u, g))
+    net.close()
