@@ -42,6 +42,7 @@
 
 #include "fused16_roles.h"
 #include "grad_chunks.h"
+#include "store_offsets.h"
 
 namespace marl {
 
@@ -82,11 +83,6 @@ __device__ __forceinline__ void publish_block(bf16x8 (*dst)[P][64], int w, int l
     *reinterpret_cast<bf16x4 *>(at) = hi;
     if constexpr (P == 2) *reinterpret_cast<bf16x4 *>(at + 1024) = lo;
 }
-
-// Every global access inside the loops over the slots is unconditional, so that their bodies are straight-line code and
-// the waits for the prefetched inputs count exactly the stores issued after them: rows past the end store through
-// buffer descriptors at an offset beyond the descriptor, which the hardware drops.
-constexpr uint32_t kDrop = 0xFFFFFFF0u;
 
 // Four adjoints of one lane -> element offset `at` of the array behind `buf`, fp32 or, for a one-plane network, bf16.
 template <int P>
@@ -167,9 +163,7 @@ __global__ __launch_bounds__(BpttRoles::kThreads, BpttRoles::kThreads / 256) voi
     auto da_at = [](int t) { return Bs::oDa + (t & 1) * Bs::kDaBytes; };
     auto fac_of = [&](int t, int f, int blk) { return reinterpret_cast<f32x4 *>(lds + Bs::oFac + (t & 1) * Bs::kFacBytes + (f * FBK + blk) * 1024) + lane; };
     const uint32_t bt0 = (uint32_t)b * T, btn0 = bt0 * N + n;      // the host bounds 4 H samples to 2^30
-    // A store's offset: the lane's own part (past every array, where the store is to be dropped), and the slot's, the same in
-    // every lane.
-    constexpr uint32_t kPast = 0x80000000u;
+    // A store's offset: the lane's own part (kPast, where the store is to be dropped), and the slot's, the same in every lane.
 
     for (int i = threadIdx.x; i < 4 * H; i += Bs::kThreads) {
         const int gate = i / H, j = i % H;
@@ -965,17 +959,18 @@ __global__ __launch_bounds__(BpttSplit8<P>::kThreads, BpttSplit8<P>::kThreads / 
         const size_t samples = (size_t)rows * T;
         auto buffer = [&](void *p, size_t per_sample) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(uint32_t)(samples * per_sample * kElem), kRawBuffer); };
         const __amdgpu_buffer_rsrc_t da_buf = buffer(a.da, 4 * H), dq_buf = buffer(a.dq, a.a16), pre_buf = buffer(a.dpre1, H);
-        // A store's offset: the lane's own part (past every array, where the store is to be dropped), and the slot's, the same in
-        // every lane.  da: two planes, a row per access, 16 bytes a lane; one plane, both rows.
-        constexpr uint32_t kPast = 0x80000000u;
-        uint32_t da_lane[P];
+        // A store's offset: the lane's own part (dpre1 and the adjoint of Q: kPast, where the store is to be dropped), and the slot's,
+        // the same in every lane.  da, of which kPast may be in the middle in fp32, has a mask beside them; two planes, a row per
+        // access, 16 bytes a lane; one plane, both rows.
+        uint32_t da_lane[P], da_drop[P];
         int da_from[P];
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             const int r = P == 2 ? 2 * w + i : mr, piece = P == 2 ? lane : j;
             const bool there = row0 + r < rows;
             const int rb = there ? (row0 + r) / N : 0, rn = there ? (row0 + r) % N : 0;
-            da_lane[i] = there ? ((uint32_t)rb * T * N + rn) * 4 * H * kElem + 16 * piece : kPast;
+            da_lane[i] = ((uint32_t)rb * T * N + rn) * 4 * H * kElem + 16 * piece;
+            da_drop[i] = there ? 0u : kDrop;
             da_from[i] = Bs::oOut + r * Bs::kOutPitch + 16 * piece;
         }
         const uint32_t pre_lane = valid ? (btn0 * H + 2 * j) * kElem : kPast, dq_lane = valid && 2 * j < a.a16 ? (btn0 * a.a16 + 2 * j) * kElem : kPast;
@@ -1007,7 +1002,7 @@ __global__ __launch_bounds__(BpttSplit8<P>::kThreads, BpttSplit8<P>::kThreads / 
             for (int i = 0; i < P; ++i) {
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(lds + da_from[i] + (t & 1) * Bs::kOutBytes);
                 // (the slot's part not as a scalar offset: see the 16-byte stores of bptt_back_roles_kernel)
-                __builtin_amdgcn_raw_buffer_store_b128(v, da_buf, t < a.t_end ? da_lane[i] + (uint32_t)t * da_slot : kPast, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, da_buf, store_offset(da_lane[i], (uint32_t)t * da_slot, da_drop[i] | (t < a.t_end ? 0u : kDrop)), 0, 0);
             }
         };
 

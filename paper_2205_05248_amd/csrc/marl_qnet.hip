@@ -11,6 +11,7 @@
 #include <new>
 
 #include "qnet_internal.h"
+#include "store_offsets.h"
 
 // Input-projection buffer of marl_unroll_td_static: device memory that exists from the moment the library is loaded
 // on a device, so that the call allocates nothing.  The name stands for the array in host code only as a symbol to
@@ -652,8 +653,7 @@ int marl_unroll_td_double(marl_qnet *online, marl_qnet *target, int32_t pool_epi
 int marl_qnet_grad_workspace_bytes(const marl_qnet *q, int32_t B, int32_t T, size_t *bytes)
 {
     if (!q || !bytes) return MARL_ERR_NULL;
-    if (B < 1 || T < 1 || (int64_t)B * q->desc.n_agents * ((int64_t)T + 1) * 4 * q->desc.hidden >= (int64_t)1 << 30)
-        return MARL_ERR_BAD_DIM;
+    if (B < 1 || T < 1 || !marl::gradient_in_range(B, q->desc.n_agents, T, q->desc.hidden)) return MARL_ERR_BAD_DIM;
     if (!marl::qnet_grad_fits(q->net)) return MARL_ERR_BAD_DIM;
     *bytes = marl::qnet_grad_workspace_bytes(q->net, B, T);
     return MARL_OK;
