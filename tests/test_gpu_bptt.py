@@ -85,14 +85,14 @@ CASES = [(0, 4, 6, {}), (0, 32, 25, {}), (1, 5, 9, {}), (2, 7, 12, {}), (3, 33, 
          # bf16 networks over sixteen slots or more: the slots are walked in two launches (an odd count: halves of
          # eight and nine) and the products run per half; the last one's first layer keeps the narrow loads
          (4, 2, 17, {}), (1, 3, 24, dict(dtype="bf16")), (0, 2, 16, dict(N=17, D=33, A=64, dtype="bf16")),
-         # two launches of unequal halves, for 64 hidden units with every remainder of the unrolled loop on either side;
+         # two launches of unequal halves, for 64 hidden units on tiles of eight rows, with odd and even counts on either side;
          # the halves fill more chunks of partial sums together than all slots at once would
          (2, 3, 17, dict(N=5, D=96, dtype="bf16")), (2, 12, 17, dict(N=5, D=96, dtype="bf16")),
          (2, 2, 19, dict(N=5, D=96, dtype="bf16")), (2, 3, 21, dict(N=5, D=96, dtype="bf16")),
          (2, 12, 61, dict(N=5, D=96, dtype="bf16")), (4, 12, 17, dict(N=5, D=96, A=11)),
          # one launch, just past the samples up to which a chunk of a bf16 network has 64
          (2, 37, 14, dict(N=5, D=55, dtype="bf16")),
-         # more row tiles than compute units: two workgroups of a bf16 network share one, fp32 ones follow one another
+         # more tiles of sixteen rows than compute units: two workgroups of a bf16 network share one, fp32 ones follow one another
          (2, 823, 5, dict(N=5, D=24, dtype="bf16")), (2, 823, 3, dict(N=5, D=24))]
 
 
@@ -113,8 +113,8 @@ def test_gradient_matches_the_oracle(ci, B, T, over):
     net.close()
 
 
-# The reverse recurrence of a 64-unit network walks the slots in an unrolled loop of three with two slots of inputs in
-# flight: the fewest slots, every remainder, and row counts on both sides of a tile of sixteen.
+# The reverse recurrence of a 64-unit network with few rows (tiles of eight) walks the slots two a round, an odd one first, with the
+# inputs of the slots before in flight: the fewest slots, odd and even, and row counts on both sides of a tile.
 @pytest.mark.parametrize("T", [1, 2, 3, 4])
 @pytest.mark.parametrize("dtype,B,N", [("fp32", 1, 2), ("fp32", 17, 1), ("bf16", 5, 3), ("bf16", 16, 1)])
 def test_gradient_of_the_fewest_slots(dtype, B, N, T):
@@ -124,6 +124,27 @@ def test_gradient_of_the_fewest_slots(dtype, B, N, T):
     g = np.random.default_rng(7).standard_normal(u["actions"].shape).astype(np.float32)
     net = binding.QNet(wl.dims(cfg), w, dtype)
     compare(cfg, gpu_grad(net, cfg, u, g), *oracle_grad(cfg, w, u, g))
+    net.close()
+
+
+# With more rows than tiles of eight are taken for, a 64-unit network walks the slots on tiles of sixteen, in an unrolled loop of
+# three with two slots of inputs in flight: the fewest slots and every remainder in one launch, and, for a bf16 network, every
+# remainder of either half of two launches, whose second goes on from what the first carried.
+@pytest.mark.parametrize("dtype,B,T,N", [(d, 683, T, 3) for d in ("fp32", "bf16") for T in (1, 2, 3, 4)]
+                         + [("bf16", 257, 17, 5), ("bf16", 257, 19, 5), ("bf16", 257, 21, 5), ("bf16", 1024, 18, 3)])
+def test_gradient_on_tiles_of_sixteen_rows(dtype, B, T, N):
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    eights, two_launches = -(-B * N // 8), dtype == "bf16" and T >= 16 and 2 * -(-B * N // 16) <= 3 * n_cu // 2
+    assert eights > (5 * n_cu // 8 if two_launches else n_cu) and two_launches == (T >= 16)
+    cfg = dict(wl.config(0), dtype=dtype, N=N, D=8, A=5, B=B, T=T)
+    w = wl.make_weights(cfg, 0)
+    u = wl.make_unroll_inputs(cfg, B=B, T=T)
+    # one sign: the sums grow with the samples as the oracle's ambiguity budget does
+    g = np.abs(np.random.default_rng([B, T, N]).normal(size=(B, T, N))).astype(np.float32)
+    net = binding.QNet(wl.dims(cfg), w, dtype)
+    got = gpu_grad(net, cfg, u, g)
+    compare(cfg, got, *oracle_grad(cfg, w, u, g))
+    assert (gpu_grad(net, cfg, u, g) == got).all()
     net.close()
 
 
