@@ -957,20 +957,22 @@ __global__ __launch_bounds__(BpttSplit8<P>::kThreads, BpttSplit8<P>::kThreads / 
         const int b = valid ? mrow / N : 0, n = valid ? mrow % N : 0;
         const uint32_t bt0 = (uint32_t)b * T, btn0 = bt0 * N + n;  // the host bounds 4 H samples to 2^30
         const size_t samples = (size_t)rows * T;
-        auto buffer = [&](void *p, size_t per_sample) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(uint32_t)(samples * per_sample * kElem), kRawBuffer); };
-        const __amdgpu_buffer_rsrc_t da_buf = buffer(a.da, 4 * H), dq_buf = buffer(a.dq, a.a16), pre_buf = buffer(a.dpre1, H);
-        // A store's offset: the lane's own part (dpre1 and the adjoint of Q: kPast, where the store is to be dropped), and the slot's,
-        // the same in every lane.  da, of which kPast may be in the middle in fp32, has a mask beside them; two planes, a row per
-        // access, 16 bytes a lane; one plane, both rows.
-        uint32_t da_lane[P], da_drop[P];
+        auto buffer = [&](void *p, size_t per_sample, bool exists) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)descriptor_bytes(samples * per_sample * kElem, exists), kRawBuffer); };
+        const __amdgpu_buffer_rsrc_t dq_buf = buffer(a.dq, a.a16, true), pre_buf = buffer(a.dpre1, H, true);
+        // A store's offset: the lane's own part (kPast, where the store is to be dropped), and the slot's, the same in every lane.
+        // da: one plane, both rows, 16 bytes a lane; two planes, a row per access, with a descriptor of its own, for kPast may be in
+        // the middle of the array.  (A mask over the offsets instead: seven instructions more per slot, 64 x 120 x 5 346.1 -> 347.3 us.)
+        __amdgpu_buffer_rsrc_t da_buf[P];
+        uint32_t da_lane[P];
         int da_from[P];
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             const int r = P == 2 ? 2 * w + i : mr, piece = P == 2 ? lane : j;
             const bool there = row0 + r < rows;
             const int rb = there ? (row0 + r) / N : 0, rn = there ? (row0 + r) % N : 0;
-            da_lane[i] = ((uint32_t)rb * T * N + rn) * 4 * H * kElem + 16 * piece;
-            da_drop[i] = there ? 0u : kDrop;
+            da_buf[i] = buffer(a.da, 4 * H, P == 1 || there);
+            da_lane[i] = P == 2 || there ? ((uint32_t)rb * T * N + rn) * 4 * H * kElem + 16 * piece : kPast;
+            asm volatile("" : "+v"(da_lane[i]));                   // (one vector register, not a sum with a scalar that is stepped for itself)
             da_from[i] = Bs::oOut + r * Bs::kOutPitch + 16 * piece;
         }
         const uint32_t pre_lane = valid ? (btn0 * H + 2 * j) * kElem : kPast, dq_lane = valid && 2 * j < a.a16 ? (btn0 * a.a16 + 2 * j) * kElem : kPast;
@@ -1002,7 +1004,7 @@ __global__ __launch_bounds__(BpttSplit8<P>::kThreads, BpttSplit8<P>::kThreads / 
             for (int i = 0; i < P; ++i) {
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(lds + da_from[i] + (t & 1) * Bs::kOutBytes);
                 // (the slot's part not as a scalar offset: see the 16-byte stores of bptt_back_roles_kernel)
-                __builtin_amdgcn_raw_buffer_store_b128(v, da_buf, store_offset(da_lane[i], (uint32_t)t * da_slot, da_drop[i] | (t < a.t_end ? 0u : kDrop)), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, da_buf[i], store_offset(da_lane[i], (uint32_t)t * da_slot, t < a.t_end), 0, 0);
             }
         };
 

@@ -13,9 +13,11 @@ constexpr bool gradient_in_range(int64_t B, int64_t N, int64_t T, int64_t H) { r
 // Every global access inside the loops over the slots is unconditional, so that their bodies are straight-line code and
 // the waits for the prefetched inputs count exactly the stores issued after them: rows past the end store through
 // buffer descriptors at an offset beyond the descriptor, which the hardware drops.
-// kDrop: beyond any of these arrays, ORed into a whole offset; nothing can be added to it.
+// kDrop: beyond any of these arrays, as a whole offset; nothing can be added to it.
 constexpr uint32_t kDrop = 0xFFFFFFF0u;
-constexpr uint32_t store_offset(uint32_t lane_at, uint32_t slot_at, uint32_t drop) { return (lane_at + slot_at) | drop; }
+constexpr uint32_t store_offset(uint32_t lane_at, uint32_t slot_at, bool exists) { return exists ? lane_at + slot_at : kDrop; }
+// A row of a whole wave that does not exist: a descriptor of no bytes.
+constexpr uint32_t descriptor_bytes(uint64_t bytes, bool exists) { return exists ? (uint32_t)bytes : 0u; }
 // kPast: beyond the arrays of less than 2^31 bytes, in place of a lane's part; a slot's part within such an array may be added.
 constexpr uint32_t kPast = 0x80000000u;
 

@@ -11,10 +11,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "store_offsets.h"
 extern "C" int in_range(long B, long N, long T, long H) { return marl::gradient_in_range(B, N, T, H); }
-extern "C" unsigned store_offset(unsigned lane_at, unsigned slot_at, int dropped)
-{
-    return marl::store_offset(lane_at, slot_at, dropped ? marl::kDrop : 0u);
-}
+extern "C" unsigned store_offset(unsigned lane_at, unsigned slot_at, int exists) { return marl::store_offset(lane_at, slot_at, exists != 0); }
+extern "C" unsigned descriptor_bytes(unsigned long bytes, int exists) { return marl::descriptor_bytes(bytes, exists != 0); }
 extern "C" unsigned past() { return marl::kPast; }
 """
 
@@ -26,7 +24,8 @@ def lib(tmp_path_factory):
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", os.path.join(ROOT, "paper_2205_05248_amd", "csrc"),
                            str(d / "shim.cpp"), "-o", str(d / "shim.so")])
     so = ctypes.CDLL(str(d / "shim.so"))
-    so.store_offset.restype = so.past.restype = ctypes.c_uint
+    so.store_offset.restype = so.descriptor_bytes.restype = so.past.restype = ctypes.c_uint
+    so.descriptor_bytes.argtypes = [ctypes.c_ulong, ctypes.c_int]
     so.in_range.argtypes = [ctypes.c_long] * 4
     so.store_offset.argtypes = [ctypes.c_uint, ctypes.c_uint, ctypes.c_int]
     return so
@@ -59,16 +58,18 @@ def test_stores_of_what_does_not_exist_are_dropped(lib, planes, hidden):
             slots = [t for t in sorted({0, 1, T // 2, T - 1, half - 1, half, half + 1}) if 0 <= t < T]
             # the gates' adjoints: 4 H a sample, 16 bytes a lane
             row, slot = 4 * hidden * element, N * 4 * hidden * element
+            assert lib.descriptor_bytes(samples * row, 1) == samples * row
             for b, n in {(0, 0), (0, N - 1), (B // 2, 0), (B - 1, N - 1)}:
                 for piece in (0, row // 16 - 1):
                     lane = (b * T * N + n) * row + 16 * piece
                     for t in slots:
                         at = ((b * T + t) * N + n) * row + 16 * piece
-                        assert lib.store_offset(lane, t * slot, 0) == at and at + 16 <= samples * row, (B, N, T, t)
-                        # a row past the last one takes the first one's place
-                        assert lib.store_offset(16 * piece, t * slot, 1) >= samples * row, (B, N, T, t)
+                        assert lib.store_offset(lane, t * slot, 1) == at and at + 16 <= samples * row, (B, N, T, t)
+                        # a row past the last one: two planes, on the first one's place behind a descriptor of its own; one, kPast
+                        size, part = (lib.descriptor_bytes(samples * row, 0), 16 * piece) if planes == 2 else (samples * row, lib.past())
+                        assert lib.store_offset(part, t * slot, 1) >= size and part + t * slot < 1 << 32, (B, N, T, t)
                     # the step before the first: slot T
-                    assert lib.store_offset(lane & 0xFFFFFFFF, (T * slot) & 0xFFFFFFFF, 1) >= samples * row, (B, N, T)
+                    assert lib.store_offset(lane, (T * slot) & 0xFFFFFFFF, 0) >= samples * row, (B, N, T)
             # the arrays in whose stores kPast takes the lane's place; a slot's part is added, by the kernel or by the hardware
             arrays = [hidden, 16, 64] + ([4 * hidden] if planes == 1 else [])
             for per_sample in arrays:
