@@ -12,7 +12,8 @@
 //                                      on nothing behind it are on different waves.  128 hidden units, bf16.
 //   bptt_back_split_kernel             the same for 64 hidden units, fp32 and bf16; here W_ih^T and, through the
 //                                      ReLU, the adjoint of fc1's pre-activation are part of it
-//   bptt_back_split8_kernel            the same on tiles of eight rows, for batches that leave compute units free
+//   bptt_back_split8_kernel            the same on tiles of eight rows, for batches that leave compute units free; what goes to
+//                                      memory and comes from it is moved by waves of their own
 //   tn_gemm_kernel                     the weight gradients are sums over all (row, slot) samples of outer
 //                                      products adjoint x activation: C[p][q] = sum_m A[m][p] B[m][q], four
 //                                      times (W_ih, W_hh, W1, W2).  The samples are split into chunks, one
@@ -826,7 +827,7 @@ __global__ __launch_bounds__(BpttSplit8<P>::kThreads, BpttSplit8<P>::kThreads / 
         asm volatile("" : "+v"(carry.v[0]), "+v"(carry.v[1]));
 
         const int mine_at = publish_at(r8, unit0);
-        // what is to be stored, for the gate waves
+        // what is to be stored, for the movers
         auto leave = [&](int at, const Pair &x) {
             if constexpr (P == 1) {
                 bf16x2 v;
@@ -2296,7 +2297,7 @@ hipError_t launch_qnet_grad(const NetFrags &net, int B, int T, const float *obs,
         }};
     };
 
-    // The reverse recurrence is one workgroup per 16 rows: a batch with fewer tiles than compute units leaves the
+    // The reverse recurrence is one workgroup per 8 or 16 rows: a batch with fewer tiles than compute units leaves the
     // rest of the chip idle for as long as the episodes are.  Then the slots are walked in two launches, and the
     // products over the later half run on a second stream beside the earlier half's recurrence.
     const int tiles = (B * N + 15) / 16, t_mid = plan.cut.t_mid;

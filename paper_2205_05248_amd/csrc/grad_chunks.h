@@ -96,22 +96,23 @@ inline GradChunks grad_chunks(int planes, long rows, int T)
     // for the fewest, where the steps that follow one another in a chunk are what takes time, of 128 or more beyond,
     // where the partial sums are.  Gradient with chunks of 64 / 128, 128 units and 93 observations: 720 samples 95 / 100 us,
     // 1200 104 / 109, 2250 111 / 113, 2400 131 / 132, 3000 139 / 133, 3600 121 / 120, 4000 144 / 133, 4800 284 / 279,
-    // 9900 297 / 290; 64 units, and 33 and 301 observations, change over between the same 2400 and 3000.
+    // 9900 297 / 290; 64 units, and 33 and 301 observations, change over between the same 2400 and 3000.  (Measured with the GRU
+    // products of 128 units among them, which have chunks of their own by now.)
     g.whole = planes == 2 ? cut_samples(M, 128, 32) : cut_samples(M, 256, M <= 2560 ? 64 : 128);
     g.room = g.whole.chunks;
     // 64 chunks of four workgroups each are the chip's compute units once.
     auto cut_gru = [](long samples, long most) { return cut_samples(samples, std::min(64L, most), 64); };
     if (planes == 1 && T >= kForkSlots) {
-        // the later half's products share the chip with the recurrence, whose workgroups hold half the compute units
-        // or less: half as many chunks.  The earlier half's too: its two GRU products then run side by side, one on
-        // each stream, 128 workgroups each (256 chunks for the first layer's product, which runs last and alone,
-        // changed nothing).  Both halves' partial sums wait for one sum.
+        // the later half's products share the chip with the recurrence, whose workgroups hold three quarters of the compute
+        // units at most: half as many chunks.  The earlier half's too: the two GRU products of 64 units then run side by
+        // side, one on each stream, 128 workgroups each (256 chunks for the first layer's product, which runs last and
+        // alone, changed nothing).  Both halves' partial sums wait for one sum.
         g.t_mid = T / 2;
         g.late = cut_samples(rows * (T - g.t_mid), 128, 32);
         g.early = cut_samples(rows * g.t_mid, 128, 32);
-        // (beside the recurrence half as many, 128 workgroups for the 128 or more compute units that it leaves: with 64 chunks 64
-        // episodes x 200 slots x 32 agents 1196 us for the learner iteration, with 32 1191; 64 x 120 x 8 466 / 458, 9 x 200 x 32
-        // 698 / 688)
+        // 128 units: both GRU products are one launch, the earlier half's on the caller's stream.  (Beside the recurrence half as
+        // many chunks, 128 workgroups for the 128 compute units that it leaves on 64 x 200 x 32: with 64 chunks 64 episodes x 200
+        // slots x 32 agents 1196 us for the learner iteration, with 32 1191; 64 x 120 x 8 466 / 458, 9 x 200 x 32 698 / 688)
         g.gru_late = cut_samples(rows * (T - g.t_mid), 32, 64);
         g.gru_early = cut_gru(rows * g.t_mid, 64);
         g.room = std::max(g.room, g.late.chunks + g.early.chunks);
